@@ -42,8 +42,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // Header words (int32 unless stated).
 enum : int {
   kHdrErr = 0,
-  kHdrStats = 4,      // [0] max d, [1] max d+
-  kHdrDeg2 = 6,       // nodes with d >= 2
+  kHdrStats = 4,      // [0] max d, [1] max d+, [2] nodes with d >= 2
   kHdrBinCnt = 16,    // [kNumBins]
   kHdrLimits = 24,    // [kNumBins - 1]
   kHdrListElems = 32, // u64 at byte 128
@@ -56,6 +55,7 @@ enum : int {
   kHdrInItems = 184,  // int64[kNumBins + 1] at byte 736: chunk prefix at the boundaries
   kHdrCheck = 200,    // u64[2] at byte 800: the last count's total and sum of T(v)
   kHdrBinKBytes = 208, // u64[kNumBins] at byte 832: modelled kernel bytes per bin
+  kHdrM = 220,        // int64 at byte 880: DAG edges
 };
 constexpr size_t kHdrBytes = 1024;
 
@@ -256,31 +256,72 @@ int classify(tricc_graph* g, int nc, Launch launch, int64_t* d_cls_off, int64_t*
   return sync_copy(h_off, d_cls_off, sizeof(int64_t) * (nc + 1), s);
 }
 
-int bin_nodes(tricc_graph* g) {
+// DAG offsets, in-degrees, edge records, node bins and in-list items from
+// the degrees (d, d+), into the workspace and its header; no host wait.
+int layout_and_bins(tricc_graph* g) {
   hipStream_t s = g->stream;
   const Layout& L = g->L;
-  int32_t* hdr = g->hdr32();
-  const int32_t n = g->n;
-  int rc = upload(hdr + kHdrLimits, g->tuning.bin_limit, sizeof(int32_t) * (kNumBins - 1), s);
-  if (rc) return rc;
-  int64_t* d_bin_off = reinterpret_cast<int64_t*>(g->ws + L.hdr + kHdrBinOff * 4);
-  const int32_t* dplus = g->at<int32_t>(L.dplus);
-  int32_t* binlist = g->at<int32_t>(L.binlist);
-  auto launch = [&](int pass, int32_t* hist, const int64_t* off) {
-    return launch_classify_bins(pass, n, dplus, hdr + kHdrLimits, hist, off, L.cls_nblk, binlist, s);
-  };
-  if (n == 0) {
-    for (int b = 0; b <= kNumBins; ++b) g->bin_off[b] = 0;
-  } else if ((rc = classify(g, kNumBins, launch, d_bin_off, g->bin_off))) {
-    return rc;
+  BinParams bp;
+  for (int b = 0; b < kNumBins - 1; ++b) bp.limit[b] = g->tuning.bin_limit[b];
+  for (int b = 0; b < kNumBins; ++b)
+    bp.cap[b] = std::max(1, std::min(1 << 20, count_variant_capacity(g->tuning.bin_variant[b])));
+  bp.min_side = g->tuning.min_side;
+  auto hdr64 = [&](int word) { return reinterpret_cast<int64_t*>(g->hdr32() + word); };
+  LayoutOut o;
+  o.deg = g->at<int32_t>(L.deg);
+  o.dplus = g->at<int32_t>(L.dplus);
+  o.raw_off = g->at<int64_t>(L.raw_off);
+  o.doff = g->at<int64_t>(L.doff);
+  o.dinoff = g->at<int64_t>(L.dinoff);
+  o.din = g->at<int32_t>(L.din);
+  o.rec = g->at<int2>(L.rec);
+  o.binlist = g->at<int32_t>(L.binlist);
+  o.inlist = g->at<int32_t>(L.inlist);
+  o.incoff = g->at<int64_t>(L.incoff);
+  o.bin_off = hdr64(kHdrBinOff);
+  o.in_off = hdr64(kHdrInOff);
+  o.in_items = hdr64(kHdrInItems);
+  o.stats = g->hdr32() + kHdrStats;
+  o.m = hdr64(kHdrM);
+  o.limit = g->hdr32() + kHdrLimits;
+  o.cap = g->hdr32() + kHdrInCap;
+  // the per-tile sums sit in the chunk-count area, which nothing else uses
+  HIPCHK(launch_layout(g->n, bp, g->at<int32_t>(L.inch), o, s));
+  return TRICC_OK;
+}
+
+// The chunk -> owner map, in tmp (free after the orientation: at most one
+// chunk per owner plus d-(w) / 16 per owner, below the 2 m_raw entries), and
+// the one read-back of a4-a5: sizes, bounds and totals from the header.
+int finish_bins(tricc_graph* g) {
+  hipStream_t s = g->stream;
+  const Layout& L = g->L;
+  alignas(8) char h[kHdrBytes] = {};
+  if (g->n > 0) {
+    if (g->tuning.min_side)
+      HIPCHK(launch_in_owners(g->n, reinterpret_cast<int64_t*>(g->hdr32() + kHdrInOff) + kNumBins,
+                              g->at<int64_t>(L.incoff), g->at<int32_t>(L.tmp), s));
+    int rc = sync_copy(h, g->ws + L.hdr, kHdrBytes, s);
+    if (rc) return rc;
   }
+  const int32_t* h32 = reinterpret_cast<const int32_t*>(h);
+  std::memcpy(g->bin_off, h32 + kHdrBinOff, sizeof(g->bin_off));
+  std::memcpy(g->in_off, h32 + kHdrInOff, sizeof(g->in_off));
+  std::memcpy(g->in_items, h32 + kHdrInItems, sizeof(g->in_items));
+  std::memcpy(&g->info.m, h32 + kHdrM, sizeof(int64_t));
+  g->info.max_deg = h32[kHdrStats];
+  g->info.max_outdeg = h32[kHdrStats + 1];
+  g->info.n_deg2 = h32[kHdrStats + 2];
+  g->info.list_elems = 0;
   for (int b = 0; b < kNumBins; ++b) {
-    const int64_t cnt = g->bin_off[b + 1] - g->bin_off[b];
-    g->info.bin_count[b] = cnt;
+    g->info.bin_count[b] = g->bin_off[b + 1] - g->bin_off[b];
     g->info.bin_list_elems[b] = 0;
     g->info.bin_edges[b] = 0;
     g->info.bin_kernel_bytes[b] = 0;
-    if (!cnt) continue;
+    g->info.bin_in_items[b] = 0;
+  }
+  for (int b = 0; b < kNumBins; ++b) {
+    if (!g->info.bin_count[b]) continue;
     int64_t bound = g->info.max_outdeg;
     if (b < kNumBins - 1) bound = std::min<int64_t>(bound, g->tuning.bin_limit[b]);
     const int cap = count_variant_capacity(g->tuning.bin_variant[b]);
@@ -288,33 +329,13 @@ int bin_nodes(tricc_graph* g) {
       return fail(TRICC_EINVAL, "tuning: bin %d holds out-degrees up to %lld but variant %d accepts %d", b,
                   (long long)bound, g->tuning.bin_variant[b], cap);
   }
-  g->info.list_elems = 0;
-  // in-list items (min-side): owners by d+(w), chunks of the bin variant's capacity
-  for (int b = 0; b <= kNumBins; ++b) g->in_off[b] = g->in_items[b] = 0;
-  if (g->tuning.min_side && n > 0) {
-    int64_t* d_in_off = reinterpret_cast<int64_t*>(g->ws + L.hdr + kHdrInOff * 4);
-    int32_t* inlist = g->at<int32_t>(L.inlist);
-    auto launch_in = [&](int pass, int32_t* hist, const int64_t* off) {
-      return launch_classify_inbins(pass, n, dplus, g->at<int32_t>(L.deg), hdr + kHdrLimits, hist, off, L.cls_nblk,
-                                    inlist, s);
-    };
-    if ((rc = classify(g, kNumBins, launch_in, d_in_off, g->in_off))) return rc;
-    int32_t caps[kNumBins];
-    for (int b = 0; b < kNumBins; ++b) caps[b] = std::max(1, std::min(1 << 20, count_variant_capacity(g->tuning.bin_variant[b])));
-    if ((rc = upload(hdr + kHdrInCap, caps, sizeof(caps), s))) return rc;
-    const int64_t nin = g->in_off[kNumBins];
-    HIPCHK(launch_in_chunks(inlist, nin, g->at<int32_t>(L.din), hdr + kHdrInCap, d_in_off, g->at<int32_t>(L.inch), s));
-    int64_t* incoff = g->at<int64_t>(L.incoff);
-    HIPCHK(launch_scan_i32(g->at<int32_t>(L.inch), nin, incoff, g->at<int64_t>(L.scan_tmp), s));
-    // chunk -> owner map in tmp (free after the orientation): at most one
-    // chunk per owner plus d-(w) / 16 per owner, below the 2 m_raw entries
-    HIPCHK(launch_in_owners(nin, incoff, g->at<int32_t>(L.tmp), s));
-    int64_t* d_items = reinterpret_cast<int64_t*>(g->ws + L.hdr + kHdrInItems * 4);
-    HIPCHK(launch_gather_offsets(incoff, d_in_off, kNumBins + 1, d_items, s));
-    if ((rc = sync_copy(g->in_items, d_items, sizeof(g->in_items), s))) return rc;
-  }
   for (int b = 0; b < kNumBins; ++b) g->info.bin_in_items[b] = g->in_items[b + 1] - g->in_items[b];
   return TRICC_OK;
+}
+
+int bin_nodes(tricc_graph* g) {
+  int rc = layout_and_bins(g);
+  return rc ? rc : finish_bins(g);
 }
 
 // Algorithmic-size statistics (not needed for counting).
@@ -355,16 +376,13 @@ int orient_impl(tricc_graph* g, const int32_t* key) {
   hipStream_t s = g->stream;
   const Layout& L = g->L;
   const int32_t n = g->n;
-  int32_t* hdr = g->hdr32();
   int32_t* len = g->at<int32_t>(L.len);
   int32_t* deg = g->at<int32_t>(L.deg);
   int64_t* raw_off = g->at<int64_t>(L.raw_off);
-  int64_t* scan_tmp = g->at<int64_t>(L.scan_tmp);
   int32_t* adj = g->at<int32_t>(L.adj);
   int32_t* rowlist = g->at<int32_t>(L.rowlist);
   const int64_t* cls_off = g->cls_off;
   int rc;
-  HIPCHK(hipMemsetAsync(hdr + kHdrStats, 0, sizeof(int32_t) * 3, s));  // max d, max d+, nodes with d >= 2
   // a4: orientation (rows longer than 64 raw entries: classes kRow128 ..
   // kRowLds4k are medium, the classes above them are long; the row lists
   // are class-major, so each range is contiguous)
@@ -380,27 +398,17 @@ int orient_impl(tricc_graph* g, const int32_t* key) {
   int32_t* part = g->at<int32_t>(L.tmp);
   // the degree-class words (n / 4 bytes) sit in binlist, free until the binning
   uint32_t* cls = reinterpret_cast<uint32_t*>(g->at<int32_t>(L.binlist));
-  HIPCHK(launch_orient(n, raw_off, len, deg, key, adj, med_rows, nmed, long_rows, nlong, cls, dplus, part,
-                       hdr + kHdrStats, s));
-  HIPCHK(launch_scan_i32(dplus, n, doff, scan_tmp, s));
-  int32_t* din = g->at<int32_t>(L.din);
-  int64_t* dinoff = g->at<int64_t>(L.dinoff);
-  HIPCHK(launch_indeg(n, deg, dplus, din, hdr + kHdrDeg2, s));
-  HIPCHK(launch_scan_i32(din, n, dinoff, scan_tmp, s));
-  HIPCHK(launch_orient_copy(n, raw_off, len, deg, dplus, part, med_rows, nmed, long_rows, nlong, doff, dcol, dinoff,
-                            g->at<int32_t>(L.dincol), s));
-  HIPCHK(launch_edge_records(n, raw_off, deg, g->at<int32_t>(L.rec), s));
-  int32_t stats[3];  // max d, max d+, nodes with d >= 2
-  if ((rc = sync_copy(stats, hdr + kHdrStats, sizeof(stats), s))) return rc;
-  int64_t m = 0;
-  if ((rc = sync_copy(&m, doff + n, sizeof(m), s))) return rc;
-  g->info.m = m;
-  g->info.max_deg = stats[0];
-  g->info.max_outdeg = stats[1];
-  g->info.n_deg2 = stats[2];
+  HIPCHK(launch_orient(n, raw_off, len, deg, key, adj, med_rows, nmed, long_rows, nlong, cls, dplus, part, s));
+  if (n == 0) {
+    HIPCHK(hipMemsetAsync(doff, 0, sizeof(int64_t), s));
+    HIPCHK(hipMemsetAsync(g->at<int64_t>(L.dinoff), 0, sizeof(int64_t), s));
+  }
+  // a5 with the offsets; the copy reads them, and frees tmp for the owner map
+  if ((rc = layout_and_bins(g))) return rc;
+  HIPCHK(launch_orient_copy(n, raw_off, len, deg, dplus, part, med_rows, nmed, long_rows, nlong, doff, dcol,
+                            g->at<int64_t>(L.dinoff), g->at<int32_t>(L.dincol), s));
   g->oriented_by_key = key != nullptr;
-  // a5: binning
-  return bin_nodes(g);
+  return finish_bins(g);
 }
 
 // Builds a1-a5. With presorted set, adj, raw_off, len and deg already hold
@@ -1284,10 +1292,10 @@ void batch_graph_tuning(const tricc_batch_tuning& bt, tricc_tuning* t) {
   t->min_side = 0;
 }
 
-int batch_bin(tricc_batch* b) {
-  batch_graph_tuning(b->tuning, &b->g.tuning);
-  int rc = bin_nodes(&b->g);
-  if (rc) return rc;
+// Segments of the persistent kernel and its grid, from the bins that the
+// build (or a re-binning) left.
+int batch_segments(tricc_batch* b) {
+  int rc;
   // phase-2 segments: consecutive graphs with equal shares of the input pairs
   {
     const int32_t G = b->G;
@@ -1436,7 +1444,7 @@ int tricc_batch_build(int32_t num_graphs, const int64_t* h_node_off, const int64
   if ((rc = sync_copy(&err, b->d_err, sizeof(err), s))) return bail(rc);
   if (err) return bail(fail(TRICC_ERANGE, "a local node id is outside its graph's [0, n_g)"));
   if ((rc = build_impl(g, b->gsrc, b->gdst))) return bail(rc);
-  if ((rc = batch_bin(b))) return bail(rc);
+  if ((rc = batch_segments(b))) return bail(rc);
   *out = b;
   return TRICC_OK;
 }
@@ -1515,7 +1523,7 @@ int tricc_batch_build_csr(int32_t num_graphs, const int64_t* h_node_off, int64_t
   if ((rc = sync_copy(&err, b->d_err, sizeof(err), s))) return bail(rc);
   if (err) return bail(fail(TRICC_ERANGE, "a local node id is outside its graph's [0, n_g)"));
   if ((rc = csr_build(g, nnz, d_rowptr, b->gdst, assume_simple_sorted_symmetric))) return bail(rc);
-  if ((rc = batch_bin(b))) return bail(rc);
+  if ((rc = batch_segments(b))) return bail(rc);
   *out = b;
   return TRICC_OK;
 }
@@ -1593,7 +1601,9 @@ int tricc_batch_retune(tricc_batch* b, const tricc_batch_tuning* tuning, void* s
   batch_drop_plan(b);
   b->tuning = *tuning;
   b->g.stream = static_cast<hipStream_t>(stream);
-  return batch_bin(b);
+  batch_graph_tuning(b->tuning, &b->g.tuning);
+  if ((rc = bin_nodes(&b->g))) return rc;
+  return batch_segments(b);
 }
 
 int tricc_batch_info_get(const tricc_batch* b, tricc_batch_info* out) {

@@ -539,35 +539,6 @@ struct RowClassOf {  // by raw row length; trivial rows are not listed
   }
 };
 
-struct NodeBinOf {  // by DAG out-degree; nodes with d+ < 2 are not listed
-  const int32_t* dplus;
-  const int32_t* limit;
-  __device__ int operator()(int64_t v, int) const {
-    const int32_t d = dplus[v];
-    if (d < 2) return -1;
-    int b = kNumBins - 1;
-#pragma unroll
-    for (int q = kNumBins - 2; q >= 0; --q)
-      if (d <= limit[q]) b = q;
-    return b;
-  }
-};
-
-struct InBinOf {  // in-list pass owners: 3 <= d+(w) <= limit[4], at least one in-neighbour
-  const int32_t* dplus;
-  const int32_t* deg;
-  const int32_t* limit;
-  __device__ int operator()(int64_t v, int) const {
-    const int32_t d = dplus[v];
-    if (d < 3 || deg[v] - d < 1 || d > limit[kNumBins - 2]) return -1;
-    int b = kNumBins - 2;
-#pragma unroll
-    for (int q = kNumBins - 3; q >= 0; --q)
-      if (d <= limit[q]) b = q;
-    return b;
-  }
-};
-
 template <int NC, class F>
 __global__ __launch_bounds__(kClsThreads) void k_classify(int pass, int64_t n, F f, int32_t* __restrict__ hist,
                                                           const int64_t* __restrict__ off, int64_t nblk,
@@ -599,22 +570,6 @@ hipError_t launch_classify_rows(int pass, int32_t n, const int32_t* len, int32_t
   if (n == 0) return hipSuccess;
   k_classify<kNumRowClasses, RowClassOf><<<(unsigned)nblk, kClsThreads, 0, s>>>(pass, n, RowClassOf{len, deg}, hist,
                                                                                off, nblk, list);
-  return hipGetLastError();
-}
-
-hipError_t launch_classify_bins(int pass, int32_t n, const int32_t* dplus, const int32_t* limit, int32_t* hist,
-                                const int64_t* off, int64_t nblk, int32_t* list, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_classify<kNumBins, NodeBinOf><<<(unsigned)nblk, kClsThreads, 0, s>>>(pass, n, NodeBinOf{dplus, limit}, hist, off,
-                                                                        nblk, list);
-  return hipGetLastError();
-}
-
-hipError_t launch_classify_inbins(int pass, int32_t n, const int32_t* dplus, const int32_t* deg, const int32_t* limit,
-                                  int32_t* hist, const int64_t* off, int64_t nblk, int32_t* list, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_classify<kNumBins, InBinOf><<<(unsigned)nblk, kClsThreads, 0, s>>>(pass, n, InBinOf{dplus, deg, limit}, hist, off,
-                                                                      nblk, list);
   return hipGetLastError();
 }
 
@@ -1149,43 +1104,18 @@ constexpr int32_t kOrientShort = 64;
 constexpr int kOrientShortUnroll = 4;  // steps of G entries issued together (short rows)
 constexpr int kOrientMedUnroll = 4;    // chunks of 64 entries issued together (medium rows)
 
-template <typename T>
-__device__ __forceinline__ T block_max(T x, T* lds) {
-  constexpr int NW = 256 / kWave;
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o, kWave));
-  if (lane_id() == 0) lds[threadIdx.x / kWave] = x;
-  __syncthreads();
-  T r = lds[0];
-  for (int i = 1; i < NW; ++i) r = max(r, lds[i]);
-  __syncthreads();
-  return r;
-}
-
-// Raises the largest degrees seen (stats[0] = d, stats[1] = d+). One counter
-// takes about 100 atomics per microsecond, so 65,536 blocks that each issued
-// two held the whole kernel up (1.25 ms for 2.4M rows, 0.76 ms at R-MAT 20
-// whose rows need 0.1 ms). The value only grows, so a block whose maximum is
-// not above what it reads there has nothing to add, even if the read is old.
-__device__ __forceinline__ void raise_stats(int32_t* __restrict__ stats, int32_t d, int32_t p) {
-  if (d > __hip_atomic_load(&stats[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&stats[0], d);
-  if (p > __hip_atomic_load(&stats[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&stats[1], p);
-}
-
 __global__ __launch_bounds__(256) void k_orient_short(int32_t n, const int64_t* __restrict__ off,
                                                       const int32_t* __restrict__ len,
                                                       const int32_t* __restrict__ deg,
                                                       const int32_t* __restrict__ key,
                                                       const uint32_t* __restrict__ cls,
                                                       const int32_t* __restrict__ adj,
-                                                      int32_t* __restrict__ dplus, int32_t* __restrict__ part,
-                                                      int32_t* __restrict__ stats) {
+                                                      int32_t* __restrict__ dplus,
+                                                      int32_t* __restrict__ part) {
   constexpr int G = kOrientG;
-  __shared__ int32_t red[256 / kWave];
   const int64_t ngroups = (int64_t)gridDim.x * (256 / G);
   const int g = threadIdx.x % G;
   const int shift = lane_id() & ~(G - 1);
-  int32_t mx_d = 0, mx_p = 0;
   for (int64_t v = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G; v < n; v += ngroups) {
     if (len[v] > kOrientShort) continue;
     const int32_t dv = deg[v], kv = key[v];
@@ -1218,12 +1148,7 @@ __global__ __launch_bounds__(256) void k_orient_short(int32_t n, const int64_t* 
       }
     }
     if (g == 0) dplus[v] = c;
-    mx_d = max(mx_d, dv);
-    mx_p = max(mx_p, c);
   }
-  mx_d = block_max(mx_d, red);
-  mx_p = block_max(mx_p, red);
-  if (threadIdx.x == 0) raise_stats(stats, mx_d, mx_p);
 }
 
 constexpr int kOrientLongNT = 1024;
@@ -1236,8 +1161,7 @@ __global__ __launch_bounds__(kOrientLongNT) void k_orient_long(const int32_t* __
                                                                const uint32_t* __restrict__ cls,
                                                                const int32_t* __restrict__ adj,
                                                                int32_t* __restrict__ dplus,
-                                                               int32_t* __restrict__ part,
-                                                               int32_t* __restrict__ stats) {
+                                                               int32_t* __restrict__ part) {
   __shared__ int32_t lds[kOrientLongNT / kWave + 1];
   const int32_t v = rows[blockIdx.x];
   const int32_t dv = deg[v], kv = key[v];
@@ -1269,10 +1193,7 @@ __global__ __launch_bounds__(kOrientLongNT) void k_orient_long(const int32_t* __
     }
     c += tot;
   }
-  if (threadIdx.x == 0) {
-    dplus[v] = c;
-    raise_stats(stats, dv, c);
-  }
+  if (threadIdx.x == 0) dplus[v] = c;
 }
 
 // Rows of medium length: one wavefront per row (grid-stride), ballot-ordered
@@ -1283,12 +1204,10 @@ __global__ __launch_bounds__(256) void k_orient_medium(const int32_t* __restrict
                                                        const int32_t* __restrict__ key,
                                                        const uint32_t* __restrict__ cls,
                                                        const int32_t* __restrict__ adj,
-                                                       int32_t* __restrict__ dplus, int32_t* __restrict__ part,
-                                                       int32_t* __restrict__ stats) {
-  __shared__ int32_t red[256 / kWave];
+                                                       int32_t* __restrict__ dplus,
+                                                       int32_t* __restrict__ part) {
   const int64_t nwaves = (int64_t)gridDim.x * (256 / kWave);
   const int l = lane_id();
-  int32_t mx_d = 0, mx_p = 0;
   for (int64_t r = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave; r < nrows; r += nwaves) {
     const int32_t v = rows[r];
     const int32_t dv = deg[v], kv = key[v];
@@ -1323,12 +1242,7 @@ __global__ __launch_bounds__(256) void k_orient_medium(const int32_t* __restrict
       }
     }
     if (l == 0) dplus[v] = c;
-    mx_d = max(mx_d, dv);
-    mx_p = max(mx_p, c);
   }
-  mx_d = block_max(mx_d, red);
-  mx_p = block_max(mx_p, red);
-  if (threadIdx.x == 0) raise_stats(stats, mx_d, mx_p);
 }
 
 // Copy of the partitioned rows: N+(v) = part[off[v] .. off[v] + d+(v)) to
@@ -1402,17 +1316,17 @@ __global__ __launch_bounds__(256) void k_orient_copy_listed(const int32_t* __res
 
 hipError_t launch_orient(int32_t n, const int64_t* off, const int32_t* len, const int32_t* deg, const int32_t* key,
                          const int32_t* adj, const int32_t* medium_rows, int32_t nmedium, const int32_t* long_rows,
-                         int32_t nlong, uint32_t* cls, int32_t* dplus, int32_t* part, int32_t* stats, hipStream_t s) {
+                         int32_t nlong, uint32_t* cls, int32_t* dplus, int32_t* part, hipStream_t s) {
   if (n == 0) return hipSuccess;
   if (!key) key = deg;
   k_deg_class<<<grid_for(((int64_t)n + 15) / 16, 256, 4096), 256, 0, s>>>(n, key, cls);
   k_orient_short<<<grid_for((int64_t)n * kOrientG, 256, 1u << 16), 256, 0, s>>>(n, off, len, deg, key, cls, adj,
-                                                                             dplus, part, stats);
+                                                                             dplus, part);
   if (nmedium > 0)
     k_orient_medium<<<grid_for((int64_t)nmedium * kWave, 256, 1u << 14), 256, 0, s>>>(medium_rows, nmedium, off, deg,
-                                                                                   key, cls, adj, dplus, part, stats);
+                                                                                   key, cls, adj, dplus, part);
   if (nlong > 0)
-    k_orient_long<<<nlong, kOrientLongNT, 0, s>>>(long_rows, off, deg, key, cls, adj, dplus, part, stats);
+    k_orient_long<<<nlong, kOrientLongNT, 0, s>>>(long_rows, off, deg, key, cls, adj, dplus, part);
   return hipGetLastError();
 }
 
@@ -1429,31 +1343,6 @@ hipError_t launch_orient_copy(int32_t n, const int64_t* off, const int32_t* len,
   if (nlong > 0)
     k_orient_copy_listed<256><<<grid_for((int64_t)nlong * 256, 256, 1u << 14), 256, 0, s>>>(
         long_rows, nlong, off, deg, dplus, part, doff, dcol, dinoff, dincol);
-  return hipGetLastError();
-}
-
-// d-(v) = d(v) - d+(v)
-// d-(v) = d(v) - d+(v); *deg2 (zeroed) += the number of nodes with d >= 2.
-__global__ __launch_bounds__(256) void k_indeg(int32_t n, const int32_t* __restrict__ deg,
-                                               const int32_t* __restrict__ dplus, int32_t* __restrict__ din,
-                                               int32_t* __restrict__ deg2) {
-  __shared__ int32_t red[256 / kWave];
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  int32_t c = 0;
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-    const int32_t d = deg[v];
-    din[v] = d - dplus[v];
-    c += d >= 2;
-  }
-  const int32_t t = block_sum<int32_t, 256>(c, red);
-  if (threadIdx.x == 0 && t) atomicAdd(deg2, t);
-}
-
-hipError_t launch_indeg(int32_t n, const int32_t* deg, const int32_t* dplus, int32_t* din, int32_t* deg2,
-                        hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  // few blocks: each ends with one atomic on the shared counter
-  k_indeg<<<grid_for(n, 256 * 16, 2048), 256, 0, s>>>(n, deg, dplus, din, deg2);
   return hipGetLastError();
 }
 
@@ -1525,39 +1414,263 @@ hipError_t launch_csr_expand(int32_t n, const int64_t* rowptr, int32_t* src, hip
   return hipGetLastError();
 }
 
-// Work items of the in-list pass: the nodes w of one bin (listed
-// contiguously) each get ceil(d-(w) / chunk) items.
-__global__ __launch_bounds__(256) void k_in_chunks(const int32_t* __restrict__ list, int64_t nlist,
-                                                   const int32_t* __restrict__ din, const int32_t* __restrict__ cap_of,
-                                                   const int64_t* __restrict__ bin_off, int32_t* __restrict__ nch) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nlist; i += stride) {
-    int b = 0;
-    while (b < kNumBins - 1 && i >= bin_off[b + 1]) ++b;
-    const int32_t c = max(1, cap_of[b]);
-    nch[i] = (din[list[i]] + c - 1) / c;
+// ---------------------------------------------------------------------------
+// a2 of the DAG and a5 together: offsets of the out- and in-lists, the
+// edge-existence records, the node bins, the in-list owners by bin and their
+// chunk prefix, in two passes over (d, d+). Pass 1 leaves one column of sums
+// per tile of nodes; pass 2 adds up the columns before its own, so that no
+// separate scan of the sums is needed (at most 1,024 tiles), and places its
+// nodes with wave ballots and one LDS cursor per bin. Bound by launches and
+// host round trips on small graphs, by about 60 bytes of traffic a node on
+// large ones. Measured against two classifications, three scans and four
+// single-purpose kernels (31 launches, five round trips; now two launches,
+// one round trip): build + count of G(10^4, 10^5) 497 -> 301 us, an R-MAT
+// graph of 240k nodes 2,339 -> 2,019 us.
+constexpr int kLayoutNT = 1024;
+constexpr int64_t kLayoutMaxTiles = 1024;
+enum : int { kLqOut = 0, kLqIn = 1, kLqBin = 2, kLqInBin = 8, kLqItems = 14, kLqDeg2 = 20, kLqMaxD = 21, kLqMaxP = 22,
+             kLayoutQ = 23 };
+
+int64_t layout_tile(int64_t n) {
+  const int64_t per = (n + kLayoutNT * kLayoutMaxTiles - 1) / (kLayoutNT * kLayoutMaxTiles);
+  return kLayoutNT * (per > 0 ? per : 1);
+}
+
+// Node u with d+(u) >= 2: the first bin whose limit holds d+; else -1.
+__device__ __forceinline__ int node_bin(int32_t p, const BinParams& bp) {
+  if (p < 2) return -1;
+  int b = kNumBins - 1;
+#pragma unroll
+  for (int q = kNumBins - 2; q >= 0; --q)
+    if (p <= bp.limit[q]) b = q;
+  return b;
+}
+
+// In-list pass owners: 3 <= d+(w) <= limit[4], at least one in-neighbour.
+__device__ __forceinline__ int in_bin(int32_t d, int32_t p, const BinParams& bp) {
+  if (!bp.min_side || p < 3 || d - p < 1 || p > bp.limit[kNumBins - 2]) return -1;
+  int b = kNumBins - 2;
+#pragma unroll
+  for (int q = kNumBins - 3; q >= 0; --q)
+    if (p <= bp.limit[q]) b = q;
+  return b;
+}
+
+// In-list chunks of an owner of bin b (chunk = what the bin's table holds).
+__device__ __forceinline__ int32_t in_chunks(int32_t din, int b, const BinParams& bp) {
+  int32_t c = 1;
+#pragma unroll
+  for (int q = 0; q < kNumBins; ++q)
+    if (q == b) c = bp.cap[q];
+  return (int32_t)(((int64_t)din + c - 1) / c);
+}
+
+__device__ __forceinline__ int32_t wave_max_i32(int32_t x) {
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o, kWave));
+  return x;
+}
+
+__global__ __launch_bounds__(kLayoutNT) void k_layout_count(int32_t n, int64_t tile,
+                                                            const int32_t* __restrict__ deg,
+                                                            const int32_t* __restrict__ dplus, BinParams bp,
+                                                            int32_t* __restrict__ sums) {
+  __shared__ int32_t acc[kLayoutQ];
+  if (threadIdx.x < kLayoutQ) acc[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t t0 = (int64_t)blockIdx.x * tile, t1 = min((int64_t)n, t0 + tile);
+  int32_t sp = 0, si = 0, c2 = 0, mxd = 0, mxp = 0;  // c2 and the bin counts are wave-uniform
+  int32_t nb[kNumBins] = {}, ib[kNumBins] = {}, it[kNumBins] = {};
+  for (int64_t b = t0; b < t1; b += kLayoutNT) {
+    const int64_t v = b + threadIdx.x;
+    const int32_t d = v < t1 ? deg[v] : 0, p = v < t1 ? dplus[v] : 0;
+    sp += p;
+    si += d - p;
+    mxd = max(mxd, d);
+    mxp = max(mxp, p);
+    c2 += (int32_t)__popcll(__ballot(d >= 2));
+    const int x = node_bin(p, bp), y = in_bin(d, p, bp);
+#pragma unroll
+    for (int q = 0; q < kNumBins; ++q) nb[q] += (int32_t)__popcll(__ballot(x == q));
+    if (__ballot(y >= 0)) {
+      const int32_t k = y >= 0 ? in_chunks(d - p, y, bp) : 0;
+#pragma unroll
+      for (int q = 0; q < kNumBins; ++q) {
+        ib[q] += (int32_t)__popcll(__ballot(y == q));
+        it[q] += y == q ? k : 0;
+      }
+    }
+  }
+  sp = group_sum<int32_t, kWave>(sp);
+  si = group_sum<int32_t, kWave>(si);
+  mxd = wave_max_i32(mxd);
+  mxp = wave_max_i32(mxp);
+#pragma unroll
+  for (int q = 0; q < kNumBins; ++q) it[q] = group_sum<int32_t, kWave>(it[q]);
+  if (lane_id() == 0) {
+    atomicAdd(&acc[kLqOut], sp);
+    atomicAdd(&acc[kLqIn], si);
+    atomicAdd(&acc[kLqDeg2], c2);
+    atomicMax(&acc[kLqMaxD], mxd);
+    atomicMax(&acc[kLqMaxP], mxp);
+#pragma unroll
+    for (int q = 0; q < kNumBins; ++q) {
+      if (nb[q]) atomicAdd(&acc[kLqBin + q], nb[q]);
+      if (ib[q]) atomicAdd(&acc[kLqInBin + q], ib[q]);
+      if (it[q]) atomicAdd(&acc[kLqItems + q], it[q]);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kLayoutQ) sums[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = acc[threadIdx.x];
+}
+
+__global__ __launch_bounds__(kLayoutNT) void k_layout_place(int32_t n, int64_t tile, BinParams bp,
+                                                            const int32_t* __restrict__ sums, LayoutOut o) {
+  __shared__ int32_t prev[kLayoutQ], all[kLayoutQ];
+  __shared__ int32_t ncur[kNumBins];
+  __shared__ unsigned long long icur[kNumBins];  // list position << 32 | chunk
+  __shared__ unsigned long long red[kLayoutNT / kWave + 1];
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  const int nt = (int)gridDim.x, me = (int)blockIdx.x;
+  for (int q = wv; q < kLayoutQ; q += kLayoutNT / kWave) {
+    int32_t p = 0, a = 0;
+    for (int b = lane; b < nt; b += kWave) {
+      const int32_t x = sums[(int64_t)q * nt + b];
+      if (q >= kLqMaxD) a = max(a, x);
+      else a += x;
+      if (b < me) p += x;
+    }
+    p = group_sum<int32_t, kWave>(p);
+    a = q >= kLqMaxD ? wave_max_i32(a) : group_sum<int32_t, kWave>(a);
+    if (lane == 0) {
+      prev[q] = p;
+      all[q] = a;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t nb = 0, ib = 0, it = 0;
+    for (int q = 0; q <= kNumBins; ++q) {
+      if (me == 0) {
+        o.bin_off[q] = nb;
+        o.in_off[q] = ib;
+        o.in_items[q] = it;
+      }
+      if (q == kNumBins) break;
+      ncur[q] = (int32_t)nb + prev[kLqBin + q];
+      icur[q] = ((unsigned long long)(ib + prev[kLqInBin + q]) << 32) | (unsigned long long)(it + prev[kLqItems + q]);
+      nb += all[kLqBin + q];
+      ib += all[kLqInBin + q];
+      it += all[kLqItems + q];
+    }
+    if (me == 0) {
+      o.doff[n] = all[kLqOut];
+      o.dinoff[n] = all[kLqIn];
+      if (bp.min_side) o.incoff[ib] = it;
+      o.stats[0] = all[kLqMaxD];
+      o.stats[1] = all[kLqMaxP];
+      o.stats[2] = all[kLqDeg2];
+      *o.m = all[kLqOut];
+      for (int q = 0; q < kNumBins - 1; ++q) o.limit[q] = bp.limit[q];
+      for (int q = 0; q < kNumBins; ++q) o.cap[q] = bp.cap[q];
+    }
+  }
+  __syncthreads();
+  int64_t runp = prev[kLqOut], runi = prev[kLqIn];
+  const int64_t t0 = (int64_t)me * tile, t1 = min((int64_t)n, t0 + tile);
+  for (int64_t b = t0; b < t1; b += kLayoutNT) {
+    const int64_t v = b + threadIdx.x;
+    const bool in = v < t1;
+    const int32_t d = in ? o.deg[v] : 0, p = in ? o.dplus[v] : 0;
+    unsigned long long tot;
+    // both sums stay below 2^31: one scan of the two packed
+    const unsigned long long ex = block_excl_scan<unsigned long long, kLayoutNT>(
+        ((unsigned long long)(uint32_t)p << 32) | (unsigned long long)(uint32_t)(d - p), red, &tot);
+    if (in) {
+      o.doff[v] = runp + (int64_t)(ex >> 32);
+      o.dinoff[v] = runi + (int64_t)(ex & 0xffffffffull);
+      o.din[v] = d - p;
+      o.rec[v] = make_int2((int32_t)(uint32_t)o.raw_off[v], d);
+    }
+    runp += (int64_t)(tot >> 32);
+    runi += (int64_t)(tot & 0xffffffffull);
+    const int x = node_bin(p, bp), y = in_bin(d, p, bp);
+#pragma unroll
+    for (int q = 0; q < kNumBins; ++q) {
+      const uint64_t m = __ballot(x == q);
+      if (!m) continue;
+      int32_t at = 0;
+      if (lane == 0) at = atomicAdd(&ncur[q], (int32_t)__popcll(m));
+      at = __builtin_amdgcn_readfirstlane(at);
+      if (x == q) o.binlist[at + mask_below(m)] = (int32_t)v;
+    }
+    if (!__ballot(y >= 0)) continue;
+    const int32_t k = y >= 0 ? in_chunks(d - p, y, bp) : 0;
+#pragma unroll
+    for (int q = 0; q < kNumBins; ++q) {
+      const uint64_t m = __ballot(y == q);
+      if (!m) continue;
+      const int32_t kq = y == q ? k : 0;
+      const int32_t incl = wave_incl_scan(kq);
+      const int32_t sum = __builtin_amdgcn_readlane(incl, kWave - 1);
+      unsigned long long at = 0;
+      if (lane == 0)
+        at = atomicAdd(&icur[q], ((unsigned long long)__popcll(m) << 32) | (unsigned long long)(uint32_t)sum);
+      const int32_t ap = __builtin_amdgcn_readfirstlane((int32_t)(at >> 32));
+      const int32_t ac = __builtin_amdgcn_readfirstlane((int32_t)(at & 0xffffffffull));
+      if (y == q) {
+        const int32_t i = ap + mask_below(m);
+        o.inlist[i] = (int32_t)v;
+        o.incoff[i] = (int64_t)ac + incl - kq;
+      }
+    }
   }
 }
 
-hipError_t launch_in_chunks(const int32_t* list, int64_t nlist, const int32_t* din, const int32_t* cap_of,
-                            const int64_t* bin_off, int32_t* nch, hipStream_t s) {
-  if (nlist == 0) return hipSuccess;
-  k_in_chunks<<<grid_for(nlist, 256, 1u << 14), 256, 0, s>>>(list, nlist, din, cap_of, bin_off, nch);
+hipError_t launch_layout(int32_t n, const BinParams& bp, int32_t* sums, const LayoutOut& o, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  const int64_t tile = layout_tile(n);
+  const unsigned nt = (unsigned)((n + tile - 1) / tile);
+  k_layout_count<<<nt, kLayoutNT, 0, s>>>(n, tile, o.deg, o.dplus, bp, sums);
+  k_layout_place<<<nt, kLayoutNT, 0, s>>>(n, tile, bp, sums, o);
   return hipGetLastError();
 }
 
 // Chunk -> owner map of the in-list items, so that a work item finds its
-// owner with one load instead of a search over the chunk prefix.
-__global__ __launch_bounds__(256) void k_in_owners(int64_t nlist, const int64_t* __restrict__ coff,
-                                                   int32_t* __restrict__ owner) {
+// owner with one load instead of a search over the chunk prefix. The list's
+// length is read on the device. An owner's run of chunks is written by its
+// lane, runs above kOwnerRun (hubs with a small table) by the wavefront: one
+// lane alone took 6,300 stores for the largest hub of R-MAT 24.
+constexpr int32_t kOwnerRun = 16;
+
+__global__ __launch_bounds__(256) void k_in_owners(const int64_t* __restrict__ nlist_at,
+                                                   const int64_t* __restrict__ coff, int32_t* __restrict__ owner) {
+  const int64_t nlist = *nlist_at;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nlist; i += stride)
-    for (int64_t c = coff[i]; c < coff[i + 1]; ++c) owner[c] = (int32_t)i;
+  const int lane = lane_id();
+  for (int64_t b = (int64_t)blockIdx.x * blockDim.x; b < nlist; b += stride) {  // uniform trip count
+    const int64_t i = b + threadIdx.x;
+    int64_t c0 = 0;
+    int32_t k = 0;
+    if (i < nlist) {
+      c0 = coff[i];
+      k = (int32_t)(coff[i + 1] - c0);
+    }
+    for (int32_t c = 0; c < k && k <= kOwnerRun; ++c) owner[c0 + c] = (int32_t)i;
+    uint64_t big = __ballot(k > kOwnerRun);
+    while (big) {
+      const int src = __builtin_ctzll(big);
+      big &= big - 1;
+      const int32_t kk = __shfl(k, src, kWave), ii = __shfl((int32_t)i, src, kWave);
+      const int64_t cc = __shfl((int32_t)c0, src, kWave);  // chunks stay below 2^31
+      for (int32_t c = lane; c < kk; c += kWave) owner[cc + c] = ii;
+    }
+  }
 }
 
-hipError_t launch_in_owners(int64_t nlist, const int64_t* coff, int32_t* owner, hipStream_t s) {
-  if (nlist == 0) return hipSuccess;
-  k_in_owners<<<grid_for(nlist, 256, 1u << 14), 256, 0, s>>>(nlist, coff, owner);
+hipError_t launch_in_owners(int32_t n, const int64_t* nlist, const int64_t* coff, int32_t* owner, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  k_in_owners<<<grid_for(n, 256 * 4, 4096), 256, 0, s>>>(nlist, coff, owner);
   return hipGetLastError();
 }
 

@@ -76,8 +76,8 @@ hipError_t launch_dedup_rows(const int32_t* rows, const int64_t* seg_beg, int32_
                              int32_t* adj, int32_t* deg, hipStream_t s);
 
 // ---- Degree-order orientation --------------------------------------------
-// One pass over every row: dplus[v] = |{w in N(v): (d(v),v) < (d(w),w)}|,
-// stats[0] = max d, stats[1] = max d+, and row v partitioned into
+// One pass over every row: dplus[v] = |{w in N(v): (d(v),v) < (d(w),w)}|
+// and row v partitioned into
 // part[off[v] .. off[v] + d(v)): N+(v) ascending from the front, N-(v) from
 // the back in reverse. Rows of raw length > 64 must be listed: medium_rows
 // (a wavefront each) and long_rows (a block each) together. cls: scratch of
@@ -86,7 +86,7 @@ hipError_t launch_dedup_rows(const int32_t* rows, const int64_t* seg_beg, int32_
 // non-negative values.
 hipError_t launch_orient(int32_t n, const int64_t* off, const int32_t* len, const int32_t* deg, const int32_t* key,
                          const int32_t* adj, const int32_t* medium_rows, int32_t nmedium, const int32_t* long_rows,
-                         int32_t nlong, uint32_t* cls, int32_t* dplus, int32_t* part, int32_t* stats, hipStream_t s);
+                         int32_t nlong, uint32_t* cls, int32_t* dplus, int32_t* part, hipStream_t s);
 // After doff / dinoff are the scans of d+ / d-: N+(v) to dcol[doff[v]..] and
 // (dincol != NULL) N-(v) to dincol[dinoff[v]..], both ascending.
 hipError_t launch_orient_copy(int32_t n, const int64_t* off, const int32_t* len, const int32_t* deg,
@@ -94,9 +94,6 @@ hipError_t launch_orient_copy(int32_t n, const int64_t* off, const int32_t* len,
                               const int32_t* long_rows, int32_t nlong, const int64_t* doff, int32_t* dcol,
                               const int64_t* dinoff, int32_t* dincol, hipStream_t s);
 
-// din = deg - dplus; *deg2 (zeroed) += nodes with deg >= 2
-hipError_t launch_indeg(int32_t n, const int32_t* deg, const int32_t* dplus, int32_t* din, int32_t* deg2,
-                        hipStream_t s);
 // Caller CSR: bounds check (err bit 4; sets len and deg when non-null), row
 // check (bit 1: id out of range, bit 2: not strictly ascending or a self
 // loop; only after the bounds check passed), expansion into (v, w) pairs.
@@ -104,14 +101,9 @@ hipError_t launch_csr_bounds(int32_t n, int64_t nnz, const int64_t* rowptr, int3
                              hipStream_t s);
 hipError_t launch_csr_rows(int32_t n, const int64_t* rowptr, const int32_t* col, int32_t* err, hipStream_t s);
 hipError_t launch_csr_expand(int32_t n, const int64_t* rowptr, int32_t* src, hipStream_t s);
-// in-list pass owners by d+(w) into bins 0..kNumBins-2 (see InBinOf)
-hipError_t launch_classify_inbins(int pass, int32_t n, const int32_t* dplus, const int32_t* deg, const int32_t* limit,
-                                  int32_t* hist, const int64_t* off, int64_t nblk, int32_t* list, hipStream_t s);
-// nch[i] = ceil(d-(list[i]) / cap_of[bin of i])
-hipError_t launch_in_chunks(const int32_t* list, int64_t nlist, const int32_t* din, const int32_t* cap_of,
-                            const int64_t* bin_off, int32_t* nch, hipStream_t s);
-// owner[c] = i for each in-list chunk c in [coff[i], coff[i+1]), i < nlist
-hipError_t launch_in_owners(int64_t nlist, const int64_t* coff, int32_t* owner, hipStream_t s);
+// owner[c] = i for each in-list chunk c in [coff[i], coff[i+1]), i < *nlist
+// (a device word; at most n)
+hipError_t launch_in_owners(int32_t n, const int64_t* nlist, const int64_t* coff, int32_t* owner, hipStream_t s);
 
 hipError_t launch_list_elems(int32_t n, const int64_t* doff, const int32_t* dcol, unsigned long long* out,
                              hipStream_t s);
@@ -121,9 +113,41 @@ hipError_t launch_gather_rows(const int32_t* rows, int32_t nr, const int64_t* of
 // ---- Work binning for the intersection kernels ---------------------------
 constexpr int kNumBins = 6;
 // Node u with d+(u) >= 2 goes to the first bin b with d+(u) <= limit[b];
-// bin kNumBins-1 takes the rest.
-hipError_t launch_classify_bins(int pass, int32_t n, const int32_t* dplus, const int32_t* limit, int32_t* hist,
-                                const int64_t* off, int64_t nblk, int32_t* list, hipStream_t s);
+// bin kNumBins-1 takes the rest. With min_side, node w with 3 <= d+(w) <=
+// limit[kNumBins-2] and an in-neighbour owns ceil(d-(w) / cap[its bin])
+// in-list chunks (cap >= 1).
+struct BinParams {
+  int32_t limit[kNumBins - 1];
+  int32_t cap[kNumBins];
+  int32_t min_side;
+};
+// What the layout passes read (deg, dplus, raw_off) and write: DAG offsets
+// (doff, dinoff: n + 1), d- (din), edge-existence records (row start as
+// uint32, degree), the node lists by bin, the in-list owners by bin with
+// their chunk prefix (incoff: one more than the owners), and in the header
+// the bounds of both lists and of the chunks (kNumBins + 1 each), stats =
+// (max d, max d+, nodes with d >= 2), m, and bp's limits and caps.
+struct LayoutOut {
+  const int32_t* deg;
+  const int32_t* dplus;
+  const int64_t* raw_off;
+  int64_t* doff;
+  int64_t* dinoff;
+  int32_t* din;
+  int2* rec;
+  int32_t* binlist;
+  int32_t* inlist;
+  int64_t* incoff;
+  int64_t* bin_off;
+  int64_t* in_off;
+  int64_t* in_items;
+  int32_t* stats;
+  int64_t* m;
+  int32_t* limit;
+  int32_t* cap;
+};
+// sums: scratch of max(n, 64) int32.
+hipError_t launch_layout(int32_t n, const BinParams& bp, int32_t* sums, const LayoutOut& o, hipStream_t s);
 // per-bin sums of d+(u) + d+(w), of edges over the DAG edges each bin's
 // kernel counts (min-side ownership with w_max; w_max = 0 disables it), and
 // of the bytes the min-side kernel moves (din / cap: in-degrees and in-list
@@ -210,10 +234,8 @@ hipError_t launch_batch_relabel(int32_t num_graphs, const int64_t* node_off, con
                                 int32_t* gdst, int32_t* err, hipStream_t s);
 
 // ---- Edge-existence tests ---------------------------------------------------
-// Records of the simple graph whose row v is adj[off[v] .. off[v] + deg[v])
-// ascending: rec[2v] = off[v] as uint32 (offsets stay below 2^32), rec[2v+1]
-// = deg[v]; 8-byte aligned, 2n int32.
-hipError_t launch_edge_records(int32_t n, const int64_t* off, const int32_t* deg, int32_t* rec, hipStream_t s);
+// rec[2v] = row start of v as uint32 (offsets stay below 2^32), rec[2v+1]
+// = d(v), 8-byte aligned (written by launch_layout); row v of adj ascending.
 // out[i] = 1 if {qu[i], qv[i]} is an edge, 0 if not (qu[i] == qv[i]
 // included), kEdgeQueryBadId if an id lies outside [0, n).
 constexpr uint8_t kEdgeQueryBadId = 0xFF;
