@@ -61,11 +61,12 @@ constexpr size_t kHdrBytes = 1024;
 
 struct Layout {
   size_t hdr, raw_off, len, deg, dplus, doff, scan_tmp, rowlist, binlist, adj, tmp, dcol, part_cc,
-      part_T, meta, cls_hist, cls_off, din, dinoff, dincol, inlist, inch, incoff, part, hubmap, rec, tot,
+      part_T, meta, spare, spare8, din, dinoff, dincol, inlist, inch, incoff, part, hubmap, rec, tot,
       total;
-  int64_t cls_nblk;
   int64_t max_jobs;
 };
+
+constexpr int kSpareClasses = 13;
 
 Layout make_layout(int64_t n, int64_t m_raw) {
   Layout L{};
@@ -78,11 +79,11 @@ Layout make_layout(int64_t n, int64_t m_raw) {
   L.deg = take(sizeof(int32_t) * n);
   L.dplus = take(sizeof(int32_t) * n);
   L.doff = take(sizeof(int64_t) * (n + 1));
-  L.cls_nblk = classify_blocks(n) > 0 ? classify_blocks(n) : 1;
-  const int64_t cls_elems = (int64_t)kNumRowClasses * L.cls_nblk;
+  // kept at its size: callers size their workspaces and budgets by the total
+  const int64_t cls_elems = (int64_t)kSpareClasses * std::max<int64_t>((n + 4095) / 4096, 1);
   L.scan_tmp = take(sizeof(int64_t) * std::max(scan_tmp_elems(n + 1), scan_tmp_elems(cls_elems + 1)));
-  L.cls_hist = take(sizeof(int32_t) * cls_elems);
-  L.cls_off = take(sizeof(int64_t) * (cls_elems + 1));
+  L.spare = take(sizeof(int32_t) * cls_elems);
+  L.spare8 = take(sizeof(int64_t) * (cls_elems + 1));
   L.rowlist = take(sizeof(int32_t) * n);
   L.binlist = take(sizeof(int32_t) * n);
   L.adj = take(sizeof(int32_t) * 2 * m_raw);
@@ -242,20 +243,6 @@ int sort_large_rows(tricc_graph* g, int32_t nl, const int32_t* rows_dev) {
   return TRICC_OK;
 }
 
-// Runs a two-pass classification; h_off receives nc + 1 class offsets.
-template <typename Launch>
-int classify(tricc_graph* g, int nc, Launch launch, int64_t* d_cls_off, int64_t* h_off) {
-  hipStream_t s = g->stream;
-  const Layout& L = g->L;
-  int32_t* hist = g->at<int32_t>(L.cls_hist);
-  int64_t* off = g->at<int64_t>(L.cls_off);
-  HIPCHK(launch(0, hist, off));
-  HIPCHK(launch_scan_i32(hist, (int64_t)nc * L.cls_nblk, off, g->at<int64_t>(L.scan_tmp), s));
-  HIPCHK(launch_class_offsets(off, L.cls_nblk, nc, d_cls_off, s));
-  HIPCHK(launch(1, hist, off));
-  return sync_copy(h_off, d_cls_off, sizeof(int64_t) * (nc + 1), s);
-}
-
 // DAG offsets, in-degrees, edge records, node bins and in-list items from
 // the degrees (d, d+), into the workspace and its header; no host wait.
 int layout_and_bins(tricc_graph* g) {
@@ -330,6 +317,16 @@ int finish_bins(tricc_graph* g) {
                   (long long)bound, g->tuning.bin_variant[b], cap);
   }
   for (int b = 0; b < kNumBins; ++b) g->info.bin_in_items[b] = g->in_items[b + 1] - g->in_items[b];
+  // the hub variant expects zeroed bitmaps and leaves them zeroed; graphs
+  // without such a node spare the clearing (up to 256 MB). Waited for: a count
+  // may run on another stream.
+  for (int b = 0; b < kNumBins; ++b)
+    if (g->info.bin_count[b] && g->tuning.bin_variant[b] == count_variant_hub()) {
+      HIPCHK(hipMemsetAsync(g->ws + L.hubmap, 0,
+                            sizeof(uint32_t) * (size_t)hub_map_words(g->n) * (size_t)hub_map_slots(g->n), s));
+      HIPCHK(hipStreamSynchronize(s));
+      break;
+    }
   return TRICC_OK;
 }
 
@@ -427,12 +424,10 @@ int build_impl(tricc_graph* g, const int32_t* src, const int32_t* dst, bool pres
   int32_t* adj = g->at<int32_t>(L.adj);
   int rc;
 
-  // the hub variant expects zeroed bitmaps and leaves them zeroed
-  HIPCHK(hipMemsetAsync(g->ws + L.hubmap, 0, sizeof(uint32_t) * (size_t)hub_map_words(n) * hub_map_slots(n), s));
-  if (!presorted) HIPCHK(hipMemsetAsync(hdr, 0, kHdrBytes, s));
-  if (!presorted) HIPCHK(hipMemsetAsync(len, 0, sizeof(int32_t) * (size_t)n, s));
   const int pbits = m_raw > 0 && !presorted ? part_bits(n) : -1;
-  int32_t err = 0;
+  // the host reads the header once, after the row classes: error flags, class sizes
+  alignas(8) char h[kHdrBytes] = {};
+  const int32_t* h32 = reinterpret_cast<const int32_t*>(h);
   if (presorted) {
     // rows in place
   } else if (pbits >= 0) {
@@ -447,18 +442,15 @@ int build_impl(tricc_graph* g, const int32_t* src, const int32_t* dst, bool pres
     int32_t* pv = g->at<int32_t>(L.tmp);
     uint16_t* pu = g->at<uint16_t>(L.dcol);
     int32_t* cur = g->at<int32_t>(L.binlist);
-    HIPCHK(hipMemsetAsync(ptotal, 0, 2 * sizeof(uint32_t) * kPartMaxParts, s));
+    HIPCHK(launch_build_clear(hdr, kHdrBytes / 4, ptotal, 2 * kPartMaxParts, part_may_split(2 * m_raw) ? len : nullptr,
+                              n, s));
     HIPCHK(launch_part_count(src, dst, m_raw, n, pbits, P, ptotal, hdr + kHdrErr, s));
-    if ((rc = sync_copy(&err, hdr + kHdrErr, sizeof(err), s))) return rc;
-    if (err) return fail(TRICC_ERANGE, "edge list holds a node id outside [0, %d)", n);
-    HIPCHK(launch_part_scan(ptotal, P, pstart, cstart, s));
-    HIPCHK(launch_part_place(src, dst, m_raw, pbits, P, pstart, pcur, pv, pu, s));
-    HIPCHK(launch_part_rows(0, pbits, P, n, 2 * m_raw, pstart, cstart, pu, pv, len, raw_off, cur, adj, s));
-    HIPCHK(launch_scan_i32(len, n, raw_off, scan_tmp, s));
-    HIPCHK(hipMemsetAsync(cur, 0, sizeof(int32_t) * (size_t)n, s));
-    HIPCHK(launch_part_rows(1, pbits, P, n, 2 * m_raw, pstart, cstart, pu, pv, len, raw_off, cur, adj, s));
+    HIPCHK(launch_part_place(src, dst, m_raw, n, pbits, P, ptotal, pstart, cstart, pcur, pv, pu, s));
+    HIPCHK(launch_part_rows(pbits, P, n, 2 * m_raw, pstart, cstart, pu, pv, len, raw_off, cur, adj, s));
   } else {
+    HIPCHK(launch_build_clear(hdr, kHdrBytes / 4, nullptr, 0, len, n, s));
     // a1: validate + raw degrees
+    int32_t err = 0;
     HIPCHK(launch_degree_raw(src, dst, m_raw, n, len, hdr + kHdrErr, s));
     if ((rc = sync_copy(&err, hdr + kHdrErr, sizeof(err), s))) return rc;
     if (err) return fail(TRICC_ERANGE, "edge list holds a node id outside [0, %d)", n);
@@ -470,13 +462,21 @@ int build_impl(tricc_graph* g, const int32_t* src, const int32_t* dst, bool pres
   }
   // a3: row sort and dedup
   int32_t* rowlist = g->at<int32_t>(L.rowlist);
-  int64_t* d_cls_off = reinterpret_cast<int64_t*>(g->ws + L.hdr + kHdrClsOff * 4);
   int64_t cls_off[kNumRowClasses + 1] = {};
   if (n > 0) {
-    auto launch = [&](int pass, int32_t* hist, const int64_t* off) {
-      return launch_classify_rows(pass, n, len, deg, hist, off, L.cls_nblk, rowlist, s);
-    };
-    if ((rc = classify(g, kNumRowClasses, launch, d_cls_off, cls_off))) return rc;
+    // the per-tile sums sit in the chunk-count area, as those of the layout
+    HIPCHK(launch_row_classes(n, len, deg, g->at<int32_t>(L.inch), rowlist,
+                              reinterpret_cast<int64_t*>(hdr + kHdrClsOff), s));
+    if ((rc = sync_copy(h, hdr, kHdrBytes, s))) return rc;
+    if (presorted) {
+      const int32_t err = h32[kHdrErr];
+      if (err & 4) return fail(TRICC_EINVAL, "CSR row offsets are not a non-decreasing sequence from 0 to nnz");
+      if (err & 1) return fail(TRICC_ERANGE, "CSR holds a node id outside [0, %d)", n);
+      if (err) return fail(TRICC_EINVAL, "CSR row not strictly ascending or holding its own id");
+    } else if (h32[kHdrErr]) {
+      return fail(TRICC_ERANGE, "edge list holds a node id outside [0, %d)", n);
+    }
+    std::memcpy(cls_off, h32 + kHdrClsOff, sizeof(cls_off));
   }
   int32_t cnt[kNumRowClasses];
   for (int c = 0; c < kNumRowClasses; ++c) cnt[c] = (int32_t)(cls_off[c + 1] - cls_off[c]);
@@ -511,24 +511,21 @@ int csr_build(tricc_graph* g, int64_t nnz, const int64_t* d_rowptr, const int32_
   if (!assume_simple_sorted_symmetric) {
     // rows as (v, w) pairs through the full build; the pair sources sit in
     // the in-list area, which the build writes only after a3
-    HIPCHK(launch_csr_bounds(n, nnz, d_rowptr, nullptr, nullptr, hdr + kHdrErr, s));
+    HIPCHK(launch_csr_bounds(n, nnz, d_rowptr, hdr + kHdrErr, s));
     if ((r = sync_copy(&err, hdr + kHdrErr, sizeof(err), s))) return r;
     if (err) return fail(TRICC_EINVAL, "CSR row offsets are not a non-decreasing sequence from 0 to nnz");
     int32_t* src = g->at<int32_t>(L.dincol);
     HIPCHK(launch_csr_expand(n, d_rowptr, src, s));
     return build_impl(g, src, d_col);
   }
-  int64_t* raw_off = g->at<int64_t>(L.raw_off);
-  int32_t* adj = g->at<int32_t>(L.adj);
-  HIPCHK(hipMemcpyAsync(raw_off, d_rowptr, sizeof(int64_t) * (size_t)(n + 1), hipMemcpyDeviceToDevice, s));
-  HIPCHK(launch_csr_bounds(n, nnz, raw_off, g->at<int32_t>(L.len), g->at<int32_t>(L.deg), hdr + kHdrErr, s));
-  if ((r = sync_copy(&err, hdr + kHdrErr, sizeof(err), s))) return r;
-  if (err) return fail(TRICC_EINVAL, "CSR row offsets are not a non-decreasing sequence from 0 to nnz");
-  if (nnz > 0) HIPCHK(hipMemcpyAsync(adj, d_col, sizeof(int32_t) * (size_t)nnz, hipMemcpyDeviceToDevice, s));
-  HIPCHK(launch_csr_rows(n, raw_off, adj, hdr + kHdrErr, s));
-  if ((r = sync_copy(&err, hdr + kHdrErr, sizeof(err), s))) return r;
-  if (err & 1) return fail(TRICC_ERANGE, "CSR holds a node id outside [0, %d)", n);
-  if (err) return fail(TRICC_EINVAL, "CSR row not strictly ascending or holding its own id");
+  // rows checked as they are copied; the build reads the flags back with the
+  // row classes, before anything follows the row offsets
+  HIPCHK(launch_csr_take(n, nnz, d_rowptr, d_col, g->at<int64_t>(L.raw_off), g->at<int32_t>(L.len),
+                         g->at<int32_t>(L.deg), g->at<int32_t>(L.adj), hdr + kHdrErr, s));
+  if (n == 0) {
+    if ((r = sync_copy(&err, hdr + kHdrErr, sizeof(err), s))) return r;
+    if (err) return fail(TRICC_EINVAL, "CSR row offsets are not a non-decreasing sequence from 0 to nnz");
+  }
   return build_impl(g, nullptr, nullptr, true);
 }
 
@@ -1438,12 +1435,11 @@ int tricc_batch_build(int32_t num_graphs, const int64_t* h_node_off, const int64
   b->h_node_off.assign(h_node_off, h_node_off + num_graphs + 1);
   b->h_edge_off.assign(h_edge_off, h_edge_off + num_graphs + 1);
   if (launch_batch_relabel(num_graphs, b->d_node_off, b->d_edge_off, d_src, d_dst, m_total, b->gsrc, b->gdst,
-                           b->d_err, s) != hipSuccess)
+                           nullptr, s) != hipSuccess)
     return bail(fail(TRICC_EHIP, "relabel launch failed"));
-  int32_t err = 0;
-  if ((rc = sync_copy(&err, b->d_err, sizeof(err), s))) return bail(rc);
-  if (err) return bail(fail(TRICC_ERANGE, "a local node id is outside its graph's [0, n_g)"));
-  if ((rc = build_impl(g, b->gsrc, b->gdst))) return bail(rc);
+  rc = build_impl(g, b->gsrc, b->gdst);
+  if (rc == TRICC_ERANGE) return bail(fail(rc, "a local node id is outside its graph's [0, n_g)"));
+  if (rc) return bail(rc);
   if ((rc = batch_segments(b))) return bail(rc);
   *out = b;
   return TRICC_OK;

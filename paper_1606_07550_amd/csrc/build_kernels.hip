@@ -7,6 +7,8 @@
 // Here all vectors live in one array: row v occupies adj[off[v], off[v+1])
 // of which the first deg[v] entries are the sorted, duplicate-free
 // neighbours once the build is done.
+#include <algorithm>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(kPartNT) void k_part_count(const int32_t* __restric
   for (int64_t e = (int64_t)blockIdx.x * kPartNT + threadIdx.x; e < m_raw; e += stride) {
     const int32_t u = src[e], v = dst[e];
     if ((uint32_t)u >= (uint32_t)n || (uint32_t)v >= (uint32_t)n) { bad = true; continue; }
-    if (u == v) continue;
+    if (u == v) continue;  // dropped, as a pair with an id out of range is (the build is refused later)
     atomicAdd(&hist[u >> pbits], 1u);
     atomicAdd(&hist[v >> pbits], 1u);
   }
@@ -196,8 +198,12 @@ __global__ __launch_bounds__(kPartNT) void k_part_count(const int32_t* __restric
     if (hist[b]) atomicAdd(&ptotal[b], hist[b]);
 }
 
+// Chunks of a partition of t entries (an empty one has one too: its block
+// writes the empty rows' offsets).
+__device__ __forceinline__ int64_t part_chunks(int64_t t) { return t > 0 ? (t + kRowsChunk - 1) / kRowsChunk : 1; }
+
 // Single block: pstart = exclusive scan of the partition sizes, cstart =
-// exclusive scan of their chunk counts (ceil(size / kRowsChunk)).
+// exclusive scan of their chunk counts.
 __global__ __launch_bounds__(1024) void k_part_scan(const uint32_t* __restrict__ ptotal, int32_t P,
                                                     int64_t* __restrict__ pstart, int64_t* __restrict__ cstart) {
   __shared__ int64_t lds[1024 / kWave + 1];
@@ -205,7 +211,7 @@ __global__ __launch_bounds__(1024) void k_part_scan(const uint32_t* __restrict__
   for (int32_t base = 0; base < P; base += 1024) {
     const int32_t i = base + threadIdx.x;
     const int64_t t = i < P ? (int64_t)ptotal[i] : 0;
-    const int64_t ch = (t + kRowsChunk - 1) / kRowsChunk;
+    const int64_t ch = i < P ? part_chunks(t) : 0;
     int64_t tot0, tot1;
     const int64_t e0 = block_excl_scan<int64_t, 1024>(t, lds, &tot0);
     const int64_t e1 = block_excl_scan<int64_t, 1024>(ch, lds, &tot1);
@@ -222,9 +228,16 @@ __global__ __launch_bounds__(1024) void k_part_scan(const uint32_t* __restrict__
   }
 }
 
-// Pass B: ids are known to be in range (pass A checked them).
+// A pair that pass B places: both ids in range (pass A flags the others, and
+// counts as pass B does) and not a self loop.
+__device__ __forceinline__ bool pair_ok(int32_t u, int32_t v, int32_t n) {
+  return (uint32_t)u < (uint32_t)n && (uint32_t)v < (uint32_t)n && u != v;
+}
+
+// Pass B.
 __global__ __launch_bounds__(kPartNT) void k_part_place(const int32_t* __restrict__ src,
-                                                       const int32_t* __restrict__ dst, int64_t m_raw, int pbits,
+                                                       const int32_t* __restrict__ dst, int64_t m_raw, int32_t n,
+                                                       int pbits,
                                                        int32_t P, const int64_t* __restrict__ pstart,
                                                        uint32_t* __restrict__ pcur, int32_t* __restrict__ pv,
                                                        uint16_t* __restrict__ pu) {
@@ -250,7 +263,7 @@ __global__ __launch_bounds__(kPartNT) void k_part_place(const int32_t* __restric
     uint32_t ra[kPartPairs], rc[kPartPairs];
 #pragma unroll
     for (int k = 0; k < kPartPairs; ++k) {
-      if (a[k] == c[k]) a[k] = -1;  // self loop or past the end
+      if (!pair_ok(a[k], c[k], n)) a[k] = -1;  // also past the end
       if (a[k] >= 0) {
         ra[k] = atomicAdd(&hist[a[k] >> pbits], 1u);
         rc[k] = atomicAdd(&hist[c[k] >> pbits], 1u);
@@ -288,8 +301,10 @@ constexpr int kStagedPer = kStagedPairs / kStagedNT;
 
 __global__ __launch_bounds__(kStagedNT) void k_part_place_staged(const int32_t* __restrict__ src,
                                                                  const int32_t* __restrict__ dst, int64_t m_raw,
-                                                                 int pbits, int32_t P,
-                                                                 const int64_t* __restrict__ pstart,
+                                                                 int32_t n, int pbits, int32_t P,
+                                                                 const uint32_t* __restrict__ ptotal,
+                                                                 int64_t* __restrict__ pstart,
+                                                                 int64_t* __restrict__ cstart,
                                                                  uint32_t* __restrict__ pcur, int32_t* __restrict__ pv,
                                                                  uint16_t* __restrict__ pu) {
   __shared__ uint32_t cnt[kStagedParts];   // entries of each partition in the tile
@@ -300,7 +315,26 @@ __global__ __launch_bounds__(kStagedNT) void k_part_place_staged(const int32_t* 
   __shared__ uint32_t red[kStagedNT / kWave + 1];
   const int64_t ntiles = (m_raw + kStagedPairs - 1) / kStagedPairs;
   const int32_t lmask = (1 << pbits) - 1;
-  constexpr int BPT = kStagedParts / kStagedNT;  // bins per thread in the scan
+  static_assert(kStagedParts == kStagedNT, "one partition per thread in the scans");
+  // every block scans the partition sizes itself (one launch less); thread b
+  // keeps partition b's start, block 0 writes the starts for the later passes
+  __shared__ int64_t red64[kStagedNT / kWave + 1];
+  const int64_t psize = threadIdx.x < P ? (int64_t)ptotal[threadIdx.x] : 0;
+  int64_t all;
+  const int64_t mystart = block_excl_scan<int64_t, kStagedNT>(psize, red64, &all);
+  if (blockIdx.x == 0) {
+    int64_t chunks;
+    const int64_t mychunk =
+        block_excl_scan<int64_t, kStagedNT>(threadIdx.x < P ? part_chunks(psize) : 0, red64, &chunks);
+    if (threadIdx.x < P) {
+      pstart[threadIdx.x] = mystart;
+      cstart[threadIdx.x] = mychunk;
+    }
+    if (threadIdx.x == 0) {
+      pstart[P] = all;
+      cstart[P] = chunks;
+    }
+  }
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     for (int b = threadIdx.x; b < P; b += kStagedNT) cnt[b] = 0;
     __syncthreads();
@@ -319,32 +353,19 @@ __global__ __launch_bounds__(kStagedNT) void k_part_place_staged(const int32_t* 
     }
 #pragma unroll
     for (int k = 0; k < kStagedPer; ++k) {
-      if (a[k] == c[k]) a[k] = -1;  // self loop or past the end
+      if (!pair_ok(a[k], c[k], n)) a[k] = -1;  // also past the end
       if (a[k] >= 0) {
         ra[k] = atomicAdd(&cnt[a[k] >> pbits], 1u);
         rc[k] = atomicAdd(&cnt[c[k] >> pbits], 1u);
       }
     }
     __syncthreads();
-    // exclusive scan of cnt over the partitions (BPT consecutive bins per thread)
-    uint32_t loc[BPT > 0 ? BPT : 1];
-    uint32_t sum = 0;
-#pragma unroll
-    for (int q = 0; q < BPT; ++q) {
-      const int b = threadIdx.x * BPT + q;
-      loc[q] = b < P ? cnt[b] : 0u;
-      sum += loc[q];
-    }
+    const uint32_t mine = threadIdx.x < P ? cnt[threadIdx.x] : 0u;
     uint32_t tot;
-    uint32_t run = block_excl_scan<uint32_t, kStagedNT>(sum, red, &tot);
-#pragma unroll
-    for (int q = 0; q < BPT; ++q) {
-      const int b = threadIdx.x * BPT + q;
-      if (b < P) {
-        lst[b] = run;
-        if (loc[q]) hoff[b] = pstart[b] + atomicAdd(&pcur[b], loc[q]);
-      }
-      run += loc[q];
+    const uint32_t run = block_excl_scan<uint32_t, kStagedNT>(mine, red, &tot);
+    if (threadIdx.x < P) {
+      lst[threadIdx.x] = run;
+      if (mine) hoff[threadIdx.x] = mystart + atomicAdd(&pcur[threadIdx.x], mine);
     }
     __syncthreads();
 #pragma unroll
@@ -369,34 +390,77 @@ __global__ __launch_bounds__(kStagedNT) void k_part_place_staged(const int32_t* 
   }
 }
 
-// Passes C (pass 0) and D (pass 1). Block c takes chunk c; blocks past the
-// last chunk exit. A partition held by one chunk writes its rows directly;
-// one spread over several chunks combines them with global atomics (len for
-// C, the zeroed cursors cur for D).
-__global__ __launch_bounds__(kRowsNT) void k_part_rows(int pass, int pbits, int32_t P, int32_t n,
+// Passes C and D. A partition held by one chunk is finished by one block of
+// mode 0: row lengths, their prefix inside the partition (whose slice starts
+// at pstart[p], so no scan over all nodes is needed) and the entries. One
+// spread over several chunks takes three launches: mode 0 adds up its row
+// lengths (global atomics on the zeroed len), mode 1 (one block per
+// partition) turns them into row offsets and clears the cursors cur, mode 2
+// reserves each row's range and places the entries. The launcher leaves
+// modes 1 and 2 out when no partition can have two chunks.
+__device__ __forceinline__ void part_offsets(int32_t v0, int32_t W, int64_t pb, int64_t total, int32_t n,
+                                             uint32_t* cnt, const int32_t* __restrict__ len,
+                                             int64_t* __restrict__ raw_off, int32_t* __restrict__ cur,
+                                             uint32_t* red) {
+  // cnt (LDS) = row lengths (loaded from len when it is given) -> offsets
+  // inside the partition; one run of W / kRowsNT rows per thread
+  if (len) {
+    for (int j = threadIdx.x; j < W; j += kRowsNT) {
+      cnt[j] = (uint32_t)len[v0 + j];
+      cur[v0 + j] = 0;
+    }
+    __syncthreads();
+  }
+  const int per = (W + kRowsNT - 1) / kRowsNT;
+  const int j0 = threadIdx.x * per, j1 = min(W, j0 + per);
+  uint32_t sum = 0;
+  for (int j = j0; j < j1; ++j) sum += cnt[j];
+  uint32_t tot;
+  uint32_t run = block_excl_scan<uint32_t, kRowsNT>(sum, red, &tot);
+  for (int j = j0; j < j1; ++j) {
+    const uint32_t k = cnt[j];
+    cnt[j] = run;
+    run += k;
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < W; j += kRowsNT) raw_off[v0 + j] = pb + (int64_t)cnt[j];
+  if (threadIdx.x == 0 && v0 + W == n) raw_off[n] = total;
+}
+
+__global__ __launch_bounds__(kRowsNT) void k_part_rows(int mode, int pbits, int32_t P, int32_t n,
                                                       const int64_t* __restrict__ pstart,
                                                       const int64_t* __restrict__ cstart,
                                                       const uint16_t* __restrict__ pu,
                                                       const int32_t* __restrict__ pv, int32_t* __restrict__ len,
-                                                      const int64_t* __restrict__ raw_off,
+                                                      int64_t* __restrict__ raw_off,
                                                       int32_t* __restrict__ cur, int32_t* __restrict__ adj) {
   __shared__ uint32_t cnt[1 << kPartMaxBits];
-  const int64_t c = blockIdx.x;
-  if (c >= cstart[P]) return;
-  // partition of chunk c: the last p with cstart[p] <= c (empty partitions
-  // share their start with the next one and are skipped)
-  int32_t lo = 0, hi = P - 1;
-  while (lo < hi) {
-    const int32_t mid = (lo + hi + 1) >> 1;
-    if (cstart[mid] <= c) lo = mid; else hi = mid - 1;
+  __shared__ uint32_t red[kRowsNT / kWave + 1];
+  int32_t p;
+  int64_t c = 0;
+  if (mode == 1) {
+    p = (int32_t)blockIdx.x;
+  } else {
+    c = blockIdx.x;
+    if (c >= cstart[P]) return;
+    int32_t lo = 0, hi = P - 1;  // partition of chunk c: the last p with cstart[p] <= c
+    while (lo < hi) {
+      const int32_t mid = (lo + hi + 1) >> 1;
+      if (cstart[mid] <= c) lo = mid; else hi = mid - 1;
+    }
+    p = lo;
   }
-  const int32_t p = lo;
-  const int64_t pb = pstart[p];
-  const int64_t i0 = pb + (c - cstart[p]) * kRowsChunk;
-  const int64_t i1 = min(pstart[p + 1], i0 + kRowsChunk);
   const bool single = cstart[p + 1] - cstart[p] == 1;
+  if (mode != 0 && single) return;  // finished by mode 0
+  const int64_t pb = pstart[p];
   const int32_t v0 = p << pbits;
   const int32_t W = min(1 << pbits, n - v0);
+  if (mode == 1) {
+    part_offsets(v0, W, pb, pstart[P], n, cnt, len, raw_off, cur, red);
+    return;
+  }
+  const int64_t i0 = pb + (c - cstart[p]) * kRowsChunk;
+  const int64_t i1 = min(pstart[p + 1], i0 + kRowsChunk);
   for (int j = threadIdx.x; j < W; j += kRowsNT) cnt[j] = 0;
   __syncthreads();
   // aligned groups of 8 entries, one 16-byte load of local rows each (the
@@ -423,20 +487,21 @@ __global__ __launch_bounds__(kRowsNT) void k_part_rows(int pass, int pbits, int3
     }
   }
   __syncthreads();
-  if (pass == 0) {
+  if (single) {
+    for (int j = threadIdx.x; j < W; j += kRowsNT) len[v0 + j] = (int32_t)cnt[j];
+    __syncthreads();
+    part_offsets(v0, W, pb, pstart[P], n, cnt, nullptr, raw_off, nullptr, red);
+  } else if (mode == 0) {
     for (int j = threadIdx.x; j < W; j += kRowsNT) {
       const uint32_t k = cnt[j];
-      if (!k) continue;
-      if (single) len[v0 + j] = (int32_t)k;
-      else atomicAdd(&len[v0 + j], (int32_t)k);
+      if (k) atomicAdd(&len[v0 + j], (int32_t)k);
     }
     return;
-  }
-  for (int j = threadIdx.x; j < W; j += kRowsNT) {
-    const uint32_t k = cnt[j];
-    if (!k) continue;
-    const int32_t at = single ? 0 : atomicAdd(&cur[v0 + j], (int32_t)k);
-    cnt[j] = (uint32_t)(raw_off[v0 + j] - pb) + (uint32_t)at;
+  } else {
+    for (int j = threadIdx.x; j < W; j += kRowsNT) {
+      const uint32_t k = cnt[j];
+      if (k) cnt[j] = (uint32_t)(raw_off[v0 + j] - pb) + (uint32_t)atomicAdd(&cur[v0 + j], (int32_t)k);
+    }
   }
   __syncthreads();
   for (int64_t gs = g0 + 8 * (int64_t)threadIdx.x; gs < i1; gs += 8 * kRowsNT * kRowsUnroll) {
@@ -464,6 +529,26 @@ __global__ __launch_bounds__(kRowsNT) void k_part_rows(int pass, int pbits, int3
   }
 }
 
+// Clears what the build accumulates into: the header, the partition counters
+// and (len given) the row lengths.
+__global__ __launch_bounds__(256) void k_build_clear(int32_t* __restrict__ hdr, int32_t words,
+                                                     uint32_t* __restrict__ part, int32_t nparts,
+                                                     int32_t* __restrict__ len, int32_t n) {
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  for (int64_t i = i0; i < words; i += stride) hdr[i] = 0;
+  for (int64_t i = i0; i < nparts; i += stride) part[i] = 0;
+  if (len)
+    for (int64_t i = i0; i < n; i += stride) len[i] = 0;
+}
+
+hipError_t launch_build_clear(int32_t* hdr, int32_t words, uint32_t* part, int32_t nparts, int32_t* len, int32_t n,
+                              hipStream_t s) {
+  const int64_t most = std::max<int64_t>(std::max(words, nparts), len ? n : 0);
+  k_build_clear<<<grid_for(most, 256 * 4, 2048), 256, 0, s>>>(hdr, words, part, nparts, len, n);
+  return hipGetLastError();
+}
+
 hipError_t launch_part_count(const int32_t* src, const int32_t* dst, int64_t m_raw, int32_t n, int pbits, int32_t P,
                              uint32_t* ptotal, int32_t* err, hipStream_t s) {
   if (m_raw == 0) return hipSuccess;
@@ -471,31 +556,49 @@ hipError_t launch_part_count(const int32_t* src, const int32_t* dst, int64_t m_r
   return hipGetLastError();
 }
 
-hipError_t launch_part_scan(const uint32_t* ptotal, int32_t P, int64_t* pstart, int64_t* cstart, hipStream_t s) {
-  k_part_scan<<<1, 1024, 0, s>>>(ptotal, P, pstart, cstart);
-  return hipGetLastError();
-}
-
-hipError_t launch_part_place(const int32_t* src, const int32_t* dst, int64_t m_raw, int pbits, int32_t P,
-                             const int64_t* pstart, uint32_t* pcur, int32_t* pv, uint16_t* pu, hipStream_t s) {
+// Partition starts and chunk starts, then pass B.
+hipError_t launch_part_place(const int32_t* src, const int32_t* dst, int64_t m_raw, int32_t n, int pbits, int32_t P,
+                             const uint32_t* ptotal, int64_t* pstart, int64_t* cstart, uint32_t* pcur, int32_t* pv,
+                             uint16_t* pu, hipStream_t s) {
   if (m_raw == 0) return hipSuccess;
   if (P <= kStagedParts) {
-    k_part_place_staged<<<grid_for(m_raw, kStagedPairs, 4096), kStagedNT, 0, s>>>(src, dst, m_raw, pbits, P, pstart,
-                                                                                 pcur, pv, pu);
+    k_part_place_staged<<<grid_for(m_raw, kStagedPairs, 4096), kStagedNT, 0, s>>>(
+        src, dst, m_raw, n, pbits, P, ptotal, pstart, cstart, pcur, pv, pu);
     return hipGetLastError();
   }
-  k_part_place<<<grid_for(m_raw, (int)kPartTile, 4096), kPartNT, 0, s>>>(src, dst, m_raw, pbits, P, pstart, pcur,
+  k_part_scan<<<1, 1024, 0, s>>>(ptotal, P, pstart, cstart);
+  k_part_place<<<grid_for(m_raw, (int)kPartTile, 4096), kPartNT, 0, s>>>(src, dst, m_raw, n, pbits, P, pstart, pcur,
                                                                          pv, pu);
   return hipGetLastError();
 }
 
-hipError_t launch_part_rows(int pass, int pbits, int32_t P, int32_t n, int64_t max_entries, const int64_t* pstart,
+bool part_may_split(int64_t entries) { return entries > kRowsChunk; }
+
+hipError_t launch_part_rows(int pbits, int32_t P, int32_t n, int64_t max_entries, const int64_t* pstart,
                             const int64_t* cstart, const uint16_t* pu, const int32_t* pv, int32_t* len,
-                            const int64_t* raw_off, int32_t* cur, int32_t* adj, hipStream_t s) {
+                            int64_t* raw_off, int32_t* cur, int32_t* adj, hipStream_t s) {
   // every partition has at most ceil(size / chunk) <= size / chunk + 1 chunks
-  const int64_t blocks = max_entries / kRowsChunk + P + 1;
-  k_part_rows<<<(unsigned)blocks, kRowsNT, 0, s>>>(pass, pbits, P, n, pstart, cstart, pu, pv, len, raw_off, cur, adj);
+  const unsigned blocks = (unsigned)(max_entries / kRowsChunk + P);
+  k_part_rows<<<blocks, kRowsNT, 0, s>>>(0, pbits, P, n, pstart, cstart, pu, pv, len, raw_off, cur, adj);
+  if (part_may_split(max_entries)) {
+    k_part_rows<<<(unsigned)P, kRowsNT, 0, s>>>(1, pbits, P, n, pstart, cstart, pu, pv, len, raw_off, cur, adj);
+    k_part_rows<<<blocks, kRowsNT, 0, s>>>(2, pbits, P, n, pstart, cstart, pu, pv, len, raw_off, cur, adj);
+  }
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Tiles of nodes of the two-pass layouts (row classes, DAG layout): at most
+// kLayoutMaxTiles, so that every block of the second pass can add up the sums
+// of the tiles before its own. sums holds one column per tile.
+constexpr int kLayoutNT = 1024;
+constexpr int64_t kLayoutMaxTiles = 1024;
+enum : int { kLqOut = 0, kLqIn = 1, kLqBin = 2, kLqInBin = 8, kLqItems = 14, kLqDeg2 = 20, kLqMaxD = 21, kLqMaxP = 22,
+             kLayoutQ = 23 };
+
+int64_t layout_tile(int64_t n) {
+  const int64_t per = (n + kLayoutNT * kLayoutMaxTiles - 1) / (kLayoutNT * kLayoutMaxTiles);
+  return kLayoutNT * (per > 0 ? per : 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -516,60 +619,94 @@ __device__ __forceinline__ int row_class(int32_t len) {
   return kRowLarge;
 }
 
-// Classification of [0, n) into classes with per-block histograms: pass 0
-// counts each block's members per class (LDS atomics) into
-// hist[c * nblk + blk]; the host scans hist; pass 1 writes each member at
-// off[c * nblk + blk] + its rank inside the block. No global atomics.
-constexpr int kClsThreads = 256;
-constexpr int64_t kClsChunk = 4096;
-
-int64_t classify_blocks(int64_t n) { return (n + kClsChunk - 1) / kClsChunk; }
-
-struct RowClassOf {  // by raw row length; trivial rows are not listed
-  const int32_t* len;
-  int32_t* deg;
-  __device__ int operator()(int64_t v, int pass) const {
-    const int32_t L = len[v];
-    const int c = row_class(L);
-    if (c == kRowTrivial) {
-      if (pass == 0) deg[v] = L;
-      return -1;
-    }
-    return c;
-  }
-};
-
-template <int NC, class F>
-__global__ __launch_bounds__(kClsThreads) void k_classify(int pass, int64_t n, F f, int32_t* __restrict__ hist,
-                                                          const int64_t* __restrict__ off, int64_t nblk,
-                                                          int32_t* __restrict__ list) {
-  __shared__ int32_t cnt[NC];
-  if (threadIdx.x < NC) cnt[threadIdx.x] = 0;
+// Rows by class, listed class-major: pass 1 leaves each tile's class counts,
+// pass 2 adds up the counts of the classes and tiles before its own and
+// places its rows with wave ballots and one LDS cursor per class. Rows of
+// length <= 1 are not listed; their degree is set here. Tiles as for the DAG
+// layout (at most 1,024 of them), so no scan stands between the passes: as a
+// histogram, a three-launch scan, an offset gather and a placement it took
+// six launches.
+__global__ __launch_bounds__(kLayoutNT) void k_rows_count(int32_t n, int64_t tile, const int32_t* __restrict__ len,
+                                                          int32_t* __restrict__ deg, int32_t* __restrict__ sums) {
+  __shared__ int32_t acc[kNumRowClasses];
+  if (threadIdx.x < kNumRowClasses) acc[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t b0 = (int64_t)blockIdx.x * kClsChunk;
-  const int64_t b1 = min(n, b0 + kClsChunk);
-  for (int64_t v = b0 + threadIdx.x; v < b1; v += kClsThreads) {
-    const int c = f(v, pass);
-    if (c < 0) continue;
-    const int32_t r = atomicAdd(&cnt[c], 1);
-    if (pass == 1) list[off[(int64_t)c * nblk + blockIdx.x] + r] = (int32_t)v;
+  const int64_t t0 = (int64_t)blockIdx.x * tile, t1 = min((int64_t)n, t0 + tile);
+  int32_t nc[kNumRowClasses] = {};  // wave-uniform
+  for (int64_t b = t0; b < t1; b += kLayoutNT) {
+    const int64_t v = b + threadIdx.x;
+    int c = kRowTrivial;
+    if (v < t1) {
+      const int32_t L = len[v];
+      c = row_class(L);
+      if (c == kRowTrivial) deg[v] = L;
+    }
+#pragma unroll
+    for (int q = kRowTrivial + 1; q < kNumRowClasses; ++q) nc[q] += (int32_t)__popcll(__ballot(c == q));
   }
-  if (pass == 0) {
-    __syncthreads();
-    if (threadIdx.x < NC) hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = cnt[threadIdx.x];
+  if (lane_id() == 0)
+#pragma unroll
+    for (int q = kRowTrivial + 1; q < kNumRowClasses; ++q)
+      if (nc[q]) atomicAdd(&acc[q], nc[q]);
+  __syncthreads();
+  if (threadIdx.x < kNumRowClasses) sums[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = acc[threadIdx.x];
+}
+
+__global__ __launch_bounds__(kLayoutNT) void k_rows_place(int32_t n, int64_t tile, const int32_t* __restrict__ len,
+                                                          const int32_t* __restrict__ sums,
+                                                          int32_t* __restrict__ list, int64_t* __restrict__ cls_off) {
+  __shared__ int32_t prev[kNumRowClasses], all[kNumRowClasses], cur[kNumRowClasses];
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  const int nt = (int)gridDim.x, me = (int)blockIdx.x;
+  if (wv < kNumRowClasses) {
+    int32_t p = 0, a = 0;
+    for (int b = lane; b < nt; b += kWave) {
+      const int32_t x = sums[(int64_t)wv * nt + b];
+      a += x;
+      if (b < me) p += x;
+    }
+    p = group_sum<int32_t, kWave>(p);
+    a = group_sum<int32_t, kWave>(a);
+    if (lane == 0) {
+      prev[wv] = p;
+      all[wv] = a;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t o = 0;
+    for (int q = 0; q < kNumRowClasses; ++q) {
+      if (me == 0) cls_off[q] = o;
+      cur[q] = o + prev[q];
+      o += all[q];
+    }
+    if (me == 0) cls_off[kNumRowClasses] = o;
+  }
+  __syncthreads();
+  const int64_t t0 = (int64_t)me * tile, t1 = min((int64_t)n, t0 + tile);
+  for (int64_t b = t0; b < t1; b += kLayoutNT) {
+    const int64_t v = b + threadIdx.x;
+    const int c = v < t1 ? row_class(len[v]) : kRowTrivial;
+#pragma unroll
+    for (int q = kRowTrivial + 1; q < kNumRowClasses; ++q) {
+      const uint64_t m = __ballot(c == q);
+      if (!m) continue;
+      int32_t at = 0;
+      if (lane == 0) at = atomicAdd(&cur[q], (int32_t)__popcll(m));
+      at = __builtin_amdgcn_readfirstlane(at);
+      if (c == q) list[at + mask_below(m)] = (int32_t)v;
+    }
   }
 }
 
-__global__ void k_class_offsets(const int64_t* __restrict__ off, int64_t nblk, int nc, int64_t* __restrict__ cls_off) {
-  const int c = threadIdx.x;
-  if (c <= nc) cls_off[c] = off[(int64_t)c * nblk];
-}
-
-hipError_t launch_classify_rows(int pass, int32_t n, const int32_t* len, int32_t* deg, int32_t* hist,
-                                const int64_t* off, int64_t nblk, int32_t* list, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_classify<kNumRowClasses, RowClassOf><<<(unsigned)nblk, kClsThreads, 0, s>>>(pass, n, RowClassOf{len, deg}, hist,
-                                                                               off, nblk, list);
+hipError_t launch_row_classes(int32_t n, const int32_t* len, int32_t* deg, int32_t* sums, int32_t* list,
+                              int64_t* cls_off, hipStream_t s) {
+  static_assert(kNumRowClasses <= kLayoutNT / kWave && kNumRowClasses <= kLayoutQ, "one wavefront per class");
+  if (n <= 0) return hipSuccess;
+  const int64_t tile = layout_tile(n);
+  const unsigned nt = (unsigned)((n + tile - 1) / tile);
+  k_rows_count<<<nt, kLayoutNT, 0, s>>>(n, tile, len, deg, sums);
+  k_rows_place<<<nt, kLayoutNT, 0, s>>>(n, tile, len, sums, list, cls_off);
   return hipGetLastError();
 }
 
@@ -581,11 +718,6 @@ __global__ void k_gather_offsets(const int64_t* __restrict__ prefix, const int64
 hipError_t launch_gather_offsets(const int64_t* prefix, const int64_t* at, int k, int64_t* out, hipStream_t s) {
   if (k <= 0) return hipSuccess;
   k_gather_offsets<<<(unsigned)std::min(1024, (k + 255) / 256), 256, 0, s>>>(prefix, at, k, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_class_offsets(const int64_t* off, int64_t nblk, int nc, int64_t* cls_off, hipStream_t s) {
-  k_class_offsets<<<1, 64, 0, s>>>(off, nblk, nc, cls_off);
   return hipGetLastError();
 }
 
@@ -1348,41 +1480,86 @@ hipError_t launch_orient_copy(int32_t n, const int64_t* off, const int32_t* len,
 
 // ---------------------------------------------------------------------------
 // Graphs handed over as a CSR (rows d_col[rowptr[v] .. rowptr[v+1])).
-// k_csr_bounds: rowptr[0] == 0, non-decreasing, rowptr[n] == nnz (else bit
-// 4 of err); len = deg = row lengths. Rows are read only after this passed.
+// Row v's bounds: rowptr[0] == 0, non-decreasing, rowptr[n] == nnz.
+__device__ __forceinline__ bool csr_row_ok(int64_t v, int32_t n, int64_t nnz, int64_t b, int64_t e) {
+  return !(b > e || b < 0 || e > nnz || (v == 0 && b != 0) || (v == n - 1 && e != nnz));
+}
+
 __global__ __launch_bounds__(256) void k_csr_bounds(int32_t n, int64_t nnz, const int64_t* __restrict__ rowptr,
-                                                    int32_t* __restrict__ len, int32_t* __restrict__ deg,
                                                     int32_t* __restrict__ err) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   bool bad = false;
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-    const int64_t b = rowptr[v], e = rowptr[v + 1];
-    if (b > e || b < 0 || e > nnz || (v == 0 && b != 0) || (v == n - 1 && e != nnz)) bad = true;
-    const int32_t l = bad ? 0 : (int32_t)(e - b);
-    if (len) len[v] = l;
-    if (deg) deg[v] = l;
-  }
+  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride)
+    bad |= !csr_row_ok(v, n, nnz, rowptr[v], rowptr[v + 1]);
   if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0 && (rowptr[0] != 0 || nnz != 0)) bad = true;
   if (__ballot(bad) && lane_id() == 0) atomicOr(err, 4);
 }
 
-// One wavefront per row: ids in [0, n) (else bit 1), strictly ascending and
-// without the row's own id (else bit 2).
-__global__ __launch_bounds__(256) void k_csr_rows(int32_t n, const int64_t* __restrict__ rowptr,
-                                                  const int32_t* __restrict__ col, int32_t* __restrict__ err) {
-  const int lane = lane_id();
-  const int64_t nw = (int64_t)gridDim.x * (blockDim.x / kWave);
-  bool range = false, order = false;
-  for (int64_t v = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; v < n; v += nw) {
+// Rows taken as they are: off = rowptr, len = deg = row lengths (0 for a row
+// whose bounds are bad: bit 4 of err), adj = col, and the rows checked: ids in
+// [0, n) (else bit 1), strictly ascending and without the row's own id (else
+// bit 2). Entries are shared out evenly, whatever the rows' lengths: one
+// wavefront per row took 446 us at R-MAT 20, most of them on its few rows of
+// 10^4 to 6 10^4 entries. A step down from col[i - 1] to col[i] is right only
+// where a row starts, so an entry searches the row offsets only there (at
+// most once per row in a well-formed CSR), and a row's own id is searched in
+// its sorted row. Both searches stay inside the arrays whatever they hold.
+__global__ __launch_bounds__(256) void k_csr_take(int32_t n, int64_t nnz, const int64_t* __restrict__ rowptr,
+                                                  const int32_t* __restrict__ col, int64_t* __restrict__ off,
+                                                  int32_t* __restrict__ len, int32_t* __restrict__ deg,
+                                                  int32_t* __restrict__ adj, int32_t* __restrict__ err) {
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  int32_t bad = 0;
+  for (int64_t v = t; v < n; v += stride) {
     const int64_t b = rowptr[v], e = rowptr[v + 1];
-    for (int64_t i = b + lane; i < e; i += kWave) {
-      const int32_t x = col[i];
-      if ((uint32_t)x >= (uint32_t)n) range = true;
-      if (x == (int32_t)v || (i > b && col[i - 1] >= x)) order = true;
+    const bool ok = csr_row_ok(v, n, nnz, b, e);
+    if (!ok) bad |= 4;
+    const int32_t l = ok ? (int32_t)(e - b) : 0;
+    off[v] = b;
+    len[v] = l;
+    deg[v] = l;
+    if (l > 0) {
+      int64_t lo = b, hi = e;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (col[mid] < (int32_t)v) lo = mid + 1; else hi = mid;
+      }
+      if (lo < e && col[lo] == (int32_t)v) bad |= 2;
     }
   }
-  const uint64_t r = __ballot(range), o = __ballot(order);
-  if (lane == 0 && (r | o)) atomicOr(err, (r ? 1 : 0) | (o ? 2 : 0));
+  if (t == 0) {
+    off[n] = rowptr[n];
+    if (n == 0 && (rowptr[0] != 0 || nnz != 0)) bad |= 4;
+  }
+  constexpr int U = 4;
+  for (int64_t i0 = t; i0 < nnz; i0 += stride * U) {
+    int32_t x[U], y[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int64_t i = i0 + q * stride;
+      x[q] = i < nnz ? col[i] : 0;
+      y[q] = i < nnz && i > 0 ? col[i - 1] : -1;
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int64_t i = i0 + q * stride;
+      if (i >= nnz) break;
+      adj[i] = x[q];
+      if ((uint32_t)x[q] >= (uint32_t)n) bad |= 1;
+      if (y[q] >= x[q]) {
+        int64_t lo = 0, hi = n;  // first offset >= i
+        while (lo < hi) {
+          const int64_t mid = (lo + hi) >> 1;
+          if (rowptr[mid] < i) lo = mid + 1; else hi = mid;
+        }
+        if (rowptr[lo] != i) bad |= 2;
+      }
+    }
+  }
+#pragma unroll
+  for (int bit = 1; bit <= 4; bit <<= 1)
+    if (__ballot(bad & bit) && lane_id() == 0) atomicOr(err, bit);
 }
 
 // src[i] = v for every entry i of row v: the CSR as a list of (v, w) pairs.
@@ -1396,15 +1573,15 @@ __global__ __launch_bounds__(256) void k_csr_expand(int32_t n, const int64_t* __
   }
 }
 
-hipError_t launch_csr_bounds(int32_t n, int64_t nnz, const int64_t* rowptr, int32_t* len, int32_t* deg, int32_t* err,
-                             hipStream_t s) {
-  k_csr_bounds<<<grid_for(n > 0 ? n : 1, 256, 1u << 16), 256, 0, s>>>(n, nnz, rowptr, len, deg, err);
+hipError_t launch_csr_bounds(int32_t n, int64_t nnz, const int64_t* rowptr, int32_t* err, hipStream_t s) {
+  k_csr_bounds<<<grid_for(n > 0 ? n : 1, 256, 1u << 16), 256, 0, s>>>(n, nnz, rowptr, err);
   return hipGetLastError();
 }
 
-hipError_t launch_csr_rows(int32_t n, const int64_t* rowptr, const int32_t* col, int32_t* err, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_csr_rows<<<grid_for(n, 4, 1u << 16), 256, 0, s>>>(n, rowptr, col, err);
+hipError_t launch_csr_take(int32_t n, int64_t nnz, const int64_t* rowptr, const int32_t* col, int64_t* off,
+                           int32_t* len, int32_t* deg, int32_t* adj, int32_t* err, hipStream_t s) {
+  k_csr_take<<<grid_for(std::max<int64_t>(n, nnz / 4), 256, 1u << 13), 256, 0, s>>>(n, nnz, rowptr, col, off, len,
+                                                                                  deg, adj, err);
   return hipGetLastError();
 }
 
@@ -1426,16 +1603,6 @@ hipError_t launch_csr_expand(int32_t n, const int64_t* rowptr, int32_t* src, hip
 // single-purpose kernels (31 launches, five round trips; now two launches,
 // one round trip): build + count of G(10^4, 10^5) 497 -> 301 us, an R-MAT
 // graph of 240k nodes 2,339 -> 2,019 us.
-constexpr int kLayoutNT = 1024;
-constexpr int64_t kLayoutMaxTiles = 1024;
-enum : int { kLqOut = 0, kLqIn = 1, kLqBin = 2, kLqInBin = 8, kLqItems = 14, kLqDeg2 = 20, kLqMaxD = 21, kLqMaxP = 22,
-             kLayoutQ = 23 };
-
-int64_t layout_tile(int64_t n) {
-  const int64_t per = (n + kLayoutNT * kLayoutMaxTiles - 1) / (kLayoutNT * kLayoutMaxTiles);
-  return kLayoutNT * (per > 0 ? per : 1);
-}
-
 // Node u with d+(u) >= 2: the first bin whose limit holds d+; else -1.
 __device__ __forceinline__ int node_bin(int32_t p, const BinParams& bp) {
   if (p < 2) return -1;
@@ -1828,14 +1995,14 @@ __global__ __launch_bounds__(256) void k_batch_relabel(int32_t G, const int64_t*
     const int32_t u = src ? src[e] : 0, v = dst[e];
     if (u < 0 || v < 0 || u >= ng || v >= ng) {
       bad = true;
-      if (src) gsrc[e] = (int32_t)base;  // keeps the union well formed; the build is refused anyway
-      gdst[e] = (int32_t)base;
+      if (src) gsrc[e] = -1;  // out of range in the union too: its build refuses the batch
+      gdst[e] = src ? -1 : (int32_t)base;  // keeps the CSR well formed; refused by err
       continue;
     }
     if (src) gsrc[e] = (int32_t)(base + u);
     gdst[e] = (int32_t)(base + v);
   }
-  if (__ballot(bad) && lane_id() == 0) atomicOr(err, 1);
+  if (err && __ballot(bad) && lane_id() == 0) atomicOr(err, 1);
 }
 
 hipError_t launch_batch_relabel(int32_t num_graphs, const int64_t* node_off, const int64_t* edge_off,

@@ -1258,6 +1258,8 @@ int count_variant_valid(int v) { return v >= 0 && v < kNumVariants; }
 int count_variant_capacity(int v) { return count_variant_valid(v) ? kVariants[v].cap : -1; }
 int count_variant_min_side(int v) { return count_variant_valid(v) && kVariants[v].slots > 0; }
 
+int count_variant_hub() { return kVariantBitmap; }
+
 template <int NT, int G, int SLOTS, int CAP, bool CK = false, int U = 8>
 static void launch_ms(const BinLaunch& b, const int64_t* doff, const int32_t* dcol, unsigned long long* T,
                       unsigned long long* tot, hipStream_t s) {

@@ -37,25 +37,27 @@ constexpr int kPartMaxParts = 4096;
 int part_bits(int64_t n);
 hipError_t launch_part_count(const int32_t* src, const int32_t* dst, int64_t m_raw, int32_t n, int pbits, int32_t P,
                              uint32_t* ptotal, int32_t* err, hipStream_t s);
-hipError_t launch_part_scan(const uint32_t* ptotal, int32_t P, int64_t* pstart, int64_t* cstart, hipStream_t s);
-hipError_t launch_part_place(const int32_t* src, const int32_t* dst, int64_t m_raw, int pbits, int32_t P,
-                             const int64_t* pstart, uint32_t* pcur, int32_t* pv, uint16_t* pu, hipStream_t s);
-// pass 0: len (zeroed) = raw row lengths; pass 1 (after raw_off = scan of
-// len, cur zeroed): adj rows filled.
-hipError_t launch_part_rows(int pass, int pbits, int32_t P, int32_t n, int64_t max_entries, const int64_t* pstart,
+// Partition starts, chunk starts and pass B. Pairs with an id out of range
+// are dropped (launch_part_count flags them in err).
+hipError_t launch_part_place(const int32_t* src, const int32_t* dst, int64_t m_raw, int32_t n, int pbits, int32_t P,
+                             const uint32_t* ptotal, int64_t* pstart, int64_t* cstart, uint32_t* pcur, int32_t* pv,
+                             uint16_t* pu, hipStream_t s);
+// Row lengths, row offsets and adj rows (unsorted) from the staged entries.
+// Where part_may_split(max_entries), len must be zeroed and cur is scratch.
+bool part_may_split(int64_t entries);
+hipError_t launch_part_rows(int pbits, int32_t P, int32_t n, int64_t max_entries, const int64_t* pstart,
                             const int64_t* cstart, const uint16_t* pu, const int32_t* pv, int32_t* len,
-                            const int64_t* raw_off, int32_t* cur, int32_t* adj, hipStream_t s);
-// Classification with per-block histograms (see build_kernels.hip): pass 0
-// fills hist[c * nblk + blk]; after an exclusive scan of hist into off,
-// pass 1 writes the members of class c at list[off[c * nblk] ...].
-int64_t classify_blocks(int64_t n);
-// rows by raw length (rows of length <= 1 are not listed; pass 0 sets their deg)
-hipError_t launch_classify_rows(int pass, int32_t n, const int32_t* len, int32_t* deg, int32_t* hist,
-                                const int64_t* off, int64_t nblk, int32_t* list, hipStream_t s);
+                            int64_t* raw_off, int32_t* cur, int32_t* adj, hipStream_t s);
+// Zeroes hdr[words], part[nparts] and (if not null) len[n].
+hipError_t launch_build_clear(int32_t* hdr, int32_t words, uint32_t* part, int32_t nparts, int32_t* len, int32_t n,
+                              hipStream_t s);
+// Rows by raw length: list holds class c's rows at [cls_off[c], cls_off[c+1])
+// (c = 0..kNumRowClasses-1; rows of length <= 1 are not listed, their deg is
+// set). sums: scratch of max(n, 64) int32.
+hipError_t launch_row_classes(int32_t n, const int32_t* len, int32_t* deg, int32_t* sums, int32_t* list,
+                              int64_t* cls_off, hipStream_t s);
 // out[i] = prefix[at[i]] for i < k (k <= 64)
 hipError_t launch_gather_offsets(const int64_t* prefix, const int64_t* at, int k, int64_t* out, hipStream_t s);
-// cls_off[c] = off[c * nblk] for c = 0..nc
-hipError_t launch_class_offsets(const int64_t* off, int64_t nblk, int nc, int64_t* cls_off, hipStream_t s);
 // Sorts + dedups rows of one class in place; writes deg.
 hipError_t launch_sort_rows(int cls, const int32_t* rows, int32_t nrows, const int64_t* off,
                             const int32_t* len, int32_t* adj, int32_t* deg, hipStream_t s);
@@ -94,12 +96,13 @@ hipError_t launch_orient_copy(int32_t n, const int64_t* off, const int32_t* len,
                               const int32_t* long_rows, int32_t nlong, const int64_t* doff, int32_t* dcol,
                               const int64_t* dinoff, int32_t* dincol, hipStream_t s);
 
-// Caller CSR: bounds check (err bit 4; sets len and deg when non-null), row
-// check (bit 1: id out of range, bit 2: not strictly ascending or a self
-// loop; only after the bounds check passed), expansion into (v, w) pairs.
-hipError_t launch_csr_bounds(int32_t n, int64_t nnz, const int64_t* rowptr, int32_t* len, int32_t* deg, int32_t* err,
-                             hipStream_t s);
-hipError_t launch_csr_rows(int32_t n, const int64_t* rowptr, const int32_t* col, int32_t* err, hipStream_t s);
+// Caller CSR: bounds check (err bit 4), the whole check with the copy into
+// the workspace (err bits 1 = id out of range, 2 = not strictly ascending or
+// a self loop, 4 = bounds; off, len, deg, adj written), expansion into (v, w)
+// pairs (only after the bounds check passed).
+hipError_t launch_csr_bounds(int32_t n, int64_t nnz, const int64_t* rowptr, int32_t* err, hipStream_t s);
+hipError_t launch_csr_take(int32_t n, int64_t nnz, const int64_t* rowptr, const int32_t* col, int64_t* off,
+                           int32_t* len, int32_t* deg, int32_t* adj, int32_t* err, hipStream_t s);
 hipError_t launch_csr_expand(int32_t n, const int64_t* rowptr, int32_t* src, hipStream_t s);
 // owner[c] = i for each in-list chunk c in [coff[i], coff[i+1]), i < *nlist
 // (a device word; at most n)
@@ -188,6 +191,7 @@ hipError_t launch_count_bin(const BinLaunch& b, const int64_t* doff, const int32
 int count_variant_capacity(int variant);  // max d+(u) a variant accepts
 int count_variant_valid(int variant);
 int count_variant_min_side(int variant);  // out-list + in-list kernel
+int count_variant_hub();                  // the variant that uses the hub bitmaps
 // Clears T[n] and tot[kTotSlots].
 hipError_t launch_zero_counts(unsigned long long* T, int64_t n, unsigned long long* tot, hipStream_t s);
 // cc[v] (fp32) from T and deg; block partials of the FP64 ratio sum and of T.
@@ -228,7 +232,8 @@ hipError_t launch_graph_epilogue(int32_t num_graphs, const int64_t* node_off, co
                                  const int32_t* deg, float* cc, unsigned long long* graph_tri, double* graph_avg,
                                  const unsigned long long* tot, unsigned long long* batch_tri, hipStream_t s);
 // Local -> global ids of a packed batch: edge e of graph g gets node_off[g]
-// added; err is set if a local id is outside [0, n_g).
+// added. A pair with a local id outside [0, n_g) becomes (-1, -1), which the
+// union's build refuses; with src null (a packed CSR's columns) err is set.
 hipError_t launch_batch_relabel(int32_t num_graphs, const int64_t* node_off, const int64_t* edge_off,
                                 const int32_t* src, const int32_t* dst, int64_t m_raw, int32_t* gsrc,
                                 int32_t* gdst, int32_t* err, hipStream_t s);

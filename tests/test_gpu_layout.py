@@ -7,7 +7,6 @@ import torch
 
 import oracle
 import paper_1606_07550_amd as P
-from paper_1606_07550_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -40,3 +39,85 @@ def test_layout_tiles(n):
     ref = oracle.count(n, s, d)
     np.testing.assert_array_equal(out["T"].cpu().numpy().view(np.uint64), ref["T"])
     assert g.count_check() == (ref["total"], 3 * ref["total"])
+
+
+def _parity(n, s, d):
+    g = P.Graph(n, torch.from_numpy(s).to(DEV), torch.from_numpy(d).to(DEV))
+    out = g.count()
+    torch.cuda.synchronize()
+    ref = oracle.count(n, s, d)
+    np.testing.assert_array_equal(out["T"].cpu().numpy().view(np.uint64), ref["T"])
+    assert g.info["m"] == ref["m"]
+    a = g.arrays()
+    off, deg = a["off"].cpu().numpy(), a["deg"].cpu().numpy()
+    loops = s == d
+    raw = np.bincount(s[~loops], minlength=n) + np.bincount(d[~loops], minlength=n)
+    np.testing.assert_array_equal(np.diff(off), raw)
+    assert off[0] == 0 and int(deg.sum()) == 2 * ref["m"]
+
+
+# a chunk of the row passes holds 2**18 entries (two per pair): one chunk per
+# partition, the last size with one, the first with two, several, and
+# partitions without an entry before, between and after the others
+@pytest.mark.parametrize("n,lo,hi,m", [(5000, 0, 5000, 1000), (5000, 3000, 3100, 5000), (9000, 0, 900, 1 << 17),
+                                       (9000, 0, 900, (1 << 17) + 1), (70_000, 40_000, 40_900, 500_000),
+                                       (1024, 0, 1024, 1 << 17), (1025, 0, 1025, 300_000)])
+def test_partition_chunks(n, lo, hi, m):
+    rng = np.random.default_rng(m + n)
+    s, d = (rng.integers(lo, hi, m, dtype=np.int32) for _ in range(2))
+    _parity(n, s, d)
+
+
+@pytest.mark.parametrize("n,deg", [(1, 0), (64, 0), (300, 5), (1000, 255), (1000, 64)])
+def test_csr_rows_checked_everywhere(n, deg):
+    """Trusted rows: accepted as they are; one wrong entry anywhere, or wrong
+    bounds, is refused with the status of its kind."""
+    rng = np.random.default_rng(deg)
+    m = n * deg // 2
+    s, d = (rng.integers(0, n, m, dtype=np.int32) for _ in range(2))
+    rowptr, col = oracle_csr(n, s, d)
+    dev = lambda a: torch.from_numpy(a).to(DEV)  # noqa: E731
+    g = P.Graph.from_csr(n, dev(rowptr), dev(col), assume_simple_sorted_symmetric=True)
+    assert g.info["m"] == col.size // 2
+
+    def refused(rp, cl, status):
+        with pytest.raises(P.TriccError) as e:
+            P.Graph.from_csr(n, dev(rp), dev(cl), assume_simple_sorted_symmetric=True)
+        assert e.value.status == status
+
+    EINVAL, ERANGE = 1, 2
+    bad = rowptr.copy()
+    bad[-1] += 1
+    refused(bad, col, EINVAL)
+    if not col.size:
+        return
+    rows = np.repeat(np.arange(n), np.diff(rowptr))
+    inner = np.flatnonzero(np.diff(rows) == 0) + 1  # entries with a predecessor in their row
+    for i in inner[[0, inner.size // 2, -1]]:
+        c = col.copy()
+        c[i] = c[i - 1]
+        refused(rowptr, c, EINVAL)
+    for i in (0, col.size // 2, col.size - 1):
+        c = col.copy()
+        c[i] = n
+        refused(rowptr, c, ERANGE)
+        c[i] = -1
+        refused(rowptr, c, ERANGE)
+    v = int(np.flatnonzero(np.diff(rowptr))[-1])  # the last row's own id in its place
+    r = np.unique(np.concatenate([col[rowptr[v]:rowptr[v + 1]][1:], [v]])).astype(np.int32)
+    c = col.copy()
+    c[rowptr[v]:rowptr[v] + r.size] = r
+    refused(rowptr, c, EINVAL)
+    bad = rowptr.copy()
+    bad[n // 2] = col.size + 5
+    refused(bad, col, EINVAL)
+
+
+def oracle_csr(n, s, d):
+    keep = s != d
+    a = np.concatenate([s[keep], d[keep]]).astype(np.int64)
+    b = np.concatenate([d[keep], s[keep]]).astype(np.int64)
+    key = np.unique(a * n + b)
+    rowptr = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(key // n, minlength=n), out=rowptr[1:])
+    return rowptr, (key % n).astype(np.int32)
