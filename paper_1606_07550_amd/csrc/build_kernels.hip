@@ -613,9 +613,10 @@ __device__ __forceinline__ int row_class(int32_t len) {
   if (len <= 256) return kRow256;
   if (len <= 512) return kRow512;
   if (len <= 1024) return kRow1024;
-  if (len <= 4096) return kRowLds4k;
-  if (len <= 8192) return kRowLds8k;
-  if (len <= kLargeChunk) return kRowLds32k;
+  if (len <= 4096) return kRow4k;
+  if (len <= 8192) return kRow8k;
+  if (len <= 16384) return kRow16k;
+  if (len <= 32768) return kRow32k;
   return kRowLarge;
 }
 
@@ -765,112 +766,6 @@ __global__ __launch_bounds__(256) void k_sort_small(const int32_t* __restrict__ 
   if (active && g == 0) deg[v] = (int32_t)__popcll(gm);
 }
 
-// Bitonic compare-exchanges of one stride j of stage k on kSortRun ids held
-// by one thread in registers (x[r] is id base + r); run-local strides only.
-constexpr int kSortRun = 32;
-__device__ __forceinline__ void run_stage(int32_t (&x)[kSortRun], int base, int j, int k) {
-#pragma unroll
-  for (int r = 0; r < kSortRun; ++r) {
-    const int pr = r ^ j;
-    if (pr > r) {
-      const bool up = ((base + r) & k) == 0;
-      const int32_t a = x[r], b = x[pr];
-      x[r] = up ? min(a, b) : max(a, b);
-      x[pr] = up ? max(a, b) : min(a, b);
-    }
-  }
-}
-
-// Rows of up to CAP entries: one block sorts one row (or one chunk) in LDS
-// with a bitonic network. Each thread owns a run of 32 consecutive ids: the
-// strides below 32 run in its registers (one LDS read and write for all of
-// them, the first five stages in one pass), the larger strides in LDS, one
-// barrier each. The LDS holds id i at i + i / 32, so a run's ids sit in
-// distinct banks for the 32 lanes that read them together. DEDUP: compact
-// the unique values in place and write deg; otherwise write the sorted chunk
-// back as is. Rows of at most lmin entries are left to another kernel.
-template <int CAP, int NT, bool DEDUP>
-__global__ __launch_bounds__(NT) void k_sort_lds(const int32_t* __restrict__ rows,
-                                                 const int64_t* __restrict__ seg_beg,
-                                                 const int32_t* __restrict__ seg_len,
-                                                 const int64_t* __restrict__ off,
-                                                 const int32_t* __restrict__ len,
-                                                 int32_t* __restrict__ adj, int32_t* __restrict__ deg,
-                                                 int32_t lmin) {
-  constexpr int R = kSortRun;
-  static_assert(CAP % R == 0 && CAP / R <= NT, "one run per thread");
-  __shared__ int32_t s[CAP + CAP / R];
-  __shared__ int32_t lds_scan[NT / kWave + 1];
-  auto at = [](int i) { return i + (i >> 5); };
-  int32_t v = -1;
-  int64_t beg;
-  int32_t L;
-  if (DEDUP) {
-    v = rows[blockIdx.x];
-    beg = off[v];
-    L = len[v];
-  } else {
-    beg = seg_beg[blockIdx.x];
-    L = seg_len[blockIdx.x];
-  }
-  if (L <= lmin) return;  // block-uniform
-  int P = R;
-  while (P < L) P <<= 1;
-  for (int i = threadIdx.x; i < P; i += NT) s[at(i)] = i < L ? adj[beg + i] : kPad;
-  __syncthreads();
-  const int g = threadIdx.x;
-  const bool owner = g < P / R;  // thread g owns ids g R .. g R + R - 1, at g (R + 1) + r
-  int32_t x[R];
-  if (owner) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) x[r] = s[g * (R + 1) + r];
-#pragma unroll
-    for (int k = 2; k <= R; k <<= 1) {
-#pragma unroll
-      for (int j = k >> 1; j > 0; j >>= 1) run_stage(x, g * R, j, k);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) s[g * (R + 1) + r] = x[r];
-  }
-  __syncthreads();
-  for (int k = 2 * R; k <= P; k <<= 1) {
-    for (int j = k >> 1; j >= R; j >>= 1) {
-      for (int i = threadIdx.x; i < (P >> 1); i += NT) {
-        const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-        const int hi = lo + j;
-        const bool up = (lo & k) == 0;
-        const int32_t a = s[at(lo)], b = s[at(hi)];
-        if ((a > b) == up) { s[at(lo)] = b; s[at(hi)] = a; }
-      }
-      __syncthreads();
-    }
-    if (owner) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) x[r] = s[g * (R + 1) + r];
-#pragma unroll
-      for (int j = R >> 1; j > 0; j >>= 1) run_stage(x, g * R, j, k);
-#pragma unroll
-      for (int r = 0; r < R; ++r) s[g * (R + 1) + r] = x[r];
-    }
-    __syncthreads();
-  }
-  if (!DEDUP) {
-    for (int i = threadIdx.x; i < L; i += NT) adj[beg + i] = s[at(i)];
-    return;
-  }
-  int32_t carry = 0;
-  for (int base = 0; base < L; base += NT) {
-    const int i = base + threadIdx.x;
-    const int32_t x0 = i < L ? s[at(i)] : kPad;
-    const bool u = i < L && (i == 0 || x0 != s[at(i - 1)]);
-    int32_t tot;
-    const int32_t ex = block_excl_scan<int32_t, NT>(u ? 1 : 0, lds_scan, &tot);
-    if (u) adj[beg + carry + ex] = x0;
-    carry += tot;
-  }
-  if (threadIdx.x == 0) deg[v] = carry;
-}
-
 // Rows of up to 64 * E raw entries: one wavefront per row (grid-stride), the
 // row in registers (id i in lane i % 64, register i / 64), a bitonic network
 // whose strides >= 64 swap registers inside a lane and whose smaller strides
@@ -937,7 +832,7 @@ __global__ __launch_bounds__(256) void k_sort_wave(const int32_t* __restrict__ r
   }
 }
 
-// Rows (or chunks) of up to 64 * E * W ids: one block of W wavefronts holds
+// Rows of up to 64 * E * W ids: one block of W wavefronts holds
 // the row in registers (id i in wavefront i / (64 E), register (i / 64) % E,
 // lane i % 64) and runs a bitonic network on it: strides below 64 exchange
 // by shuffles, strides below 64 E swap registers inside a lane, and only the
@@ -945,13 +840,10 @@ __global__ __launch_bounds__(256) void k_sort_wave(const int32_t* __restrict__ r
 // barrier). The stages run in a loop over k with the strides unrolled, which
 // keeps the code small. The network spans only the next power of two Q >= L
 // (the first Q ids, ascending; the pads beyond are left as they are), and
-// wavefronts wholly past Q skip the register and shuffle stages. DEDUP: the
-// unique ids, compacted to the row start, and deg[v]; otherwise the sorted
-// chunk back in place. Rows longer than the block holds are left alone.
-template <int E, int W, bool DEDUP>
+// wavefronts wholly past Q skip the register and shuffle stages. Then the
+// unique ids, compacted to the row start, and deg[v].
+template <int E, int W>
 __global__ __launch_bounds__(kWave * W) void k_sort_block(const int32_t* __restrict__ rows,
-                                                          const int64_t* __restrict__ seg_beg,
-                                                          const int32_t* __restrict__ seg_len,
                                                           const int64_t* __restrict__ off,
                                                           const int32_t* __restrict__ len,
                                                           int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
@@ -963,18 +855,9 @@ __global__ __launch_bounds__(kWave * W) void k_sort_block(const int32_t* __restr
   const int lane = lane_id();
   const int wv = threadIdx.x / kWave;
   const int32_t i0 = wv * PW + lane;  // index of x[0]; x[e] is i0 + 64 e
-  int32_t v = -1;
-  int64_t beg;
-  int32_t L;
-  if (DEDUP) {
-    v = rows[blockIdx.x];
-    beg = off[v];
-    L = len[v];
-  } else {
-    beg = seg_beg[blockIdx.x];
-    L = seg_len[blockIdx.x];
-  }
-  if (L > P) return;  // block-uniform: a longer row is another kernel's
+  const int32_t v = rows[blockIdx.x];
+  const int64_t beg = off[v];
+  const int32_t L = len[v];
   int32_t Q = 2;
   while (Q < L) Q <<= 1;
   const bool idle = wv * PW >= Q;  // wavefront-uniform
@@ -1025,14 +908,6 @@ __global__ __launch_bounds__(kWave * W) void k_sort_block(const int32_t* __restr
       }
     }
   }
-  if (!DEDUP) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int32_t i = i0 + e * kWave;
-      if (i < L) adj[beg + i] = x[e];
-    }
-    return;
-  }
   // in-order dedup: the id before x[0] of lane 0 is the previous wavefront's
   // last; the unique flags are formed twice (count, then write) rather than
   // kept in registers
@@ -1061,130 +936,180 @@ __global__ __launch_bounds__(kWave * W) void k_sort_block(const int32_t* __restr
   if (wv == W - 1 && lane == 0) deg[v] = base;
 }
 
-hipError_t launch_sort_rows(int cls, const int32_t* rows, int32_t nrows, const int64_t* off,
-                            const int32_t* len, int32_t* adj, int32_t* deg, hipStream_t s) {
-  if (nrows == 0) return hipSuccess;
-  switch (cls) {
-    case kRow8: k_sort_small<8><<<grid_for((int64_t)nrows * 8, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-    case kRow16: k_sort_small<16><<<grid_for((int64_t)nrows * 16, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-    case kRow32: k_sort_small<32><<<grid_for((int64_t)nrows * 32, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-    case kRow64: k_sort_small<64><<<grid_for((int64_t)nrows * 64, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-    case kRow128: k_sort_wave<2><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-    case kRow256: k_sort_wave<4><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-    case kRow512: k_sort_wave<8><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-    case kRow1024: k_sort_wave<16><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-    case kRowLds4k: k_sort_block<16, 4, true><<<nrows, 256, 0, s>>>(rows, nullptr, nullptr, off, len, adj, deg); break;
-    case kRowLds8k: k_sort_block<16, 8, true><<<nrows, 512, 0, s>>>(rows, nullptr, nullptr, off, len, adj, deg); break;
-    case kRowLds32k:  // up to 16,384 ids in registers (32 per lane would spill), longer rows by the LDS network
-      k_sort_block<16, 16, true><<<nrows, 1024, 0, s>>>(rows, nullptr, nullptr, off, len, adj, deg);
-      k_sort_lds<kLargeChunk, 1024, true><<<nrows, 1024, 0, s>>>(rows, nullptr, nullptr, off, len, adj, deg,
-                                                                 kWave * 16 * 16);
-      break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
+// Long rows: the ids of a row that fall into one range of 32 * WORDS ids are
+// set in an LDS bitmap (which drops the repeats) and written out in order,
+// each wavefront its share of the words. One block per row and range. With
+// one range (n <= 32 * WORDS) the row is rewritten in place; with more, each
+// block also counts the row's entries below its range, writes its ids to the
+// span of `out` that starts there, and k_row_compact closes the gaps.
+// Measured against sorting networks in LDS (above 32,768 entries chunk
+// sorts, merge passes and a dedup pass, planned on the host), whose one block
+// per row left the chip idle: build + count of an R-MAT graph of 240k nodes
+// 1,890 -> 1,331 us, R-MAT 24 94.9 -> 91.5 ms.
+// Bound by the LDS passes over the words where rows are short for their range
+// (about 8 us a range), by reading the row once per range where they are long.
+constexpr int kBitmapNT = 1024;
+constexpr int kBitmapUnroll = 8;
+constexpr int kBitmapWords = 32768;      // 2^20 ids, 128 KB of LDS
+constexpr int kBitmapWordsSmall = 8192;  // 2^18 ids, four blocks per CU
 
-hipError_t launch_sort_chunks(const int64_t* chunk_beg, const int32_t* chunk_len, int32_t nchunks,
-                              int32_t* buf, hipStream_t s) {
-  if (nchunks == 0) return hipSuccess;
-  k_sort_lds<kLargeChunk, 1024, false><<<nchunks, 1024, 0, s>>>(nullptr, chunk_beg, chunk_len, nullptr, nullptr, buf,
-                                                                 nullptr, 0);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Merge pass for large rows (merge path partition, A first on ties).
-constexpr int kMergeItems = 8;
-static_assert(kMergeTile == 256 * kMergeItems, "tile");
-
-__global__ __launch_bounds__(256) void k_merge(const int64_t* __restrict__ a_beg, const int32_t* __restrict__ la_,
-                                               const int32_t* __restrict__ lb_, const int64_t* __restrict__ out_beg,
-                                               const int64_t* __restrict__ tile_off, int32_t njobs,
-                                               const int32_t* __restrict__ in, int32_t* __restrict__ out) {
-  const int64_t tile = blockIdx.x;
-  int lo = 0, hi = njobs - 1;  // job = last k with tile_off[k] <= tile
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (tile_off[mid] <= tile) lo = mid; else hi = mid - 1;
-  }
-  const int job = lo;
-  const int32_t la = la_[job], lb = lb_[job];
-  const int32_t* A = in + a_beg[job];
-  const int32_t* B = A + la;
-  int32_t* O = out + out_beg[job];
-  const int64_t k0l = (tile - tile_off[job]) * (int64_t)kMergeTile + (int64_t)threadIdx.x * kMergeItems;
-  if (k0l >= (int64_t)la + lb) return;
-  const int32_t k0 = (int32_t)k0l;
-  int32_t b0 = max(0, k0 - lb), e0 = min(k0, la);
-  while (b0 < e0) {
-    const int32_t mid = (b0 + e0) >> 1;
-    if (A[mid] <= B[k0 - 1 - mid]) b0 = mid + 1; else e0 = mid;
-  }
-  int32_t i = b0, j = k0 - b0;
-#pragma unroll
-  for (int t = 0; t < kMergeItems; ++t) {
-    if (k0 + t >= la + lb) break;
-    const bool takeA = j >= lb || (i < la && A[i] <= B[j]);
-    O[k0 + t] = takeA ? A[i] : B[j];
-    if (takeA) ++i; else ++j;
-  }
-}
-
-hipError_t launch_merge_pass(const int64_t* a_beg, const int32_t* la, const int32_t* lb,
-                             const int64_t* out_beg, const int64_t* tile_off, int32_t njobs,
-                             int64_t ntiles, const int32_t* buf_in, int32_t* buf_out, hipStream_t s) {
-  if (njobs == 0 || ntiles == 0) return hipSuccess;
-  k_merge<<<(unsigned)ntiles, 256, 0, s>>>(a_beg, la, lb, out_beg, tile_off, njobs, buf_in, buf_out);
-  return hipGetLastError();
-}
-
-constexpr int kDedupNT = 1024;
-constexpr int kDedupPer = 4;  // consecutive entries per thread per step
-
-__global__ __launch_bounds__(kDedupNT) void k_dedup_rows(const int32_t* __restrict__ rows,
-                                                         const int64_t* __restrict__ seg_beg,
-                                                         const int32_t* __restrict__ len,
-                                                         const int32_t* __restrict__ sorted,
-                                                         const int64_t* __restrict__ off,
-                                                         int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
-  __shared__ int32_t lds_scan[kDedupNT / kWave + 1];
-  const int32_t v = rows[blockIdx.x];
+template <int WORDS>
+__global__ __launch_bounds__(kBitmapNT) void k_sort_bitmap(const int32_t* __restrict__ rows, int32_t nrows,
+                                                           int32_t ranges, int32_t n,
+                                                           const int64_t* __restrict__ off,
+                                                           const int32_t* __restrict__ len, int32_t* adj,
+                                                           int32_t* __restrict__ out, int32_t* __restrict__ deg,
+                                                           int2* __restrict__ part) {
+  constexpr int NW = kBitmapNT / kWave;
+  __shared__ uint4 map[WORDS / 4];
+  __shared__ int32_t wtot[NW], wlow[NW];
+  // the ranges of one row run on one XCD (blocks go to the 8 XCDs in turn):
+  // its entries come from that L2 after the first read
+  const int32_t per = 8 * ranges;
+  const int32_t row = (int32_t)(blockIdx.x / per) * 8 + (int32_t)(blockIdx.x % per) % 8;
+  const int32_t r = (int32_t)(blockIdx.x % per) / 8;
+  if (row >= nrows) return;
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  const int32_t v = rows[row];
+  const int64_t beg = off[v];
   const int32_t L = len[v];
-  const int32_t* S = sorted + seg_beg[blockIdx.x];
-  int32_t* D = adj + off[v];
-  int32_t carry = 0;
-  for (int base = 0; base < L; base += kDedupNT * kDedupPer) {
-    const int i0 = base + threadIdx.x * kDedupPer;
-    int32_t x[kDedupPer];
-    bool u[kDedupPer];
-    int32_t c = 0;
-    int32_t prev = i0 > 0 && i0 - 1 < L ? S[i0 - 1] : kPad;
+  const int32_t base = r * (32 * WORDS);
+  const uint32_t lim = (uint32_t)min((int64_t)32 * WORDS, (int64_t)n - base);
+  const int quads = ((int)((lim + 31) / 32) + 3) / 4;
+  for (int i = threadIdx.x; i < quads; i += kBitmapNT) map[i] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+  uint32_t* word = reinterpret_cast<uint32_t*>(map);
+  int32_t low = 0;
+  for (int32_t i0 = threadIdx.x; i0 < L; i0 += kBitmapNT * kBitmapUnroll) {
+    int32_t x[kBitmapUnroll];
 #pragma unroll
-    for (int q = 0; q < kDedupPer; ++q) {
-      const int i = i0 + q;
-      x[q] = i < L ? S[i] : kPad;
-      u[q] = i < L && (i == 0 || x[q] != prev);
-      prev = x[q];
-      c += u[q];
+    for (int q = 0; q < kBitmapUnroll; ++q) {
+      const int32_t i = i0 + q * kBitmapNT;
+      x[q] = i < L ? adj[beg + i] : kPad;  // kPad is above every range (ids are below it)
     }
-    __syncthreads();  // every read of this step precedes the writes (S may alias D)
-    int32_t tot;
-    int32_t at = carry + block_excl_scan<int32_t, kDedupNT>(c, lds_scan, &tot);
 #pragma unroll
-    for (int q = 0; q < kDedupPer; ++q)
-      if (u[q]) D[at++] = x[q];
-    carry += tot;
-    __syncthreads();
+    for (int q = 0; q < kBitmapUnroll; ++q) {
+      const uint32_t d = (uint32_t)(x[q] - base);
+      if (d < lim) atomicOr(&word[d >> 5], 1u << (d & 31));
+      low += x[q] < base;
+    }
   }
-  if (threadIdx.x == 0) deg[v] = carry;
+  low = group_sum<int32_t, kWave>(low);
+  __syncthreads();
+  // wavefront w owns quads [w seg, (w + 1) seg)
+  const int seg = (quads + NW * kWave - 1) / (NW * kWave) * kWave;
+  const int q0 = wv * seg, q1 = min(quads, q0 + seg);
+  int32_t cnt = 0;
+  for (int i = q0 + lane; i < q1; i += kWave) {
+    const uint4 w = map[i];
+    cnt += __popc(w.x) + __popc(w.y) + __popc(w.z) + __popc(w.w);
+  }
+  cnt = group_sum<int32_t, kWave>(cnt);
+  if (lane == 0) {
+    wtot[wv] = cnt;
+    wlow[wv] = low;
+  }
+  __syncthreads();
+  int32_t at = 0, tot = 0, lower = 0;
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {
+    if (k < wv) at += wtot[k];
+    tot += wtot[k];
+    lower += wlow[k];
+  }
+  int32_t* O = ranges == 1 ? adj + beg : out + beg + lower;
+  for (int i = q0; i < q1; i += kWave) {
+    const uint4 w = i + lane < q1 ? map[i + lane] : make_uint4(0, 0, 0, 0);
+    const int32_t c = __popc(w.x) + __popc(w.y) + __popc(w.z) + __popc(w.w);
+    if (!__ballot(c != 0)) continue;
+    const int32_t incl = wave_incl_scan(c);
+    int32_t o = at + incl - c;
+    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+    const int32_t id0 = base + (i + lane) * 128;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      uint32_t bits = ws[k];
+      while (bits) {
+        O[o++] = id0 + 32 * k + __builtin_ctz(bits);
+        bits &= bits - 1;
+      }
+    }
+    at += __builtin_amdgcn_readlane(incl, kWave - 1);
+  }
+  if (threadIdx.x == 0) {
+    if (ranges == 1) deg[v] = tot;
+    else part[(int64_t)row * ranges + r] = make_int2(lower, tot);
+  }
 }
 
-hipError_t launch_dedup_rows(const int32_t* rows, const int64_t* seg_beg, int32_t nrows,
-                             const int32_t* len, const int32_t* sorted, const int64_t* off,
-                             int32_t* adj, int32_t* deg, hipStream_t s) {
-  if (nrows == 0) return hipSuccess;
-  k_dedup_rows<<<nrows, kDedupNT, 0, s>>>(rows, seg_beg, len, sorted, off, adj, deg);
+// Joins the ranges of each row: range r's ids move from out[off + lower_r ..]
+// to adj behind those of the ranges before it. One block per row and range.
+__global__ __launch_bounds__(256) void k_row_compact(const int32_t* __restrict__ rows, int32_t ranges,
+                                                     const int64_t* __restrict__ off, const int2* __restrict__ part,
+                                                     const int32_t* __restrict__ out, int32_t* __restrict__ adj,
+                                                     int32_t* __restrict__ deg) {
+  __shared__ int32_t red[256 / kWave + 1];
+  const int32_t row = (int32_t)(blockIdx.x / ranges), r = (int32_t)(blockIdx.x % ranges);
+  const int2* mine = part + (int64_t)row * ranges;
+  int32_t before = 0;
+  for (int32_t k = threadIdx.x; k < r; k += 256) before += mine[k].y;
+  int32_t at;
+  (void)block_excl_scan<int32_t, 256>(before, red, &at);
+  const int32_t v = rows[row];
+  const int64_t beg = off[v];
+  const int2 m = mine[r];
+  const int32_t* I = out + beg + m.x;
+  int32_t* O = adj + beg + at;
+  for (int32_t i = threadIdx.x; i < m.y; i += 256) O[i] = I[i];
+  if (r == ranges - 1 && threadIdx.x == 0) deg[v] = at + m.y;
+}
+
+int32_t sort_ranges(int32_t n) { return (int32_t)(((int64_t)n + 32 * kBitmapWords - 1) / (32 * kBitmapWords)); }
+
+// Sorts and dedups the rows of every class in place and writes deg. Rows
+// above 4,096 entries go by bitmap where the graph's ids fit one (n <= 2^20);
+// with more ids a bitmap pass per 2^20 of them costs more than the register
+// networks up to 16,384 entries and less above.
+hipError_t launch_sort_rows(const int32_t* rowlist, const int64_t* cls_off, int32_t n, const int64_t* off,
+                            const int32_t* len, int32_t* adj, int32_t* deg, int32_t* tmp, int32_t* scratch,
+                            hipStream_t s) {
+  const int32_t ranges = sort_ranges(n);
+  for (int cls = kRow8; cls <= kRow4k; ++cls) {
+    const int32_t nrows = (int32_t)(cls_off[cls + 1] - cls_off[cls]);
+    const int32_t* rows = rowlist + cls_off[cls];
+    if (nrows == 0) continue;
+    switch (cls) {
+      case kRow8: k_sort_small<8><<<grid_for((int64_t)nrows * 8, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
+      case kRow16: k_sort_small<16><<<grid_for((int64_t)nrows * 16, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
+      case kRow32: k_sort_small<32><<<grid_for((int64_t)nrows * 32, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
+      case kRow64: k_sort_small<64><<<grid_for((int64_t)nrows * 64, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
+      case kRow128: k_sort_wave<2><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
+      case kRow256: k_sort_wave<4><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
+      case kRow512: k_sort_wave<8><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
+      case kRow1024: k_sort_wave<16><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
+      default: k_sort_block<16, 4><<<nrows, 256, 0, s>>>(rows, off, len, adj, deg); break;
+    }
+  }
+  const int first = ranges == 1 ? kRow8k : kRow32k;  // the first class sorted by bitmap
+  for (int cls = kRow8k; cls < first; ++cls) {
+    const int32_t nrows = (int32_t)(cls_off[cls + 1] - cls_off[cls]);
+    const int32_t* rows = rowlist + cls_off[cls];
+    if (nrows == 0) continue;
+    if (cls == kRow8k) k_sort_block<16, 8><<<nrows, 512, 0, s>>>(rows, off, len, adj, deg);
+    else k_sort_block<16, 16><<<nrows, 1024, 0, s>>>(rows, off, len, adj, deg);
+  }
+  const int32_t nbig = (int32_t)(cls_off[kNumRowClasses] - cls_off[first]);
+  if (nbig > 0) {
+    const int32_t* rows = rowlist + cls_off[first];
+    int2* part = reinterpret_cast<int2*>(scratch);
+    const unsigned grid = (unsigned)((nbig + 7) / 8 * 8 * ranges);
+    if (n <= 32 * kBitmapWordsSmall)
+      k_sort_bitmap<kBitmapWordsSmall><<<grid, kBitmapNT, 0, s>>>(rows, nbig, 1, n, off, len, adj, tmp, deg, part);
+    else
+      k_sort_bitmap<kBitmapWords><<<grid, kBitmapNT, 0, s>>>(rows, nbig, ranges, n, off, len, adj, tmp, deg, part);
+    if (ranges > 1)
+      k_row_compact<<<(unsigned)(nbig * ranges), 256, 0, s>>>(rows, ranges, off, part, tmp, adj, deg);
+  }
   return hipGetLastError();
 }
 
@@ -2011,20 +1936,6 @@ hipError_t launch_batch_relabel(int32_t num_graphs, const int64_t* node_off, con
   if (m_raw == 0) return hipSuccess;
   k_batch_relabel<<<grid_for(m_raw, 256 * 8, 1u << 16), 256, 0, s>>>(num_graphs, node_off, edge_off, src, dst,
                                                                      m_raw, gsrc, gdst, err);
-  return hipGetLastError();
-}
-
-__global__ void k_gather_rows(const int32_t* __restrict__ rows, int32_t nr, const int64_t* __restrict__ off,
-                              const int32_t* __restrict__ len, int64_t* __restrict__ out_off,
-                              int32_t* __restrict__ out_len) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nr) { out_off[i] = off[rows[i]]; out_len[i] = len[rows[i]]; }
-}
-
-hipError_t launch_gather_rows(const int32_t* rows, int32_t nr, const int64_t* off, const int32_t* len,
-                              int64_t* out_off, int32_t* out_len, hipStream_t s) {
-  if (nr == 0) return hipSuccess;
-  k_gather_rows<<<(nr + 255) / 256, 256, 0, s>>>(rows, nr, off, len, out_off, out_len);
   return hipGetLastError();
 }
 

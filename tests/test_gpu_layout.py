@@ -121,3 +121,36 @@ def oracle_csr(n, s, d):
     rowptr = np.zeros(n + 1, np.int64)
     np.cumsum(np.bincount(key // n, minlength=n), out=rowptr[1:])
     return rowptr, (key % n).astype(np.int32)
+
+
+@pytest.mark.parametrize("n", [40_000, 1 << 18, (1 << 18) + 1, 1 << 20, (1 << 20) + 1, 3 * (1 << 20) + 5])
+def test_long_rows(n):
+    """Rows at the edges of the sort classes, with repeats, below and above
+    the widths of the bitmaps: sorted and unique in the built graph."""
+    rng = np.random.default_rng(n)
+    lens = [2, 8, 9, 64, 65, 1024, 1025, 4096, 4097, 8192, 8193, 16_384, 16_385, 32_768, 32_769, 70_001]
+    hubs = np.concatenate([[0, n - 1], rng.choice(np.arange(1, n - 1), len(lens) - 2, replace=False)])
+    want, s, d = {}, [], []
+    for h, k in zip(hubs, lens):
+        others = np.setdiff1d(np.arange(n, dtype=np.int32), hubs.astype(np.int32))
+        lo, hi = (0, others.size) if k % 2 else (others.size // 3, others.size // 3 + 3 * k)  # spread or dense
+        w = others[rng.integers(lo, min(hi, others.size), k)]
+        w[:2] = others[[0, -1]][:k]
+        flip = rng.random(k) < 0.5
+        s.append(np.where(flip, h, w))
+        d.append(np.where(flip, w, h))
+        want[int(h)] = np.unique(w)
+    s, d = np.concatenate(s).astype(np.int32), np.concatenate(d).astype(np.int32)
+    mix = rng.permutation(s.size)
+    s, d = s[mix], d[mix]
+    g = P.Graph(n, torch.from_numpy(s).to(DEV), torch.from_numpy(d).to(DEV))
+    a = g.arrays()
+    off, deg, adj = (a[k].cpu().numpy() for k in ("off", "deg", "adj"))
+    for h, w in want.items():
+        assert deg[h] == w.size
+        np.testing.assert_array_equal(adj[off[h]:off[h] + deg[h]], w)
+    assert g.info["large_rows"] == 2
+    out = g.count()
+    ref = oracle.count(n, s, d)
+    np.testing.assert_array_equal(out["T"].cpu().numpy().view(np.uint64), ref["T"])
+    assert int(deg.sum()) == 2 * ref["m"]
