@@ -658,11 +658,9 @@ int tricc_count_finish(tricc_graph* g, const uint64_t* d_node_tri, float* d_node
   double* part_cc = g->at<double>(L.part_cc);
   unsigned long long* part_T = g->at<unsigned long long>(L.part_T);
   const unsigned long long* T = reinterpret_cast<const unsigned long long*>(d_node_tri);
-  HIPCHK(launch_epilogue(g->n, T, g->at<int32_t>(L.deg), d_node_cc, part_cc, part_T, s));
   unsigned long long* check = reinterpret_cast<unsigned long long*>(g->ws + L.hdr + kHdrCheck * 4);
-  HIPCHK(launch_finish(epilogue_blocks(g->n), g->n, part_cc, part_T, g->at<unsigned long long>(L.tot),
-                       reinterpret_cast<unsigned long long*>(d_total), d_avg_cc, check + 1, s));
-  HIPCHK(hipMemcpyAsync(check, d_total, sizeof(unsigned long long), hipMemcpyDeviceToDevice, s));
+  HIPCHK(launch_epilogue(g->n, T, g->at<int32_t>(L.deg), d_node_cc, part_cc, part_T, g->at<unsigned long long>(L.tot),
+                         reinterpret_cast<unsigned long long*>(d_total), d_avg_cc, check, s));
   return TRICC_OK;
 }
 

@@ -729,13 +729,13 @@ __device__ __forceinline__ constexpr uint64_t group_bits() {
 }
 
 // Rows of up to G entries: a group of G lanes sorts one row in registers with
-// a bitonic network over __shfl_xor, then compacts the unique values.
+// a bitonic network over __shfl_xor, then compacts the unique values. blk:
+// the block's place among the class's blocks of 256 / G rows.
 template <int G>
-__global__ __launch_bounds__(256) void k_sort_small(const int32_t* __restrict__ rows, int32_t nrows,
-                                                    const int64_t* __restrict__ off,
-                                                    const int32_t* __restrict__ len,
-                                                    int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
-  const int gi = (blockIdx.x * 256 + threadIdx.x) / G;
+__device__ __forceinline__ void sort_small(int64_t blk, const int32_t* __restrict__ rows, int32_t nrows,
+                                           const int64_t* __restrict__ off, const int32_t* __restrict__ len,
+                                           int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
+  const int64_t gi = blk * (256 / G) + threadIdx.x / G;
   const int g = threadIdx.x % G;
   const bool active = gi < nrows;
   int32_t v = 0, L = 0;
@@ -766,70 +766,69 @@ __global__ __launch_bounds__(256) void k_sort_small(const int32_t* __restrict__ 
   if (active && g == 0) deg[v] = (int32_t)__popcll(gm);
 }
 
-// Rows of up to 64 * E raw entries: one wavefront per row (grid-stride), the
+// Rows of up to 64 * E raw entries: one wavefront per row, the
 // row in registers (id i in lane i % 64, register i / 64), a bitonic network
 // whose strides >= 64 swap registers inside a lane and whose smaller strides
 // exchange with the lane i ^ j by a shuffle, so no LDS and no barrier.
 // Then an in-order dedup and a compacted, coalesced write to the row start.
 template <int E>
-__global__ __launch_bounds__(256) void k_sort_wave(const int32_t* __restrict__ rows, int32_t nrows,
-                                                   const int64_t* __restrict__ off, const int32_t* __restrict__ len,
-                                                   int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
+__device__ __forceinline__ void sort_wave(int64_t blk, const int32_t* __restrict__ rows, int32_t nrows,
+                                          const int64_t* __restrict__ off, const int32_t* __restrict__ len,
+                                          int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
   constexpr int P = kWave * E;
   const int lane = lane_id();
-  const int64_t nw = (int64_t)gridDim.x * (256 / kWave);
-  for (int64_t r = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave; r < nrows; r += nw) {
-    const int32_t v = rows[r];
-    const int64_t beg = off[v];
-    const int32_t L = len[v];
-    int32_t x[E];
+  const int64_t r = blk * (256 / kWave) + threadIdx.x / kWave;
+  if (r >= nrows) return;
+  const int32_t v = rows[r];
+  const int64_t beg = off[v];
+  const int32_t L = len[v];
+  int32_t x[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int32_t i = e * kWave + lane;
-      x[e] = i < L ? adj[beg + i] : kPad;
-    }
+  for (int e = 0; e < E; ++e) {
+    const int32_t i = e * kWave + lane;
+    x[e] = i < L ? adj[beg + i] : kPad;
+  }
 #pragma unroll
-    for (int k = 2; k <= P; k <<= 1) {
+  for (int k = 2; k <= P; k <<= 1) {
 #pragma unroll
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        if (j >= kWave) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      if (j >= kWave) {
 #pragma unroll
-          for (int e = 0; e < E; ++e) {
-            const int pe = e ^ (j / kWave);
-            if (pe > e) {
-              const bool up = ((e * kWave) & k) == 0;  // k > 64: the lane bits do not matter
-              const int32_t a = x[e], b = x[pe];
-              x[e] = up ? min(a, b) : max(a, b);
-              x[pe] = up ? max(a, b) : min(a, b);
-            }
+        for (int e = 0; e < E; ++e) {
+          const int pe = e ^ (j / kWave);
+          if (pe > e) {
+            const bool up = ((e * kWave) & k) == 0;  // k > 64: the lane bits do not matter
+            const int32_t a = x[e], b = x[pe];
+            x[e] = up ? min(a, b) : max(a, b);
+            x[pe] = up ? max(a, b) : min(a, b);
           }
-        } else {
+        }
+      } else {
 #pragma unroll
-          for (int e = 0; e < E; ++e) {
-            const int32_t y = __shfl_xor(x[e], j, kWave);
-            const bool up = ((e * kWave + lane) & k) == 0;
-            const bool lo = (lane & j) == 0;
-            x[e] = (lo == up) ? min(x[e], y) : max(x[e], y);
-          }
+        for (int e = 0; e < E; ++e) {
+          const int32_t y = __shfl_xor(x[e], j, kWave);
+          const bool up = ((e * kWave + lane) & k) == 0;
+          const bool lo = (lane & j) == 0;
+          x[e] = (lo == up) ? min(x[e], y) : max(x[e], y);
         }
       }
     }
-    int32_t base = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int32_t i = e * kWave + lane;
-      int32_t prev = __shfl_up(x[e], 1, kWave);
-      if (e > 0) {
-        const int32_t last = __builtin_amdgcn_readlane(x[e > 0 ? e - 1 : 0], kWave - 1);
-        if (lane == 0) prev = last;
-      }
-      const bool u = i < L && (i == 0 || x[e] != prev);
-      const uint64_t m = __ballot(u);
-      if (u) adj[beg + base + mask_below(m)] = x[e];
-      base += (int32_t)__popcll(m);
-    }
-    if (lane == 0) deg[v] = base;
   }
+  int32_t base = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int32_t i = e * kWave + lane;
+    int32_t prev = __shfl_up(x[e], 1, kWave);
+    if (e > 0) {
+      const int32_t last = __builtin_amdgcn_readlane(x[e > 0 ? e - 1 : 0], kWave - 1);
+      if (lane == 0) prev = last;
+    }
+    const bool u = i < L && (i == 0 || x[e] != prev);
+    const uint64_t m = __ballot(u);
+    if (u) adj[beg + base + mask_below(m)] = x[e];
+    base += (int32_t)__popcll(m);
+  }
+  if (lane == 0) deg[v] = base;
 }
 
 // Rows of up to 64 * E * W ids: one block of W wavefronts holds
@@ -843,19 +842,24 @@ __global__ __launch_bounds__(256) void k_sort_wave(const int32_t* __restrict__ r
 // wavefronts wholly past Q skip the register and shuffle stages. Then the
 // unique ids, compacted to the row start, and deg[v].
 template <int E, int W>
-__global__ __launch_bounds__(kWave * W) void k_sort_block(const int32_t* __restrict__ rows,
-                                                          const int64_t* __restrict__ off,
-                                                          const int32_t* __restrict__ len,
-                                                          int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
+struct SortBlockLds {
+  int32_t s[kWave * E * W];
+  int32_t wsum[W + 1];
+  int32_t wlast[W];
+};
+
+template <int E, int W>
+__device__ __forceinline__ void sort_block(SortBlockLds<E, W>& lds, int32_t v, const int64_t* __restrict__ off,
+                                           const int32_t* __restrict__ len, int32_t* __restrict__ adj,
+                                           int32_t* __restrict__ deg) {
   constexpr int PW = kWave * E;  // ids per wavefront
   constexpr int P = PW * W;
-  __shared__ int32_t s[P];
-  __shared__ int32_t wsum[W + 1];
-  __shared__ int32_t wlast[W];
+  int32_t* s = lds.s;
+  int32_t* wsum = lds.wsum;
+  int32_t* wlast = lds.wlast;
   const int lane = lane_id();
   const int wv = threadIdx.x / kWave;
   const int32_t i0 = wv * PW + lane;  // index of x[0]; x[e] is i0 + 64 e
-  const int32_t v = rows[blockIdx.x];
   const int64_t beg = off[v];
   const int32_t L = len[v];
   int32_t Q = 2;
@@ -934,6 +938,69 @@ __global__ __launch_bounds__(kWave * W) void k_sort_block(const int32_t* __restr
     base += (int32_t)__popcll(um);
   }
   if (wv == W - 1 && lane == 0) deg[v] = base;
+}
+
+template <int E, int W>
+__global__ __launch_bounds__(kWave * W) void k_sort_block(const int32_t* __restrict__ rows,
+                                                          const int64_t* __restrict__ off,
+                                                          const int32_t* __restrict__ len,
+                                                          int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
+  __shared__ SortBlockLds<E, W> lds;
+  sort_block<E, W>(lds, rows[blockIdx.x], off, len, adj, deg);
+}
+
+// Rows of up to 4,096 entries in two launches (above 256 entries, and the
+// rest, whose kernel needs a third of the registers), the blocks of the
+// longest rows first: the last of them run beside the shorter classes instead
+// of alone before the next launch, and a small graph pays one launch, not one
+// per class.
+constexpr int kSortClasses = kRow4k - kRow8 + 1;
+struct SortPlan {
+  int32_t row0[kSortClasses];   // first row in the list, from kRow4k down to kRow8
+  int32_t nrows[kSortClasses];
+  uint32_t blk0[kSortClasses];  // first block in the class's launch
+};
+
+__device__ __forceinline__ int sort_plan_class(const SortPlan& plan, int k0, int k1) {
+  int k = k0;
+  for (int q = k0 + 1; q < k1; ++q)
+    if (blockIdx.x >= plan.blk0[q]) k = q;
+  return k;
+}
+
+constexpr int kSortLongClasses = kRow4k - kRow256;  // kRow4k, kRow1024, kRow512
+
+__global__ __launch_bounds__(256) void k_sort_rows_long(SortPlan plan, const int32_t* __restrict__ list,
+                                                        const int64_t* __restrict__ off,
+                                                        const int32_t* __restrict__ len, int32_t* __restrict__ adj,
+                                                        int32_t* __restrict__ deg) {
+  __shared__ SortBlockLds<16, 4> lds;
+  const int k = sort_plan_class(plan, 0, kSortLongClasses);
+  const int64_t blk = blockIdx.x - plan.blk0[k];
+  const int32_t* rows = list + plan.row0[k];
+  switch (kRow4k - k) {
+    case kRow4k: sort_block<16, 4>(lds, rows[blk], off, len, adj, deg); break;
+    case kRow1024: sort_wave<16>(blk, rows, plan.nrows[k], off, len, adj, deg); break;
+    default: sort_wave<8>(blk, rows, plan.nrows[k], off, len, adj, deg); break;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_sort_rows_short(SortPlan plan, const int32_t* __restrict__ list,
+                                                         const int64_t* __restrict__ off,
+                                                         const int32_t* __restrict__ len, int32_t* __restrict__ adj,
+                                                         int32_t* __restrict__ deg) {
+  const int k = sort_plan_class(plan, kSortLongClasses, kSortClasses);
+  const int64_t blk = blockIdx.x - plan.blk0[k];
+  const int32_t* rows = list + plan.row0[k];
+  const int32_t n = plan.nrows[k];
+  switch (kRow4k - k) {
+    case kRow256: sort_wave<4>(blk, rows, n, off, len, adj, deg); break;
+    case kRow128: sort_wave<2>(blk, rows, n, off, len, adj, deg); break;
+    case kRow64: sort_small<64>(blk, rows, n, off, len, adj, deg); break;
+    case kRow32: sort_small<32>(blk, rows, n, off, len, adj, deg); break;
+    case kRow16: sort_small<16>(blk, rows, n, off, len, adj, deg); break;
+    default: sort_small<8>(blk, rows, n, off, len, adj, deg); break;
+  }
 }
 
 // Long rows: the ids of a row that fall into one range of 32 * WORDS ids are
@@ -1074,21 +1141,15 @@ hipError_t launch_sort_rows(const int32_t* rowlist, const int64_t* cls_off, int3
                             const int32_t* len, int32_t* adj, int32_t* deg, int32_t* tmp, int32_t* scratch,
                             hipStream_t s) {
   const int32_t ranges = sort_ranges(n);
-  for (int cls = kRow8; cls <= kRow4k; ++cls) {
-    const int32_t nrows = (int32_t)(cls_off[cls + 1] - cls_off[cls]);
-    const int32_t* rows = rowlist + cls_off[cls];
-    if (nrows == 0) continue;
-    switch (cls) {
-      case kRow8: k_sort_small<8><<<grid_for((int64_t)nrows * 8, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-      case kRow16: k_sort_small<16><<<grid_for((int64_t)nrows * 16, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-      case kRow32: k_sort_small<32><<<grid_for((int64_t)nrows * 32, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-      case kRow64: k_sort_small<64><<<grid_for((int64_t)nrows * 64, 256, 1u << 30), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-      case kRow128: k_sort_wave<2><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-      case kRow256: k_sort_wave<4><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-      case kRow512: k_sort_wave<8><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-      case kRow1024: k_sort_wave<16><<<grid_for((int64_t)nrows * kWave, 256, 1u << 16), 256, 0, s>>>(rows, nrows, off, len, adj, deg); break;
-      default: k_sort_block<16, 4><<<nrows, 256, 0, s>>>(rows, off, len, adj, deg); break;
-    }
+  SortPlan plan;
+  uint32_t blocks[2] = {};  // long, short
+  for (int k = 0; k < kSortClasses; ++k) {
+    const int cls = kRow4k - k, x = k >= kSortLongClasses;
+    static constexpr int kPerBlock[kSortClasses] = {1, 4, 4, 4, 4, 4, 8, 16, 32};  // rows per block
+    plan.row0[k] = (int32_t)cls_off[cls];
+    plan.nrows[k] = (int32_t)(cls_off[cls + 1] - cls_off[cls]);
+    plan.blk0[k] = blocks[x];
+    blocks[x] += (uint32_t)((plan.nrows[k] + kPerBlock[k] - 1) / kPerBlock[k]);
   }
   const int first = ranges == 1 ? kRow8k : kRow32k;  // the first class sorted by bitmap
   for (int cls = kRow8k; cls < first; ++cls) {
@@ -1098,6 +1159,8 @@ hipError_t launch_sort_rows(const int32_t* rowlist, const int64_t* cls_off, int3
     if (cls == kRow8k) k_sort_block<16, 8><<<nrows, 512, 0, s>>>(rows, off, len, adj, deg);
     else k_sort_block<16, 16><<<nrows, 1024, 0, s>>>(rows, off, len, adj, deg);
   }
+  if (blocks[0] > 0) k_sort_rows_long<<<blocks[0], 256, 0, s>>>(plan, rowlist, off, len, adj, deg);
+  if (blocks[1] > 0) k_sort_rows_short<<<blocks[1], 256, 0, s>>>(plan, rowlist, off, len, adj, deg);
   const int32_t nbig = (int32_t)(cls_off[kNumRowClasses] - cls_off[first]);
   if (nbig > 0) {
     const int32_t* rows = rowlist + cls_off[first];
@@ -1138,8 +1201,10 @@ __device__ __forceinline__ uint32_t deg_class(int32_t d) {
 // test serves the degree order and a caller's order (e.g. degeneracy).
 __device__ __forceinline__ bool ranks_above(int32_t kv, uint32_t cv, int32_t v, int32_t w,
                                             const int32_t* __restrict__ key, const uint32_t* __restrict__ cls) {
-  const uint32_t cw = (cls[w >> 4] >> (2 * (w & 15))) & 3u;
-  if (cw != cv) return cw > cv;
+  if (cls) {  // uniform
+    const uint32_t cw = (cls[w >> 4] >> (2 * (w & 15))) & 3u;
+    if (cw != cv) return cw > cv;
+  }
   return rank_below(kv, v, key[w], w);
 }
 
@@ -1161,19 +1226,18 @@ constexpr int32_t kOrientShort = 64;
 constexpr int kOrientShortUnroll = 4;  // steps of G entries issued together (short rows)
 constexpr int kOrientMedUnroll = 4;    // chunks of 64 entries issued together (medium rows)
 
-__global__ __launch_bounds__(256) void k_orient_short(int32_t n, const int64_t* __restrict__ off,
-                                                      const int32_t* __restrict__ len,
-                                                      const int32_t* __restrict__ deg,
-                                                      const int32_t* __restrict__ key,
-                                                      const uint32_t* __restrict__ cls,
-                                                      const int32_t* __restrict__ adj,
-                                                      int32_t* __restrict__ dplus,
-                                                      int32_t* __restrict__ part) {
+// Short rows, a group of 8 lanes each (grid-stride over all nodes, the listed
+// rows left out). blk of nblk: this block's place among them.
+__device__ __forceinline__ void orient_short(int64_t blk, int64_t nblk, int32_t n, const int32_t* __restrict__ len,
+                                             const int64_t* __restrict__ off,
+                                             const int32_t* __restrict__ deg, const int32_t* __restrict__ key,
+                                             const uint32_t* __restrict__ cls, const int32_t* __restrict__ adj,
+                                             int32_t* __restrict__ dplus, int32_t* __restrict__ part) {
   constexpr int G = kOrientG;
-  const int64_t ngroups = (int64_t)gridDim.x * (256 / G);
+  const int64_t ngroups = nblk * (256 / G);
   const int g = threadIdx.x % G;
   const int shift = lane_id() & ~(G - 1);
-  for (int64_t v = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G; v < n; v += ngroups) {
+  for (int64_t v = blk * (256 / G) + threadIdx.x / G; v < n; v += ngroups) {
     if (len[v] > kOrientShort) continue;
     const int32_t dv = deg[v], kv = key[v];
     const uint32_t cv = deg_class(kv);
@@ -1206,6 +1270,66 @@ __global__ __launch_bounds__(256) void k_orient_short(int32_t n, const int64_t* 
     }
     if (g == 0) dplus[v] = c;
   }
+}
+
+// Rows of medium length: one wavefront per row (grid-stride), ballot-ordered
+// compaction, no block barriers.
+__device__ __forceinline__ void orient_medium(int64_t blk, int64_t nblk, const int32_t* __restrict__ rows,
+                                              int32_t nrows, const int64_t* __restrict__ off,
+                                              const int32_t* __restrict__ deg, const int32_t* __restrict__ key,
+                                              const uint32_t* __restrict__ cls, const int32_t* __restrict__ adj,
+                                              int32_t* __restrict__ dplus, int32_t* __restrict__ part) {
+  const int64_t nwaves = nblk * (256 / kWave);
+  const int l = lane_id();
+  for (int64_t r = blk * (256 / kWave) + threadIdx.x / kWave; r < nrows; r += nwaves) {
+    const int32_t v = rows[r];
+    const int32_t dv = deg[v], kv = key[v];
+    const uint32_t cv = deg_class(kv);
+    const int64_t rb = off[v];
+    const int32_t* row = adj + rb;
+    int32_t* prow = part + rb;
+    int32_t c = 0;
+    // kOrientMedUnroll chunks of 64 entries per step: their row loads, then
+    // their degree gathers, are issued together
+    for (int32_t b = 0; b < dv; b += kWave * kOrientMedUnroll) {
+      int32_t w[kOrientMedUnroll];
+      bool f[kOrientMedUnroll];
+#pragma unroll
+      for (int q = 0; q < kOrientMedUnroll; ++q) {
+        const int32_t i = b + q * kWave + l;
+        w[q] = i < dv ? row[i] : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < kOrientMedUnroll; ++q) {
+        const int32_t i = b + q * kWave + l;
+        f[q] = i < dv && ranks_above(kv, cv, v, w[q], key, cls);
+      }
+#pragma unroll
+      for (int q = 0; q < kOrientMedUnroll; ++q) {
+        const int32_t i = b + q * kWave + l;
+        const uint64_t m = __ballot(f[q]);
+        const int32_t below = mask_below(m);
+        if (f[q]) prow[c + below] = w[q];
+        else if (i < dv) prow[dv - 1 - (i - (c + below))] = w[q];
+        c += (int32_t)__popcll(m);
+      }
+    }
+    if (l == 0) dplus[v] = c;
+  }
+}
+
+// Both in one launch, the medium rows' blocks first: their last ones run
+// beside the short rows.
+__global__ __launch_bounds__(256) void k_orient(unsigned nmed_blocks, const int32_t* __restrict__ med_rows,
+                                                int32_t nmed, int32_t n, const int32_t* __restrict__ len,
+                                                const int64_t* __restrict__ off, const int32_t* __restrict__ deg,
+                                                const int32_t* __restrict__ key, const uint32_t* __restrict__ cls,
+                                                const int32_t* __restrict__ adj, int32_t* __restrict__ dplus,
+                                                int32_t* __restrict__ part) {
+  if (blockIdx.x < nmed_blocks)
+    orient_medium(blockIdx.x, nmed_blocks, med_rows, nmed, off, deg, key, cls, adj, dplus, part);
+  else
+    orient_short(blockIdx.x - nmed_blocks, gridDim.x - nmed_blocks, n, len, off, deg, key, cls, adj, dplus, part);
 }
 
 constexpr int kOrientLongNT = 1024;
@@ -1253,55 +1377,6 @@ __global__ __launch_bounds__(kOrientLongNT) void k_orient_long(const int32_t* __
   if (threadIdx.x == 0) dplus[v] = c;
 }
 
-// Rows of medium length: one wavefront per row (grid-stride), ballot-ordered
-// compaction, no block barriers.
-__global__ __launch_bounds__(256) void k_orient_medium(const int32_t* __restrict__ rows, int32_t nrows,
-                                                       const int64_t* __restrict__ off,
-                                                       const int32_t* __restrict__ deg,
-                                                       const int32_t* __restrict__ key,
-                                                       const uint32_t* __restrict__ cls,
-                                                       const int32_t* __restrict__ adj,
-                                                       int32_t* __restrict__ dplus,
-                                                       int32_t* __restrict__ part) {
-  const int64_t nwaves = (int64_t)gridDim.x * (256 / kWave);
-  const int l = lane_id();
-  for (int64_t r = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave; r < nrows; r += nwaves) {
-    const int32_t v = rows[r];
-    const int32_t dv = deg[v], kv = key[v];
-    const uint32_t cv = deg_class(kv);
-    const int64_t rb = off[v];
-    const int32_t* row = adj + rb;
-    int32_t* prow = part + rb;
-    int32_t c = 0;
-    // kOrientMedUnroll chunks of 64 entries per step: their row loads, then
-    // their degree gathers, are issued together
-    for (int32_t b = 0; b < dv; b += kWave * kOrientMedUnroll) {
-      int32_t w[kOrientMedUnroll];
-      bool f[kOrientMedUnroll];
-#pragma unroll
-      for (int q = 0; q < kOrientMedUnroll; ++q) {
-        const int32_t i = b + q * kWave + l;
-        w[q] = i < dv ? row[i] : 0;
-      }
-#pragma unroll
-      for (int q = 0; q < kOrientMedUnroll; ++q) {
-        const int32_t i = b + q * kWave + l;
-        f[q] = i < dv && ranks_above(kv, cv, v, w[q], key, cls);
-      }
-#pragma unroll
-      for (int q = 0; q < kOrientMedUnroll; ++q) {
-        const int32_t i = b + q * kWave + l;
-        const uint64_t m = __ballot(f[q]);
-        const int32_t below = mask_below(m);
-        if (f[q]) prow[c + below] = w[q];
-        else if (i < dv) prow[dv - 1 - (i - (c + below))] = w[q];
-        c += (int32_t)__popcll(m);
-      }
-    }
-    if (l == 0) dplus[v] = c;
-  }
-}
-
 // Copy of the partitioned rows: N+(v) = part[off[v] .. off[v] + d+(v)) to
 // dcol[doff[v] ..]; N-(v) = part[off[v] + d(v) - 1 - k], k < d-(v), to
 // dincol[dinoff[v] + k] (ascending again). G lanes per row (G = 8, 64 or
@@ -1339,51 +1414,60 @@ __device__ __forceinline__ void orient_copy_row(int32_t v, int g, const int64_t*
   }
 }
 
-__global__ __launch_bounds__(256) void k_orient_copy_short(int32_t n, const int64_t* __restrict__ off,
-                                                           const int32_t* __restrict__ len,
-                                                           const int32_t* __restrict__ deg,
-                                                           const int32_t* __restrict__ dplus,
-                                                           const int32_t* __restrict__ part,
-                                                           const int64_t* __restrict__ doff,
-                                                           int32_t* __restrict__ dcol,
-                                                           const int64_t* __restrict__ dinoff,
-                                                           int32_t* __restrict__ dincol) {
+// The copies of all rows in one launch: blocks for the long rows (a block per
+// row), then the medium ones (a wavefront per row), then all short ones.
+struct CopyGrid {
+  unsigned long_blocks, medium_blocks;
+};
+
+__global__ __launch_bounds__(256) void k_orient_copy(CopyGrid grid, const int32_t* __restrict__ long_rows,
+                                                     int32_t nlong, const int32_t* __restrict__ medium_rows,
+                                                     int32_t nmedium, int32_t n, const int64_t* __restrict__ off,
+                                                     const int32_t* __restrict__ len,
+                                                     const int32_t* __restrict__ deg,
+                                                     const int32_t* __restrict__ dplus,
+                                                     const int32_t* __restrict__ part,
+                                                     const int64_t* __restrict__ doff, int32_t* __restrict__ dcol,
+                                                     const int64_t* __restrict__ dinoff,
+                                                     int32_t* __restrict__ dincol) {
+  int64_t blk = blockIdx.x;
+  if (blk < grid.long_blocks) {
+    for (int64_t r = blk; r < nlong; r += grid.long_blocks)
+      orient_copy_row<256>(long_rows[r], threadIdx.x, off, deg, dplus, part, doff, dcol, dinoff, dincol);
+    return;
+  }
+  blk -= grid.long_blocks;
+  if (blk < grid.medium_blocks) {
+    const int64_t step = (int64_t)grid.medium_blocks * (256 / kWave);
+    for (int64_t r = blk * (256 / kWave) + threadIdx.x / kWave; r < nmedium; r += step)
+      orient_copy_row<kWave>(medium_rows[r], threadIdx.x % kWave, off, deg, dplus, part, doff, dcol, dinoff, dincol);
+    return;
+  }
+  blk -= grid.medium_blocks;
   constexpr int G = kOrientG;
-  const int64_t ngroups = (int64_t)gridDim.x * (256 / G);
-  for (int64_t v = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G; v < n; v += ngroups) {
+  const int64_t step = ((int64_t)gridDim.x - grid.long_blocks - grid.medium_blocks) * (256 / G);
+  for (int64_t v = blk * (256 / G) + threadIdx.x / G; v < n; v += step) {
     if (len[v] > kOrientShort) continue;
     orient_copy_row<G>((int32_t)v, threadIdx.x % G, off, deg, dplus, part, doff, dcol, dinoff, dincol);
   }
 }
 
-template <int G>
-__global__ __launch_bounds__(256) void k_orient_copy_listed(const int32_t* __restrict__ rows, int32_t nrows,
-                                                            const int64_t* __restrict__ off,
-                                                            const int32_t* __restrict__ deg,
-                                                            const int32_t* __restrict__ dplus,
-                                                            const int32_t* __restrict__ part,
-                                                            const int64_t* __restrict__ doff,
-                                                            int32_t* __restrict__ dcol,
-                                                            const int64_t* __restrict__ dinoff,
-                                                            int32_t* __restrict__ dincol) {
-  const int64_t ngroups = (int64_t)gridDim.x * (256 / G);
-  for (int64_t r = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G; r < nrows; r += ngroups)
-    orient_copy_row<G>(rows[r], threadIdx.x % G, off, deg, dplus, part, doff, dcol, dinoff, dincol);
-}
+// Up to this many ids the keys themselves stay in L2 (4 MB per XCD): no class
+// words, which cost a launch to form.
+constexpr int32_t kOrientClassMin = 1 << 20;
 
 hipError_t launch_orient(int32_t n, const int64_t* off, const int32_t* len, const int32_t* deg, const int32_t* key,
                          const int32_t* adj, const int32_t* medium_rows, int32_t nmedium, const int32_t* long_rows,
                          int32_t nlong, uint32_t* cls, int32_t* dplus, int32_t* part, hipStream_t s) {
   if (n == 0) return hipSuccess;
   if (!key) key = deg;
-  k_deg_class<<<grid_for(((int64_t)n + 15) / 16, 256, 4096), 256, 0, s>>>(n, key, cls);
-  k_orient_short<<<grid_for((int64_t)n * kOrientG, 256, 1u << 16), 256, 0, s>>>(n, off, len, deg, key, cls, adj,
-                                                                             dplus, part);
-  if (nmedium > 0)
-    k_orient_medium<<<grid_for((int64_t)nmedium * kWave, 256, 1u << 14), 256, 0, s>>>(medium_rows, nmedium, off, deg,
-                                                                                   key, cls, adj, dplus, part);
+  if (n <= kOrientClassMin) cls = nullptr;
+  if (cls) k_deg_class<<<grid_for(((int64_t)n + 15) / 16, 256, 4096), 256, 0, s>>>(n, key, cls);
   if (nlong > 0)
     k_orient_long<<<nlong, kOrientLongNT, 0, s>>>(long_rows, off, deg, key, cls, adj, dplus, part);
+  const unsigned mb = nmedium > 0 ? grid_for((int64_t)nmedium * kWave, 256, 1u << 14) : 0;
+  const unsigned sb = grid_for((int64_t)n * kOrientG, 256, 1u << 16);
+  k_orient<<<mb + sb, 256, 0, s>>>(mb, medium_rows, nmedium, n, len, off, deg, key, cls, adj, dplus, part);
   return hipGetLastError();
 }
 
@@ -1392,14 +1476,12 @@ hipError_t launch_orient_copy(int32_t n, const int64_t* off, const int32_t* len,
                               const int32_t* long_rows, int32_t nlong, const int64_t* doff, int32_t* dcol,
                               const int64_t* dinoff, int32_t* dincol, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  k_orient_copy_short<<<grid_for((int64_t)n * kOrientG, 256, 1u << 16), 256, 0, s>>>(n, off, len, deg, dplus, part,
-                                                                                  doff, dcol, dinoff, dincol);
-  if (nmedium > 0)
-    k_orient_copy_listed<kWave><<<grid_for((int64_t)nmedium * kWave, 256, 1u << 14), 256, 0, s>>>(
-        medium_rows, nmedium, off, deg, dplus, part, doff, dcol, dinoff, dincol);
-  if (nlong > 0)
-    k_orient_copy_listed<256><<<grid_for((int64_t)nlong * 256, 256, 1u << 14), 256, 0, s>>>(
-        long_rows, nlong, off, deg, dplus, part, doff, dcol, dinoff, dincol);
+  CopyGrid g;
+  g.long_blocks = (unsigned)std::min(nlong, 1 << 14);
+  g.medium_blocks = nmedium > 0 ? grid_for((int64_t)nmedium * kWave, 256, 1u << 14) : 0;
+  const unsigned sb = grid_for((int64_t)n * kOrientG, 256, 1u << 16);
+  k_orient_copy<<<g.long_blocks + g.medium_blocks + sb, 256, 0, s>>>(g, long_rows, nlong, medium_rows, nmedium, n, off,
+                                                                 len, deg, dplus, part, doff, dcol, dinoff, dincol);
   return hipGetLastError();
 }
 

@@ -1359,10 +1359,33 @@ constexpr int kEpiThreads = 256;
 constexpr int kEpiItems = 16;
 int64_t epilogue_blocks(int64_t n) { return (n + kEpiThreads * kEpiItems - 1) / (kEpiThreads * kEpiItems); }
 
+// The total from the intersection kernels' counters (not from T), the
+// average from the epilogue's FP64 partials (s: their sum), and the sum of
+// the per-node counts (3x the total when both are right); check: total and
+// sum again, kept with the graph. One block calls it.
+__device__ __forceinline__ void count_results(int32_t n, double s, unsigned long long st,
+                                              const unsigned long long* __restrict__ tot, unsigned long long* red,
+                                              unsigned long long* __restrict__ total, double* __restrict__ avg,
+                                              unsigned long long* __restrict__ check) {
+  const unsigned long long all = sum_total(tot, red);
+  if (threadIdx.x == 0) {
+    *total = all;
+    *avg = n > 0 ? s / (double)n : 0.0;
+    check[0] = all;
+    check[1] = st;
+  }
+}
+
+// With one block (n <= 4,096) it writes the results too, and no second
+// launch follows.
 __global__ __launch_bounds__(kEpiThreads) void k_epilogue(int32_t n, const unsigned long long* __restrict__ T,
                                                           const int32_t* __restrict__ deg,
                                                           float* __restrict__ cc, double* __restrict__ part_cc,
-                                                          unsigned long long* __restrict__ part_T) {
+                                                          unsigned long long* __restrict__ part_T,
+                                                          const unsigned long long* __restrict__ tot,
+                                                          unsigned long long* __restrict__ total,
+                                                          double* __restrict__ avg,
+                                                          unsigned long long* __restrict__ check) {
   __shared__ double red_d[kEpiThreads / kWave];
   __shared__ unsigned long long red_t[kEpiThreads / kWave];
   const int64_t base = (int64_t)blockIdx.x * kEpiThreads * kEpiItems;
@@ -1382,17 +1405,18 @@ __global__ __launch_bounds__(kEpiThreads) void k_epilogue(int32_t n, const unsig
   }
   const double s = block_sum<double, kEpiThreads>(acc, red_d);
   const unsigned long long st = block_sum<unsigned long long, kEpiThreads>(tacc, red_t);
+  if (gridDim.x == 1) {
+    count_results(n, s, st, tot, red_t, total, avg, check);
+    return;
+  }
   if (threadIdx.x == 0) { part_cc[blockIdx.x] = s; part_T[blockIdx.x] = st; }
 }
 
-// The total from the intersection kernels' counters (not from T), the
-// average from the epilogue's FP64 partials in block order, and sum_T =
-// sum of the per-node counts (3x the total when both are right).
 __global__ __launch_bounds__(256) void k_finish(int64_t nb, int32_t n, const double* __restrict__ part_cc,
                                                 const unsigned long long* __restrict__ part_T,
                                                 const unsigned long long* __restrict__ tot,
                                                 unsigned long long* __restrict__ total, double* __restrict__ avg,
-                                                unsigned long long* __restrict__ sum_T) {
+                                                unsigned long long* __restrict__ check) {
   __shared__ double red_d[256 / kWave];
   __shared__ unsigned long long red_t[256 / kWave];
   double acc = 0.0;
@@ -1400,26 +1424,16 @@ __global__ __launch_bounds__(256) void k_finish(int64_t nb, int32_t n, const dou
   for (int64_t i = threadIdx.x; i < nb; i += 256) { acc += part_cc[i]; tacc += part_T[i]; }
   const double s = block_sum<double, 256>(acc, red_d);
   const unsigned long long st = block_sum<unsigned long long, 256>(tacc, red_t);
-  const unsigned long long all = sum_total(tot, red_t);
-  if (threadIdx.x == 0) {
-    *total = all;
-    *avg = n > 0 ? s / (double)n : 0.0;
-    *sum_T = st;
-  }
+  count_results(n, s, st, tot, red_t, total, avg, check);
 }
 
-hipError_t launch_epilogue(int32_t n, const unsigned long long* T, const int32_t* deg, float* cc,
-                           double* part_cc, unsigned long long* part_T, hipStream_t s) {
+hipError_t launch_epilogue(int32_t n, const unsigned long long* T, const int32_t* deg, float* cc, double* part_cc,
+                           unsigned long long* part_T, const unsigned long long* tot, unsigned long long* total,
+                           double* avg, unsigned long long* check, hipStream_t s) {
   const int64_t nb = epilogue_blocks(n);
-  if (nb == 0) return hipSuccess;
-  k_epilogue<<<(unsigned)nb, kEpiThreads, 0, s>>>(n, T, deg, cc, part_cc, part_T);
-  return hipGetLastError();
-}
-
-hipError_t launch_finish(int64_t nb, int32_t n, const double* part_cc, const unsigned long long* part_T,
-                         const unsigned long long* tot, unsigned long long* total, double* avg,
-                         unsigned long long* sum_T, hipStream_t s) {
-  k_finish<<<1, 256, 0, s>>>(nb, n, part_cc, part_T, tot, total, avg, sum_T);
+  if (nb > 0)
+    k_epilogue<<<(unsigned)nb, kEpiThreads, 0, s>>>(n, T, deg, cc, part_cc, part_T, tot, total, avg, check);
+  if (nb != 1) k_finish<<<1, 256, 0, s>>>(nb, n, part_cc, part_T, tot, total, avg, check);
   return hipGetLastError();
 }
 

@@ -181,15 +181,13 @@ int count_variant_min_side(int variant);  // out-list + in-list kernel
 int count_variant_hub();                  // the variant that uses the hub bitmaps
 // Clears T[n] and tot[kTotSlots].
 hipError_t launch_zero_counts(unsigned long long* T, int64_t n, unsigned long long* tot, hipStream_t s);
-// cc[v] (fp32) from T and deg; block partials of the FP64 ratio sum and of T.
 int64_t epilogue_blocks(int64_t n);
-hipError_t launch_epilogue(int32_t n, const unsigned long long* T, const int32_t* deg, float* cc,
-                           double* part_cc, unsigned long long* part_T, hipStream_t s);
-// *total = sum of tot (the intersection kernels' own count), *avg from the
-// FP64 partials, *sum_T = sum of the T partials.
-hipError_t launch_finish(int64_t nb, int32_t n, const double* part_cc, const unsigned long long* part_T,
-                         const unsigned long long* tot, unsigned long long* total, double* avg,
-                         unsigned long long* sum_T, hipStream_t s);
+// cc[v] (fp32) from T and deg, through block partials of the FP64 ratio sum
+// and of T; *total = sum of tot (the intersection kernels' own count), *avg
+// from the FP64 partials, check = (total, sum of T).
+hipError_t launch_epilogue(int32_t n, const unsigned long long* T, const int32_t* deg, float* cc, double* part_cc,
+                           unsigned long long* part_T, const unsigned long long* tot, unsigned long long* total,
+                           double* avg, unsigned long long* check, hipStream_t s);
 
 // ---- Batched graphs ---------------------------------------------------------
 // Persistent intersection kernel over four node lists (hubs -> global
