@@ -620,6 +620,7 @@ int count_bins(tricc_graph* g, int b0, int b1, uint64_t* d_node_tri, void* strea
     bl.dinoff = g->at<int64_t>(L.dinoff);
     bl.dincol = g->at<int32_t>(L.dincol);
   }
+  bl.max_outdeg = g->info.max_outdeg;
   bl.hubmap = g->at<uint32_t>(L.hubmap);
   bl.hub_slots = hub_map_slots(g->n);
   bl.map_words = hub_map_words(g->n);
@@ -1239,6 +1240,7 @@ int batch_launch(tricc_batch* b, hipStream_t s) {
   // the heaviest nodes first, with the large LDS tables
   for (int bin = 4; bin >= 3; --bin) {
     BinLaunch bl{g->tuning.bin_variant[bin], binlist + g->bin_off[bin], (int32_t)(g->bin_off[bin + 1] - g->bin_off[bin])};
+    bl.max_outdeg = g->info.max_outdeg;
     HIPCHK(launch_count_bin(bl, g->at<int64_t>(L.doff), g->at<int32_t>(L.dcol), b->T, tot, s));
   }
   const int32_t nbk = (int32_t)(g->bin_off[3] - g->bin_off[2]);

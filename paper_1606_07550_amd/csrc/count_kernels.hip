@@ -467,11 +467,12 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
 }
 
 // In-list side of the min-side split: a group owns node w and one chunk of
-// at most CAP of its in-neighbours u (rank(u) < rank(w)). N+(w) is the LDS
+// at most CH (by default CAP) of its in-neighbours u (rank(u) < rank(w)). N+(w) is the LDS
 // table; for every in-neighbour with 2 <= d+(u) < d+(w) one wavefront
 // streams N+(u) against it. A hit x is the triangle u < w < x: x is credited
 // in the table, w in the group total, u with one global atomic per in-edge.
-template <int G, int SLOTS, int CAP, int U, bool CK = false>
+// CH > CAP: the chunk runs in parts of CAP lists on one table.
+template <int G, int SLOTS, int CAP, int U, bool CK = false, int CH = CAP>
 __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGroupLds<SLOTS, CAP>& S,
                                                unsigned long long* red, const int64_t* __restrict__ doff,
                                                const int32_t* __restrict__ dcol,
@@ -491,8 +492,8 @@ __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGro
   if (active) {
     beg = doff[w];
     len = (int32_t)(doff[w + 1] - beg);
-    ib = dinoff[w] + chunk * CAP;
-    nin = (int32_t)min((int64_t)CAP, dinoff[w + 1] - ib);
+    ib = dinoff[w] + chunk * CH;
+    nin = (int32_t)min((int64_t)CH, dinoff[w + 1] - ib);
   }
   for (int s = g; s < SLOTS; s += G) { K[s] = -1; S.C[s] = 0; }
   if (g == 0) { S.nlong = 0; S.fail = 0; }
@@ -500,36 +501,44 @@ __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGro
   bool ck = false;
   if constexpr (CK) ck = build_cuckoo<G>(S, dcol + beg, len, g);
   else for (int i = g; i < len; i += G) bucket_insert<NB>(K, dcol[beg + i]);
-  for (int i = g; i < nin; i += G) {
-    const int32_t u = dincol[ib + i];
-    const int64_t b = doff[u];
-    int32_t nu = (int32_t)(doff[u + 1] - b);
-    if (nu < 2 || nu >= len) nu = 0;
-    S.Wb[i] = (int32_t)b;
-    S.Wn[i] = nu;
-    S.Ws[i] = u;
-    S.Wc[i] = 0;
-    if (nu >= kPackShort) S.Wl[atomicAdd(&S.nlong, 1)] = i;
+  uint32_t tw = 0;  // wave-uniform
+  for (int32_t part = 0; part == 0 || (CH > CAP && part < nin); part += CAP) {
+    const int32_t np = CH > CAP ? min(nin - part, CAP) : nin;
+    for (int i = g; i < np; i += G) {
+      const int32_t u = dincol[ib + part + i];
+      const int64_t b = doff[u];
+      int32_t nu = (int32_t)(doff[u + 1] - b);
+      if (nu < 2 || nu >= len) nu = 0;
+      S.Wb[i] = (int32_t)b;
+      S.Wn[i] = nu;
+      S.Ws[i] = u;
+      S.Wc[i] = 0;
+      if (nu >= kPackShort) S.Wl[atomicAdd(&S.nlong, 1)] = i;
+    }
+    group_sync<G>();
+    const int32_t nl = __builtin_amdgcn_readfirstlane(S.nlong);
+    auto done = [&](int32_t i, uint32_t cu) {
+      if (cu && lane == 0) atomicAdd(&T[S.Ws[i]], (unsigned long long)cu);
+    };
+    const int32_t p0 = wv * np / WPG, p1 = (wv + 1) * np / WPG;
+    if (ck) {
+      const CuckooProbe<SLOTS> probe{K};
+      tw += stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done);
+      tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
+    } else {
+      const BucketProbe<NB> probe{S.K};
+      tw += stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done);
+      tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
+    }
+    group_sync<G>();
+    for (int i = g; i < np; i += G)
+      if (S.Wc[i]) atomicAdd(&T[S.Ws[i]], (unsigned long long)S.Wc[i]);
+    if (CH > CAP) {  // the lists of the next part take this one's place
+      group_sync<G>();
+      if (g == 0) S.nlong = 0;
+      group_sync<G>();
+    }
   }
-  group_sync<G>();
-  const int32_t nl = __builtin_amdgcn_readfirstlane(S.nlong);
-  auto done = [&](int32_t i, uint32_t cu) {
-    if (cu && lane == 0) atomicAdd(&T[S.Ws[i]], (unsigned long long)cu);
-  };
-  const int32_t p0 = wv * nin / WPG, p1 = (wv + 1) * nin / WPG;
-  uint32_t tw;  // wave-uniform
-  if (ck) {
-    const CuckooProbe<SLOTS> probe{K};
-    tw = stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done);
-    tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
-  } else {
-    const BucketProbe<NB> probe{S.K};
-    tw = stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done);
-    tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
-  }
-  group_sync<G>();
-  for (int i = g; i < nin; i += G)
-    if (S.Wc[i]) atomicAdd(&T[S.Ws[i]], (unsigned long long)S.Wc[i]);
   for (int s = g; s < SLOTS; s += G) {
     const int32_t k = K[s];
     const uint32_t c = S.C[s];
@@ -578,8 +587,22 @@ __device__ __forceinline__ void in_item(const InItems& in, int64_t j, int32_t* w
   *chunk = in.coff[0] + j - in.coff[p];
 }
 
-template <int NT, int G, int SLOTS, int CAP, int U, bool CK>
-__global__ __launch_bounds__(NT) void k_count_ms(const int32_t* __restrict__ list, int32_t nlist, InItems in,
+// Wavefronts per SIMD that a block's LDS leaves room for, at most 8: what the
+// bin kernels ask their register allocation for. Eight take at most 64 vector
+// and 80 scalar registers each: a SIMD has 800 scalar registers, given out by
+// 16, and a wavefront's trap handler takes 16 of its own, so at 81 a CU holds
+// one block of 1,024 threads instead of two. Left to itself the allocation
+// went past that with small changes of the code around the loops (bin 3 of
+// R-MAT 24: 79 registers 24.4 ms, 83 registers 32.7 ms, same inner loops).
+constexpr int waves_per_simd(int nt, size_t lds) {
+  const int blocks = (int)(160 * 1024 / lds);
+  const int waves = blocks * nt / 256;
+  return waves < 1 ? 1 : waves > 8 ? 8 : waves;
+}
+
+template <int NT, int G, int SLOTS, int CAP, int U, bool CK, int CH>
+__global__ __launch_bounds__(NT, waves_per_simd(NT, (NT / G) * sizeof(WaveGroupLds<SLOTS, CAP>) + NT / 8)) void
+k_count_ms(const int32_t* __restrict__ list, int32_t nlist, InItems in,
                                                  int32_t w_max, const int64_t* __restrict__ doff,
                                                  const int32_t* __restrict__ dcol,
                                                  const int64_t* __restrict__ dinoff,
@@ -600,7 +623,7 @@ __global__ __launch_bounds__(NT) void k_count_ms(const int32_t* __restrict__ lis
   int32_t w;
   int64_t chunk;
   in_item(in, ((int64_t)blockIdx.x - nbu) * GPB + gi, &w, &chunk);
-  node_count_inw<G, SLOTS, CAP, U, CK>(w, chunk, lds[gi], red, doff, dcol, dinoff, dincol, T, tot);
+  node_count_inw<G, SLOTS, CAP, U, CK, CH>(w, chunk, lds[gi], red, doff, dcol, dinoff, dincol, T, tot);
 }
 
 // Merge variant for short lists: a group of G lanes owns node u and each
@@ -921,7 +944,7 @@ __device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict_
 // by one as node_count_wave does. The in-list side (blocks after the first
 // ceil(nlist / (GPB * 64 / GS))) is k_count_ms's.
 template <int NT, int SLOTS, int CAP, int U, bool CK, int GS>
-__global__ __launch_bounds__(NT) void k_count_mss(const int32_t* __restrict__ list, int32_t nlist, InItems in,
+__global__ __launch_bounds__(NT, 8) void k_count_mss(const int32_t* __restrict__ list, int32_t nlist, InItems in,
                                                   int32_t w_max, const int64_t* __restrict__ doff,
                                                   const int32_t* __restrict__ dcol,
                                                   const int64_t* __restrict__ dinoff,
@@ -1260,7 +1283,7 @@ int count_variant_min_side(int v) { return count_variant_valid(v) && kVariants[v
 
 int count_variant_hub() { return kVariantBitmap; }
 
-template <int NT, int G, int SLOTS, int CAP, bool CK = false, int U = 8>
+template <int NT, int G, int SLOTS, int CAP, bool CK = false, int CH = CAP, int U = 8>
 static void launch_ms(const BinLaunch& b, const int64_t* doff, const int32_t* dcol, unsigned long long* T,
                       unsigned long long* tot, hipStream_t s) {
   constexpr int GPB = NT / G;
@@ -1268,7 +1291,7 @@ static void launch_ms(const BinLaunch& b, const int64_t* doff, const int32_t* dc
   const int64_t nbw = (b.in_items + GPB - 1) / GPB;
   if (nbu + nbw == 0) return;
   InItems in{b.in_list, b.in_coff, b.in_owner, b.in_base, b.in_nodes, b.in_items};
-  k_count_ms<NT, G, SLOTS, CAP, U, CK><<<(unsigned)(nbu + nbw), NT, 0, s>>>(b.list, b.count, in, b.w_max, doff, dcol,
+  k_count_ms<NT, G, SLOTS, CAP, U, CK, CH><<<(unsigned)(nbu + nbw), NT, 0, s>>>(b.list, b.count, in, b.w_max, doff, dcol,
                                                                         b.dinoff, b.dincol, T, tot);
 }
 
@@ -1308,7 +1331,13 @@ hipError_t launch_count_bin(const BinLaunch& b, const int64_t* doff, const int32
     case 11: launch_ms<256, 64, 256, 64, true>(b, doff, dcol, T, tot, s); break;
     case 12: launch_ms<256, 256, 1024, 256, true>(b, doff, dcol, T, tot, s); break;
     case 13: launch_ms<512, 512, 4096, 1024, true>(b, doff, dcol, T, tot, s); break;
-    case 14: launch_ms<1024, 1024, 8192, 4096, true>(b, doff, dcol, T, tot, s); break;
+    case 14:
+      // its table's LDS lets one block of 16 wavefronts on a CU; a graph whose
+      // largest d+ fits variant 20's table takes that, two blocks a CU, the
+      // in-list chunks in two parts (bin 4 of R-MAT 24: 25.1 -> 18.9 ms)
+      if (b.max_outdeg <= 2048) launch_ms<1024, 1024, 4096, 2048, true, 4096>(b, doff, dcol, T, tot, s);
+      else launch_ms<1024, 1024, 8192, 4096, true>(b, doff, dcol, T, tot, s);
+      break;
     case 15: launch_ms<512, 512, 2048, 1024, true>(b, doff, dcol, T, tot, s); break;
     case 16: launch_ms<512, 512, 4096, 2048, true>(b, doff, dcol, T, tot, s); break;
     case 17: launch_ms<256, 256, 512, 256, true>(b, doff, dcol, T, tot, s); break;

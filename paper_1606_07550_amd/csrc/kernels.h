@@ -162,6 +162,7 @@ struct BinLaunch {
   int32_t w_max = 0;
   const int64_t* dinoff = nullptr;
   const int32_t* dincol = nullptr;
+  int64_t max_outdeg = INT64_MAX;  // the graph's largest d+, where known
   // hub bitmap variant only: hub_slots zeroed bitmaps of map_words words
   uint32_t* hubmap = nullptr;
   int32_t hub_slots = 0;

@@ -154,3 +154,27 @@ def test_long_rows(n):
     ref = oracle.count(n, s, d)
     np.testing.assert_array_equal(out["T"].cpu().numpy().view(np.uint64), ref["T"])
     assert int(deg.sum()) == 2 * ref["m"]
+
+
+@pytest.mark.parametrize("outer", [1500, 2725, 2735, 5460, 5475, 9000])
+def test_in_list_parts(outer):
+    """Owners with more in-neighbours than a table kernel takes lists at a
+    time: chunks of 4,096 in-neighbours in parts of 2,048 (the large-table
+    variant on a graph whose out-degrees fit the smaller table)."""
+    rng = np.random.default_rng(outer)
+    core = 48
+    i, j = np.triu_indices(core, 1)
+    s, d = [i], [j]
+    for v in range(core, core + outer):  # each outer node meets 36 of the 48 core nodes, and two outer ones
+        s.append(np.full(38, v))
+        d.append(np.concatenate([rng.choice(core, 36, replace=False), rng.integers(core, core + outer, 2)]))
+    s, d = np.concatenate(s).astype(np.int32), np.concatenate(d).astype(np.int32)
+    n = core + outer
+    perm = rng.permutation(n).astype(np.int32)
+    s, d = perm[s], perm[d]
+    tuning = {"bin_limit": [2, 3, 4, 5, 4096], "bin_variant": [21, 23, 24, 20, 14, 9], "min_side": 1}
+    g = P.Graph(n, torch.from_numpy(s).to(DEV), torch.from_numpy(d).to(DEV), tuning=tuning)
+    out = g.count()
+    ref = oracle.count(n, s, d)
+    np.testing.assert_array_equal(out["T"].cpu().numpy().view(np.uint64), ref["T"])
+    assert g.count_check() == (ref["total"], 3 * ref["total"])
