@@ -296,12 +296,15 @@ __device__ __forceinline__ void load_chunk(int32_t (&x)[U], const int32_t* L, in
 // One wavefront streams the long lists Wl[j] (j = j0, j0 + step, ... < nl)
 // against the table, U loads of 64 ids per step: the next step's loads
 // (same list, or the first chunk of the next one) are in flight while the
-// current chunk is probed. Base and length of a list are wave-uniform
-// (scalar registers). Each hit credits its table slot and the lane's hit
-// count; at the end of a list the lanes' counts are summed (DPP) and
-// done(i, hits) receives list i's hit count (wave-uniform). Per chunk of 64
-// ids only the exit test and the credit's exec mask use the scalar unit.
-// Returns the wave's hits.
+// current chunk is probed. Lane k holds begin and length of the k-th list to
+// come, 64 lists at a time, and takes its hit count when it ends, so that a
+// list costs two readlanes and no LDS round trip, and done(i, hits), called by
+// the lane of each list i with hits, credits up to 64 lists in one go (lists
+// of 64 to 200 ids spend as much on their ends as on their ids). Each hit
+// credits its table slot and the lane's hit count; at the end of a list the
+// lanes' counts are summed (DPP). Per chunk of 64 ids only the exit test and
+// the credit's exec mask use the scalar unit. Returns the sum over the lists
+// that this lane held.
 template <int U, typename Probe, typename Done>
 __device__ __forceinline__ uint32_t stream_long(int32_t j0, int32_t step, int32_t nl, const int32_t* Wl,
                                                 const int32_t* Wb, const int32_t* Wn,
@@ -309,55 +312,63 @@ __device__ __forceinline__ uint32_t stream_long(int32_t j0, int32_t step, int32_
                                                 Done done) {
   // j0 is the wave's index inside its group: uniform, but not provably so
   int32_t j = __builtin_amdgcn_readfirstlane(j0);
-  if (j >= nl) return 0;
   const int lane = lane_id();
-  int32_t i = __builtin_amdgcn_readfirstlane(Wl[j]);
-  int32_t b = __builtin_amdgcn_readfirstlane(Wb[i]);
-  int32_t n = __builtin_amdgcn_readfirstlane(Wn[i]);
-  int32_t p = 0;
-  uint32_t total = 0, hv = 0;  // hv: this lane's hits in list i
-  // one pipeline step: load the chunk after (i, p) into nxt, probe cur;
-  // false once the last list is done. Two register sets alternate, so no
-  // copy has to wait for the loads in flight.
-  auto advance = [&](int32_t (&cur)[U], int32_t (&nxt)[U]) -> bool {
-    int32_t nj = j, ni = i, nb = b, nn = n, np = p + U * kWave;
-    if (np >= n) {  // list i ends with this chunk
-      nj = j + step;
-      np = 0;
-      nn = 0;
-      if (nj < nl) {
-        ni = __builtin_amdgcn_readfirstlane(Wl[nj]);
-        nb = __builtin_amdgcn_readfirstlane(Wb[ni]);
-        nn = __builtin_amdgcn_readfirstlane(Wn[ni]);
+  uint32_t total = 0;
+  while (j < nl) {
+    const int32_t left = (nl - j + step - 1) / step;
+    const int32_t cnt = left < kWave ? left : kWave;
+    int32_t who = 0, vb = 0, vn = 0;
+    if (lane < cnt) {
+      who = Wl[j + lane * step];
+      vb = Wb[who];
+      vn = Wn[who];
+    }
+    uint32_t hits = 0, hv = 0;  // this lane's list's; this lane's in the list being streamed
+    int32_t k = 0, p = 0;
+    int32_t b = __builtin_amdgcn_readlane(vb, 0), n = __builtin_amdgcn_readlane(vn, 0);
+    // one pipeline step: load the chunk after (k, p) into nxt, probe cur;
+    // false once the last list is done. Two register sets alternate, so no
+    // copy has to wait for the loads in flight.
+    auto advance = [&](int32_t (&cur)[U], int32_t (&nxt)[U]) -> bool {
+      int32_t nk = k, nb = b, nn = n, np = p + U * kWave;
+      if (np >= n) {  // list k ends with this chunk
+        nk = k + 1;
+        np = 0;
+        nn = 0;
+        if (nk < cnt) {
+          nb = __builtin_amdgcn_readlane(vb, nk);
+          nn = __builtin_amdgcn_readlane(vn, nk);
+        }
       }
-    }
-    load_chunk<U>(nxt, dcol + nb, np, nn, lane);
-    const int32_t rem = n - p;  // ids of list i from p on
+      load_chunk<U>(nxt, dcol + nb, np, nn, lane);
+      const int32_t rem = n - p;  // ids of list k from p on
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      if (k * kWave >= rem) break;
-      int off;
-      const bool hit = probe(cur[k], lane + k * kWave < rem, &off);
-      if (hit) credit(C, off);
-      hv += (uint32_t)hit;
+      for (int q = 0; q < U; ++q) {
+        if (q * kWave >= rem) break;
+        int off;
+        const bool hit = probe(cur[q], lane + q * kWave < rem, &off);
+        if (hit) credit(C, off);
+        hv += (uint32_t)hit;
+      }
+      if (np == 0) {
+        const uint32_t cw = wave_sum_u32(hv);
+        hv = 0;
+        hits = lane == k ? cw : hits;
+        if (nk >= cnt) return false;
+      }
+      k = nk;
+      b = nb;
+      n = nn;
+      p = np;
+      return true;
+    };
+    int32_t x[U], y[U];
+    load_chunk<U>(x, dcol + b, 0, n, lane);
+    while (advance(x, y) && advance(y, x)) {
     }
-    if (np == 0) {
-      const uint32_t cw = wave_sum_u32(hv);
-      hv = 0;
-      done(i, cw);
-      total += cw;
-      if (nj >= nl) return false;
-    }
-    j = nj;
-    i = ni;
-    b = nb;
-    n = nn;
-    p = np;
-    return true;
-  };
-  int32_t x[U], y[U];
-  load_chunk<U>(x, dcol + b, 0, n, lane);
-  while (advance(x, y) && advance(y, x)) {
+    if (hits) done(who, hits);
+    total += hits;
+    j += cnt * step;
   }
   return total;
 }
@@ -425,18 +436,16 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
   }
   group_sync<G>();
   const int32_t nl = __builtin_amdgcn_readfirstlane(S.nlong);
-  auto done = [&](int32_t i, uint32_t cw) {
-    if (cw && lane == 0) atomicAdd(&S.C[S.Ws[i]], cw);
-  };
+  auto done = [&](int32_t i, uint32_t cw) { atomicAdd(&S.C[S.Ws[i]], cw); };
   const int32_t p0 = wv * len / WPG, p1 = (wv + 1) * len / WPG;
   uint32_t tu;  // wave-uniform
   if (ck) {
     const CuckooProbe<SLOTS> probe{K};
-    tu = stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done);
+    tu = wave_sum_u32(stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done));
     tu += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
   } else {
     const BucketProbe<NB> probe{S.K};
-    tu = stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done);
+    tu = wave_sum_u32(stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done));
     tu += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
   }
   group_sync<G>();
@@ -517,17 +526,15 @@ __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGro
     }
     group_sync<G>();
     const int32_t nl = __builtin_amdgcn_readfirstlane(S.nlong);
-    auto done = [&](int32_t i, uint32_t cu) {
-      if (cu && lane == 0) atomicAdd(&T[S.Ws[i]], (unsigned long long)cu);
-    };
+    auto done = [&](int32_t i, uint32_t cu) { atomicAdd(&T[S.Ws[i]], (unsigned long long)cu); };
     const int32_t p0 = wv * np / WPG, p1 = (wv + 1) * np / WPG;
     if (ck) {
       const CuckooProbe<SLOTS> probe{K};
-      tw += stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done);
+      tw += wave_sum_u32(stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done));
       tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
     } else {
       const BucketProbe<NB> probe{S.K};
-      tw += stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done);
+      tw += wave_sum_u32(stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done));
       tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
     }
     group_sync<G>();
