@@ -879,14 +879,10 @@ int tricc_core_workspace_size(int32_t n, size_t* bytes) {
 
 namespace {
 
-// Levels per window of the core peeling: a scan of every node left opens a
-// window [k, k + kCoreWindow], whose levels then scan the near list only.
-constexpr int32_t kCoreWindow = 32;
-
-// Peeling loop of the core decomposition; with d_order, every node's removal
-// round as well (frontiers counted across levels).
+// Core decomposition; with d_order, every node's removal round as well
+// (frontiers counted across levels).
 int core_impl(const tricc_graph* g, int32_t k_stop, int32_t* d_core, int32_t* d_order, void* d_ws, size_t ws_bytes,
-              int32_t* h_max_core, int32_t* h_rounds, void* stream) {
+              int32_t* h_max_core, void* stream) {
   if (!g) return fail(TRICC_EINVAL, "null graph");
   const int32_t n = g->n;
   size_t need = 0;
@@ -894,93 +890,36 @@ int core_impl(const tricc_graph* g, int32_t k_stop, int32_t* d_core, int32_t* d_
   if (n > 0 && (!d_core || !d_ws)) return fail(TRICC_EINVAL, "null core output or workspace");
   if (n > 0 && ws_bytes < need) return fail(TRICC_ENOMEM, "core workspace of %zu bytes, %zu needed", ws_bytes, need);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int32_t maxc = 0, round = 0;
+  int32_t maxc = 0;
   if (n > 0) {
     char* w = static_cast<char*>(d_ws);
     const size_t slice = align_up(sizeof(int32_t) * (size_t)n);
-    int32_t* cur = reinterpret_cast<int32_t*>(w);
-    int32_t* F = reinterpret_cast<int32_t*>(w + slice);
-    int32_t* G = reinterpret_cast<int32_t*>(w + 2 * slice);
-    int32_t* A = reinterpret_cast<int32_t*>(w + 3 * slice);  // nodes left, listed by the last full scan
-    int32_t* S = reinterpret_cast<int32_t*>(w + 4 * slice);
-    int32_t* near[2] = {reinterpret_cast<int32_t*>(w + 5 * slice), reinterpret_cast<int32_t*>(w + 6 * slice)};
-    int32_t* cnt = reinterpret_cast<int32_t*>(w + 7 * slice);
+    auto part = [&](int i) { return reinterpret_cast<int32_t*>(w + i * slice); };
     const Layout& L = g->L;
-    const int64_t* off = g->at<int64_t>(L.raw_off);
-    const int32_t* deg = g->at<int32_t>(L.deg);
-    const int32_t* adj = g->at<int32_t>(L.adj);
-    HIPCHK(launch_core_init(n, deg, cur, d_core, s));
-    int64_t left = n;
-    int32_t k = 0;
-    int rc;
-    // full-scan candidates: all ids, until at most a quarter of the nodes
-    // are left; from then on each full scan lists the survivors for the next
-    const int32_t* cand = nullptr;
-    int32_t ncand = n;
-    // the window of levels [.., U] and its near list near[x] (length nx):
-    // every node left with current degree <= U is on it
-    int32_t U = -1, nx = 0, x = 0;
-    while (left > 0 && (k_stop < 0 || k < k_stop)) {
-      const bool full = k > U || nx == 0;
-      const int y = x ^ 1;  // the scan lists this level's near nodes in near[y]
-      int32_t c[8];
-      if (full) {
-        U = k + kCoreWindow;
-        if (k_stop >= 0) U = std::min(U, k_stop - 1);  // no level at or above k_stop is peeled
-        const bool listing = cand != nullptr || left <= n / 4;
-        HIPCHK(launch_core_reset(cnt, 0, 6 + y, s));
-        HIPCHK(launch_core_scan(ncand, cand, k, cur, d_core, F, listing ? S : nullptr, cnt, d_order, round, U, near[y],
-                                cnt + 6 + y, s));
-        if ((rc = sync_copy(c, cnt, sizeof(c), s))) return rc;
-        if (listing) {
-          std::swap(A, S);
-          cand = A;
-          ncand = c[3];
-        }
-      } else {
-        HIPCHK(launch_core_reset(cnt, 0, 6 + y, s));
-        HIPCHK(launch_core_scan(nx, near[x], k, cur, d_core, F, nullptr, cnt, d_order, round, U, near[y], cnt + 6 + y,
-                                s));
-        if ((rc = sync_copy(c, cnt, sizeof(c), s))) return rc;
-      }
-      x = y;
-      nx = c[6 + x];
-      if (c[0] == 0) {  // no node at this level: jump to the smallest current degree seen
-        if (c[2] == 0x7fffffff) {
-          if (full) break;  // no node left at all
-          k = U + 1;        // none left in the window: every node left is above U
-        } else {
-          k = c[2];
-        }
-        continue;
-      }
-      int32_t nf = c[0];
-      const int R = core_peel_batch();  // even: the frontier left ends in F
-      while (nf > 0) {
-        // R rounds per read-back; the ones after the level's last frontier
-        // find an empty frontier and do nothing
-        HIPCHK(launch_core_peel_batch(F, G, nf, k, off, deg, adj, cur, d_core, cnt, d_order, round, U, near[x],
-                                      cnt + 6 + x, s));
-        int32_t b[16 + 8];
-        if ((rc = sync_copy(b, cnt, sizeof(int32_t) * (16 + R), s))) return rc;
-        left -= nf;
-        for (int i = 0; i + 1 < R; ++i) left -= b[16 + i];
-        round += R;
-        nf = b[16 + R - 1];
-        c[6 + x] = b[6 + x];
-      }
-      nx = c[6 + x];
-      maxc = k;
-      ++k;
-    }
-    if (k_stop >= 0 && left > 0) {
+    const CoreBuffers b{g->at<int64_t>(L.raw_off), g->at<int32_t>(L.deg), g->at<int32_t>(L.adj), part(0), d_core,
+                        d_order, {part(1), part(2)}, {part(3), part(4)}, {part(5), part(6)}, part(7)};
+    HIPCHK(launch_core_init(n, k_stop, b, s));
+    // steps launched ahead of each look at the state: few at first (a small
+    // k_stop or graph ends early), then more; those past the end are empty
+    int step = 0, ahead = 8;
+    CoreProgress pr;
+    do {
+      HIPCHK(launch_core_steps(step + 1, ahead, n, k_stop, b, s));
+      step += ahead;
+      ahead = std::min(2 * ahead, 64);
+      int32_t cnt[64];
+      const int rc = sync_copy(cnt, b.cnt, sizeof(cnt), s);
+      if (rc) return rc;
+      pr = core_progress(cnt, step);
+    } while (!pr.done);
+    maxc = pr.max_core;
+    if (k_stop >= 0 && pr.left > 0) {
       HIPCHK(launch_core_fill(n, k_stop, d_core, s));
       maxc = k_stop;
     }
     HIPCHK(hipStreamSynchronize(s));
   }
   if (h_max_core) *h_max_core = maxc;
-  if (h_rounds) *h_rounds = round;
   return TRICC_OK;
 }
 
@@ -990,14 +929,14 @@ extern "C" {
 
 int tricc_graph_core(const tricc_graph* g, int32_t k_stop, int32_t* d_core, void* d_ws, size_t ws_bytes,
                      int32_t* h_max_core, void* stream) {
-  return core_impl(g, k_stop, d_core, nullptr, d_ws, ws_bytes, h_max_core, nullptr, stream);
+  return core_impl(g, k_stop, d_core, nullptr, d_ws, ws_bytes, h_max_core, stream);
 }
 
 int tricc_graph_degeneracy(const tricc_graph* g, int32_t* d_order, int32_t* d_core, void* d_ws, size_t ws_bytes,
                            int32_t* h_degeneracy, void* stream) {
   if (!g) return fail(TRICC_EINVAL, "null graph");
   if (g->n > 0 && (!d_order || !d_core)) return fail(TRICC_EINVAL, "null order or core output");
-  return core_impl(g, -1, d_core, d_order, d_ws, ws_bytes, h_degeneracy, nullptr, stream);
+  return core_impl(g, -1, d_core, d_order, d_ws, ws_bytes, h_degeneracy, stream);
 }
 
 int tricc_graph_reorient(tricc_graph* g, const int32_t* d_key, void* stream) {

@@ -14,6 +14,15 @@
 // U + 1 to U. Every node left with current degree <= U is thus on the near
 // list, so the levels up to U scan that list alone.
 //
+// The whole peeling is a state machine on the device: one kernel per step (a
+// scan or one round of a level), every block of which works out the step from
+// the state and the counters that the step before left, so the host only
+// launches steps ahead and reads the state now and then. The steps are short
+// (a frontier of tens to thousands of nodes), so the decomposition is bound by
+// their number and latency: R-MAT 20 takes 888 steps of about 5 us and the gap
+// to the next, 7.7 ms in all, against 32.4 ms with a read-back after each scan
+// and every fourth round and rows walked by one wavefront each.
+//
 // With `order` given, each node also records the round in which it was
 // removed (rounds count every frontier, across levels). A node removed in
 // round r had current degree <= k then, counting exactly its neighbours
@@ -30,93 +39,216 @@ namespace tricc {
 namespace {
 
 constexpr int kCoreNT = 256;
-constexpr int kPeelG = 8;  // lanes per frontier node in the peel
+constexpr int kPeelG = 8;  // lanes per node in the peel of large frontiers
+// Levels per window of the peeling: a scan of every node left opens a window
+// [k, k + kCoreWindow], whose levels then scan the near list only.
+constexpr int32_t kCoreWindow = 32;
+// A level's rounds take order values in multiples of this many.
+constexpr int32_t kOrderRounds = 4;
+constexpr int32_t kNoDegree = 0x7fffffff;
 
-// Rounds launched together by launch_core_peel_batch, the later ones reading
-// their frontier size on the device (a round whose frontier is empty does
-// nothing), so the host reads the counters back once per batch.
-constexpr int kPeelBatch = 4;
-constexpr int64_t kPeelBatchMinNodes = 1024;
+enum : int32_t { kCoreScan = 0, kCorePeel = 1, kCoreDone = 2 };
+
+// The step that a launch is to do. Buffers: the frontier is F[fb] (nf nodes),
+// the near list near[xb] (nx nodes), the candidates of a full scan all ids or
+// the list A[ab] (ncand either way).
+struct CoreState {
+  int32_t phase, k, U, nf, fb, nx, xb, listed, ab, ncand, left, round, rounds, maxc, full, listing;
+};
+// Counters of a step: frontier found (scan) or next frontier (peel),
+// survivors listed, near nodes added, smallest degree above k seen.
+struct CoreCount {
+  int32_t f, survivors, near, least;
+};
+
+// What follows the levels done so far: a scan for level k, or the end.
+__device__ __forceinline__ void core_plan(CoreState& s, int32_t n, int32_t k_stop) {
+  if (!(s.left > 0 && (k_stop < 0 || s.k < k_stop))) {
+    s.phase = kCoreDone;
+    return;
+  }
+  s.phase = kCoreScan;
+  s.full = s.k > s.U || s.nx == 0;
+  s.listing = 0;
+  if (s.full) {
+    s.U = s.k + kCoreWindow;
+    if (k_stop >= 0) s.U = min(s.U, k_stop - 1);  // no level at or above k_stop is peeled
+    // full scans list the survivors for the next one once at most a quarter
+    // of the nodes are left
+    s.listing = s.listed || s.left <= n / 4;
+  }
+}
+
+// The state after step s, whose counters were c.
+__device__ __forceinline__ void core_next(CoreState& s, const CoreCount& c, int32_t n, int32_t k_stop) {
+  if (s.phase == kCoreScan) {
+    s.xb ^= 1;
+    s.nx = c.near;
+    if (s.listing) {
+      s.ab ^= 1;
+      s.listed = 1;
+      s.ncand = c.survivors;
+    }
+    if (c.f > 0) {
+      s.phase = kCorePeel;
+      s.nf = c.f;
+      s.fb = 0;
+      s.rounds = 0;
+      return;
+    }
+    // no node at this level: the smallest current degree seen comes next
+    if (c.least != kNoDegree) s.k = c.least;
+    else if (s.full) s.left = 0;  // no node left at all
+    else s.k = s.U + 1;           // none left in the window: every node left is above U
+    core_plan(s, n, k_stop);
+  } else if (s.phase == kCorePeel) {
+    s.left -= s.nf;
+    s.rounds += 1;
+    s.nx += c.near;
+    s.nf = c.f;
+    s.fb ^= 1;
+    if (s.nf > 0) return;
+    s.round += (s.rounds + kOrderRounds - 1) / kOrderRounds * kOrderRounds;
+    s.maxc = s.k;
+    s.k += 1;
+    core_plan(s, n, k_stop);
+  }
+}
 
 // Appends the items of the lanes with `take` to q[*cnt ..], one atomic per
 // wavefront. All lanes of the wavefront must call it.
-__device__ __forceinline__ void wave_push(bool take, int32_t item, int32_t* __restrict__ q, int32_t* __restrict__ cnt) {
+__device__ __forceinline__ void wave_push(bool take, int32_t item, int32_t* __restrict__ q,
+                                          int32_t* __restrict__ cnt) {
   const uint64_t m = __ballot(take);
   if (!m) return;
   const int leader = __builtin_ctzll(m);
-  int32_t base = 0;
-  if (lane_id() == leader) base = atomicAdd(cnt, (int32_t)__popcll(m));
-  base = __shfl(base, leader, kWave);
-  if (take) q[base + mask_below(m)] = item;
+  int32_t at = 0;
+  if (lane_id() == leader) at = atomicAdd(cnt, (int32_t)__popcll(m));
+  at = __shfl(at, leader, kWave);
+  if (take) q[at + mask_below(m)] = item;
 }
 
-__global__ __launch_bounds__(kCoreNT) void k_core_init(int32_t n, const int32_t* __restrict__ deg,
-                                                       int32_t* __restrict__ cur, int32_t* __restrict__ core) {
+// Layout of the counter area (64 int32): two states, three counter sets.
+__device__ __forceinline__ CoreState* core_state(int32_t* cnt, int i) {
+  return reinterpret_cast<CoreState*>(cnt) + (i & 1);
+}
+__device__ __forceinline__ CoreCount* core_count(int32_t* cnt, int i) {
+  return reinterpret_cast<CoreCount*>(cnt + 2 * sizeof(CoreState) / 4) + i % 3;
+}
+static_assert(2 * sizeof(CoreState) + 3 * sizeof(CoreCount) <= 256, "counter area");
+
+__global__ __launch_bounds__(kCoreNT) void k_core_init(int32_t n, int32_t k_stop, const int32_t* __restrict__ deg,
+                                                       int32_t* __restrict__ cur, int32_t* __restrict__ core,
+                                                       int32_t* __restrict__ cnt) {
   const int64_t stride = (int64_t)gridDim.x * kCoreNT;
   for (int64_t v = (int64_t)blockIdx.x * kCoreNT + threadIdx.x; v < n; v += stride) {
     cur[v] = deg[v];
     core[v] = -1;
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    CoreState s{};
+    s.U = -1;
+    s.ncand = n;
+    s.left = n;
+    core_plan(s, n, k_stop);
+    *core_state(cnt, 0) = s;
+    *core_count(cnt, 0) = CoreCount{0, 0, 0, kNoDegree};
+    *core_count(cnt, 1) = CoreCount{0, 0, 0, kNoDegree};
+  }
 }
 
-// cnt[0] = frontier size, cnt[1] = next frontier size, cnt[2] = smallest
-// current degree above k among the nodes scanned, cnt[3] = survivors
-// listed, cnt[6] and cnt[7] = lengths of the two near-list buffers.
-__global__ void k_core_reset(int32_t* __restrict__ cnt, int which, int near) {
-  if (which == 2) {  // the speculative rounds' next-frontier counters
-    if (threadIdx.x < kPeelBatch) cnt[16 + threadIdx.x] = 0;
-    return;
-  }
-  if (threadIdx.x == 0) {
-    if (which == 0) {
-      cnt[0] = 0;
-      cnt[2] = 0x7fffffff;
-      cnt[3] = 0;
-    } else {
-      cnt[1] = 0;
+struct CoreArrays {
+  const int64_t* off;
+  const int32_t* deg;
+  const int32_t* adj;
+  int32_t* cur;
+  int32_t* core;
+  int32_t* order;  // may be null
+  int32_t* F[2];
+  int32_t* A[2];
+  int32_t* near[2];
+  int32_t* cnt;
+};
+
+// Scan for level k: among the candidates, the nodes left whose current degree
+// is <= k become the frontier; the others still left are listed (listing) and
+// go on the near list up to degree U. A block takes tiles of kScanTile
+// candidates and adds each tile's items to the three lists with one atomic per
+// list: one counter takes about 100 atomics per microsecond, which held up the
+// first levels, whose near lists hold most nodes, when every wavefront issued
+// its own (first scan of R-MAT 20: 422 us for 10^6 nodes, the next 32 near
+// lists 180 to 10 us each).
+constexpr int kScanPer = 8;
+constexpr int kScanTile = kCoreNT * kScanPer;
+
+struct ScanLds {
+  int32_t count[3], base[3];
+};
+
+__device__ __forceinline__ void core_scan(const CoreState& s, const CoreArrays& g, CoreCount* c, ScanLds& lds) {
+  const int32_t na = s.full ? s.ncand : s.nx;
+  const int32_t* list = s.full ? (s.listed ? g.A[s.ab] : nullptr) : g.near[s.xb];
+  int32_t* const q[3] = {g.F[0], g.near[s.xb ^ 1], g.A[s.ab ^ 1]};
+  int32_t* const cnt[3] = {&c->f, &c->near, &c->survivors};
+  const int lists = s.listing ? 3 : 2;
+  const int64_t stride = (int64_t)gridDim.x * kScanTile;
+  int32_t mn = kNoDegree;
+  for (int64_t b = (int64_t)blockIdx.x * kScanTile; b < na; b += stride) {  // uniform trip count
+    if (threadIdx.x < 3) lds.count[threadIdx.x] = 0;
+    __syncthreads();
+    int32_t v[kScanPer];
+    uint32_t on[3] = {0, 0, 0};  // bit r: item r goes on the list
+#pragma unroll
+    for (int r = 0; r < kScanPer; ++r) {
+      const int64_t i = b + r * kCoreNT + threadIdx.x;
+      v[r] = i < na ? (list ? list[i] : (int32_t)i) : -1;
     }
-    if (near >= 0) cnt[near] = 0;
-  }
-}
-
-// Frontier of level k: the nodes left whose current degree is <= k, among
-// the listed candidates A[0, na) (A == NULL: all ids 0 .. na-1). The other
-// nodes still left are listed in S (S == NULL: not listed), so later scans
-// only visit them.
-__global__ __launch_bounds__(kCoreNT) void k_core_scan(int32_t na, const int32_t* __restrict__ A, int32_t k,
-                                                       const int32_t* __restrict__ cur, int32_t* __restrict__ core,
-                                                       int32_t* __restrict__ F, int32_t* __restrict__ S,
-                                                       int32_t* __restrict__ cnt, int32_t* __restrict__ order,
-                                                       int32_t round, int32_t U, int32_t* __restrict__ Nr,
-                                                       int32_t* __restrict__ ncnt) {
-  const int64_t stride = (int64_t)gridDim.x * kCoreNT;
-  int32_t mn = 0x7fffffff;
-  for (int64_t b = (int64_t)blockIdx.x * kCoreNT; b < na; b += stride) {  // uniform trip count
-    const int64_t i = b + threadIdx.x;
-    bool take = false, keep = false, near = false;
-    int32_t v = 0;
-    if (i < na) {
-      v = A ? A[i] : (int32_t)i;
-      if (core[v] < 0) {
-        const int32_t c = cur[v];
-        if (c <= k) {
-          core[v] = k;
-          if (order) order[v] = round;
-          take = true;
-        } else {
-          mn = min(mn, c);
-          keep = true;
-          near = c <= U;
-        }
+#pragma unroll
+    for (int r = 0; r < kScanPer; ++r) {
+      if (v[r] < 0 || g.core[v[r]] >= 0) continue;
+      const int32_t d = g.cur[v[r]];
+      if (d <= s.k) {
+        g.core[v[r]] = s.k;
+        if (g.order) g.order[v[r]] = s.round;
+        on[0] |= 1u << r;
+      } else {
+        mn = min(mn, d);
+        if (d <= s.U) on[1] |= 1u << r;
+        on[2] |= 1u << r;
       }
     }
-    wave_push(take, v, F, cnt);
-    if (S) wave_push(keep, v, S, cnt + 3);
-    if (Nr) wave_push(near, v, Nr, ncnt);
+    // the wavefront's place in the tile, then the tile's in the list
+    int32_t at[3];
+    for (int l = 0; l < lists; ++l) {
+      int32_t k = 0;
+#pragma unroll
+      for (int r = 0; r < kScanPer; ++r) k += (int32_t)__popcll(__ballot((on[l] >> r) & 1u));
+      int32_t w = 0;
+      if (lane_id() == 0 && k) w = atomicAdd(&lds.count[l], k);
+      at[l] = __builtin_amdgcn_readfirstlane(w);
+    }
+    __syncthreads();
+    if (threadIdx.x < lists) {
+      const int32_t k = lds.count[threadIdx.x];
+      if (k) lds.base[threadIdx.x] = atomicAdd(cnt[threadIdx.x], k);
+    }
+    __syncthreads();
+    for (int l = 0; l < lists; ++l) {
+      int32_t p = lds.base[l] + at[l];
+#pragma unroll
+      for (int r = 0; r < kScanPer; ++r) {
+        const bool take = (on[l] >> r) & 1u;
+        const uint64_t m = __ballot(take);
+        if (take) q[l][p + mask_below(m)] = v[r];
+        p += (int32_t)__popcll(m);
+      }
+    }
   }
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) mn = min(mn, __shfl_xor(mn, o, kWave));
-  if (lane_id() == 0 && mn != 0x7fffffff) atomicMin(cnt + 2, mn);
+  if (lane_id() == 0 && mn != kNoDegree &&
+      mn < __hip_atomic_load(&c->least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMin(&c->least, mn);
 }
 
 // Rows up to this length are walked by their node's 8-lane group; longer
@@ -127,13 +259,13 @@ constexpr int32_t kPeelShort = 64;
 constexpr int kPeelU = 8;
 
 // kPeelU steps of a walk over row[0, d): the entries j0 + q * W + t, q <
-// kPeelU (t = the lane's place among the W walkers). Every lane of the
-// wavefront calls it (the pushes are wave-wide).
+// kPeelU (t = the lane's place among the W walkers): every neighbour left
+// loses one from its current degree; the one decrement from k + 1 to k gives
+// it core number k and puts it on the next frontier, the one from U + 1 to U
+// on the near list. Every lane of the wavefront calls it (the pushes are
+// wave-wide).
 __device__ __forceinline__ void peel_steps(const int32_t* __restrict__ row, int32_t d, int32_t j0, int32_t W,
-                                           int32_t t, int32_t k, int32_t U, int32_t* __restrict__ cur,
-                                           int32_t* __restrict__ core, int32_t* __restrict__ order,
-                                           int32_t next_round, int32_t* __restrict__ G, int32_t* __restrict__ gcnt,
-                                           int32_t* __restrict__ Nr, int32_t* __restrict__ ncnt) {
+                                           int32_t t, const CoreState& s, const CoreArrays& g, CoreCount* c) {
   int32_t w[kPeelU];
   bool live[kPeelU];
 #pragma unroll
@@ -143,73 +275,98 @@ __device__ __forceinline__ void peel_steps(const int32_t* __restrict__ row, int3
     w[q] = live[q] ? row[j] : 0;
   }
 #pragma unroll
-  for (int q = 0; q < kPeelU; ++q) live[q] = live[q] && core[w[q]] < 0;
+  for (int q = 0; q < kPeelU; ++q) live[q] = live[q] && g.core[w[q]] < 0;
   int32_t old[kPeelU];
 #pragma unroll
-  for (int q = 0; q < kPeelU; ++q) old[q] = live[q] ? atomicSub(&cur[w[q]], 1) : 0;
+  for (int q = 0; q < kPeelU; ++q) old[q] = live[q] ? atomicSub(&g.cur[w[q]], 1) : 0;
 #pragma unroll
   for (int q = 0; q < kPeelU; ++q) {
-    // the one decrement from k + 1 to k gives w core number k; the one from
-    // U + 1 to U puts it on the near list
-    const bool take = live[q] && old[q] == k + 1;
-    const bool enter = live[q] && old[q] == U + 1;
+    const bool take = live[q] && old[q] == s.k + 1;
+    const bool enter = live[q] && old[q] == s.U + 1;
     if (take) {
-      core[w[q]] = k;
-      if (order) order[w[q]] = next_round;
+      g.core[w[q]] = s.k;
+      if (g.order) g.order[w[q]] = s.round + s.rounds + 1;
     }
-    wave_push(take, w[q], G, gcnt);
-    if (Nr) wave_push(enter, w[q], Nr, ncnt);
+    wave_push(take, w[q], g.F[s.fb ^ 1], &c->f);
+    wave_push(enter, w[q], g.near[s.xb] + s.nx, &c->near);
   }
 }
 
-// Removes the frontier F[0, nf) of level k: every neighbour w still left
-// loses one from its current degree; the one decrement that takes it from
-// k + 1 to k gives it core number k and puts it on the next frontier G.
-// nf_dev (may be null): the frontier size is read there (the previous
-// round's next-frontier count), not taken from nf; gcnt counts the next
-// frontier.
-__global__ __launch_bounds__(kCoreNT) void k_core_peel(const int32_t* __restrict__ F, int32_t nf,
-                                                       const int32_t* __restrict__ nf_dev, int32_t k,
-                                                       const int64_t* __restrict__ off,
-                                                       const int32_t* __restrict__ deg,
-                                                       const int32_t* __restrict__ adj, int32_t* __restrict__ cur,
-                                                       int32_t* __restrict__ core, int32_t* __restrict__ G,
-                                                       int32_t* __restrict__ gcnt, int32_t* __restrict__ order,
-                                                       int32_t round, int32_t U, int32_t* __restrict__ Nr,
-                                                       int32_t* __restrict__ ncnt) {
-  if (nf_dev) nf = *nf_dev;
-  constexpr int GPB = kCoreNT / kPeelG;
+// One round: the frontier's nodes by 8-lane groups while there are many (8 per
+// wavefront and more), else by a wavefront each, or by several blocks each when
+// the frontier is smaller than the grid (late levels: tens of nodes with rows
+// of thousands of entries, which one wavefront walks 512 at a time).
+__device__ __forceinline__ void core_peel(const CoreState& s, const CoreArrays& g, CoreCount* c) {
+  const int32_t* F = g.F[s.fb];
+  const int32_t nf = s.nf;
   const int lane = lane_id();
-  const int g = threadIdx.x % kPeelG;
-  const int64_t step = (int64_t)gridDim.x * GPB;
+  const int32_t blocks = (int32_t)gridDim.x;
+  if (nf <= blocks) {
+    const int32_t per = blocks / nf;  // blocks per node
+    const int32_t i = (int32_t)blockIdx.x % nf, part = (int32_t)blockIdx.x / nf;
+    if (part >= per) return;
+    const int32_t v = F[i];
+    const int32_t d = g.deg[v];
+    const int32_t* row = g.adj + g.off[v];
+    for (int32_t j0 = part * kCoreNT * kPeelU; j0 < d; j0 += per * kCoreNT * kPeelU)
+      peel_steps(row, d, j0, kCoreNT, threadIdx.x, s, g, c);
+    return;
+  }
+  if (nf <= 8 * blocks * (kCoreNT / kWave)) {
+    const int64_t step = (int64_t)blocks * (kCoreNT / kWave);
+    for (int64_t i = (int64_t)blockIdx.x * (kCoreNT / kWave) + threadIdx.x / kWave; i < nf; i += step) {
+      const int32_t v = F[i];
+      const int32_t d = g.deg[v];
+      const int32_t* row = g.adj + g.off[v];
+      for (int32_t j0 = 0; j0 < d; j0 += kWave * kPeelU) peel_steps(row, d, j0, kWave, lane, s, g, c);
+    }
+    return;
+  }
+  constexpr int GPB = kCoreNT / kPeelG;
+  const int t = threadIdx.x % kPeelG;
+  const int64_t step = (int64_t)blocks * GPB;
   for (int64_t b = (int64_t)blockIdx.x * GPB; b < nf; b += step) {  // uniform trip count
     const int64_t fi = b + threadIdx.x / kPeelG;
     int32_t dv = 0;
     int64_t rb = 0;
     if (fi < nf) {
       const int32_t v = F[fi];
-      dv = deg[v];
-      rb = off[v];
+      dv = g.deg[v];
+      rb = g.off[v];
     }
     // short rows: each group walks its own, the wavefront its longest short one
     const int32_t ds = dv <= kPeelShort ? dv : 0;
     int32_t dmax = ds;
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) dmax = max(dmax, __shfl_xor(dmax, o, kWave));
-    for (int32_t j0 = 0; j0 < dmax; j0 += kPeelG * kPeelU)
-      peel_steps(adj + rb, ds, j0, kPeelG, g, k, U, cur, core, order, round + 1, G, gcnt, Nr, ncnt);
+    for (int32_t j0 = 0; j0 < dmax; j0 += kPeelG * kPeelU) peel_steps(g.adj + rb, ds, j0, kPeelG, t, s, g, c);
     // long rows: the whole wavefront on each in turn (group leaders' bits)
-    uint64_t longs = __ballot(g == 0 && dv > kPeelShort);
+    uint64_t longs = __ballot(t == 0 && dv > kPeelShort);
     while (longs) {
       const int src = __builtin_ctzll(longs);
       longs &= longs - 1;
       const int32_t d = __shfl(dv, src, kWave);
       const int64_t r = ((int64_t)__shfl((int32_t)(rb >> 32), src, kWave) << 32) |
                         (uint32_t)__shfl((int32_t)rb, src, kWave);
-      for (int32_t j0 = 0; j0 < d; j0 += kWave * kPeelU)
-        peel_steps(adj + r, d, j0, kWave, lane, k, U, cur, core, order, round + 1, G, gcnt, Nr, ncnt);
+      for (int32_t j0 = 0; j0 < d; j0 += kWave * kPeelU) peel_steps(g.adj + r, d, j0, kWave, lane, s, g, c);
     }
   }
+}
+
+// Step i (1, 2, ..): forms its state from state and counters of step i - 1,
+// does it into counters i, and prepares what step i + 1 reads: state i and
+// zeroed counters i + 1 (those of step i - 2, which nothing reads any more).
+__global__ __launch_bounds__(kCoreNT) void k_core_step(int step, int32_t n, int32_t k_stop, CoreArrays g) {
+  CoreState s = *core_state(g.cnt, step - 1);
+  if (step > 1) core_next(s, *core_count(g.cnt, step - 1), n, k_stop);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *core_state(g.cnt, step) = s;
+    *core_count(g.cnt, step + 1) = CoreCount{0, 0, 0, kNoDegree};
+  }
+  CoreCount* c = core_count(g.cnt, step);
+  __shared__ ScanLds lds;
+  if (s.phase == kCoreScan) core_scan(s, g, c, lds);
+  else if (s.phase == kCorePeel) core_peel(s, g, c);
 }
 
 __global__ __launch_bounds__(kCoreNT) void k_core_fill(int32_t n, int32_t k, int32_t* __restrict__ core) {
@@ -223,50 +380,30 @@ unsigned core_grid(int64_t work) {
   return (unsigned)(b < 1 ? 1 : b > 8192 ? 8192 : b);
 }
 
+CoreArrays core_arrays(const CoreBuffers& b) {
+  return CoreArrays{b.off, b.deg, b.adj, b.cur, b.core, b.order, {b.F[0], b.F[1]}, {b.A[0], b.A[1]},
+                    {b.near[0], b.near[1]}, b.cnt};
+}
+
 }  // namespace
 
-hipError_t launch_core_init(int32_t n, const int32_t* deg, int32_t* cur, int32_t* core, hipStream_t s) {
-  k_core_init<<<core_grid(n), kCoreNT, 0, s>>>(n, deg, cur, core);
+hipError_t launch_core_init(int32_t n, int32_t k_stop, const CoreBuffers& b, hipStream_t s) {
+  k_core_init<<<core_grid(n), kCoreNT, 0, s>>>(n, k_stop, b.deg, b.cur, b.core, b.cnt);
   return hipGetLastError();
 }
 
-hipError_t launch_core_reset(int32_t* cnt, int which, int near, hipStream_t s) {
-  k_core_reset<<<1, 64, 0, s>>>(cnt, which, near);
+hipError_t launch_core_steps(int first, int count, int32_t n, int32_t k_stop, const CoreBuffers& b, hipStream_t s) {
+  // four blocks a CU: with 512 blocks the first levels took longer (8.0 ms at
+  // R-MAT 20), with more the short steps
+  const unsigned grid = std::min(core_grid((int64_t)n * kPeelG), 1024u);
+  const CoreArrays g = core_arrays(b);
+  for (int i = first; i < first + count; ++i) k_core_step<<<grid, kCoreNT, 0, s>>>(i, n, k_stop, g);
   return hipGetLastError();
 }
 
-hipError_t launch_core_scan(int32_t na, const int32_t* A, int32_t k, const int32_t* cur, int32_t* core, int32_t* F,
-                            int32_t* S, int32_t* cnt, int32_t* order, int32_t round, int32_t U, int32_t* Nr,
-                            int32_t* ncnt, hipStream_t s) {
-  if (na <= 0) return hipSuccess;
-  k_core_scan<<<core_grid(na), kCoreNT, 0, s>>>(na, A, k, cur, core, F, S, cnt, order, round, U, Nr, ncnt);
-  return hipGetLastError();
-}
-
-hipError_t launch_core_peel(const int32_t* F, int32_t nf, int32_t k, const int64_t* off, const int32_t* deg,
-                            const int32_t* adj, int32_t* cur, int32_t* core, int32_t* G, int32_t* cnt, int32_t* order,
-                            int32_t round, int32_t U, int32_t* Nr, int32_t* ncnt, hipStream_t s) {
-  if (nf <= 0) return hipSuccess;
-  k_core_peel<<<core_grid((int64_t)nf * kPeelG), kCoreNT, 0, s>>>(F, nf, nullptr, k, off, deg, adj, cur, core, G,
-                                                                  cnt + 1, order, round, U, Nr, ncnt);
-  return hipGetLastError();
-}
-
-int core_peel_batch() { return kPeelBatch; }
-
-hipError_t launch_core_peel_batch(int32_t* B0, int32_t* B1, int32_t nf, int32_t k, const int64_t* off,
-                                  const int32_t* deg, const int32_t* adj, int32_t* cur, int32_t* core, int32_t* cnt,
-                                  int32_t* order, int32_t round, int32_t U, int32_t* Nr, int32_t* ncnt,
-                                  hipStream_t s) {
-  if (nf <= 0) return hipSuccess;
-  k_core_reset<<<1, 64, 0, s>>>(cnt, 2, -1);
-  // later rounds read their size on the device; their grid follows the
-  // first round's (grid-stride loops take larger frontiers)
-  const unsigned grid = core_grid(std::max<int64_t>((int64_t)nf, kPeelBatchMinNodes) * kPeelG);
-  for (int i = 0; i < kPeelBatch; ++i)
-    k_core_peel<<<grid, kCoreNT, 0, s>>>((i & 1) ? B1 : B0, nf, i ? cnt + 16 + i - 1 : nullptr, k, off, deg, adj,
-                                         cur, core, (i & 1) ? B0 : B1, cnt + 16 + i, order, round + i, U, Nr, ncnt);
-  return hipGetLastError();
+CoreProgress core_progress(const int32_t* cnt, int step) {
+  const CoreState* s = reinterpret_cast<const CoreState*>(cnt) + (step & 1);
+  return CoreProgress{s->phase == kCoreDone, s->left, s->maxc};
 }
 
 hipError_t launch_core_fill(int32_t n, int32_t k, int32_t* core, hipStream_t s) {
