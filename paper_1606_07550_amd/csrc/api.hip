@@ -956,7 +956,7 @@ int tricc_graph_count_k4(const tricc_graph* g, uint64_t* d_total, void* stream) 
     return fail(TRICC_EOVERFLOW, "4-clique counting takes out-degrees up to %d (this graph: %lld)", kK4Cap,
                 (long long)g->info.max_outdeg);
   const Layout& L = g->L;
-  HIPCHK(launch_count_k4(g->n, g->at<int64_t>(L.doff), g->at<int32_t>(L.dcol),
+  HIPCHK(launch_count_k4(g->n, g->info.max_outdeg, g->at<int64_t>(L.doff), g->at<int32_t>(L.dcol),
                          reinterpret_cast<unsigned long long*>(d_total), static_cast<hipStream_t>(stream)));
   return TRICC_OK;
 }
@@ -968,7 +968,7 @@ int tricc_graph_count_k5(const tricc_graph* g, uint64_t* d_total, void* stream) 
     return fail(TRICC_EOVERFLOW, "5-clique counting takes out-degrees up to %d (this graph: %lld)", kK5Cap,
                 (long long)g->info.max_outdeg);
   const Layout& L = g->L;
-  HIPCHK(launch_count_k5(g->n, g->at<int64_t>(L.doff), g->at<int32_t>(L.dcol),
+  HIPCHK(launch_count_k5(g->n, g->info.max_outdeg, g->at<int64_t>(L.doff), g->at<int32_t>(L.dcol),
                          reinterpret_cast<unsigned long long*>(d_total), static_cast<hipStream_t>(stream)));
   return TRICC_OK;
 }

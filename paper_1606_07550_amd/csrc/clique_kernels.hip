@@ -5,18 +5,25 @@
 // more level of the same intersection.
 #include "device_common.h"
 #include "kernels.h"
+#include "tables.h"
 
 namespace tricc {
 
 namespace {
 
 constexpr int kK4NT = 256;
-// Out-degrees up to kK4BitsMid take the bit-row kernel with 256 threads and
-// 39 KB of LDS; up to kK4BitsMax the one with 1,024 threads and 136 KB (one
+// Loads of 64 ids per step while rows are built, two steps in flight (four
+// steps of 1 to 3 loads measured no faster).
+constexpr int kK4U = 4;
+// Out-degrees up to 64 take the kernel with a wavefront per node; up to
+// kK4BitsLow and kK4BitsMid the bit-row kernel with 256 threads (16 and 47 KB
+// of LDS); up to kK4BitsMax the one with 1,024 threads and 146 KB (one
 // block per CU); up to 2,048 the pass kernel over quarters of the positions
 // (1,024 threads, 142 KB); up to 4,096 the pass kernel over sixteenths
 // (150 KB); up to kK4Cap = 8,192 the pass kernel over blocks of 64
 // positions (2 words per row, 102 KB).
+constexpr int kK4BitsSmall = 64;
+constexpr int kK4BitsLow = 256;
 constexpr int kK4BitsMid = 512;
 constexpr int kK4BitsMax = 1024;
 
@@ -29,6 +36,108 @@ __device__ __forceinline__ int32_t pow2_lower_pos(const int32_t* L, int32_t P, i
   for (int32_t s = P >> 1; s > 0; s >>= 1)
     if (L[p + s - 1] < x) p += s;
   return p;
+}
+
+// Places of the ids of N+(u) in it, by a table in LDS (cuckoo, or buckets where
+// a build gives up): two reads that do not depend on each other find an id,
+// against a chain of log2 d in a search of the sorted list.
+template <int SLOTS>
+struct PlaceTable {
+  int4 K[SLOTS / 4];
+  uint16_t place[SLOTS];
+  int32_t fail;
+};
+
+// Table of src[0, d) (d <= SLOTS / 2) for a group of G lanes, g = lane in group;
+// true for the cuckoo layout. Callers separate it from the table's last use.
+template <int G, int SLOTS>
+__device__ __forceinline__ bool build_places(PlaceTable<SLOTS>& S, const int32_t* __restrict__ src, int32_t d, int g) {
+  int32_t* K = reinterpret_cast<int32_t*>(S.K);
+  for (int s = g; s < SLOTS; s += G) K[s] = -1;
+  if (g == 0) S.fail = 0;
+  group_sync<G>();
+  for (int i = g; i < d; i += G)
+    if (!cuckoo_insert<SLOTS>(K, src[i])) S.fail = 1;
+  group_sync<G>();
+  const bool ck = __builtin_amdgcn_readfirstlane(S.fail) == 0;
+  if (!ck) {
+    for (int s = g; s < SLOTS; s += G) K[s] = -1;
+    group_sync<G>();
+    for (int i = g; i < d; i += G) bucket_insert<SLOTS / 4>(K, src[i]);
+    group_sync<G>();
+  }
+  for (int i = g; i < d; i += G) {
+    const int32_t x = src[i];
+    S.place[ck ? cuckoo_find<SLOTS>(K, x) : table_find<SLOTS>(K, x)] = (uint16_t)i;
+  }
+  group_sync<G>();
+  return ck;
+}
+
+// Bit rows of the subgraph induced on N+(u) = dcol[ub, ub + d): for the lists
+// i = wv, wv + NW, .. every id of N+(w_i) that is in N+(u) calls set(i, place).
+// Begin and length of 64 lists at a time sit in the lanes; of each list, U
+// loads of 64 ids are in flight while the ones before are looked up.
+template <int NW, int U, typename Probe, typename Set>
+__device__ __forceinline__ void stream_rows(int32_t wv0, int32_t d, int64_t ub, const int64_t* __restrict__ doff,
+                                            const int32_t* __restrict__ dcol, const uint16_t* place, Probe probe,
+                                            Set set) {
+  const int32_t wv = __builtin_amdgcn_readfirstlane(wv0);
+  const int lane = lane_id();
+  for (int32_t i0 = wv; i0 < d; i0 += NW * kWave) {
+    const int32_t left = (d - i0 + NW - 1) / NW;
+    const int32_t cnt = left < kWave ? left : kWave;
+    int32_t vb = 0, vn = 0;
+    if (lane < cnt) {
+      const int32_t w = dcol[ub + i0 + lane * NW];
+      const int64_t b = doff[w];
+      vb = (int32_t)b;
+      vn = (int32_t)(doff[w + 1] - b);
+    }
+    int32_t k = 0, p = 0;
+    int32_t b = __builtin_amdgcn_readlane(vb, 0), n = __builtin_amdgcn_readlane(vn, 0);
+    auto advance = [&](int32_t (&cur)[U], int32_t (&nxt)[U]) -> bool {
+      int32_t nk = k, nb = b, nn = n, np = p + U * kWave;
+      if (np >= n) {
+        nk = k + 1;
+        np = 0;
+        nn = 0;
+        if (nk < cnt) {
+          nb = __builtin_amdgcn_readlane(vb, nk);
+          nn = __builtin_amdgcn_readlane(vn, nk);
+        }
+      }
+      load_chunk<U>(nxt, dcol + nb, np, nn, lane);
+      const int32_t rem = n - p;
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        if (q * kWave >= rem) break;
+        int off;
+        if (probe(cur[q], lane + q * kWave < rem, &off)) set(i0 + k * NW, (int32_t)place[off >> 2]);
+      }
+      if (np == 0 && nk >= cnt) return false;
+      k = nk;
+      b = nb;
+      n = nn;
+      p = np;
+      return true;
+    };
+    int32_t x[U], y[U];
+    load_chunk<U>(x, dcol + b, 0, n, lane);
+    while (advance(x, y) && advance(y, x)) {
+    }
+  }
+}
+
+// Both layouts of the table.
+template <int NW, int U, int SLOTS, typename Set>
+__device__ __forceinline__ void stream_rows_of(bool ck, int32_t wv, int32_t d, int64_t ub,
+                                               const int64_t* __restrict__ doff, const int32_t* __restrict__ dcol,
+                                               const PlaceTable<SLOTS>& S, Set set) {
+  if (ck)
+    stream_rows<NW, U>(wv, d, ub, doff, dcol, S.place, CuckooProbe<SLOTS>{reinterpret_cast<const int32_t*>(S.K)}, set);
+  else
+    stream_rows<NW, U>(wv, d, ub, doff, dcol, S.place, BucketProbe<SLOTS / 4>{S.K}, set);
 }
 
 // Block-wide total of the per-lane counts, one 64-bit atomic per block.
@@ -53,8 +162,8 @@ __device__ __forceinline__ void k4_block_total(unsigned long long acc, unsigned 
 // per node. The block scans `chunk` (<= NT) consecutive ids at a time
 // (grid-stride over such chunks), queues the ones in range in LDS, then
 // takes them in turn. The block builds the subgraph induced on N+(u) as bit rows in
-// LDS (row i: the positions in N+(u) of N+(L[i]) ∩ N+(u), each wavefront
-// building the rows of its w's by searching N+(w) in N+(u)); then every pair
+// LDS (row i: the places in N+(u) of N+(w_i) ∩ N+(u), each wavefront
+// building the rows of its w's by looking N+(w) up in a table of N+(u)); then every pair
 // (w, x) with x in row w adds popcount(row w & row x): the z that close the
 // 4-clique {u, w, x, z}. Rows take RS = 2^rs words (RS >= d / 32), and the
 // lanes of a wavefront cover 64 / RS rows x at once, one word each. LISTED:
@@ -68,7 +177,7 @@ __global__ __launch_bounds__(NT) void k_count_k4_bits(int32_t n, int32_t chunk, 
   constexpr int NW = NT / kWave;
   static_assert(DMAX % 32 == 0 && DMAX <= 65536, "positions are stored in 16 bits");
   static_assert(LISTED || (DMIN >= 512 && DMAX <= 1024), "unlisted rows must be 32 words");
-  __shared__ int32_t L[DMAX];
+  __shared__ PlaceTable<2 * DMAX> S;
   __shared__ uint32_t B[DMAX * (DMAX / 32)];
   __shared__ uint16_t Pl[LISTED ? NW : 1][LISTED ? DMAX : 1];
   __shared__ unsigned long long red[NW];
@@ -94,21 +203,11 @@ __global__ __launch_bounds__(NT) void k_count_k4_bits(int32_t n, int32_t chunk, 
       const int32_t d = (int32_t)(doff[u + 1] - ub);
       const int rs = d <= 32 ? 0 : 32 - __builtin_clz((uint32_t)((d + 31) / 32 - 1));
       const int RS = 1 << rs;
-      const int32_t P = 1 << (32 - __builtin_clz((uint32_t)(d - 1)));  // power of two >= d, <= DMAX
-      __syncthreads();  // L and B of the previous node are no longer read
-      for (int32_t i = threadIdx.x; i < P; i += NT) L[i] = i < d ? dcol[ub + i] : kPad;
+      __syncthreads();  // the table and B of the previous node are no longer read
       for (int32_t q = threadIdx.x; q < d * RS; q += NT) B[q] = 0u;
-      __syncthreads();
-      for (int32_t i = wv; i < d; i += NW) {
-        const int32_t w = L[i];
-        const int64_t wb = doff[w];
-        const int32_t dw = (int32_t)(doff[w + 1] - wb);
-        for (int32_t t = lane; t < dw; t += kWave) {
-          const int32_t y = dcol[wb + t];
-          const int32_t p = pow2_lower_pos(L, P, y);
-          if (L[p] == y) atomicOr(&B[i * RS + (p >> 5)], 1u << (p & 31));
-        }
-      }
+      const bool ck = build_places<NT>(S, dcol + ub, d, threadIdx.x);
+      stream_rows_of<NW, kK4U>(ck, wv, d, ub, doff, dcol, S,
+                               [&](int32_t i, int32_t p) { atomicOr(&B[i * RS + (p >> 5)], 1u << (p & 31)); });
       __syncthreads();
       for (int32_t i = wv; i < d && !LISTED; i += NW) {
         // RS == 32: half-wave h takes the h-th of each next two bits of row i
@@ -152,6 +251,61 @@ __global__ __launch_bounds__(NT) void k_count_k4_bits(int32_t n, int32_t chunk, 
           }
         }
         wave_sync();  // the next row reuses Pl
+      }
+    }
+  }
+  k4_block_total<NW>(acc, red, total);
+}
+
+// Nodes with 3 <= d+(u) <= 64: a wavefront per node and no block barrier. Row
+// i is a 64-bit word: built in LDS, then held by lane i. For each place x the
+// lanes whose row has x add popcount(row & row x). The nodes of a block's
+// chunk of ids go to its wavefronts in turn. Three quarters of the nodes of an
+// R-MAT graph are this small; a block of 256 threads for each spent their time
+// in barriers.
+__global__ __launch_bounds__(kK4NT) void k_count_k4_small(int32_t n, int32_t chunk, const int64_t* __restrict__ doff,
+                                                          const int32_t* __restrict__ dcol,
+                                                          unsigned long long* __restrict__ total) {
+  constexpr int NW = kK4NT / kWave;
+  __shared__ PlaceTable<2 * kK4BitsSmall> S[NW];
+  __shared__ unsigned long long R[NW][kWave];
+  __shared__ unsigned long long red[NW];
+  const int wv = threadIdx.x / kWave;
+  const int lane = lane_id();
+  uint32_t* B = reinterpret_cast<uint32_t*>(R[wv]);
+  unsigned long long acc = 0;
+  const int64_t step = (int64_t)gridDim.x * chunk;
+  for (int64_t base = (int64_t)blockIdx.x * chunk; base < n; base += step) {
+    const int32_t ids = (int32_t)min((int64_t)chunk, (int64_t)n - base);
+    for (int32_t v0 = 0; v0 < ids; v0 += NW * kWave) {
+      const int32_t vi = v0 + wv + lane * NW;  // ids in turn
+      int32_t d0 = 0;
+      int64_t b0 = 0;
+      if (vi < ids) {
+        b0 = doff[base + vi];
+        d0 = (int32_t)(doff[base + vi + 1] - b0);
+      }
+      uint64_t todo = __ballot(d0 >= 3 && d0 <= kK4BitsSmall);
+      while (todo) {
+        const int src = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int32_t d = __builtin_amdgcn_readlane(d0, src);
+        const int64_t ub = __builtin_amdgcn_readlane((int32_t)b0, src);  // DAG offsets stay below 2^30
+        wave_sync();  // the table and rows of the previous node are no longer read
+        R[wv][lane] = 0ull;
+        const bool ck = build_places<kWave>(S[wv], dcol + ub, d, lane);
+        stream_rows_of<1, kK4U>(ck, 0, d, ub, doff, dcol, S[wv],
+                                [&](int32_t i, int32_t p) { atomicOr(&B[2 * i + (p >> 5)], 1u << (p & 31)); });
+        wave_sync();
+        const unsigned long long row = R[wv][lane];
+        const int32_t lo = (int32_t)(uint32_t)row, hi = (int32_t)(uint32_t)(row >> 32);
+        uint32_t c = 0;
+        for (int32_t x = 0; x < d; ++x) {
+          const unsigned long long rx = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(hi, x) << 32) |
+                                        (uint32_t)__builtin_amdgcn_readlane(lo, x);
+          if ((row >> x) & 1ull) c += (uint32_t)__popcll(row & rx);
+        }
+        acc += c;
       }
     }
   }
@@ -268,7 +422,7 @@ __global__ __launch_bounds__(NT) void k_count_k5_bits(int32_t n, int32_t chunk, 
                                                       unsigned long long* __restrict__ total) {
   constexpr int NW = NT / kWave;
   static_assert(DMAX % 32 == 0 && DMAX <= 1024, "rows of at most 32 words");
-  __shared__ int32_t L[DMAX];
+  __shared__ PlaceTable<2 * DMAX> S;
   __shared__ uint32_t B[DMAX * (DMAX / 32)];
   __shared__ uint16_t Y[NW][DMAX];
   __shared__ unsigned long long red[NW];
@@ -294,21 +448,11 @@ __global__ __launch_bounds__(NT) void k_count_k5_bits(int32_t n, int32_t chunk, 
       const int32_t d = (int32_t)(doff[u + 1] - ub);
       const int rs = d <= 32 ? 0 : 32 - __builtin_clz((uint32_t)((d + 31) / 32 - 1));
       const int RS = 1 << rs;
-      const int32_t P = 1 << (32 - __builtin_clz((uint32_t)(d - 1)));  // power of two >= d, <= DMAX
-      __syncthreads();  // L and B of the previous node are no longer read
-      for (int32_t i = threadIdx.x; i < P; i += NT) L[i] = i < d ? dcol[ub + i] : kPad;
+      __syncthreads();  // the table and B of the previous node are no longer read
       for (int32_t q = threadIdx.x; q < d * RS; q += NT) B[q] = 0u;
-      __syncthreads();
-      for (int32_t i = wv; i < d; i += NW) {
-        const int32_t w = L[i];
-        const int64_t wb = doff[w];
-        const int32_t dw = (int32_t)(doff[w + 1] - wb);
-        for (int32_t t = lane; t < dw; t += kWave) {
-          const int32_t y = dcol[wb + t];
-          const int32_t p = pow2_lower_pos(L, P, y);
-          if (L[p] == y) atomicOr(&B[i * RS + (p >> 5)], 1u << (p & 31));
-        }
-      }
+      const bool ck = build_places<NT>(S, dcol + ub, d, threadIdx.x);
+      stream_rows_of<NW, kK4U>(ck, wv, d, ub, doff, dcol, S,
+                               [&](int32_t i, int32_t p) { atomicOr(&B[i * RS + (p >> 5)], 1u << (p & 31)); });
       __syncthreads();
       const int32_t k = lane & (RS - 1);
       const int32_t js = lane >> rs;
@@ -366,30 +510,49 @@ static unsigned k4_grid(int32_t n, int32_t chunk, int64_t cap) {
   return (unsigned)(g < cap ? g : cap);
 }
 
-hipError_t launch_count_k4(int32_t n, const int64_t* doff, const int32_t* dcol, unsigned long long* total,
-                           hipStream_t s) {
+// The bit-row kernels get a block per few ids (the dispatcher balances them; a
+// grid of a few blocks a CU took 30% longer on an R-MAT graph of 240k nodes).
+// Kernels of out-degrees that the graph does not reach are left out. Measured
+// on that graph, largest out-degree 396: 3.35 -> 1.60 ms against one bit-row
+// kernel for all out-degrees up to 512 whose rows were built by searches of
+// N+(u) (of the 1.60 ms, 0.40 up to out-degree 64, 0.71 up to 256).
+hipError_t launch_count_k4(int32_t n, int64_t max_outdeg, const int64_t* doff, const int32_t* dcol,
+                           unsigned long long* total, hipStream_t s) {
   k_zero_one<<<1, 64, 0, s>>>(total);
-  if (n > 0) {
+  if (n > 0 && max_outdeg >= 3) {
+    const int32_t cs = k4_chunk(n, 16384, 1024);
+    k_count_k4_small<<<k4_grid(n, cs, 16384), kK4NT, 0, s>>>(n, cs, doff, dcol, total);
     const int32_t cm = k4_chunk(n, 65536, kK4NT);
-    k_count_k4_bits<0, kK4BitsMid, kK4NT, true><<<k4_grid(n, cm, 65536), kK4NT, 0, s>>>(n, cm, doff, dcol, total);
+    if (max_outdeg > kK4BitsSmall)
+      k_count_k4_bits<kK4BitsSmall, kK4BitsLow, kK4NT, true><<<k4_grid(n, cm, 65536), kK4NT, 0, s>>>(n, cm, doff, dcol,
+                                                                                                  total);
+    if (max_outdeg > kK4BitsLow)
+      k_count_k4_bits<kK4BitsLow, kK4BitsMid, 512, true><<<k4_grid(n, cm, 65536), 512, 0, s>>>(n, cm, doff, dcol, total);
     const int32_t cb = k4_chunk(n, 1024, 1024);
-    k_count_k4_bits<kK4BitsMid, kK4BitsMax, 1024, false><<<k4_grid(n, cb, 1024), 1024, 0, s>>>(n, cb, doff, dcol,
-                                                                                                 total);
-    k_count_k4_passes<kK4BitsMax, 2048, 512><<<k4_grid(n, cb, 1024), kK4QNT, 0, s>>>(n, cb, doff, dcol, total);
-    k_count_k4_passes<2048, 4096, 256><<<k4_grid(n, cb, 1024), kK4QNT, 0, s>>>(n, cb, doff, dcol, total);
-    k_count_k4_passes<4096, kK4Cap, 64><<<k4_grid(n, cb, 1024), kK4QNT, 0, s>>>(n, cb, doff, dcol, total);
+    if (max_outdeg > kK4BitsMid)
+      k_count_k4_bits<kK4BitsMid, kK4BitsMax, 1024, false><<<k4_grid(n, cb, 1024), 1024, 0, s>>>(n, cb, doff, dcol,
+                                                                                                total);
+    if (max_outdeg > kK4BitsMax)
+      k_count_k4_passes<kK4BitsMax, 2048, 512><<<k4_grid(n, cb, 1024), kK4QNT, 0, s>>>(n, cb, doff, dcol, total);
+    if (max_outdeg > 2048)
+      k_count_k4_passes<2048, 4096, 256><<<k4_grid(n, cb, 1024), kK4QNT, 0, s>>>(n, cb, doff, dcol, total);
+    if (max_outdeg > 4096)
+      k_count_k4_passes<4096, kK4Cap, 64><<<k4_grid(n, cb, 1024), kK4QNT, 0, s>>>(n, cb, doff, dcol, total);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_count_k5(int32_t n, const int64_t* doff, const int32_t* dcol, unsigned long long* total,
-                           hipStream_t s) {
+hipError_t launch_count_k5(int32_t n, int64_t max_outdeg, const int64_t* doff, const int32_t* dcol,
+                           unsigned long long* total, hipStream_t s) {
   k_zero_one<<<1, 64, 0, s>>>(total);
-  if (n > 0) {
+  if (n > 0 && max_outdeg >= 4) {
     const int32_t cm = k4_chunk(n, 65536, kK4NT);
-    k_count_k5_bits<0, kK4BitsMid, kK4NT><<<k4_grid(n, cm, 65536), kK4NT, 0, s>>>(n, cm, doff, dcol, total);
+    k_count_k5_bits<0, kK4BitsLow, kK4NT><<<k4_grid(n, cm, 65536), kK4NT, 0, s>>>(n, cm, doff, dcol, total);
+    if (max_outdeg > kK4BitsLow)
+      k_count_k5_bits<kK4BitsLow, kK4BitsMid, kK4NT><<<k4_grid(n, cm, 65536), kK4NT, 0, s>>>(n, cm, doff, dcol, total);
     const int32_t cb = k4_chunk(n, 2048, 512);
-    k_count_k5_bits<kK4BitsMid, kK5Cap, 512><<<k4_grid(n, cb, 2048), 512, 0, s>>>(n, cb, doff, dcol, total);
+    if (max_outdeg > kK4BitsMid)
+      k_count_k5_bits<kK4BitsMid, kK5Cap, 512><<<k4_grid(n, cb, 2048), 512, 0, s>>>(n, cb, doff, dcol, total);
   }
   return hipGetLastError();
 }

@@ -191,3 +191,27 @@ def test_k4_complete_graph_above_4096():
     g = P.Graph(n, dev(s), dev(d))
     assert g.info["max_outdeg"] == 4099
     assert gpu_k4(g) == comb(4100, 4)
+
+
+@pytest.mark.parametrize("core", [3, 4, 63, 64, 65, 127, 129, 256, 257, 511, 512])
+def test_out_degrees_at_the_kernels_edges(core):
+    """Centres whose out-degree is `core` (the centres share a random core that
+    leaves lift above them in degree), with sparse rows, beside an R-MAT graph
+    whose out-degrees take the kernels of smaller rows."""
+    rng = np.random.default_rng(core)
+    centres = 3
+    iu, ju = np.triu_indices(core, 1)
+    keep = rng.random(iu.size) < (0.9 if core < 10 else 0.15)
+    c = np.repeat(np.arange(core, core + centres), core)
+    leaves = centres + 2
+    leaf = core + centres + np.arange(core * (core + leaves))
+    parts = [(iu[keep], ju[keep]), (c, np.tile(np.arange(core), centres)),
+             (np.repeat(np.arange(core), core + leaves), leaf)]
+    n1 = int(core + centres + leaf.size)
+    n2, s2, d2 = I.rmat(9, 8, seed=core)
+    s = np.concatenate([p[0] for p in parts] + [s2.astype(np.int64) + n1])
+    d = np.concatenate([p[1] for p in parts] + [d2.astype(np.int64) + n1])
+    g = P.Graph(n1 + n2, dev(s), dev(d))
+    assert core <= g.info["max_outdeg"] <= max(core, 64)
+    assert gpu_k4(g) == oracle.k4(n1 + n2, s, d, order=1)
+    assert gpu_k5(g) == oracle.k5(n1 + n2, s, d, order=1)
