@@ -45,10 +45,10 @@ __device__ __forceinline__ void credit(uint32_t* C, int off) {
 // DPP lane permutations (pairs, quads, half-row and row mirrors), then the
 // four row sums read on the scalar unit.
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xb1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4e, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, false);  // row_half_mirror
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xf, 0xf, false);  // row_mirror
+  x += dpp<0xb1>(x);   // quad_perm [1,0,3,2]
+  x += dpp<0x4e>(x);   // quad_perm [2,3,0,1]
+  x += dpp<0x141>(x);  // row_half_mirror
+  x += dpp<0x140>(x);  // row_mirror
   return (uint32_t)(__builtin_amdgcn_readlane((int)x, 0) + __builtin_amdgcn_readlane((int)x, 16) +
                     __builtin_amdgcn_readlane((int)x, 32) + __builtin_amdgcn_readlane((int)x, 48));
 }
@@ -76,15 +76,65 @@ constexpr int kPackUnroll = 3;
 // Lanes per node on the packed small-node path by default (d+ <= kSmallGS).
 constexpr int kSmallGS = 16;
 
-// Packed streaming of the short lists among items [i0, i1) of a group: a
-// window of up to 64 lists sits in the lanes (begin, length, inclusive
-// prefix of lengths); each step gives every lane one id of the window's
-// concatenation, found by a shuffle binary search over the prefixes. A hit
-// credits its table slot and its list's counter Wc. Returns the wave's hits.
+// Positions of a concatenation of lists whose starts are marked at a time: five
+// steps of the packed streams, one bit a position.
+constexpr int32_t kPackWindow = 5 * kPackUnroll * kWave;
+struct PackStarts {
+  uint64_t bits[(kPackWindow / kWave + 1) & ~1];
+};
+
+// The concatenation of 64 lists, one per lane (begin b, length n, 0 for none),
+// 64 ids per step: body(x, k, valid) gets the lane's id and the number of its
+// list among the lists that are not empty. The list of position t is the number
+// of list starts in (0, t]: the starts are marked as bits in LDS, so a step
+// takes one read of 64 bits, a lane-mask count and, through where(k), the offset
+// of list k against its place in the concatenation. (A search of the lanes'
+// prefixes by shuffles is six dependent LDS round trips and 30 instructions a
+// step.) kPackUnroll independent gathers are in flight before their bodies.
+template <typename Where, typename Body>
+__device__ __forceinline__ void stream_lists(int32_t n, int32_t ex, int32_t total, PackStarts& P,
+                                             const int32_t* __restrict__ dcol, Where where, Body body) {
+  const int lane = lane_id();
+  uint32_t* bits = reinterpret_cast<uint32_t*>(P.bits);
+  int32_t before = 0;  // starts in (0, t0]
+  for (int32_t w0 = 0; w0 < total; w0 += kPackWindow) {
+    wave_sync();  // the previous window's bits are no longer read
+    if (lane < (int)(sizeof(PackStarts) / 4)) bits[lane] = 0u;
+    wave_sync();
+    const int32_t at = ex - 1 - w0;
+    if (n > 0 && (uint32_t)at < (uint32_t)kPackWindow) atomicOr(&bits[at >> 5], 1u << (at & 31));
+    wave_sync();
+    const int32_t end = min(total, w0 + kPackWindow);
+    for (int32_t t0 = w0; t0 < end; t0 += kPackUnroll * kWave) {
+      int32_t x[kPackUnroll], kk[kPackUnroll];
+#pragma unroll
+      for (int r = 0; r < kPackUnroll; ++r) {
+        const int32_t t = t0 + r * kWave + lane;
+        const uint64_t mv = P.bits[(t0 - w0) / kWave + r];
+        const uint64_t m = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(mv >> 32)) << 32) |
+                           (uint32_t)__builtin_amdgcn_readfirstlane((int)mv);
+        const int2 l = where(before + mask_below(m));
+        before += (int32_t)__popcll(m);
+        x[r] = t < total ? dcol[l.x + t] : -1;
+        kk[r] = l.y;
+      }
+#pragma unroll
+      for (int r = 0; r < kPackUnroll; ++r) {
+        if (t0 + r * kWave >= total) break;
+        body(x[r], kk[r], t0 + r * kWave + lane < total);
+      }
+    }
+  }
+}
+
+// Packed streaming of the short lists among items [i0, i1) of a group, a window
+// of up to 64 lists at a time. A hit credits its table slot and its list's
+// counter Wc (inside a window the counters of the lists that are not empty come
+// first; they move to their places when it ends). Returns the wave's hits.
 template <typename Probe>
 __device__ __forceinline__ uint32_t stream_packed(int32_t i0, int32_t i1, const int32_t* Wb, const int32_t* Wn,
-                                                  uint32_t* Wc, const int32_t* __restrict__ dcol, Probe probe,
-                                                  uint32_t* C) {
+                                                  uint32_t* Wc, PackStarts& P, const int32_t* __restrict__ dcol,
+                                                  Probe probe, uint32_t* C) {
   const int lane = lane_id();
   uint32_t hits = 0;
   for (int32_t base = i0; base < i1; base += kWave) {
@@ -96,37 +146,27 @@ __device__ __forceinline__ uint32_t stream_packed(int32_t i0, int32_t i1, const 
       if (nb >= kPackShort) nb = 0;  // long lists are streamed one by one
     }
     const int32_t incl = wave_incl_scan(nb);
-    const int32_t total = __shfl(incl, kWave - 1, kWave);
-    const int32_t dlt = bb - (incl - nb);  // list k's id at t: dcol[dlt_k + t]
-    for (int32_t t0 = 0; t0 < total; t0 += kPackUnroll * kWave) {
-      // kPackUnroll independent gathers in flight before the probes
-      int32_t x[kPackUnroll];
-      int kk[kPackUnroll];
-#pragma unroll
-      for (int r = 0; r < kPackUnroll; ++r) {
-        const int32_t t = t0 + r * kWave + lane;
-        int k = 0;
-#pragma unroll
-        for (int step = kWave / 2; step > 0; step >>= 1) {
-          const int32_t v = __shfl(incl, k + step - 1, kWave);
-          if (v <= t) k += step;
-        }
-        const int32_t at = __shfl(dlt, k, kWave) + t;
-        x[r] = t < total ? dcol[at] : -1;
-        kk[r] = k;
-      }
-#pragma unroll
-      for (int r = 0; r < kPackUnroll; ++r) {
-        if (t0 + r * kWave >= total) break;
-        int off;
-        const bool hit = probe(x[r], t0 + r * kWave + lane < total, &off);
-        hits += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(hit));
-        if (hit) {
-          credit(C, off);
-          atomicAdd(&Wc[base + kk[r]], 1u);
-        }
-      }
-    }
+    const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    if (total == 0) continue;
+    const uint64_t some = __builtin_amdgcn_ballot_w64(nb > 0);
+    const int32_t ci = mask_below(some);  // place among the lists that are not empty
+    const int32_t to = nb > 0 ? ci : (int32_t)__popcll(some) + lane - ci;
+    const int32_t dlt = __builtin_amdgcn_ds_permute(to * 4, bb - (incl - nb));  // list k's id at t: dcol[dlt_k + t]
+    stream_lists(
+        nb, incl - nb, total, P, dcol, [&](int32_t k) { return make_int2(__shfl(dlt, k, kWave), k); },
+        [&](int32_t x, int32_t k, bool valid) {
+          int off;
+          const bool hit = probe(x, valid, &off);
+          hits += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(hit));
+          if (hit) {
+            credit(C, off);
+            atomicAdd(&Wc[base + k], 1u);
+          }
+        });
+    wave_sync();
+    const uint32_t c = nb > 0 ? Wc[base + ci] : 0u;
+    wave_sync();
+    if (li < i1) Wc[li] = c;
   }
   return hits;
 }
@@ -235,7 +275,7 @@ __device__ __forceinline__ bool build_cuckoo(WaveGroupLds<SLOTS, CAP>& S, const 
 // to w's in-list pass (node_count_inw), which then streams the shorter list.
 // CK: N+(u) goes into a cuckoo table (bucket table if its build gives up).
 template <int G, int SLOTS, int CAP, int U, bool CK = false>
-__device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, CAP>& S,
+__device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, CAP>& S, PackStarts& P,
                                                 unsigned long long* red, const int64_t* __restrict__ doff,
                                                 const int32_t* __restrict__ dcol,
                                                 unsigned long long* __restrict__ T,
@@ -254,7 +294,11 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
     beg = doff[u];
     len = (int32_t)(doff[u + 1] - beg);
   }
-  for (int s = g; s < SLOTS; s += G) { K[s] = -1; S.C[s] = 0; }
+  if constexpr (WPG == 1) wave_sync();  // the wave's previous item has read its tables
+  for (int s = g; s < NB; s += G) {
+    S.K[s] = make_int4(-1, -1, -1, -1);
+    reinterpret_cast<int4*>(S.C)[s] = make_int4(0, 0, 0, 0);
+  }
   if (g == 0) { S.nlong = 0; S.fail = 0; }
   group_sync<G>();
   bool ck = false;
@@ -280,20 +324,17 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
   if (ck) {
     const CuckooProbe<SLOTS> probe{K};
     tu = wave_sum_u32(stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done));
-    tu += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
+    tu += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, P, dcol, probe, S.C);
   } else {
     const BucketProbe<NB> probe{S.K};
     tu = wave_sum_u32(stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done));
-    tu += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
+    tu += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, P, dcol, probe, S.C);
   }
   group_sync<G>();
-  for (int i = g; i < len; i += G)
-    if (S.Wc[i]) atomicAdd(&S.C[S.Ws[i]], S.Wc[i]);
-  group_sync<G>();
-  for (int s = g; s < SLOTS; s += G) {
-    const int32_t k = K[s];
-    const uint32_t c = S.C[s];
-    if (k >= 0 && c) atomicAdd(&T[k], (unsigned long long)c);
+  for (int i = g; i < len; i += G) {
+    const int32_t slot = S.Ws[i];
+    const uint32_t c = S.C[slot] + S.Wc[i];
+    if (c) atomicAdd(&T[K[slot]], (unsigned long long)c);
   }
   if constexpr (WPG == 1) {
     if (active && lane == 0 && tu) {
@@ -321,7 +362,7 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
 // CH > CAP: the chunk runs in parts of CAP lists on one table.
 template <int G, int SLOTS, int CAP, int U, bool CK = false, int CH = CAP>
 __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGroupLds<SLOTS, CAP>& S,
-                                               unsigned long long* red, const int64_t* __restrict__ doff,
+                                               PackStarts& P, unsigned long long* red, const int64_t* __restrict__ doff,
                                                const int32_t* __restrict__ dcol,
                                                const int64_t* __restrict__ dinoff,
                                                const int32_t* __restrict__ dincol,
@@ -342,7 +383,11 @@ __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGro
     ib = dinoff[w] + chunk * CH;
     nin = (int32_t)min((int64_t)CH, dinoff[w + 1] - ib);
   }
-  for (int s = g; s < SLOTS; s += G) { K[s] = -1; S.C[s] = 0; }
+  if constexpr (WPG == 1) wave_sync();  // the wave's previous item has read its tables
+  for (int s = g; s < NB; s += G) {
+    S.K[s] = make_int4(-1, -1, -1, -1);
+    reinterpret_cast<int4*>(S.C)[s] = make_int4(0, 0, 0, 0);
+  }
   if (g == 0) { S.nlong = 0; S.fail = 0; }
   group_sync<G>();
   bool ck = false;
@@ -369,11 +414,11 @@ __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGro
     if (ck) {
       const CuckooProbe<SLOTS> probe{K};
       tw += wave_sum_u32(stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done));
-      tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
+      tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, P, dcol, probe, S.C);
     } else {
       const BucketProbe<NB> probe{S.K};
       tw += wave_sum_u32(stream_long<U>(wv, WPG, nl, S.Wl, S.Wb, S.Wn, dcol, probe, S.C, done));
-      tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, dcol, probe, S.C);
+      tw += stream_packed(p0, p1, S.Wb, S.Wn, S.Wc, P, dcol, probe, S.C);
     }
     group_sync<G>();
     for (int i = g; i < np; i += G)
@@ -446,7 +491,8 @@ constexpr int waves_per_simd(int nt, size_t lds) {
 }
 
 template <int NT, int G, int SLOTS, int CAP, int U, bool CK, int CH>
-__global__ __launch_bounds__(NT, waves_per_simd(NT, (NT / G) * sizeof(WaveGroupLds<SLOTS, CAP>) + NT / 8)) void
+__global__ __launch_bounds__(NT, waves_per_simd(NT, (NT / G) * sizeof(WaveGroupLds<SLOTS, CAP>) +
+                                                         NT / kWave * (8 + sizeof(PackStarts)))) void
 k_count_ms(const int32_t* __restrict__ list, int32_t nlist, InItems in,
                                                  int32_t w_max, const int64_t* __restrict__ doff,
                                                  const int32_t* __restrict__ dcol,
@@ -457,18 +503,21 @@ k_count_ms(const int32_t* __restrict__ list, int32_t nlist, InItems in,
   static_assert(NT % G == 0 && (G == kWave || G == NT), "groups are single waves or whole blocks");
   constexpr int GPB = NT / G;
   __shared__ WaveGroupLds<SLOTS, CAP> lds[GPB];
+  __shared__ PackStarts starts[NT / kWave];
   __shared__ unsigned long long red[NT / kWave];
   const int gi = threadIdx.x / G;
   const int64_t nbu = ((int64_t)nlist + GPB - 1) / GPB;
   if ((int64_t)blockIdx.x < nbu) {
     const int64_t idx = (int64_t)blockIdx.x * GPB + gi;
-    node_count_wave<G, SLOTS, CAP, U, CK>(idx < nlist ? list[idx] : -1, lds[gi], red, doff, dcol, T, tot, w_max);
+    node_count_wave<G, SLOTS, CAP, U, CK>(idx < nlist ? list[idx] : -1, lds[gi], starts[threadIdx.x / kWave],
+                                          red, doff, dcol, T, tot, w_max);
     return;
   }
   int32_t w;
   int64_t chunk;
   in_item(in, ((int64_t)blockIdx.x - nbu) * GPB + gi, &w, &chunk);
-  node_count_inw<G, SLOTS, CAP, U, CK, CH>(w, chunk, lds[gi], red, doff, dcol, dinoff, dincol, T, tot);
+  node_count_inw<G, SLOTS, CAP, U, CK, CH>(w, chunk, lds[gi], starts[threadIdx.x / kWave], red, doff, dcol, dinoff,
+                                           dincol, T, tot);
 }
 
 // Merge variant for short lists: a group of G lanes owns node u and each
@@ -658,49 +707,27 @@ struct SmallLds {
   int4 K[kWave / GS][GS];          // GS buckets (4 * GS slots) per node
   uint32_t C[kWave / GS][4 * GS];  // per-slot credits
   uint32_t Wc[kWave];              // hits per lane's list
+  int2 list[kWave];                // offset and lane of the lists that are not empty
 };
 
 // The packed stream of the small-node path: the 64 lanes' lists (begin wb,
-// inclusive prefix incl of their lengths, total) against the lanes' node
+// length wn, inclusive prefix incl of the lengths) against the lanes' node
 // tables; a hit credits its table slot and its list's counter Wc.
 template <int GS, bool CK>
-__device__ __forceinline__ void small_stream(SmallLds<GS>& S, int32_t incl, int32_t total, int32_t excl, int32_t wb,
-                                             const int32_t* __restrict__ dcol, int lane) {
-  const int32_t dlt = wb - excl;  // list k's id at t: dcol[dlt_k + t]
-  for (int32_t t0 = 0; t0 < total; t0 += kPackUnroll * kWave) {
-    // kPackUnroll independent gathers in flight before the probes
-    int32_t x[kPackUnroll];
-    int kk[kPackUnroll];
-#pragma unroll
-    for (int r = 0; r < kPackUnroll; ++r) {
-      const int32_t t = t0 + r * kWave + lane;
-      int k = 0;
-#pragma unroll
-      for (int step = kWave / 2; step > 0; step >>= 1) {
-        const int32_t v = __shfl(incl, k + step - 1, kWave);
-        if (v <= t) k += step;
-      }
-      const int32_t at = __shfl(dlt, k, kWave) + t;
-      x[r] = t < total ? dcol[at] : -1;
-      kk[r] = k;
-    }
-#pragma unroll
-    for (int r = 0; r < kPackUnroll; ++r) {
-      if (t0 + r * kWave >= total) break;
-      int off;
-      bool hit;
-      if constexpr (CK) {
-        hit = CuckooProbe<4 * GS>{reinterpret_cast<const int32_t*>(S.K[kk[r] / GS])}(
-            x[r], t0 + r * kWave + lane < total, &off);
-      } else {
-        hit = bucket_credit<GS>(S.K[kk[r] / GS], x[r], t0 + r * kWave + lane < total, &off);
-      }
-      if (hit) {
-        credit(S.C[kk[r] / GS], off);
-        atomicAdd(&S.Wc[kk[r]], 1u);
-      }
-    }
-  }
+__device__ __forceinline__ void small_stream(SmallLds<GS>& S, int32_t wn, int32_t incl, PackStarts& P,
+                                             const int32_t* __restrict__ dcol) {
+  stream_lists(
+      wn, incl - wn, __builtin_amdgcn_readlane(incl, kWave - 1), P, dcol, [&](int32_t k) { return S.list[k]; },
+      [&](int32_t x, int32_t l, bool valid) {
+        int off;
+        bool hit;
+        if constexpr (CK) hit = CuckooProbe<4 * GS>{reinterpret_cast<const int32_t*>(S.K[l / GS])}(x, valid, &off);
+        else hit = bucket_credit<GS>(S.K[l / GS], x, valid, &off);
+        if (hit) {
+          credit(S.C[l / GS], off);
+          atomicAdd(&S.Wc[l], 1u);
+        }
+      });
 }
 
 // CK: the node tables are cuckoo tables (all of the wave's tables are
@@ -711,7 +738,7 @@ __device__ __forceinline__ void small_stream(SmallLds<GS>& S, int32_t incl, int3
 // in-list pass, as in node_count_wave.
 template <int GS, bool CK = false>
 __device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict__ list, int64_t first,
-                                                      int64_t nlist, SmallLds<GS>& S,
+                                                      int64_t nlist, SmallLds<GS>& S, PackStarts& P,
                                                       const int64_t* __restrict__ doff,
                                                       const int32_t* __restrict__ dcol,
                                                       unsigned long long* __restrict__ T,
@@ -722,10 +749,9 @@ __device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict_
   const int nd = lane / GS, j = lane % GS;
   int32_t* K = reinterpret_cast<int32_t*>(S.K[nd]);
   uint32_t* C = S.C[nd];
-  for (int s = j; s < 4 * GS; s += GS) {
-    K[s] = -1;
-    C[s] = 0;
-  }
+  wave_sync();  // the wave's previous item has read its tables
+  S.K[nd][j] = make_int4(-1, -1, -1, -1);
+  reinterpret_cast<int4*>(C)[j] = make_int4(0, 0, 0, 0);
   S.Wc[lane] = 0;
   const int64_t idx = first + nd;
   int32_t u = -1, nu = 0, w = -1, wb = 0, wn = 0;
@@ -742,10 +768,11 @@ __device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict_
   }
   wave_sync();
   bool gave_up = false;
+  int slot = 0;  // of w
   if (j < nu) {
     w = dcol[ub + j];
     if constexpr (CK) gave_up = !cuckoo_insert<4 * GS>(K, w);
-    else bucket_insert<NB>(K, w);
+    else slot = bucket_insert<NB>(K, w);
     const int64_t b = doff[w];
     wb = (int32_t)b;
     wn = (int32_t)(doff[w + 1] - b);
@@ -759,27 +786,26 @@ __device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict_
     if (!ck) {
       for (int s = j; s < 4 * GS; s += GS) K[s] = -1;
       wave_sync();
-      if (j < nu) bucket_insert<NB>(K, w);
+      if (j < nu) slot = bucket_insert<NB>(K, w);
       wave_sync();
+    } else if (j < nu) {
+      slot = cuckoo_find<4 * GS>(K, w);
     }
   }
   const int32_t incl = wave_incl_scan(wn);
-  const int32_t total = __shfl(incl, kWave - 1, kWave);
-  const int32_t excl = incl - wn;
-  if (ck) small_stream<GS, true>(S, incl, total, excl, wb, dcol, lane);
-  else small_stream<GS, false>(S, incl, total, excl, wb, dcol, lane);
+  const uint64_t some = __builtin_amdgcn_ballot_w64(wn > 0);
+  if (wn > 0) S.list[mask_below(some)] = make_int2(wb - (incl - wn), lane);
+  if (ck) small_stream<GS, true>(S, wn, incl, P, dcol);
+  else small_stream<GS, false>(S, wn, incl, P, dcol);
   wave_sync();
+  // w as the list that was streamed and as the id that was found, in one add
   const uint32_t c = S.Wc[lane];
-  if (c) atomicAdd(&T[w], (unsigned long long)c);
+  const uint32_t cw = c + C[slot];
+  if (j < nu && cw) atomicAdd(&T[w], (unsigned long long)cw);
   const uint32_t tu = group_sum<uint32_t, GS>(c);
   if (j == 0 && tu) atomicAdd(&T[u], (unsigned long long)tu);
-  const uint32_t tw = group_sum<uint32_t, kWave>(c);  // the wave's nodes together
+  const uint32_t tw = wave_sum_u32(c);  // the wave's nodes together
   if (lane == 0) credit_total(tot, tw);
-  for (int s = j; s < 4 * GS; s += GS) {
-    const int32_t key = K[s];
-    const uint32_t cs = C[s];
-    if (key >= 0 && cs) atomicAdd(&T[key], (unsigned long long)cs);
-  }
   return big;
 }
 
@@ -801,25 +827,27 @@ __global__ __launch_bounds__(NT, 8) void k_count_mss(const int32_t* __restrict__
   using WL = WaveGroupLds<SLOTS, CAP>;
   static_assert(CAP <= kWave && sizeof(SmallLds<GS>) <= sizeof(WL), "one wave's LDS holds either path");
   __shared__ WL lds[GPB];
+  __shared__ PackStarts starts[GPB];
   __shared__ unsigned long long red[GPB];
   const int gi = threadIdx.x / kWave;
   const int64_t nbu = ((int64_t)nlist + GPB * NPW - 1) / (GPB * NPW);
   if ((int64_t)blockIdx.x < nbu) {
     const int64_t first = ((int64_t)blockIdx.x * GPB + gi) * NPW;
-    uint64_t big = nodes_count_small<GS, CK>(list, first, nlist, *reinterpret_cast<SmallLds<GS>*>(&lds[gi]), doff,
-                                             dcol, T, tot, w_max);
+    uint64_t big = nodes_count_small<GS, CK>(list, first, nlist, *reinterpret_cast<SmallLds<GS>*>(&lds[gi]),
+                                             starts[gi], doff, dcol, T, tot, w_max);
     wave_sync();  // the small path's LDS is reused below
     while (big) {
       const int k = __builtin_ctzll(big) / GS;
       big &= big - 1;
-      node_count_wave<kWave, SLOTS, CAP, U, CK>(list[first + k], lds[gi], red, doff, dcol, T, tot, w_max);
+      node_count_wave<kWave, SLOTS, CAP, U, CK>(list[first + k], lds[gi], starts[gi], red, doff, dcol, T, tot,
+                                                w_max);
     }
     return;
   }
   int32_t w;
   int64_t chunk;
   in_item(in, ((int64_t)blockIdx.x - nbu) * GPB + gi, &w, &chunk);
-  node_count_inw<kWave, SLOTS, CAP, U, CK>(w, chunk, lds[gi], red, doff, dcol, dinoff, dincol, T, tot);
+  node_count_inw<kWave, SLOTS, CAP, U, CK>(w, chunk, lds[gi], starts[gi], red, doff, dcol, dinoff, dincol, T, tot);
 }
 
 // Persistent form (batched graphs): one launch covers every node of the
@@ -859,6 +887,7 @@ __global__ __launch_bounds__(256) void k_count_persist(const int32_t* __restrict
   constexpr size_t kWaveBytes = ((sizeof(WL) > sizeof(SL) ? sizeof(WL) : sizeof(SL)) + 15) / 16 * 16;
   constexpr size_t kBytes = sizeof(BL) > 4 * kWaveBytes ? sizeof(BL) : 4 * kWaveBytes;
   __shared__ __align__(16) unsigned char smem[kBytes];
+  __shared__ PackStarts starts[256 / kWave];
   __shared__ unsigned long long red[256 / kWave];
   __shared__ int32_t chunk;
   const int32_t n1 = ng + nbk;
@@ -869,7 +898,9 @@ __global__ __launch_bounds__(256) void k_count_persist(const int32_t* __restrict
     __syncthreads();
     if (c >= n1) break;
     if (c < ng) node_count_global(glist[c], red, doff, dcol, T, tot);
-    else node_count_wave<256, SB, CB, 4, CK>(blist[c - ng], *reinterpret_cast<BL*>(smem), red, doff, dcol, T, tot);
+    else
+      node_count_wave<256, SB, CB, 4, CK>(blist[c - ng], *reinterpret_cast<BL*>(smem), starts[threadIdx.x / kWave], red,
+                                          doff, dcol, T, tot);
     __syncthreads();
   }
   constexpr int NPW = SMALL ? kWave / kGS : kWave / 8;  // short-list nodes per wave item
@@ -895,11 +926,11 @@ __global__ __launch_bounds__(256) void k_count_persist(const int32_t* __restrict
       const int32_t end = min(cur + kPersistGrab, n2);
       for (int32_t it = cur; it < end; ++it) {
         if (it < nwx) {
-          node_count_wave<kWave, SW, CW, 4, CK>(wlist[wb + it], *reinterpret_cast<WL*>(mine), red, doff, dcol, T,
-                                                tot);
+          node_count_wave<kWave, SW, CW, 4, CK>(wlist[wb + it], *reinterpret_cast<WL*>(mine), starts[wv], red, doff,
+                                                dcol, T, tot);
         } else if constexpr (SMALL != 0) {
-          nodes_count_small<kGS, CK>(mlist, mb + (int64_t)(it - nwx) * NPW, me, *reinterpret_cast<SL*>(mine), doff,
-                                     dcol, T, tot);
+          nodes_count_small<kGS, CK>(mlist, mb + (int64_t)(it - nwx) * NPW, me, *reinterpret_cast<SL*>(mine),
+                                     starts[wv], doff, dcol, T, tot);
         } else {
           const int64_t k = mb + (int64_t)(it - nwx) * NPW + lane / 8;
           node_count_merge<8>(k < me ? mlist[k] : -1, doff, dcol, T, tot);

@@ -34,15 +34,36 @@ __device__ __forceinline__ int mask_below(uint64_t mask) {
                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// x moved between lanes by a DPP permutation (all lanes active): lanes without
+// a source, and rows outside `rows`, get 0.
+template <int ctrl, int rows = 0xf>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, false);
+}
+
+// Inclusive prefix sums over the 64 lanes (all active). 32-bit values take DPP
+// lane shifts inside the rows of 16 lanes, then the rows before by two row
+// broadcasts: no LDS unit, no address.
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T x) {
-  const int l = lane_id();
+  if constexpr (sizeof(T) == 4) {
+    uint32_t v = (uint32_t)x;
+    v += dpp<0x111>(v);       // row_shr:1
+    v += dpp<0x112>(v);       // row_shr:2
+    v += dpp<0x114>(v);       // row_shr:4
+    v += dpp<0x118>(v);       // row_shr:8
+    v += dpp<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+    return (T)v;
+  } else {
+    const int l = lane_id();
 #pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    T y = __shfl_up(x, o, kWave);
-    if (l >= o) x += y;
+    for (int o = 1; o < kWave; o <<= 1) {
+      T y = __shfl_up(x, o, kWave);
+      if (l >= o) x += y;
+    }
+    return x;
   }
-  return x;
 }
 
 template <typename T, int W>

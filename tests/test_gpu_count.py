@@ -542,3 +542,16 @@ def test_from_csr_rejects_malformed_input():
         with pytest.raises(N.TriccError) as ei:
             P.Graph.from_csr(3, to_dev64(good), to_dev(np.array([1, 2, 0, 7, 0, 1], np.int32)), trusted)
         assert ei.value.status == N.TRICC_ERANGE
+
+
+@pytest.mark.parametrize("k", [2, 3, 13, 24, 45, 46, 47, 62, 63, 64, 65])
+def test_packed_streams_across_windows(k):
+    """Complete graphs whose first nodes stream 0 to 1,953 ids of up to 62
+    lists (a window is 960 positions; the last node's list is empty), joined by
+    paths whose lists have one id or none, on every kernel with packed streams."""
+    n, s, d = F.disjoint_union(F.complete(k), F.path(70), F.complete(k), F.star(40))
+    ref = oracle.count(n, s, d, order=1)
+    for v in ([1, 2, 12, 13, 14, 8], [11, 12, 15, 13, 14, 8], [21, 19, 15, 20, 20, 9], [22, 23, 24, 26, 20, 9]):
+        for ms in (0, 1):
+            r = gpu_count(n, s, d, {"bin_limit": [40, 62, 256, 1024, 4096], "bin_variant": v, "min_side": ms})
+            check_against(r, ref, n)
