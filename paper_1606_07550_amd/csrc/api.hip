@@ -61,7 +61,7 @@ constexpr size_t kHdrBytes = 1024;
 
 struct Layout {
   size_t hdr, raw_off, len, deg, dplus, doff, scan_tmp, rowlist, binlist, adj, tmp, dcol, part_cc,
-      part_T, spare64, spare, spare8, din, dinoff, dincol, inlist, inch, incoff, part, hubmap, rec, tot,
+      part_T, queue, spare, spare8, din, dinoff, dincol, inlist, inch, incoff, part, hubmap, rec, tot,
       total;
 };
 
@@ -89,7 +89,8 @@ Layout make_layout(int64_t n, int64_t m_raw) {
   L.dcol = take(sizeof(int32_t) * m_raw + 16);  // 16-byte loads may run 3 ids past the end
   L.part_cc = take(sizeof(double) * epilogue_blocks(n));
   L.part_T = take(sizeof(unsigned long long) * epilogue_blocks(n));
-  L.spare64 = take(64 * (size_t)(4 * m_raw / 32768 + 16) + 4096);
+  L.queue = take(64 * (size_t)(4 * m_raw / 32768 + 16) + 4096);  // kQueueBytes used
+  static_assert(kQueueBytes <= 64 * 16 + 4096, "the work counters fit");
   L.din = take(sizeof(int32_t) * n);
   L.dinoff = take(sizeof(int64_t) * (n + 1));
   L.dincol = take(sizeof(int32_t) * m_raw + 16);
@@ -1077,8 +1078,7 @@ struct BatchLayout {
   size_t hdr, node_off, edge_off, gsrc, gdst, graph_ws, total;
 };
 
-// Header: queue counters at byte 0 (2 + kPersistSegs int32), the error flag
-// at 64, the segment bounds at 128 (2 (kPersistSegs + 1) int32), the segment
+// Header: the error flag at byte 64, the segment bounds at 128 (2 (kPersistSegs + 1) int32), the segment
 // thresholds at 256 (kPersistSegs + 1 int64).
 constexpr size_t kBatchHdr = 512;
 
@@ -1258,7 +1258,6 @@ int tricc_batch_build(int32_t num_graphs, const int64_t* h_node_off, const int64
   b->m_total = m_total;
   b->ws = ws;
   b->ws_bytes = ws_bytes;
-  b->d_queue = reinterpret_cast<int32_t*>(ws + BL.hdr);
   b->d_err = reinterpret_cast<int32_t*>(ws + BL.hdr + 64);
   b->d_seg = reinterpret_cast<int32_t*>(ws + BL.hdr + 128);
   b->d_thr = reinterpret_cast<int64_t*>(ws + BL.hdr + 256);
@@ -1274,6 +1273,7 @@ int tricc_batch_build(int32_t num_graphs, const int64_t* h_node_off, const int64
   g->L = make_layout(n_total, m_total);
   g->stream = s;
   std::memset(&g->info, 0, sizeof(g->info));
+  b->d_queue = g->at<int32_t>(g->L.queue);
   batch_graph_tuning(bt, &g->tuning);
   auto bail = [&](int code) { delete b; return code; };
   if (hipMemsetAsync(ws + BL.hdr, 0, kBatchHdr, s) != hipSuccess) return bail(fail(TRICC_EHIP, "memset failed"));
@@ -1325,7 +1325,6 @@ int tricc_batch_build_csr(int32_t num_graphs, const int64_t* h_node_off, int64_t
   b->m_total = nnz;
   b->ws = ws;
   b->ws_bytes = ws_bytes;
-  b->d_queue = reinterpret_cast<int32_t*>(ws + BL.hdr);
   b->d_err = reinterpret_cast<int32_t*>(ws + BL.hdr + 64);
   b->d_seg = reinterpret_cast<int32_t*>(ws + BL.hdr + 128);
   b->d_thr = reinterpret_cast<int64_t*>(ws + BL.hdr + 256);
@@ -1341,6 +1340,7 @@ int tricc_batch_build_csr(int32_t num_graphs, const int64_t* h_node_off, int64_t
   g->L = make_layout(n_total, nnz);
   g->stream = s;
   std::memset(&g->info, 0, sizeof(g->info));
+  b->d_queue = g->at<int32_t>(g->L.queue);
   batch_graph_tuning(bt, &g->tuning);
   auto bail = [&](int code) { delete b; return code; };
   if (hipMemsetAsync(ws + BL.hdr, 0, kBatchHdr, s) != hipSuccess) return bail(fail(TRICC_EHIP, "memset failed"));

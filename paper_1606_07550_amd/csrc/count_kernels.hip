@@ -35,6 +35,20 @@ __device__ __forceinline__ void credit_total(unsigned long long* tot, unsigned l
   if (t) atomicAdd(&tot[blockIdx.x & (kTotSlots - 1)], t);
 }
 
+// Where a wavefront's triangles go: straight to the counters (kernels in which
+// a group counts one node), or into a register that the caller credits once
+// (the persistent kernel: its wavefronts take hundreds of nodes each).
+struct TotalNow {
+  unsigned long long* tot;
+  __device__ __forceinline__ void add(unsigned long long t) { credit_total(tot, t); }  // by one lane
+  __device__ __forceinline__ void add_lanes(uint32_t c);                               // by all lanes
+};
+struct TotalHeld {
+  unsigned long long sum = 0;
+  __device__ __forceinline__ void add(unsigned long long t) { sum += t; }
+  __device__ __forceinline__ void add_lanes(uint32_t c) { sum += c; }
+};
+
 }  // namespace
 
 __device__ __forceinline__ void credit(uint32_t* C, int off) {
@@ -51,6 +65,11 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
   x += dpp<0x140>(x);  // row_mirror
   return (uint32_t)(__builtin_amdgcn_readlane((int)x, 0) + __builtin_amdgcn_readlane((int)x, 16) +
                     __builtin_amdgcn_readlane((int)x, 32) + __builtin_amdgcn_readlane((int)x, 48));
+}
+
+__device__ __forceinline__ void TotalNow::add_lanes(uint32_t c) {
+  const uint32_t t = wave_sum_u32(c);
+  if (lane_id() == 0) add(t);
 }
 
 // LDS of one node group of the wave-stream kernel.
@@ -274,12 +293,12 @@ __device__ __forceinline__ bool build_cuckoo(WaveGroupLds<SLOTS, CAP>& S, const 
 // w_max > 0 (min-side mode): edges u->w with d+(u) < d+(w) <= w_max are left
 // to w's in-list pass (node_count_inw), which then streams the shorter list.
 // CK: N+(u) goes into a cuckoo table (bucket table if its build gives up).
-template <int G, int SLOTS, int CAP, int U, bool CK = false>
+template <int G, int SLOTS, int CAP, int U, bool CK = false, typename Total>
 __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, CAP>& S, PackStarts& P,
                                                 unsigned long long* red, const int64_t* __restrict__ doff,
                                                 const int32_t* __restrict__ dcol,
                                                 unsigned long long* __restrict__ T,
-                                                unsigned long long* __restrict__ tot, int32_t w_max = 0) {
+                                                Total& tot, int32_t w_max = 0) {
   static_assert(G % kWave == 0 && SLOTS % 4 == 0 && SLOTS >= 2 * CAP, "shape");
   constexpr int WPG = G / kWave;
   constexpr int NB = SLOTS / 4;
@@ -339,7 +358,7 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
   if constexpr (WPG == 1) {
     if (active && lane == 0 && tu) {
       atomicAdd(&T[u], (unsigned long long)tu);
-      credit_total(tot, tu);
+      tot.add(tu);
     }
   } else {
     if (lane == 0) red[wv] = tu;
@@ -348,7 +367,7 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
       unsigned long long t = 0;
       for (int k = 0; k < WPG; ++k) t += red[k];
       if (t) atomicAdd(&T[u], t);
-      credit_total(tot, t);
+      tot.add(t);
     }
     __syncthreads();  // red and the table may be reused by the caller
   }
@@ -360,14 +379,14 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
 // streams N+(u) against it. A hit x is the triangle u < w < x: x is credited
 // in the table, w in the group total, u with one global atomic per in-edge.
 // CH > CAP: the chunk runs in parts of CAP lists on one table.
-template <int G, int SLOTS, int CAP, int U, bool CK = false, int CH = CAP>
+template <int G, int SLOTS, int CAP, int U, bool CK = false, int CH = CAP, typename Total>
 __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGroupLds<SLOTS, CAP>& S,
                                                PackStarts& P, unsigned long long* red, const int64_t* __restrict__ doff,
                                                const int32_t* __restrict__ dcol,
                                                const int64_t* __restrict__ dinoff,
                                                const int32_t* __restrict__ dincol,
                                                unsigned long long* __restrict__ T,
-                                               unsigned long long* __restrict__ tot) {
+                                               Total& tot) {
   constexpr int WPG = G / kWave;
   constexpr int NB = SLOTS / 4;
   const int g = threadIdx.x % G;
@@ -437,7 +456,7 @@ __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGro
   if constexpr (WPG == 1) {
     if (active && lane == 0 && tw) {
       atomicAdd(&T[w], (unsigned long long)tw);
-      credit_total(tot, tw);
+      tot.add(tw);
     }
   } else {
     if (lane == 0) red[wv] = tw;
@@ -446,7 +465,7 @@ __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGro
       unsigned long long t = 0;
       for (int k = 0; k < WPG; ++k) t += red[k];
       if (t) atomicAdd(&T[w], t);
-      credit_total(tot, t);
+      tot.add(t);
     }
     __syncthreads();
   }
@@ -505,19 +524,20 @@ k_count_ms(const int32_t* __restrict__ list, int32_t nlist, InItems in,
   __shared__ WaveGroupLds<SLOTS, CAP> lds[GPB];
   __shared__ PackStarts starts[NT / kWave];
   __shared__ unsigned long long red[NT / kWave];
+  TotalNow now{tot};
   const int gi = threadIdx.x / G;
   const int64_t nbu = ((int64_t)nlist + GPB - 1) / GPB;
   if ((int64_t)blockIdx.x < nbu) {
     const int64_t idx = (int64_t)blockIdx.x * GPB + gi;
     node_count_wave<G, SLOTS, CAP, U, CK>(idx < nlist ? list[idx] : -1, lds[gi], starts[threadIdx.x / kWave],
-                                          red, doff, dcol, T, tot, w_max);
+                                          red, doff, dcol, T, now, w_max);
     return;
   }
   int32_t w;
   int64_t chunk;
   in_item(in, ((int64_t)blockIdx.x - nbu) * GPB + gi, &w, &chunk);
   node_count_inw<G, SLOTS, CAP, U, CK, CH>(w, chunk, lds[gi], starts[threadIdx.x / kWave], red, doff, dcol, dinoff,
-                                           dincol, T, tot);
+                                           dincol, T, now);
 }
 
 // Merge variant for short lists: a group of G lanes owns node u and each
@@ -525,11 +545,11 @@ k_count_ms(const int32_t* __restrict__ list, int32_t nlist, InItems in,
 // straight from memory (the classic two-pointer intersection; N+(u) is
 // re-read by every lane of the group, from cache). Hits go to T with global
 // atomics, which suits graphs with few triangles per edge.
-template <int G>
+template <int G, typename Total>
 __device__ __forceinline__ void node_count_merge(int32_t u, const int64_t* __restrict__ doff,
                                                  const int32_t* __restrict__ dcol,
                                                  unsigned long long* __restrict__ T,
-                                                 unsigned long long* __restrict__ tot) {
+                                                 Total& tot) {
   const int g = threadIdx.x % G;
   unsigned long long tu = 0;
   if (u >= 0) {
@@ -567,7 +587,7 @@ __device__ __forceinline__ void node_count_merge(int32_t u, const int64_t* __res
   tu = group_sum<unsigned long long, G>(tu);
   if (u >= 0 && g == 0 && tu) {
     atomicAdd(&T[u], tu);
-    credit_total(tot, tu);
+    tot.add(tu);
   }
 }
 
@@ -736,13 +756,13 @@ __device__ __forceinline__ void small_stream(SmallLds<GS>& S, int32_t wn, int32_
 // set for each such node list[first + k] (wave-uniform). w_max > 0
 // (min-side mode): edges u->w with d+(u) < d+(w) <= w_max are left to w's
 // in-list pass, as in node_count_wave.
-template <int GS, bool CK = false>
+template <int GS, bool CK = false, typename Total>
 __device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict__ list, int64_t first,
                                                       int64_t nlist, SmallLds<GS>& S, PackStarts& P,
                                                       const int64_t* __restrict__ doff,
                                                       const int32_t* __restrict__ dcol,
                                                       unsigned long long* __restrict__ T,
-                                                      unsigned long long* __restrict__ tot, int32_t w_max = 0) {
+                                                      Total& tot, int32_t w_max = 0) {
   static_assert(kWave % GS == 0 && GS >= 4, "GS divides the wave");
   constexpr int NB = GS;
   const int lane = lane_id();
@@ -804,8 +824,7 @@ __device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict_
   if (j < nu && cw) atomicAdd(&T[w], (unsigned long long)cw);
   const uint32_t tu = group_sum<uint32_t, GS>(c);
   if (j == 0 && tu) atomicAdd(&T[u], (unsigned long long)tu);
-  const uint32_t tw = wave_sum_u32(c);  // the wave's nodes together
-  if (lane == 0) credit_total(tot, tw);
+  tot.add_lanes(c);  // the wave's nodes together
   return big;
 }
 
@@ -829,17 +848,18 @@ __global__ __launch_bounds__(NT, 8) void k_count_mss(const int32_t* __restrict__
   __shared__ WL lds[GPB];
   __shared__ PackStarts starts[GPB];
   __shared__ unsigned long long red[GPB];
+  TotalNow now{tot};
   const int gi = threadIdx.x / kWave;
   const int64_t nbu = ((int64_t)nlist + GPB * NPW - 1) / (GPB * NPW);
   if ((int64_t)blockIdx.x < nbu) {
     const int64_t first = ((int64_t)blockIdx.x * GPB + gi) * NPW;
     uint64_t big = nodes_count_small<GS, CK>(list, first, nlist, *reinterpret_cast<SmallLds<GS>*>(&lds[gi]),
-                                             starts[gi], doff, dcol, T, tot, w_max);
+                                             starts[gi], doff, dcol, T, now, w_max);
     wave_sync();  // the small path's LDS is reused below
     while (big) {
       const int k = __builtin_ctzll(big) / GS;
       big &= big - 1;
-      node_count_wave<kWave, SLOTS, CAP, U, CK>(list[first + k], lds[gi], starts[gi], red, doff, dcol, T, tot,
+      node_count_wave<kWave, SLOTS, CAP, U, CK>(list[first + k], lds[gi], starts[gi], red, doff, dcol, T, now,
                                                 w_max);
     }
     return;
@@ -847,7 +867,7 @@ __global__ __launch_bounds__(NT, 8) void k_count_mss(const int32_t* __restrict__
   int32_t w;
   int64_t chunk;
   in_item(in, ((int64_t)blockIdx.x - nbu) * GPB + gi, &w, &chunk);
-  node_count_inw<kWave, SLOTS, CAP, U, CK>(w, chunk, lds[gi], starts[gi], red, doff, dcol, dinoff, dincol, T, tot);
+  node_count_inw<kWave, SLOTS, CAP, U, CK>(w, chunk, lds[gi], starts[gi], red, doff, dcol, dinoff, dincol, T, now);
 }
 
 // Persistent form (batched graphs): one launch covers every node of the
@@ -859,15 +879,23 @@ __global__ __launch_bounds__(NT, 8) void k_count_mss(const int32_t* __restrict__
 // nodes (d+ <= CW), then groups of short-list nodes: 8 at a time for the
 // 8-lane merge (SMALL == 0) or 64 / SMALL at a time on the packed
 // small-node path with SMALL lanes per node (d+ <= SMALL). A wave takes
-// kPersistGrab items per atomic and issues its next grab before running the
+// several items per atomic and issues its next grab before running the
 // current items, so the atomic's latency hides behind their loads. Each wave
 // owns a private LDS region in phase 2.
+// Atomics bound this kernel when the queue's counters shared a cache line and
+// every grab took 8 items: 1.2 million at 10 ns for 4,096 graphs of 64 to 65,536
+// nodes. Each counter has its own line now, a wave credits its triangle total
+// once, and a grab is a quarter of a wave's equal share of what is left in the
+// segment, 2 to 16 items (18.1 -> 7.3 ms; 8 items each 7.5, 32 7.6, and with
+// grabs of 32 or more the graphs in work leave the L2; queries against a server,
+// fewer nodes per wave, took 10% longer with 16 each): instructions and the L2
+// bound it now (vector units 61% busy, 38% of the L2's requests).
 // Phase 2 is split into kPersistSegs segments of consecutive graphs (equal
 // shares of the edges), one per XCD: the chip hands out blocks to its XCDs
 // in turn, so block b starts on segment b mod kPersistSegs and the graphs a
 // segment holds stay in one XCD's L2 while they are counted; a wave whose
 // segment is empty takes items of the next ones.
-constexpr int kPersistGrab = 8;
+constexpr int32_t kPersistGrabMin = 2, kPersistGrabMax = 16, kPersistShare = 4;
 
 template <int SW, int CW, int SB, int CB, int SMALL = 0, bool CK = false>
 __global__ __launch_bounds__(256) void k_count_persist(const int32_t* __restrict__ glist, int32_t ng,
@@ -890,6 +918,7 @@ __global__ __launch_bounds__(256) void k_count_persist(const int32_t* __restrict
   __shared__ PackStarts starts[256 / kWave];
   __shared__ unsigned long long red[256 / kWave];
   __shared__ int32_t chunk;
+  TotalHeld held;
   const int32_t n1 = ng + nbk;
   while (true) {
     if (threadIdx.x == 0) chunk = atomicAdd(queue, 1);
@@ -900,7 +929,7 @@ __global__ __launch_bounds__(256) void k_count_persist(const int32_t* __restrict
     if (c < ng) node_count_global(glist[c], red, doff, dcol, T, tot);
     else
       node_count_wave<256, SB, CB, 4, CK>(blist[c - ng], *reinterpret_cast<BL*>(smem), starts[threadIdx.x / kWave], red,
-                                          doff, dcol, T, tot);
+                                          doff, dcol, T, held);
     __syncthreads();
   }
   constexpr int NPW = SMALL ? kWave / kGS : kWave / 8;  // short-list nodes per wave item
@@ -910,35 +939,39 @@ __global__ __launch_bounds__(256) void k_count_persist(const int32_t* __restrict
   // Phase 2 takes the items of segment x = (this block's XCD) first, then
   // moves on to the other segments once it is empty: seg[x .. x+1] bound the
   // segment's single-wave nodes in wlist, seg[kPersistSegs + 1 + x ..] its
-  // short-list nodes in mlist; queue[2 + x] counts the items taken.
+  // short-list nodes in mlist; queue[(2 + x) * kQueueStride] counts the items taken.
   const int x0 = (int)(blockIdx.x % kPersistSegs);
+  const int32_t share = kPersistShare * max(1, (int32_t)(gridDim.x * (256 / kWave) / kPersistSegs));
   for (int t = 0; t < kPersistSegs; ++t) {
     const int x = (x0 + t) % kPersistSegs;
     const int32_t wb = seg[x], nwx = seg[x + 1] - wb;
     const int32_t mb = seg[kPersistSegs + 1 + x], me = seg[kPersistSegs + 2 + x];
     const int32_t n2 = nwx + (int32_t)(((int64_t)(me - mb) + NPW - 1) / NPW);
-    int32_t got = 0;
-    if (lane == 0) got = atomicAdd(queue + 2 + x, kPersistGrab);
+    int32_t size = min(max(n2 / share, kPersistGrabMin), kPersistGrabMax), got = 0;
+    if (lane == 0) got = atomicAdd(queue + (2 + x) * kQueueStride, size);
     int32_t cur = __builtin_amdgcn_readfirstlane(got);
     while (cur < n2) {
+      const int32_t end = min(cur + size, n2);
+      size = min(max((n2 - end) / share, kPersistGrabMin), kPersistGrabMax);
       int32_t nxt = 0;
-      if (lane == 0) nxt = atomicAdd(queue + 2 + x, kPersistGrab);
-      const int32_t end = min(cur + kPersistGrab, n2);
+      if (lane == 0) nxt = atomicAdd(queue + (2 + x) * kQueueStride, size);
       for (int32_t it = cur; it < end; ++it) {
         if (it < nwx) {
           node_count_wave<kWave, SW, CW, 4, CK>(wlist[wb + it], *reinterpret_cast<WL*>(mine), starts[wv], red, doff,
-                                                dcol, T, tot);
+                                                dcol, T, held);
         } else if constexpr (SMALL != 0) {
           nodes_count_small<kGS, CK>(mlist, mb + (int64_t)(it - nwx) * NPW, me, *reinterpret_cast<SL*>(mine),
-                                     starts[wv], doff, dcol, T, tot);
+                                     starts[wv], doff, dcol, T, held);
         } else {
           const int64_t k = mb + (int64_t)(it - nwx) * NPW + lane / 8;
-          node_count_merge<8>(k < me ? mlist[k] : -1, doff, dcol, T, tot);
+          node_count_merge<8>(k < me ? mlist[k] : -1, doff, dcol, T, held);
         }
       }
       cur = __builtin_amdgcn_readlane(nxt, 0);
     }
   }
+  const unsigned long long t = group_sum<unsigned long long, kWave>(held.sum);
+  if (lane == 0) credit_total(tot, t);
 }
 
 // Segment bounds of the persistent kernel's phase 2 (see k_count_persist):
@@ -1043,7 +1076,7 @@ __global__ __launch_bounds__(256) void k_batch_zero(unsigned long long* __restri
                                                     int32_t* __restrict__ queue) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i0 < 2 + kPersistSegs) queue[i0] = 0;
+  if (i0 < 2 + kPersistSegs) queue[i0 * kQueueStride] = 0;
   if (i0 < kTotSlots) tot[i0] = 0ull;
   for (int64_t i = i0; i < n; i += stride) T[i] = 0ull;
 }

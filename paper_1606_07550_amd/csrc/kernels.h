@@ -201,8 +201,12 @@ int persist_merge_cap(int v);  // largest merge_limit the variant accepts
 const void* persist_kernel(int v);
 // Phase 2 of the persistent kernel runs in kPersistSegs segments (one per
 // XCD of the chip: 256 CUs in 8 XCDs); seg holds 2 (kPersistSegs + 1) bounds
-// (launch_persist_segments); queue needs 2 + kPersistSegs counters.
+// (launch_persist_segments); queue needs 2 + kPersistSegs counters, each on a
+// cache line of its own (counter k at queue[k * kQueueStride]): atomics on one
+// line follow each other at about 10 ns, whichever counter they are for.
 constexpr int kPersistSegs = 8;
+constexpr int kQueueStride = 32;
+constexpr size_t kQueueBytes = (2 + kPersistSegs) * kQueueStride * sizeof(int32_t);
 hipError_t launch_count_persist(int v, unsigned grid, const int32_t* glist, int32_t ng, const int32_t* blist,
                                 int32_t nbk, const int32_t* wlist, const int32_t* mlist, const int32_t* seg,
                                 int32_t* queue, const int64_t* doff, const int32_t* dcol, unsigned long long* T,

@@ -263,3 +263,19 @@ def test_packed_csr_batch_errors(mixed):
     with pytest.raises(N.TriccError) as ei:
         P.Batch.from_csr(node_off, torch.from_numpy(rp).to(DEV), dev(col), assume_simple_sorted_symmetric=True)
     assert ei.value.status in (N.TRICC_EINVAL, N.TRICC_ERANGE)
+
+
+@pytest.mark.parametrize("G", [1, 9, 300])
+def test_work_grabs_from_few_to_many_items(G):
+    """Batches whose segments hold no item, fewer items than wavefronts, and
+    enough that the grabs shrink to their smallest size."""
+    graphs = []
+    for k in range(G):
+        n = 40 if G == 9 else 3000
+        graphs.append((n, *I.er(n, 6 * n, 900 + k)))
+    graphs.append(F.complete(40))
+    node_off, edge_off, src, dst = pack(graphs)
+    b = P.Batch(node_off, edge_off, dev(src), dev(dst))
+    b.plan()
+    for _ in range(3):
+        check_batch(to_host(b.run()), graphs, node_off)
