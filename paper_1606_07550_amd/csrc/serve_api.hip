@@ -29,15 +29,16 @@
 #include "kernels.h"
 
 namespace tricc {
-hipError_t launch_serve_clear(int2* tab, int64_t total, hipStream_t s);
+hipError_t launch_serve_clear(int32_t* tab, int64_t total, hipStream_t s);
 hipError_t launch_serve_insert(int32_t Q, const int64_t* qoff, const int32_t* nodes, int64_t N, const int64_t* toff,
-                               int2* tab, int32_t n, const int32_t* deg, int32_t* nchunks, int32_t* qidx, int32_t* err,
-                               hipStream_t s);
+                               int32_t* tab, int64_t total, int32_t n, const int32_t* deg, int32_t* nchunks,
+                               int32_t* qidx, int32_t* err, hipStream_t s);
 hipError_t launch_serve_items(int64_t N, const int64_t* coff, int32_t* item, hipStream_t s);
 hipError_t launch_serve_pairs(int pass, int32_t Q, const int64_t* qoff, const int32_t* nodes, const int64_t* coff,
-                              int64_t C, const int32_t* item, const int32_t* qidx, const int64_t* toff, const int2* tab,
-                              const int64_t* off, const int32_t* deg, const int32_t* adj, int32_t* cnt,
-                              const int64_t* pos, int32_t* psrc, int32_t* pdst, hipStream_t s);
+                              int64_t C, const int32_t* item, const int32_t* qidx, const int64_t* toff,
+                              const int32_t* tab, int64_t total, const int64_t* off, const int32_t* deg,
+                              const int32_t* adj, int32_t* cnt, const int64_t* pos, int32_t* psrc, int32_t* pdst,
+                              hipStream_t s);
 hipError_t launch_serve_query_pairs(int32_t Q, const int64_t* qoff, const int64_t* coff, const int64_t* pos,
                                     int64_t* qpairs, hipStream_t s);
 }  // namespace tricc
@@ -51,7 +52,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 constexpr int32_t kChunk = 2048;  // neighbours per extraction work item (serve_kernels.hip)
 
 inline int64_t pow2_at_least(int64_t x) {
-  int64_t p = 2;
+  int64_t p = 4;  // a bucket of the tables
   while (p < x) p <<= 1;
   return p;
 }
@@ -184,7 +185,7 @@ int run_batch(tricc_server* S, char* ws, hipStream_t st, std::vector<Query>& B, 
   int32_t* nodes = reinterpret_cast<int32_t*>(at(L.nodes));
   int64_t* d_qoff = reinterpret_cast<int64_t*>(at(L.qoff));
   int64_t* d_toff = reinterpret_cast<int64_t*>(at(L.toff));
-  int2* tab = reinterpret_cast<int2*>(at(L.tab));
+  int32_t* tab = reinterpret_cast<int32_t*>(at(L.tab));
   int32_t* nchunks = reinterpret_cast<int32_t*>(at(L.nchunks));
   int32_t* qidx = reinterpret_cast<int32_t*>(at(L.qidx));
   int64_t* coff = reinterpret_cast<int64_t*>(at(L.coff));
@@ -209,7 +210,7 @@ int run_batch(tricc_server* S, char* ws, hipStream_t st, std::vector<Query>& B, 
   SCHK(hipMemcpyAsync(d_toff, toff.data(), 8 * (size_t)(G + 1), hipMemcpyHostToDevice, st));
   SCHK(hipMemsetAsync(err, 0, 64, st));
   SCHK(launch_serve_clear(tab, Tsl, st));
-  SCHK(launch_serve_insert(G, d_qoff, nodes, N, d_toff, tab, S->n, S->deg, nchunks, qidx, err, st));
+  SCHK(launch_serve_insert(G, d_qoff, nodes, N, d_toff, tab, Tsl, S->n, S->deg, nchunks, qidx, err, st));
   SCHK(launch_scan_i32(nchunks, N, coff, scan, st));
   int64_t C = 0;
   int32_t herr = 0;
@@ -219,15 +220,15 @@ int run_batch(tricc_server* S, char* ws, hipStream_t st, std::vector<Query>& B, 
   if (herr) return sfail(TRICC_EINVAL, "query node ids invalid on the device (flag %d)", herr);
   if (C > N + D / kChunk + 1) return sfail(TRICC_EOVERFLOW, "chunk bound exceeded");
   SCHK(launch_serve_items(N, coff, item, st));
-  SCHK(launch_serve_pairs(0, G, d_qoff, nodes, coff, C, item, qidx, d_toff, tab, S->off, S->deg, S->adj, cnt, nullptr,
-                          nullptr, nullptr, st));
+  SCHK(launch_serve_pairs(0, G, d_qoff, nodes, coff, C, item, qidx, d_toff, tab, Tsl, S->off, S->deg, S->adj, cnt,
+                          nullptr, nullptr, nullptr, st));
   SCHK(launch_scan_i32(cnt, C, pos, scan, st));
   SCHK(launch_serve_query_pairs(G, d_qoff, coff, pos, qpairs, st));
   std::vector<int64_t> hq(G + 1);
   SCHK(hipMemcpyAsync(hq.data(), qpairs, 8 * (size_t)(G + 1), hipMemcpyDeviceToHost, st));
   SCHK(hipStreamSynchronize(st));
   if (hq[G] > M) return sfail(TRICC_EOVERFLOW, "pair bound exceeded");
-  SCHK(launch_serve_pairs(1, G, d_qoff, nodes, coff, C, item, qidx, d_toff, tab, S->off, S->deg, S->adj, cnt, pos,
+  SCHK(launch_serve_pairs(1, G, d_qoff, nodes, coff, C, item, qidx, d_toff, tab, Tsl, S->off, S->deg, S->adj, cnt, pos,
                           psrc, pdst, st));
   tricc_batch* b = nullptr;
   int rc = tricc_batch_build(G, qoff.data(), hq.data(), psrc, pdst, at(L.batch), S->slot_bytes - L.batch, &bt, st, &b);

@@ -152,3 +152,30 @@ def test_every_batch_variant_serves(resident, tun):
     with pytest.raises(Exception):
         srv.set_tuning({"merge_limit": 17, "wave_limit": 64, "persist_variant": 2, "blocks_per_cu": 0})
     srv.close()
+
+
+@pytest.mark.parametrize("whole", [False, True])
+def test_small_tables_and_rows_at_step_edges(whole):
+    """Node sets of 1 to 12 ids (tables of one to eight buckets, some full) and
+    rows of 63 to 4,097 ids around the steps of 256 and chunks of 2,048; with
+    the set of all nodes a wavefront takes several chunks."""
+    n = 40_000
+    s, d = I.er(n, 3 * n, 31)
+    degs = [63, 64, 65, 255, 256, 257, 2047, 2048, 2049, 4097]
+    s = np.concatenate([s] + [np.full(k, i) for i, k in enumerate(degs)]).astype(np.int32)
+    d = np.concatenate([d] + [100 + np.arange(k) for k in degs]).astype(np.int32)
+    rng = np.random.default_rng(32)
+    queries = [rng.choice(30, k, replace=False) for k in range(1, 13)]
+    queries += [np.concatenate([np.arange(10), 100 + np.arange(k)]) for k in (1, 7, 300, 2000, 4200)]
+    if whole:
+        queries.append(rng.permutation(n))
+    srv = P.Server(P.Graph(n, dev(s), dev(d)), 1 << 30, slots=1)
+    for q, S in enumerate(queries):
+        assert srv.submit(q, S.astype(np.int32)) == N.TRICC_OK
+    srv.drain()
+    res = collect(srv, len(queries))
+    for q, S in enumerate(queries):
+        ref = oracle.induced(n, s, d, S.astype(np.int32))
+        assert (res[q]["triangles"], res[q]["m"]) == (ref["total"], ref["m"]), q
+        assert abs(res[q]["avg_cc"] - ref["avg"]) <= CC_RTOL * abs(ref["avg"]), q
+    srv.close()
