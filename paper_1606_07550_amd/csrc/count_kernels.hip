@@ -1102,7 +1102,10 @@ __device__ __forceinline__ unsigned long long sum_total(const unsigned long long
 // triangle total (sum of T / 3) and its average CC over its n_g nodes, each
 // summed in a fixed order that depends only on the graph. Block 0 also
 // writes the batch's total from the counters the intersection kernels fed
-// (independent of T) to *batch_tri, if that is not null.
+// (independent of T) to *batch_tri, if that is not null. The largest graph bounds
+// the launch: a thread loads eight of its nodes before it adds them up, in the
+// order it always did (200 graphs of up to 65,536 nodes: 104 -> 48 us; one node at a time
+// is a memory round trip per 256).
 __global__ __launch_bounds__(256) void k_graph_epilogue(const int64_t* __restrict__ node_off,
                                                         const unsigned long long* __restrict__ T,
                                                         const int32_t* __restrict__ deg, float* __restrict__ cc,
@@ -1115,14 +1118,26 @@ __global__ __launch_bounds__(256) void k_graph_epilogue(const int64_t* __restric
   const int64_t nb = node_off[blockIdx.x], ne = node_off[blockIdx.x + 1];
   double acc = 0.0;
   unsigned long long tacc = 0;
-  for (int64_t v = nb + threadIdx.x; v < ne; v += 256) {
-    const unsigned long long t = T[v];
-    const int64_t d = deg[v];
-    double r = 0.0;
-    if (d >= 2) r = (2.0 * (double)t) / ((double)d * (double)(d - 1));
-    cc[v] = (float)r;
-    acc += r;
-    tacc += t;
+  constexpr int U = 8;
+  for (int64_t v0 = nb + threadIdx.x; v0 < ne; v0 += U * 256) {
+    unsigned long long t[U];
+    int32_t d[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int64_t v = v0 + k * 256;
+      t[k] = v < ne ? T[v] : 0ull;
+      d[k] = v < ne ? deg[v] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int64_t v = v0 + k * 256;
+      if (v >= ne) break;
+      double r = 0.0;
+      if (d[k] >= 2) r = (2.0 * (double)t[k]) / ((double)d[k] * (double)(d[k] - 1));
+      cc[v] = (float)r;
+      acc += r;
+      tacc += t[k];
+    }
   }
   const double sd = block_sum<double, 256>(acc, red_d);
   const unsigned long long st = block_sum<unsigned long long, 256>(tacc, red_t);
