@@ -750,15 +750,30 @@ __device__ __forceinline__ void small_stream(SmallLds<GS>& S, int32_t wn, int32_
       });
 }
 
+// The node of a lane on the small-node path: u (-1: none), where N+(u) begins
+// (DAG offsets stay below 2^30) and its length.
+struct SmallNode {
+  int32_t u, ub, nu;
+};
+
+__device__ __forceinline__ SmallNode small_node(int32_t u, const int64_t* __restrict__ doff) {
+  SmallNode h{u, 0, 0};
+  if (u >= 0) {
+    const int64_t b = doff[u];
+    h.ub = (int32_t)b;
+    h.nu = (int32_t)(doff[u + 1] - b);
+  }
+  return h;
+}
+
 // CK: the node tables are cuckoo tables (all of the wave's tables are
 // rebuilt in the bucket layout if one insert gives up).
 // Nodes with d+(u) > GS are left out; the returned lane mask has bit k * GS
-// set for each such node list[first + k] (wave-uniform). w_max > 0
+// set for each such node of lanes k * GS .. (wave-uniform). w_max > 0
 // (min-side mode): edges u->w with d+(u) < d+(w) <= w_max are left to w's
 // in-list pass, as in node_count_wave.
 template <int GS, bool CK = false, typename Total>
-__device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict__ list, int64_t first,
-                                                      int64_t nlist, SmallLds<GS>& S, PackStarts& P,
+__device__ __forceinline__ uint64_t nodes_count_small(SmallNode h, SmallLds<GS>& S, PackStarts& P,
                                                       const int64_t* __restrict__ doff,
                                                       const int32_t* __restrict__ dcol,
                                                       unsigned long long* __restrict__ T,
@@ -773,14 +788,7 @@ __device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict_
   S.K[nd][j] = make_int4(-1, -1, -1, -1);
   reinterpret_cast<int4*>(C)[j] = make_int4(0, 0, 0, 0);
   S.Wc[lane] = 0;
-  const int64_t idx = first + nd;
-  int32_t u = -1, nu = 0, w = -1, wb = 0, wn = 0;
-  int64_t ub = 0;
-  if (idx < nlist) {
-    u = list[idx];
-    ub = doff[u];
-    nu = (int32_t)(doff[u + 1] - ub);
-  }
+  int32_t u = h.u, nu = h.nu, w = -1, wb = 0, wn = 0;
   const uint64_t big = __builtin_amdgcn_ballot_w64(j == 0 && nu > GS);
   if (nu > GS) {  // left to the caller
     u = -1;
@@ -790,7 +798,7 @@ __device__ __forceinline__ uint64_t nodes_count_small(const int32_t* __restrict_
   bool gave_up = false;
   int slot = 0;  // of w
   if (j < nu) {
-    w = dcol[ub + j];
+    w = dcol[h.ub + j];
     if constexpr (CK) gave_up = !cuckoo_insert<4 * GS>(K, w);
     else slot = bucket_insert<NB>(K, w);
     const int64_t b = doff[w];
@@ -853,8 +861,10 @@ __global__ __launch_bounds__(NT, 8) void k_count_mss(const int32_t* __restrict__
   const int64_t nbu = ((int64_t)nlist + GPB * NPW - 1) / (GPB * NPW);
   if ((int64_t)blockIdx.x < nbu) {
     const int64_t first = ((int64_t)blockIdx.x * GPB + gi) * NPW;
-    uint64_t big = nodes_count_small<GS, CK>(list, first, nlist, *reinterpret_cast<SmallLds<GS>*>(&lds[gi]),
-                                             starts[gi], doff, dcol, T, now, w_max);
+    const int64_t idx = first + lane_id() / GS;
+    uint64_t big = nodes_count_small<GS, CK>(small_node(idx < nlist ? list[idx] : -1, doff),
+                                             *reinterpret_cast<SmallLds<GS>*>(&lds[gi]), starts[gi], doff, dcol, T,
+                                             now, w_max);
     wave_sync();  // the small path's LDS is reused below
     while (big) {
       const int k = __builtin_ctzll(big) / GS;
@@ -955,14 +965,31 @@ __global__ __launch_bounds__(256) void k_count_persist(const int32_t* __restrict
       size = min(max((n2 - end) / share, kPersistGrabMin), kPersistGrabMax);
       int32_t nxt = 0;
       if (lane == 0) nxt = atomicAdd(queue + (2 + x) * kQueueStride, size);
-      for (int32_t it = cur; it < end; ++it) {
-        if (it < nwx) {
-          node_count_wave<kWave, SW, CW, 4, CK>(wlist[wb + it], *reinterpret_cast<WL*>(mine), starts[wv], red, doff,
-                                                dcol, T, held);
-        } else if constexpr (SMALL != 0) {
-          nodes_count_small<kGS, CK>(mlist, mb + (int64_t)(it - nwx) * NPW, me, *reinterpret_cast<SL*>(mine),
-                                     starts[wv], doff, dcol, T, held);
-        } else {
+      int32_t it = cur;
+      for (; it < min(end, nwx); ++it)
+        node_count_wave<kWave, SW, CW, 4, CK>(wlist[wb + it], *reinterpret_cast<WL*>(mine), starts[wv], red, doff, dcol,
+                                              T, held);
+      if constexpr (SMALL != 0) {
+        // two items ahead: the ids of one, the list bounds of the next (4,096
+        // graphs 7.30 -> 7.15 ms)
+        auto id = [&](int32_t i) {
+          const int32_t k = mb + (i - nwx) * NPW + lane / kGS;
+          return i < end && k < me ? mlist[k] : -1;
+        };
+        SmallNode h{-1, 0, 0};
+        int32_t u1 = -1;
+        if (it < end) {
+          h = small_node(id(it), doff);
+          u1 = id(it + 1);
+        }
+        for (; it < end; ++it) {
+          const SmallNode now = h;
+          h = small_node(u1, doff);
+          u1 = id(it + 2);
+          nodes_count_small<kGS, CK>(now, *reinterpret_cast<SL*>(mine), starts[wv], doff, dcol, T, held);
+        }
+      } else {
+        for (; it < end; ++it) {
           const int64_t k = mb + (int64_t)(it - nwx) * NPW + lane / 8;
           node_count_merge<8>(k < me ? mlist[k] : -1, doff, dcol, T, held);
         }
@@ -1102,10 +1129,10 @@ __device__ __forceinline__ unsigned long long sum_total(const unsigned long long
 // triangle total (sum of T / 3) and its average CC over its n_g nodes, each
 // summed in a fixed order that depends only on the graph. Block 0 also
 // writes the batch's total from the counters the intersection kernels fed
-// (independent of T) to *batch_tri, if that is not null. The largest graph bounds
-// the launch: a thread loads eight of its nodes before it adds them up, in the
-// order it always did (200 graphs of up to 65,536 nodes: 104 -> 48 us; one node at a time
-// is a memory round trip per 256).
+// (independent of T) to *batch_tri, if that is not null. The largest graph
+// bounds the launch: a thread loads eight of its nodes before it adds them up,
+// in the order it always did (200 graphs of up to 65,536 nodes: 104 -> 48 us;
+// one node at a time is a memory round trip per 256).
 __global__ __launch_bounds__(256) void k_graph_epilogue(const int64_t* __restrict__ node_off,
                                                         const unsigned long long* __restrict__ T,
                                                         const int32_t* __restrict__ deg, float* __restrict__ cc,
