@@ -358,7 +358,7 @@ int build_impl(tricc_graph* g, const int32_t* src, const int32_t* dst, bool pres
     HIPCHK(launch_build_clear(hdr, kHdrBytes / 4, ptotal, 2 * kPartMaxParts, part_may_split(2 * m_raw) ? len : nullptr,
                               n, s));
     HIPCHK(launch_part_count(src, dst, m_raw, n, pbits, P, ptotal, hdr + kHdrErr, s));
-    HIPCHK(launch_part_place(src, dst, m_raw, n, pbits, P, ptotal, pstart, cstart, pcur, pv, pu, s));
+    HIPCHK(launch_part_place(src, dst, m_raw, n, pbits, P, ptotal, pstart, cstart, pcur, pv, pu, hdr + kHdrErr, s));
     HIPCHK(launch_part_rows(pbits, P, n, 2 * m_raw, pstart, cstart, pu, pv, len, raw_off, cur, adj, s));
   } else {
     HIPCHK(launch_build_clear(hdr, kHdrBytes / 4, nullptr, 0, len, n, s));

@@ -38,10 +38,11 @@ int part_bits(int64_t n);
 hipError_t launch_part_count(const int32_t* src, const int32_t* dst, int64_t m_raw, int32_t n, int pbits, int32_t P,
                              uint32_t* ptotal, int32_t* err, hipStream_t s);
 // Partition starts, chunk starts and pass B. Pairs with an id out of range
-// are dropped (launch_part_count flags them in err).
+// are dropped (flagged in err by launch_part_count, or here where the pairs
+// are so few that launch_part_count has nothing to do).
 hipError_t launch_part_place(const int32_t* src, const int32_t* dst, int64_t m_raw, int32_t n, int pbits, int32_t P,
                              const uint32_t* ptotal, int64_t* pstart, int64_t* cstart, uint32_t* pcur, int32_t* pv,
-                             uint16_t* pu, hipStream_t s);
+                             uint16_t* pu, int32_t* err, hipStream_t s);
 // Row lengths, row offsets and adj rows (unsorted) from the staged entries.
 // Where part_may_split(max_entries), len must be zeroed and cur is scratch.
 bool part_may_split(int64_t entries);

@@ -7,6 +7,7 @@ import torch
 
 import oracle
 import paper_1606_07550_amd as P
+from paper_1606_07550_amd import _native
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -178,3 +179,30 @@ def test_in_list_parts(outer):
     ref = oracle.count(n, s, d)
     np.testing.assert_array_equal(out["T"].cpu().numpy().view(np.uint64), ref["T"])
     assert g.count_check() == (ref["total"], 3 * ref["total"])
+
+
+@pytest.mark.parametrize("n", [1000, 1024, 1025, 3000])
+@pytest.mark.parametrize("m", [1, 8191, 8192, 8193])
+def test_pairs_of_one_tile_and_of_two(n, m):
+    """One partition and several; pairs in one tile, where the sizes come from
+    the placing itself, and in two; ids that share a partition along a wavefront
+    and ids that do not; an id out of range is refused in every case."""
+    rng = np.random.default_rng(n + m)
+    for ordered in (False, True):
+        s = rng.integers(0, n, m).astype(np.int32)
+        d = rng.integers(0, n, m).astype(np.int32)
+        if ordered:
+            s = np.sort(s)
+        g = P.Graph(n, torch.from_numpy(s).to(DEV), torch.from_numpy(d).to(DEV))
+        out = g.count()
+        torch.cuda.synchronize()
+        ref = oracle.count(n, s, d, order=1)
+        np.testing.assert_array_equal(out["T"].cpu().numpy().view(np.uint64), ref["T"])
+        assert g.info["m"] == ref["m"]
+    for bad in (-1, n):
+        e = d.copy()
+        e[m // 2] = bad
+        for a, b in ((s, e), (e, s)):
+            with pytest.raises(_native.TriccError) as ei:
+                P.Graph(n, torch.from_numpy(a).to(DEV), torch.from_numpy(b).to(DEV))
+            assert ei.value.status == _native.TRICC_ERANGE
