@@ -141,12 +141,14 @@ def test_empty_queries_and_errors():
     assert int(o["total"].cpu().numpy().view(np.uint64)[0]) == 20
 
 
+@pytest.mark.parametrize("more", [0, 600_000, 2_800_000], ids=["halving", "blocks_of_8", "blocks_of_16"])
 @pytest.mark.parametrize("spread", ["even", "low", "high", "two_ends"])
-def test_rows_at_the_edges_of_blocks(spread):
-    """Rows of 1 to 140 ids at every offset against blocks of 16, their ids
+def test_rows_at_the_edges_of_blocks(spread, more):
+    """Rows of 1 to 140 ids at every offset against blocks of 8 and 16, their ids
     spread evenly or clustered, tested with every id that any row holds and with
-    the ids beside them; the other ends have longer rows."""
-    n, pool = 60_000, 150
+    the ids beside them; the other ends have longer rows. More pairs, among ids
+    that no test names, take the graph to each of the row searches."""
+    n, pool = 100_000, 150
     ids = {"even": np.linspace(400, n - 2, pool).astype(np.int64), "low": 400 + 2 * np.arange(pool),
            "high": n - 2 * pool + 2 * np.arange(pool),
            "two_ends": np.concatenate([400 + np.arange(pool // 2) * 3, n - pool + np.arange(pool // 2) * 2])}[spread]
@@ -155,12 +157,14 @@ def test_rows_at_the_edges_of_blocks(spread):
     s = [np.full(k, u) for u, k in enumerate(lens)]
     d = [rng.choice(ids, k, replace=False) for k in lens]
     fill = 100 + np.arange(160)  # they lift the degrees of the ids above the rows' lengths
-    s = np.concatenate(s + [np.repeat(fill, pool)])
-    d = np.concatenate(d + [np.tile(ids, fill.size)])
-    g = P.Graph(n, dev(s), dev(d))
     keys = np.unique(np.concatenate([ids, ids - 1, np.minimum(ids + 1, n - 1), [0, n - 1]]))
+    others = np.setdiff1d(np.arange(1000, n), keys)
+    s = np.concatenate(s + [np.repeat(fill, pool), rng.choice(others, more)])
+    d = np.concatenate(d + [np.tile(ids, fill.size), rng.choice(others, more)])
+    g = P.Graph(n, dev(s), dev(d))
+    m = g.info["m"]
+    assert (m < 5 * n, 8 * m > 20 << 20) == {0: (True, False), 600_000: (False, False), 2_800_000: (False, True)}[more]
     qu, qv = (a.ravel() for a in np.meshgrid(np.arange(lens.size), keys, indexing="ij"))
-    edges = set(zip(s.tolist(), d.tolist()))
-    want = np.array([(a, b) in edges or (b, a) in edges for a, b in zip(qu.tolist(), qv.tolist())], np.uint8)
+    want = np.isin(qu * n + qv, np.concatenate([s * n + d, d * n + s])).astype(np.uint8)
     np.testing.assert_array_equal(gpu_has(g, qu, qv), want)
     np.testing.assert_array_equal(gpu_has(g, qv, qu), want)
