@@ -468,7 +468,7 @@ __global__ __launch_bounds__(NT) void k_count_k5_bits(int32_t n, int32_t chunk, 
             // list the y of wx: lanes 0 .. RS-1 own one word each
             const int32_t c = lane < RS ? __popc(wx) : 0;
             const int32_t incl = wave_incl_scan(c);
-            const int32_t ny = __shfl(incl, kWave - 1, kWave);
+            const int32_t ny = __builtin_amdgcn_readlane(incl, kWave - 1);
             if (ny < 2) continue;  // y and z both lie in wx (wave-uniform)
             if (lane < RS) {
               uint32_t bits = wx;
@@ -542,14 +542,20 @@ hipError_t launch_count_k4(int32_t n, int64_t max_outdeg, const int64_t* doff, c
   return hipGetLastError();
 }
 
+// One kernel takes all nodes up to out-degree 512: a node above 256 takes a block
+// up to a millisecond, and in a launch of their own the few such nodes left the
+// chip idle (R-MAT of 100k nodes, largest out-degree 259: 11.8 ms in two
+// launches, 9.4 in one; 10.9 before the table look-ups). Without such nodes the
+// kernel for up to 256 lets more blocks share a CU.
 hipError_t launch_count_k5(int32_t n, int64_t max_outdeg, const int64_t* doff, const int32_t* dcol,
                            unsigned long long* total, hipStream_t s) {
   k_zero_one<<<1, 64, 0, s>>>(total);
   if (n > 0 && max_outdeg >= 4) {
     const int32_t cm = k4_chunk(n, 65536, kK4NT);
-    k_count_k5_bits<0, kK4BitsLow, kK4NT><<<k4_grid(n, cm, 65536), kK4NT, 0, s>>>(n, cm, doff, dcol, total);
-    if (max_outdeg > kK4BitsLow)
-      k_count_k5_bits<kK4BitsLow, kK4BitsMid, kK4NT><<<k4_grid(n, cm, 65536), kK4NT, 0, s>>>(n, cm, doff, dcol, total);
+    if (max_outdeg <= kK4BitsLow)
+      k_count_k5_bits<0, kK4BitsLow, kK4NT><<<k4_grid(n, cm, 65536), kK4NT, 0, s>>>(n, cm, doff, dcol, total);
+    else
+      k_count_k5_bits<0, kK4BitsMid, kK4NT><<<k4_grid(n, cm, 65536), kK4NT, 0, s>>>(n, cm, doff, dcol, total);
     const int32_t cb = k4_chunk(n, 2048, 512);
     if (max_outdeg > kK4BitsMid)
       k_count_k5_bits<kK4BitsMid, kK5Cap, 512><<<k4_grid(n, cb, 2048), 512, 0, s>>>(n, cb, doff, dcol, total);
