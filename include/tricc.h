@@ -78,7 +78,7 @@ typedef struct tricc_graph_info {
   int64_t max_outdeg;          /* max d+(v) */
   int64_t bin_count[TRICC_NUM_BINS];
   uint64_t list_elems;         /* sum over DAG edges u->w of d+(u) + d+(w) (*) */
-  int64_t large_rows;          /* rows of more than 32,768 raw entries (sorted by bitmap) */
+  int64_t large_rows;          /* rows of more than 32,768 raw entries */
   uint64_t bin_list_elems[TRICC_NUM_BINS]; /* d+(u) + d+(w) over the edges each bin's kernel counts (*) */
   int64_t bin_edges[TRICC_NUM_BINS];       /* DAG edges counted by each bin's kernel (*) */
   int64_t bin_in_items[TRICC_NUM_BINS];    /* in-list work items of each bin (min-side) */

@@ -58,6 +58,7 @@ enum : int {
   kHdrM = 220,        // int64 at byte 880: DAG edges
 };
 constexpr size_t kHdrBytes = 1024;
+static_assert(kHdrClsOff + 2 * (kNumRowClasses + 1) <= kHdrBinOff, "the class bounds fit");
 
 struct Layout {
   size_t hdr, raw_off, len, deg, dplus, doff, scan_tmp, rowlist, binlist, adj, tmp, dcol, part_cc,
@@ -66,6 +67,9 @@ struct Layout {
 };
 
 constexpr int kSpareClasses = 13;
+
+// Sort and merge jobs of the rows of kRowMerge: a chunk each.
+int64_t max_jobs(int64_t m_raw) { return 4 * m_raw / kMergeChunk + 16; }
 
 Layout make_layout(int64_t n, int64_t m_raw) {
   Layout L{};
@@ -89,7 +93,7 @@ Layout make_layout(int64_t n, int64_t m_raw) {
   L.dcol = take(sizeof(int32_t) * m_raw + 16);  // 16-byte loads may run 3 ids past the end
   L.part_cc = take(sizeof(double) * epilogue_blocks(n));
   L.part_T = take(sizeof(unsigned long long) * epilogue_blocks(n));
-  L.queue = take(64 * (size_t)(4 * m_raw / 32768 + 16) + 4096);  // kQueueBytes used
+  L.queue = take(64 * (size_t)max_jobs(m_raw) + 4096);  // the work counters; during the build, sort and merge jobs
   static_assert(kQueueBytes <= 64 * 16 + 4096, "the work counters fit");
   L.din = take(sizeof(int32_t) * n);
   L.dinoff = take(sizeof(int64_t) * (n + 1));
@@ -153,6 +157,91 @@ int check_tuning(const tricc_tuning* t) {
       if (!count_variant_min_side(t->bin_variant[b]))
         return fail(TRICC_EINVAL, "tuning: min_side needs min-side variants in bins 0..4 (bin %d has %d)", b,
                     t->bin_variant[b]);
+  return TRICC_OK;
+}
+
+// Rows of kRowMerge: sort chunks in LDS, merge runs pairwise between adj and
+// tmp, then dedup into adj.
+int sort_merge_rows(tricc_graph* g, int32_t nl, const int32_t* rows_dev) {
+  hipStream_t s = g->stream;
+  const Layout& L = g->L;
+  char* meta = g->ws + L.queue;
+  int64_t* d_off = reinterpret_cast<int64_t*>(meta);
+  int32_t* d_len = reinterpret_cast<int32_t*>(meta + align_up(sizeof(int64_t) * nl));
+  HIPCHK(launch_gather_rows(rows_dev, nl, g->at<int64_t>(L.raw_off), g->at<int32_t>(L.len), d_off, d_len, s));
+  std::vector<int64_t> h_off(nl), tmp_beg(nl);
+  std::vector<int32_t> h_len(nl);
+  int rc = sync_copy(h_off.data(), d_off, sizeof(int64_t) * nl, s);
+  if (rc) return rc;
+  if ((rc = sync_copy(h_len.data(), d_len, sizeof(int32_t) * nl, s))) return rc;
+  int64_t acc = 0;
+  int32_t maxL = 0;
+  for (int i = 0; i < nl; ++i) { tmp_beg[i] = acc; acc += h_len[i]; maxL = std::max(maxL, h_len[i]); }
+  int32_t* adj = g->at<int32_t>(L.adj);
+  int32_t* tmp = g->at<int32_t>(L.tmp);
+
+  std::vector<int64_t> cbeg;
+  std::vector<int32_t> clen;
+  for (int i = 0; i < nl; ++i)
+    for (int64_t c = 0; c < h_len[i]; c += kMergeChunk) {
+      cbeg.push_back(h_off[i] + c);
+      clen.push_back((int32_t)std::min<int64_t>(kMergeChunk, h_len[i] - c));
+    }
+  const int64_t nj_max = (int64_t)cbeg.size();
+  if (nj_max > max_jobs(g->m_raw)) return fail(TRICC_EOVERFLOW, "too many large-row chunks");
+  // The job arrays of a step (chunk sort, each merge pass, the dedup) sit in
+  // one block of meta, int64 arrays first, and go up in one copy: a pass has
+  // at most nj_max jobs (each covers 2 R >= 2 chunks of a row), and the
+  // block is rewritten only after the previous step's kernel (stream order).
+  int64_t* m_a = reinterpret_cast<int64_t*>(meta);
+  int64_t* m_o = m_a + nj_max;
+  int64_t* m_t = m_o + nj_max;
+  int32_t* m_la = reinterpret_cast<int32_t*>(m_t + nj_max + 1);
+  int32_t* m_lb = m_la + nj_max;
+  std::vector<int64_t> blk((size_t)(3 * nj_max + 1) + (size_t)(nj_max + 1));  // int64 view of the block
+  int32_t* blk32 = reinterpret_cast<int32_t*>(blk.data() + 3 * nj_max + 1);
+  std::copy(cbeg.begin(), cbeg.end(), blk.begin());
+  std::copy(clen.begin(), clen.end(), blk32);
+  if ((rc = upload(m_a, blk.data(), sizeof(int64_t) * blk.size(), s))) return rc;
+  HIPCHK(launch_sort_chunks(m_a, m_la, (int32_t)nj_max, adj, s));
+
+  bool in_adj = true;
+  for (int64_t R = kMergeChunk; R < maxL; R *= 2) {
+    std::vector<int64_t> a, o, t;
+    std::vector<int32_t> la, lb;
+    int64_t tiles = 0;
+    for (int i = 0; i < nl; ++i) {
+      const int64_t Li = h_len[i];
+      const int64_t bin = in_adj ? h_off[i] : tmp_beg[i];
+      const int64_t bout = in_adj ? tmp_beg[i] : h_off[i];
+      for (int64_t k = 0; k < Li; k += 2 * R) {
+        const int64_t A = std::min(R, Li - k);
+        const int64_t B = std::max<int64_t>(0, std::min(R, Li - k - R));
+        a.push_back(bin + k);
+        o.push_back(bout + k);
+        la.push_back((int32_t)A);
+        lb.push_back((int32_t)B);
+        t.push_back(tiles);
+        tiles += (A + B + kMergeTile - 1) / kMergeTile;
+      }
+    }
+    t.push_back(tiles);
+    const int32_t nj = (int32_t)a.size();
+    if (nj > nj_max) return fail(TRICC_EOVERFLOW, "merge pass with more jobs than chunks");
+    std::copy(a.begin(), a.end(), blk.begin());
+    std::copy(o.begin(), o.end(), blk.begin() + nj_max);
+    std::copy(t.begin(), t.end(), blk.begin() + 2 * nj_max);
+    std::copy(la.begin(), la.end(), blk32);
+    std::copy(lb.begin(), lb.end(), blk32 + nj_max);
+    if ((rc = upload(m_a, blk.data(), sizeof(int64_t) * blk.size(), s))) return rc;
+    HIPCHK(launch_merge_pass(m_a, m_la, m_lb, m_o, m_t, nj, tiles, in_adj ? adj : tmp, in_adj ? tmp : adj, s));
+    in_adj = !in_adj;
+  }
+  std::vector<int64_t> seg(nl);
+  for (int i = 0; i < nl; ++i) seg[i] = in_adj ? h_off[i] : tmp_beg[i];
+  if ((rc = upload(m_a, seg.data(), sizeof(int64_t) * nl, s))) return rc;
+  HIPCHK(launch_dedup_rows(rows_dev, m_a, nl, g->at<int32_t>(L.len), in_adj ? adj : tmp,
+                           g->at<int64_t>(L.raw_off), adj, g->at<int32_t>(L.deg), s));
   return TRICC_OK;
 }
 
@@ -392,10 +481,20 @@ int build_impl(tricc_graph* g, const int32_t* src, const int32_t* dst, bool pres
     std::memcpy(cls_off, h32 + kHdrClsOff, sizeof(cls_off));
   }
   // tmp and the in-list area (m_raw entries) are free until the orientation
-  g->info.large_rows = presorted ? 0 : cls_off[kRowLarge + 1] - cls_off[kRowLarge];
-  if (!presorted)
+  g->info.large_rows = presorted ? 0 : cls_off[kRowLarge + 1] - cls_off[kRowMerge];
+  if (!presorted) {
     HIPCHK(launch_sort_rows(rowlist, cls_off, n, raw_off, len, adj, deg, g->at<int32_t>(L.tmp),
                             g->at<int32_t>(L.dincol), s));
+    const int32_t nm = (int32_t)(cls_off[kRowMerge + 1] - cls_off[kRowMerge]);
+    if (nm > 0) {
+      try {
+        rc = sort_merge_rows(g, nm, rowlist + cls_off[kRowMerge]);
+      } catch (const std::bad_alloc&) {
+        rc = fail(TRICC_ENOMEM, "host allocation failed");
+      }
+      if (rc) return rc;
+    }
+  }
   for (int c = 0; c <= kNumRowClasses; ++c) g->cls_off[c] = cls_off[c];
   g->info.n = n;
   g->info.m_raw = m_raw;

@@ -639,7 +639,7 @@ int64_t layout_tile(int64_t n) {
 
 // ---------------------------------------------------------------------------
 // Row classes by raw length.
-__device__ __forceinline__ int row_class(int32_t len) {
+__device__ __forceinline__ int row_class(int32_t len, int32_t bitmap_min) {
   if (len <= 1) return kRowTrivial;
   if (len <= 8) return kRow8;
   if (len <= 16) return kRow16;
@@ -653,7 +653,7 @@ __device__ __forceinline__ int row_class(int32_t len) {
   if (len <= 8192) return kRow8k;
   if (len <= 16384) return kRow16k;
   if (len <= 32768) return kRow32k;
-  return kRowLarge;
+  return len < bitmap_min ? kRowMerge : kRowLarge;
 }
 
 // Rows by class, listed class-major: pass 1 leaves each tile's class counts,
@@ -663,7 +663,8 @@ __device__ __forceinline__ int row_class(int32_t len) {
 // layout (at most 1,024 of them), so no scan stands between the passes: as a
 // histogram, a three-launch scan, an offset gather and a placement it took
 // six launches.
-__global__ __launch_bounds__(kLayoutNT) void k_rows_count(int32_t n, int64_t tile, const int32_t* __restrict__ len,
+__global__ __launch_bounds__(kLayoutNT) void k_rows_count(int32_t n, int64_t tile, int32_t bitmap_min,
+                                                          const int32_t* __restrict__ len,
                                                           int32_t* __restrict__ deg, int32_t* __restrict__ sums) {
   __shared__ int32_t acc[kNumRowClasses];
   if (threadIdx.x < kNumRowClasses) acc[threadIdx.x] = 0;
@@ -675,7 +676,7 @@ __global__ __launch_bounds__(kLayoutNT) void k_rows_count(int32_t n, int64_t til
     int c = kRowTrivial;
     if (v < t1) {
       const int32_t L = len[v];
-      c = row_class(L);
+      c = row_class(L, bitmap_min);
       if (c == kRowTrivial) deg[v] = L;
     }
 #pragma unroll
@@ -689,7 +690,8 @@ __global__ __launch_bounds__(kLayoutNT) void k_rows_count(int32_t n, int64_t til
   if (threadIdx.x < kNumRowClasses) sums[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = acc[threadIdx.x];
 }
 
-__global__ __launch_bounds__(kLayoutNT) void k_rows_place(int32_t n, int64_t tile, const int32_t* __restrict__ len,
+__global__ __launch_bounds__(kLayoutNT) void k_rows_place(int32_t n, int64_t tile, int32_t bitmap_min,
+                                                          const int32_t* __restrict__ len,
                                                           const int32_t* __restrict__ sums,
                                                           int32_t* __restrict__ list, int64_t* __restrict__ cls_off) {
   __shared__ int32_t prev[kNumRowClasses], all[kNumRowClasses], cur[kNumRowClasses];
@@ -723,7 +725,7 @@ __global__ __launch_bounds__(kLayoutNT) void k_rows_place(int32_t n, int64_t til
   const int64_t t0 = (int64_t)me * tile, t1 = min((int64_t)n, t0 + tile);
   for (int64_t b = t0; b < t1; b += kLayoutNT) {
     const int64_t v = b + threadIdx.x;
-    const int c = v < t1 ? row_class(len[v]) : kRowTrivial;
+    const int c = v < t1 ? row_class(len[v], bitmap_min) : kRowTrivial;
 #pragma unroll
     for (int q = kRowTrivial + 1; q < kNumRowClasses; ++q) {
       const uint64_t m = __ballot(c == q);
@@ -742,8 +744,9 @@ hipError_t launch_row_classes(int32_t n, const int32_t* len, int32_t* deg, int32
   if (n <= 0) return hipSuccess;
   const int64_t tile = layout_tile(n);
   const unsigned nt = (unsigned)((n + tile - 1) / tile);
-  k_rows_count<<<nt, kLayoutNT, 0, s>>>(n, tile, len, deg, sums);
-  k_rows_place<<<nt, kLayoutNT, 0, s>>>(n, tile, len, sums, list, cls_off);
+  const int32_t least = row_bitmap_min(n);
+  k_rows_count<<<nt, kLayoutNT, 0, s>>>(n, tile, least, len, deg, sums);
+  k_rows_place<<<nt, kLayoutNT, 0, s>>>(n, tile, least, len, sums, list, cls_off);
   return hipGetLastError();
 }
 
@@ -1039,22 +1042,126 @@ __global__ __launch_bounds__(256) void k_sort_rows_short(SortPlan plan, const in
   }
 }
 
+// Bitonic compare-exchanges of one stride j of stage k on kSortRun ids held
+// by one thread in registers (x[r] is id base + r); run-local strides only.
+constexpr int kSortRun = 32;
+__device__ __forceinline__ void run_stage(int32_t (&x)[kSortRun], int base, int j, int k) {
+#pragma unroll
+  for (int r = 0; r < kSortRun; ++r) {
+    const int pr = r ^ j;
+    if (pr > r) {
+      const bool up = ((base + r) & k) == 0;
+      const int32_t a = x[r], b = x[pr];
+      x[r] = up ? min(a, b) : max(a, b);
+      x[pr] = up ? max(a, b) : min(a, b);
+    }
+  }
+}
+
+// Rows of up to CAP entries: one block sorts one row (or one chunk) in LDS
+// with a bitonic network. Each thread owns a run of 32 consecutive ids: the
+// strides below 32 run in its registers (one LDS read and write for all of
+// them, the first five stages in one pass), the larger strides in LDS, one
+// barrier each. The LDS holds id i at i + i / 32, so a run's ids sit in
+// distinct banks for the 32 lanes that read them together. DEDUP: compact
+// the unique values in place and write deg; otherwise write the sorted chunk
+// back as is.
+template <int CAP, int NT, bool DEDUP>
+__global__ __launch_bounds__(NT) void k_sort_lds(const int32_t* __restrict__ rows,
+                                                 const int64_t* __restrict__ seg_beg,
+                                                 const int32_t* __restrict__ seg_len,
+                                                 const int64_t* __restrict__ off,
+                                                 const int32_t* __restrict__ len,
+                                                 int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
+  constexpr int R = kSortRun;
+  static_assert(CAP % R == 0 && CAP / R <= NT, "one run per thread");
+  __shared__ int32_t s[CAP + CAP / R];
+  __shared__ int32_t lds_scan[NT / kWave + 1];
+  auto at = [](int i) { return i + (i >> 5); };
+  int32_t v = -1;
+  int64_t beg;
+  int32_t L;
+  if (DEDUP) {
+    v = rows[blockIdx.x];
+    beg = off[v];
+    L = len[v];
+  } else {
+    beg = seg_beg[blockIdx.x];
+    L = seg_len[blockIdx.x];
+  }
+  int P = R;
+  while (P < L) P <<= 1;
+  for (int i = threadIdx.x; i < P; i += NT) s[at(i)] = i < L ? adj[beg + i] : kPad;
+  __syncthreads();
+  const int g = threadIdx.x;
+  const bool owner = g < P / R;  // thread g owns ids g R .. g R + R - 1, at g (R + 1) + r
+  int32_t x[R];
+  if (owner) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = s[g * (R + 1) + r];
+#pragma unroll
+    for (int k = 2; k <= R; k <<= 1) {
+#pragma unroll
+      for (int j = k >> 1; j > 0; j >>= 1) run_stage(x, g * R, j, k);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[g * (R + 1) + r] = x[r];
+  }
+  __syncthreads();
+  for (int k = 2 * R; k <= P; k <<= 1) {
+    for (int j = k >> 1; j >= R; j >>= 1) {
+      for (int i = threadIdx.x; i < (P >> 1); i += NT) {
+        const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1));
+        const int hi = lo + j;
+        const bool up = (lo & k) == 0;
+        const int32_t a = s[at(lo)], b = s[at(hi)];
+        if ((a > b) == up) { s[at(lo)] = b; s[at(hi)] = a; }
+      }
+      __syncthreads();
+    }
+    if (owner) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[r] = s[g * (R + 1) + r];
+#pragma unroll
+      for (int j = R >> 1; j > 0; j >>= 1) run_stage(x, g * R, j, k);
+#pragma unroll
+      for (int r = 0; r < R; ++r) s[g * (R + 1) + r] = x[r];
+    }
+    __syncthreads();
+  }
+  if (!DEDUP) {
+    for (int i = threadIdx.x; i < L; i += NT) adj[beg + i] = s[at(i)];
+    return;
+  }
+  int32_t carry = 0;
+  for (int base = 0; base < L; base += NT) {
+    const int i = base + threadIdx.x;
+    const int32_t x0 = i < L ? s[at(i)] : kPad;
+    const bool u = i < L && (i == 0 || x0 != s[at(i - 1)]);
+    int32_t tot;
+    const int32_t ex = block_excl_scan<int32_t, NT>(u ? 1 : 0, lds_scan, &tot);
+    if (u) adj[beg + carry + ex] = x0;
+    carry += tot;
+  }
+  if (threadIdx.x == 0) deg[v] = carry;
+}
+
 // Long rows: the ids of a row that fall into one range of 32 * WORDS ids are
 // set in an LDS bitmap (which drops the repeats) and written out in order,
 // each wavefront its share of the words. One block per row and range. With
 // one range (n <= 32 * WORDS) the row is rewritten in place; with more, each
 // block also counts the row's entries below its range, writes its ids to the
 // span of `out` that starts there, and k_row_compact closes the gaps.
-// Measured against sorting networks in LDS (above 32,768 entries chunk
-// sorts, merge passes and a dedup pass, planned on the host), whose one block
-// per row left the chip idle: build + count of an R-MAT graph of 240k nodes
-// 1,890 -> 1,331 us, R-MAT 24 94.9 -> 91.5 ms.
-// Bound by the LDS passes over the words where rows are short for their range
-// (about 8 us a range), by reading the row once per range where they are long.
+// Against sorting networks in LDS (above 32,768 entries chunk sorts and merge
+// passes), whose one block per row left the chip idle: build + count of an R-MAT
+// graph of 240k nodes 1,890 -> 1,331 us, R-MAT 24 94.9 -> 91.5 ms. Bound by the
+// LDS passes over the words where rows are short for their range (about 8 us a
+// range), by reading the row once per range where they are long: rows with few
+// entries per range stay with the networks and merges (see row_bitmap_min).
 constexpr int kBitmapNT = 1024;
 constexpr int kBitmapUnroll = 8;
-constexpr int kBitmapWords = 32768;      // 2^20 ids, 128 KB of LDS
-constexpr int kBitmapWordsSmall = 8192;  // 2^18 ids, four blocks per CU
+constexpr int kBitmapWords = kBitmapIds / 32;  // 128 KB of LDS
+constexpr int kBitmapWordsSmall = 8192;        // 2^18 ids, four blocks per CU
 
 template <int WORDS>
 __global__ __launch_bounds__(kBitmapNT) void k_sort_bitmap(const int32_t* __restrict__ rows, int32_t nrows,
@@ -1167,16 +1274,12 @@ __global__ __launch_bounds__(256) void k_row_compact(const int32_t* __restrict__
   if (r == ranges - 1 && threadIdx.x == 0) deg[v] = at + m.y;
 }
 
-int32_t sort_ranges(int32_t n) { return (int32_t)(((int64_t)n + 32 * kBitmapWords - 1) / (32 * kBitmapWords)); }
-
-// Sorts and dedups the rows of every class in place and writes deg. Rows
-// above 4,096 entries go by bitmap where the graph's ids fit one (n <= 2^20);
-// with more ids a bitmap pass per 2^20 of them costs more than the register
-// networks up to 16,384 entries and less above.
+// Sorts and dedups the rows of every class but kRowMerge in place and writes
+// deg; which go by bitmap: row_first_bitmap_class.
 hipError_t launch_sort_rows(const int32_t* rowlist, const int64_t* cls_off, int32_t n, const int64_t* off,
                             const int32_t* len, int32_t* adj, int32_t* deg, int32_t* tmp, int32_t* scratch,
                             hipStream_t s) {
-  const int32_t ranges = sort_ranges(n);
+  const int32_t ranges = row_ranges(n);
   SortPlan plan;
   uint32_t blocks[2] = {};  // long, short
   for (int k = 0; k < kSortClasses; ++k) {
@@ -1187,13 +1290,14 @@ hipError_t launch_sort_rows(const int32_t* rowlist, const int64_t* cls_off, int3
     plan.blk0[k] = blocks[x];
     blocks[x] += (uint32_t)((plan.nrows[k] + kPerBlock[k] - 1) / kPerBlock[k]);
   }
-  const int first = ranges == 1 ? kRow8k : kRow32k;  // the first class sorted by bitmap
-  for (int cls = kRow8k; cls < first; ++cls) {
+  const int first = row_first_bitmap_class(n);
+  for (int cls = kRow8k; cls < std::min<int>(first, kRowMerge); ++cls) {
     const int32_t nrows = (int32_t)(cls_off[cls + 1] - cls_off[cls]);
     const int32_t* rows = rowlist + cls_off[cls];
     if (nrows == 0) continue;
     if (cls == kRow8k) k_sort_block<16, 8><<<nrows, 512, 0, s>>>(rows, off, len, adj, deg);
-    else k_sort_block<16, 16><<<nrows, 1024, 0, s>>>(rows, off, len, adj, deg);
+    else if (cls == kRow16k) k_sort_block<16, 16><<<nrows, 1024, 0, s>>>(rows, off, len, adj, deg);
+    else k_sort_lds<32768, 1024, true><<<nrows, 1024, 0, s>>>(rows, nullptr, nullptr, off, len, adj, deg);
   }
   if (blocks[0] > 0) k_sort_rows_long<<<blocks[0], 256, 0, s>>>(plan, rowlist, off, len, adj, deg);
   if (blocks[1] > 0) k_sort_rows_short<<<blocks[1], 256, 0, s>>>(plan, rowlist, off, len, adj, deg);
@@ -1201,14 +1305,133 @@ hipError_t launch_sort_rows(const int32_t* rowlist, const int64_t* cls_off, int3
   if (nbig > 0) {
     const int32_t* rows = rowlist + cls_off[first];
     int2* part = reinterpret_cast<int2*>(scratch);
-    const unsigned grid = (unsigned)((nbig + 7) / 8 * 8 * ranges);
+    const unsigned grid = (unsigned)row_bitmap_blocks(nbig, ranges);
     if (n <= 32 * kBitmapWordsSmall)
       k_sort_bitmap<kBitmapWordsSmall><<<grid, kBitmapNT, 0, s>>>(rows, nbig, 1, n, off, len, adj, tmp, deg, part);
     else
       k_sort_bitmap<kBitmapWords><<<grid, kBitmapNT, 0, s>>>(rows, nbig, ranges, n, off, len, adj, tmp, deg, part);
+    const hipError_t e = hipGetLastError();  // the next kernel follows what this one writes
+    if (e != hipSuccess) return e;
     if (ranges > 1)
       k_row_compact<<<(unsigned)(nbig * ranges), 256, 0, s>>>(rows, ranges, off, part, tmp, adj, deg);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_sort_chunks(const int64_t* chunk_beg, const int32_t* chunk_len, int32_t nchunks,
+                              int32_t* buf, hipStream_t s) {
+  if (nchunks == 0) return hipSuccess;
+  k_sort_lds<kMergeChunk, 1024, false><<<nchunks, 1024, 0, s>>>(nullptr, chunk_beg, chunk_len, nullptr, nullptr, buf,
+                                                                 nullptr);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Merge pass for the rows of kRowMerge (merge path partition, A first on ties).
+constexpr int kMergeItems = 8;
+static_assert(kMergeTile == 256 * kMergeItems, "tile");
+
+__global__ __launch_bounds__(256) void k_merge(const int64_t* __restrict__ a_beg, const int32_t* __restrict__ la_,
+                                               const int32_t* __restrict__ lb_, const int64_t* __restrict__ out_beg,
+                                               const int64_t* __restrict__ tile_off, int32_t njobs,
+                                               const int32_t* __restrict__ in, int32_t* __restrict__ out) {
+  const int64_t tile = blockIdx.x;
+  int lo = 0, hi = njobs - 1;  // job = last k with tile_off[k] <= tile
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (tile_off[mid] <= tile) lo = mid; else hi = mid - 1;
+  }
+  const int job = lo;
+  const int32_t la = la_[job], lb = lb_[job];
+  const int32_t* A = in + a_beg[job];
+  const int32_t* B = A + la;
+  int32_t* O = out + out_beg[job];
+  const int64_t k0l = (tile - tile_off[job]) * (int64_t)kMergeTile + (int64_t)threadIdx.x * kMergeItems;
+  if (k0l >= (int64_t)la + lb) return;
+  const int32_t k0 = (int32_t)k0l;
+  int32_t b0 = max(0, k0 - lb), e0 = min(k0, la);
+  while (b0 < e0) {
+    const int32_t mid = (b0 + e0) >> 1;
+    if (A[mid] <= B[k0 - 1 - mid]) b0 = mid + 1; else e0 = mid;
+  }
+  int32_t i = b0, j = k0 - b0;
+#pragma unroll
+  for (int t = 0; t < kMergeItems; ++t) {
+    if (k0 + t >= la + lb) break;
+    const bool takeA = j >= lb || (i < la && A[i] <= B[j]);
+    O[k0 + t] = takeA ? A[i] : B[j];
+    if (takeA) ++i; else ++j;
+  }
+}
+
+hipError_t launch_merge_pass(const int64_t* a_beg, const int32_t* la, const int32_t* lb,
+                             const int64_t* out_beg, const int64_t* tile_off, int32_t njobs,
+                             int64_t ntiles, const int32_t* buf_in, int32_t* buf_out, hipStream_t s) {
+  if (njobs == 0 || ntiles == 0) return hipSuccess;
+  k_merge<<<(unsigned)ntiles, 256, 0, s>>>(a_beg, la, lb, out_beg, tile_off, njobs, buf_in, buf_out);
+  return hipGetLastError();
+}
+
+constexpr int kDedupNT = 1024;
+constexpr int kDedupPer = 4;  // consecutive entries per thread per step
+
+__global__ __launch_bounds__(kDedupNT) void k_dedup_rows(const int32_t* __restrict__ rows,
+                                                         const int64_t* __restrict__ seg_beg,
+                                                         const int32_t* __restrict__ len,
+                                                         const int32_t* __restrict__ sorted,
+                                                         const int64_t* __restrict__ off,
+                                                         int32_t* __restrict__ adj, int32_t* __restrict__ deg) {
+  __shared__ int32_t lds_scan[kDedupNT / kWave + 1];
+  const int32_t v = rows[blockIdx.x];
+  const int32_t L = len[v];
+  const int32_t* S = sorted + seg_beg[blockIdx.x];
+  int32_t* D = adj + off[v];
+  int32_t carry = 0;
+  for (int base = 0; base < L; base += kDedupNT * kDedupPer) {
+    const int i0 = base + threadIdx.x * kDedupPer;
+    int32_t x[kDedupPer];
+    bool u[kDedupPer];
+    int32_t c = 0;
+    int32_t prev = i0 > 0 && i0 - 1 < L ? S[i0 - 1] : kPad;
+#pragma unroll
+    for (int q = 0; q < kDedupPer; ++q) {
+      const int i = i0 + q;
+      x[q] = i < L ? S[i] : kPad;
+      u[q] = i < L && (i == 0 || x[q] != prev);
+      prev = x[q];
+      c += u[q];
+    }
+    __syncthreads();  // every read of this step precedes the writes (S may alias D)
+    int32_t tot;
+    int32_t at = carry + block_excl_scan<int32_t, kDedupNT>(c, lds_scan, &tot);
+#pragma unroll
+    for (int q = 0; q < kDedupPer; ++q)
+      if (u[q]) D[at++] = x[q];
+    carry += tot;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) deg[v] = carry;
+}
+
+hipError_t launch_dedup_rows(const int32_t* rows, const int64_t* seg_beg, int32_t nrows,
+                             const int32_t* len, const int32_t* sorted, const int64_t* off,
+                             int32_t* adj, int32_t* deg, hipStream_t s) {
+  if (nrows == 0) return hipSuccess;
+  k_dedup_rows<<<nrows, kDedupNT, 0, s>>>(rows, seg_beg, len, sorted, off, adj, deg);
+  return hipGetLastError();
+}
+
+__global__ void k_gather_rows(const int32_t* __restrict__ rows, int32_t nr, const int64_t* __restrict__ off,
+                              const int32_t* __restrict__ len, int64_t* __restrict__ out_off,
+                              int32_t* __restrict__ out_len) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < nr) { out_off[i] = off[rows[i]]; out_len[i] = len[rows[i]]; }
+}
+
+hipError_t launch_gather_rows(const int32_t* rows, int32_t nr, const int64_t* off, const int32_t* len,
+                              int64_t* out_off, int32_t* out_len, hipStream_t s) {
+  if (nr == 0) return hipSuccess;
+  k_gather_rows<<<(nr + 255) / 256, 256, 0, s>>>(rows, nr, off, len, out_off, out_len);
   return hipGetLastError();
 }
 

@@ -3,22 +3,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "row_sort.h"
+
 namespace tricc {
 
 // ---- CSR build (symmetrise, drop loops, sort rows, dedup) ----------------
-// Row length classes used by the segmented row sort.
-enum RowClass : int {
-  kRowTrivial = 0,  // len <= 1
-  kRow8, kRow16, kRow32, kRow64,  // register bitonic sort by a lane group
-  kRow128, kRow256, kRow512, kRow1024,  // register bitonic sort by a wavefront
-  kRow4k,      // <= 4096, register bitonic sort by a block of 4 wavefronts
-  kRow8k,      // <= 8192, by 8 wavefronts, or by bitmap (see launch_sort_rows)
-  kRow16k,     // <= 16384, by 16 wavefronts, or by bitmap
-  kRow32k,     // <= 32768, by bitmap
-  kRowLarge,   // > 32768, by bitmap
-  kNumRowClasses
-};
-
 hipError_t launch_degree_raw(const int32_t* src, const int32_t* dst, int64_t m_raw, int32_t n,
                              int32_t* cnt, int32_t* err, hipStream_t s);
 // out[0..n] = exclusive prefix sum of in[0..n), out[n] = total.
@@ -60,12 +49,32 @@ hipError_t launch_row_classes(int32_t n, const int32_t* len, int32_t* deg, int32
 // out[i] = prefix[at[i]] for i < k (k <= 64)
 hipError_t launch_gather_offsets(const int64_t* prefix, const int64_t* at, int k, int64_t* out, hipStream_t s);
 // Sorts + dedups every listed row in place (rowlist, cls_off: the row
-// classes); writes deg. tmp: scratch laid out as adj; scratch: two int32 per
-// row above 16,384 entries and range of 2^20 ids, which m_raw int32 hold for
-// any n (such rows number at most m_raw / 8192, the ranges at most 2048).
+// classes) but those of kRowMerge; writes deg. tmp: scratch laid out as adj;
+// scratch: two int32 per row sorted by bitmap and range of 2^20 ids where
+// there are several, which m_raw int32 hold (such rows have at least 1,024
+// entries a range).
 hipError_t launch_sort_rows(const int32_t* rowlist, const int64_t* cls_off, int32_t n, const int64_t* off,
                             const int32_t* len, int32_t* adj, int32_t* deg, int32_t* tmp, int32_t* scratch,
                             hipStream_t s);
+// Rows of kRowMerge: sort chunks of kMergeChunk entries in place (no dedup).
+constexpr int kMergeChunk = 32768;
+hipError_t launch_sort_chunks(const int64_t* chunk_beg, const int32_t* chunk_len, int32_t nchunks,
+                              int32_t* buf, hipStream_t s);
+// One merge pass: job k merges buf_in[a_beg, a_beg+la) with
+// buf_in[a_beg+la, a_beg+la+lb) into buf_out[out_beg, ...). tile_off is the
+// prefix of per-job tiles of kMergeTile outputs.
+constexpr int kMergeTile = 2048;
+hipError_t launch_merge_pass(const int64_t* a_beg, const int32_t* la, const int32_t* lb,
+                             const int64_t* out_beg, const int64_t* tile_off, int32_t njobs,
+                             int64_t ntiles, const int32_t* buf_in, int32_t* buf_out, hipStream_t s);
+// Dedups sorted rows from `sorted` (segment seg_beg[i]) into adj at
+// off[row[i]], writes deg.
+hipError_t launch_dedup_rows(const int32_t* rows, const int64_t* seg_beg, int32_t nrows,
+                             const int32_t* len, const int32_t* sorted, const int64_t* off,
+                             int32_t* adj, int32_t* deg, hipStream_t s);
+// out_off[i], out_len[i] = off, len of rows[i]
+hipError_t launch_gather_rows(const int32_t* rows, int32_t nr, const int64_t* off, const int32_t* len,
+                              int64_t* out_off, int32_t* out_len, hipStream_t s);
 
 // ---- Degree-order orientation --------------------------------------------
 // One pass over every row: dplus[v] = |{w in N(v): (d(v),v) < (d(w),w)}|

@@ -206,3 +206,35 @@ def test_pairs_of_one_tile_and_of_two(n, m):
             with pytest.raises(_native.TriccError) as ei:
                 P.Graph(n, torch.from_numpy(a).to(DEV), torch.from_numpy(b).to(DEV))
             assert ei.value.status == _native.TRICC_ERANGE
+
+
+@pytest.mark.parametrize("ranges", [16, 17, 32, 33, 96])
+def test_long_rows_of_many_ids(ranges):
+    """Rows on both sides of the bound between bitmaps and networks or merges
+    (1,024 entries per 2^20 ids above 16 such ranges), with repeats, of graphs
+    of up to 10^8 ids: sorted and unique in the built graph."""
+    n = (ranges << 20) - 3
+    bound = 1024 * ranges
+    lens = sorted({16_384, 16_385, 32_767, 32_768, 32_769, 65_536, 65_537, bound - 1, bound, bound + 1, 100_001})
+    rng = np.random.default_rng(ranges)
+    hubs = np.sort(rng.choice(n, len(lens), replace=False)).astype(np.int64)
+    hubs[0], hubs[-1] = 0, n - 1
+    s, d, want = [], [], []
+    for i, (h, k) in enumerate(zip(hubs, lens)):
+        w = rng.integers(0, n, k) if i % 2 else n // 3 + rng.integers(0, 2 * k, k)  # spread or in one range
+        w = np.where(np.isin(w, hubs), 5, w)
+        flip = rng.random(k) < 0.5
+        s.append(np.where(flip, h, w))
+        d.append(np.where(flip, w, h))
+        want.append(np.unique(w))
+    s, d = np.concatenate(s).astype(np.int32), np.concatenate(d).astype(np.int32)
+    mix = rng.permutation(s.size)
+    g = P.Graph(n, torch.from_numpy(s[mix]).to(DEV), torch.from_numpy(d[mix]).to(DEV))
+    a = g.arrays()
+    at = torch.from_numpy(hubs).to(DEV)
+    off, deg = a["off"][at].cpu().numpy(), a["deg"][at].cpu().numpy()
+    for o, k, w in zip(off, deg, want):
+        assert k == w.size
+        np.testing.assert_array_equal(a["adj"][int(o):int(o) + int(k)].cpu().numpy(), w)
+    assert g.info["large_rows"] == sum(k > 32_768 for k in lens)
+    assert int(a["deg"].sum()) == 2 * g.info["m"] == 2 * sum(w.size for w in want)
