@@ -993,28 +993,26 @@ __global__ __launch_bounds__(kWave * W) void k_sort_block(const int32_t* __restr
 // longest rows first: the last of them run beside the shorter classes instead
 // of alone before the next launch, and a small graph pays one launch, not one
 // per class.
-constexpr int kSortClasses = kRow4k - kRow8 + 1;
 struct SortPlan {
   int32_t row0[kSortClasses];   // first row in the list, from kRow4k down to kRow8
   int32_t nrows[kSortClasses];
   uint32_t blk0[kSortClasses];  // first block in the class's launch
 };
 
-__device__ __forceinline__ int sort_plan_class(const SortPlan& plan, int k0, int k1) {
+// Class of block b of a launch of the classes [k0, k1).
+__device__ __forceinline__ int sort_plan_class(const SortPlan& plan, int k0, int k1, uint32_t b) {
   int k = k0;
   for (int q = k0 + 1; q < k1; ++q)
-    if (blockIdx.x >= plan.blk0[q]) k = q;
+    if (b >= plan.blk0[q]) k = q;
   return k;
 }
-
-constexpr int kSortLongClasses = kRow4k - kRow256;  // kRow4k, kRow1024, kRow512
 
 __global__ __launch_bounds__(256) void k_sort_rows_long(SortPlan plan, const int32_t* __restrict__ list,
                                                         const int64_t* __restrict__ off,
                                                         const int32_t* __restrict__ len, int32_t* __restrict__ adj,
                                                         int32_t* __restrict__ deg) {
   __shared__ SortBlockLds<16, 4> lds;
-  const int k = sort_plan_class(plan, 0, kSortLongClasses);
+  const int k = sort_plan_class(plan, 0, kSortLongClasses, blockIdx.x);
   const int64_t blk = blockIdx.x - plan.blk0[k];
   const int32_t* rows = list + plan.row0[k];
   switch (kRow4k - k) {
@@ -1024,12 +1022,16 @@ __global__ __launch_bounds__(256) void k_sort_rows_long(SortPlan plan, const int
   }
 }
 
-__global__ __launch_bounds__(256) void k_sort_rows_short(SortPlan plan, const int32_t* __restrict__ list,
+// Blocks b0 .. of the launch's classes (the launcher cuts long launches up: a
+// loop over blocks in the kernel took 4% more of a build of rows of 10 entries).
+__global__ __launch_bounds__(256) void k_sort_rows_short(SortPlan plan, uint32_t b0,
+                                                         const int32_t* __restrict__ list,
                                                          const int64_t* __restrict__ off,
                                                          const int32_t* __restrict__ len, int32_t* __restrict__ adj,
                                                          int32_t* __restrict__ deg) {
-  const int k = sort_plan_class(plan, kSortLongClasses, kSortClasses);
-  const int64_t blk = blockIdx.x - plan.blk0[k];
+  const uint32_t b = b0 + blockIdx.x;
+  const int k = sort_plan_class(plan, kSortLongClasses, kSortClasses, b);
+  const int64_t blk = b - plan.blk0[k];
   const int32_t* rows = list + plan.row0[k];
   const int32_t n = plan.nrows[k];
   switch (kRow4k - k) {
@@ -1284,11 +1286,10 @@ hipError_t launch_sort_rows(const int32_t* rowlist, const int64_t* cls_off, int3
   uint32_t blocks[2] = {};  // long, short
   for (int k = 0; k < kSortClasses; ++k) {
     const int cls = kRow4k - k, x = k >= kSortLongClasses;
-    static constexpr int kPerBlock[kSortClasses] = {1, 4, 4, 4, 4, 4, 8, 16, 32};  // rows per block
     plan.row0[k] = (int32_t)cls_off[cls];
     plan.nrows[k] = (int32_t)(cls_off[cls + 1] - cls_off[cls]);
     plan.blk0[k] = blocks[x];
-    blocks[x] += (uint32_t)((plan.nrows[k] + kPerBlock[k] - 1) / kPerBlock[k]);
+    blocks[x] += row_sort_blocks(plan.nrows[k], k);
   }
   const int first = row_first_bitmap_class(n);
   for (int cls = kRow8k; cls < std::min<int>(first, kRowMerge); ++cls) {
@@ -1300,7 +1301,8 @@ hipError_t launch_sort_rows(const int32_t* rowlist, const int64_t* cls_off, int3
     else k_sort_lds<32768, 1024, true><<<nrows, 1024, 0, s>>>(rows, nullptr, nullptr, off, len, adj, deg);
   }
   if (blocks[0] > 0) k_sort_rows_long<<<blocks[0], 256, 0, s>>>(plan, rowlist, off, len, adj, deg);
-  if (blocks[1] > 0) k_sort_rows_short<<<blocks[1], 256, 0, s>>>(plan, rowlist, off, len, adj, deg);
+  for (uint32_t b0 = 0; b0 < blocks[1]; b0 += kRowShortGrid)
+    k_sort_rows_short<<<row_short_grid(blocks[1] - b0), 256, 0, s>>>(plan, b0, rowlist, off, len, adj, deg);
   const int32_t nbig = (int32_t)(cls_off[kNumRowClasses] - cls_off[first]);
   if (nbig > 0) {
     const int32_t* rows = rowlist + cls_off[first];

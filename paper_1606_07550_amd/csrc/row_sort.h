@@ -48,4 +48,18 @@ inline int row_first_bitmap_class(int64_t n) {
 // sorted by bitmap hold 1,024 entries a range and more, of at most 2^31.
 inline int64_t row_bitmap_blocks(int64_t nrows, int32_t ranges) { return (nrows + 7) / 8 * 8 * ranges; }
 
+// Rows per block of 256 threads in the joint launches of the classes kRow4k,
+// kRow1024, .., kRow8; the first kSortLongClasses of them form one launch, the
+// others the other, cut up into launches of kRowShortGrid blocks (2^28 threads):
+// 2^31 entries in rows of 2 make 2^25 blocks, twice what a launch takes, and rows
+// of two classes can pass that where neither would alone.
+constexpr int kSortClasses = kRow4k - kRow8 + 1;
+constexpr int kSortLongClasses = kRow4k - kRow256;
+constexpr int kSortRowsPerBlock[kSortClasses] = {1, 4, 4, 4, 4, 4, 8, 16, 32};
+constexpr uint32_t kRowShortGrid = 1u << 20;
+inline uint32_t row_sort_blocks(int64_t nrows, int k) {
+  return (uint32_t)((nrows + kSortRowsPerBlock[k] - 1) / kSortRowsPerBlock[k]);
+}
+inline uint32_t row_short_grid(uint32_t blocks) { return std::min(blocks, kRowShortGrid); }
+
 }  // namespace tricc

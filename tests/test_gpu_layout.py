@@ -238,3 +238,20 @@ def test_long_rows_of_many_ids(ranges):
         np.testing.assert_array_equal(a["adj"][int(o):int(o) + int(k)].cpu().numpy(), w)
     assert g.info["large_rows"] == sum(k > 32_768 for k in lens)
     assert int(a["deg"].sum()) == 2 * g.info["m"] == 2 * sum(w.size for w in want)
+
+
+def test_more_short_rows_than_a_launch_has_blocks():
+    """A ring of 40 million nodes, each joined to the two after it: rows of 4
+    entries in 1.25 million blocks, more than the row sort launches at once."""
+    n = 40_000_000
+    i = torch.arange(n, device=DEV, dtype=torch.int32)
+    d = torch.cat([(i + 1) % n, (i + 2) % n])
+    mix = torch.randperm(2 * n, device=DEV)
+    g = P.Graph(n, i.repeat(2)[mix].contiguous(), d[mix].contiguous())
+    a = g.arrays()
+    assert bool((a["deg"] == 4).all()) and bool((a["off"] == 4 * torch.arange(n + 1, device=DEV)).all())
+    rows = a["adj"].view(n, 4)
+    want = torch.sort(torch.stack([(i + k) % n for k in (-2, -1, 1, 2)], 1), 1)[0]
+    assert bool((rows == want).all())
+    out = g.count()
+    assert bool((out["T"] == 3).all()) and int(out["total"]) == n

@@ -19,6 +19,9 @@ int32_t ranges(int64_t n) { return row_ranges(n); }
 int32_t bitmap_min(int64_t n) { return row_bitmap_min(n); }
 int first_class(int64_t n) { return row_first_bitmap_class(n); }
 int64_t bitmap_blocks(int64_t rows, int32_t r) { return row_bitmap_blocks(rows, r); }
+uint32_t sort_blocks(int64_t rows, int k) { return row_sort_blocks(rows, k); }
+uint32_t short_grid(uint32_t blocks) { return row_short_grid(blocks); }
+int classes() { return kSortClasses; } int long_classes() { return kSortLongClasses; }
 int k8k() { return kRow8k; } int k32k() { return kRow32k; } int klarge() { return kRowLarge; }
 }
 """
@@ -36,6 +39,8 @@ def rules(tmp_path_factory):
     for f in (L.ranges, L.bitmap_min, L.first_class):
         f.argtypes = [ctypes.c_int64]
     L.bitmap_blocks.argtypes, L.bitmap_blocks.restype = [ctypes.c_int64, ctypes.c_int32], ctypes.c_int64
+    L.sort_blocks.argtypes, L.sort_blocks.restype = [ctypes.c_int64, ctypes.c_int], ctypes.c_uint32
+    L.short_grid.argtypes, L.short_grid.restype = [ctypes.c_uint32], ctypes.c_uint32
     return L
 
 
@@ -57,3 +62,21 @@ def test_bitmap_launches_stay_in_the_limits(rules, n):
     assert rules.bitmap_blocks(rows, r) * 1024 < MOST_THREADS
     assert rows * r < 1 << 31 and rows * r * 256 < MOST_THREADS
     assert r == 1 or 8 * rows * r <= 4 * (MOST_ENTRIES // 2)  # two int32 each in m_raw int32
+
+
+SHORTEST = [1025, 513, 257, 129, 65, 33, 17, 9, 2]  # entries of a row, by class from kRow4k down
+
+
+@pytest.mark.parametrize("mix", [{k: 1.0} for k in range(9)] + [{8: 0.5, 5: 0.5}, {8: 0.45, 4: 0.55}, {0: 0.5, 2: 0.5},
+                                                               {k: 1 / 9 for k in range(9)}])
+def test_joint_launches_stay_in_the_limits(rules, mix):
+    """The most rows that 2^31 entries make, of one class and of several."""
+    assert rules.classes() == len(SHORTEST)
+    blocks = [0, 0]
+    for k, share in mix.items():
+        rows = min(MOST_NODES, int(MOST_ENTRIES * share) // SHORTEST[k])
+        blocks[k >= rules.long_classes()] += rules.sort_blocks(rows, k)
+    assert max(blocks) < 1 << 32  # counted in 32 bits
+    assert blocks[0] * 256 < MOST_THREADS
+    assert rules.short_grid(blocks[1]) * 256 < MOST_THREADS
+    assert rules.short_grid(1000) == 1000
