@@ -43,7 +43,8 @@ constexpr int kPeelG = 8;  // lanes per node in the peel of large frontiers
 // Levels per window of the peeling: a scan of every node left opens a window
 // [k, k + kCoreWindow], whose levels then scan the near list only.
 constexpr int32_t kCoreWindow = 32;
-// A level's rounds take order values in multiples of this many.
+// A level's rounds start at multiples of this many in the order values: part of
+// the results, which stay what they are however the rounds are launched.
 constexpr int32_t kOrderRounds = 4;
 constexpr int32_t kNoDegree = 0x7fffffff;
 
@@ -113,19 +114,6 @@ __device__ __forceinline__ void core_next(CoreState& s, const CoreCount& c, int3
     s.k += 1;
     core_plan(s, n, k_stop);
   }
-}
-
-// Appends the items of the lanes with `take` to q[*cnt ..], one atomic per
-// wavefront. All lanes of the wavefront must call it.
-__device__ __forceinline__ void wave_push(bool take, int32_t item, int32_t* __restrict__ q,
-                                          int32_t* __restrict__ cnt) {
-  const uint64_t m = __ballot(take);
-  if (!m) return;
-  const int leader = __builtin_ctzll(m);
-  int32_t at = 0;
-  if (lane_id() == leader) at = atomicAdd(cnt, (int32_t)__popcll(m));
-  at = __shfl(at, leader, kWave);
-  if (take) q[at + mask_below(m)] = item;
 }
 
 // Layout of the counter area (64 int32): two states, three counter sets.
@@ -251,9 +239,14 @@ __device__ __forceinline__ void core_scan(const CoreState& s, const CoreArrays& 
     atomicMin(&c->least, mn);
 }
 
-// Rows up to this length are walked by their node's 8-lane group; longer
-// ones by the whole wavefront, one node after the other.
+// Rows up to this length are walked by an 8-lane group of a wavefront that holds
+// eight of them; longer ones, and all rows of frontiers of at most kPeelFew
+// nodes, by a wavefront each. Full decomposition, ms, short rows up to 16 / 32 /
+// 64: a lattice of 128^3 nodes and 26 neighbours 18.8 / 8.2 / 8.1, 10^6 nodes of
+// 16 edges by preferential attachment 9.4 / 5.8 / 4.8, R-MAT 24 (64M pairs) 15.6 /
+// 15.3 / 15.1; kPeelFew 64 / 128 / 256 / 512: R-MAT 18 4.96 / 4.79 / 4.64 / 4.55.
 constexpr int32_t kPeelShort = 64;
+constexpr int32_t kPeelFew = 512;
 // Steps of a walk issued together: their loads and atomic subtractions are
 // in flight at once, since each waits on a round trip to memory.
 constexpr int kPeelU = 8;
@@ -262,8 +255,8 @@ constexpr int kPeelU = 8;
 // kPeelU (t = the lane's place among the W walkers): every neighbour left
 // loses one from its current degree; the one decrement from k + 1 to k gives
 // it core number k and puts it on the next frontier, the one from U + 1 to U
-// on the near list. Every lane of the wavefront calls it (the pushes are
-// wave-wide).
+// on the near list. Every lane of the wavefront calls it: all its items of a list
+// take one atomic, both lists' in flight together (a step waits for it).
 __device__ __forceinline__ void peel_steps(const int32_t* __restrict__ row, int32_t d, int32_t j0, int32_t W,
                                            int32_t t, const CoreState& s, const CoreArrays& g, CoreCount* c) {
   int32_t w[kPeelU];
@@ -279,76 +272,113 @@ __device__ __forceinline__ void peel_steps(const int32_t* __restrict__ row, int3
   int32_t old[kPeelU];
 #pragma unroll
   for (int q = 0; q < kPeelU; ++q) old[q] = live[q] ? atomicSub(&g.cur[w[q]], 1) : 0;
+  uint64_t take[kPeelU], enter[kPeelU];
+  int32_t nt = 0, ne = 0;
 #pragma unroll
   for (int q = 0; q < kPeelU; ++q) {
-    const bool take = live[q] && old[q] == s.k + 1;
-    const bool enter = live[q] && old[q] == s.U + 1;
-    if (take) {
+    take[q] = __ballot(live[q] && old[q] == s.k + 1);
+    // at the window's last level the frontier is all that enters
+    enter[q] = __ballot(live[q] && old[q] == s.U + 1 && s.U > s.k);
+    nt += (int32_t)__popcll(take[q]);
+    ne += (int32_t)__popcll(enter[q]);
+  }
+  if (nt + ne == 0) return;
+  const int lane = lane_id();
+  int32_t at = 0, et = 0;
+  if (lane == 0 && nt) at = atomicAdd(&c->f, nt);
+  if (lane == 0 && ne) et = atomicAdd(&c->near, ne);
+  at = __builtin_amdgcn_readfirstlane(at);
+  et = __builtin_amdgcn_readfirstlane(et) + s.nx;
+#pragma unroll
+  for (int q = 0; q < kPeelU; ++q) {
+    if ((take[q] >> lane) & 1) {
       g.core[w[q]] = s.k;
       if (g.order) g.order[w[q]] = s.round + s.rounds + 1;
+      g.F[s.fb ^ 1][at + mask_below(take[q])] = w[q];
     }
-    wave_push(take, w[q], g.F[s.fb ^ 1], &c->f);
-    wave_push(enter, w[q], g.near[s.xb] + s.nx, &c->near);
+    if ((enter[q] >> lane) & 1) g.near[s.xb][et + mask_below(enter[q])] = w[q];
+    at += (int32_t)__popcll(take[q]);
+    et += (int32_t)__popcll(enter[q]);
   }
 }
 
-// One round: the frontier's nodes by 8-lane groups while there are many (8 per
-// wavefront and more), else by a wavefront each, or by several blocks each when
-// the frontier is smaller than the grid (late levels: tens of nodes with rows
-// of thousands of entries, which one wavefront walks 512 at a time).
+// A frontier node as its walkers need it: row length and start (0 past the end).
+struct PeelRow {
+  int32_t d;
+  int64_t at;
+};
+__device__ __forceinline__ PeelRow peel_row(int64_t i, int32_t nf, const int32_t* F, const CoreArrays& g) {
+  PeelRow r{0, 0};
+  if (i < nf) {
+    const int32_t v = F[i];
+    r.d = g.deg[v];
+    r.at = g.off[v];
+  }
+  return r;
+}
+
+// The short rows among 8 frontier nodes (lane l holds that of group l / 8 in r),
+// one per 8-lane group of a wavefront.
+__device__ __forceinline__ void peel_short(const PeelRow& r, const CoreState& s, const CoreArrays& g, CoreCount* c) {
+  const int32_t ds = r.d <= kPeelShort ? r.d : 0;
+  int32_t dmax = ds;
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) dmax = max(dmax, __shfl_xor(dmax, o, kWave));
+  for (int32_t j0 = 0; j0 < dmax; j0 += kPeelG * kPeelU)
+    peel_steps(g.adj + r.at, ds, j0, kPeelG, threadIdx.x % kPeelG, s, g, c);
+}
+
+// One round. Short rows go eight nodes to a wavefront, whose pushes take one
+// atomic together: one counter takes about 100 atomics per microsecond, so with
+// a wavefront per node rounds of 4,096 nodes of degree 4 took 22 us, and 40 where
+// both lists grew (a grid of 2,048 x 2,048 nodes 45 and 79 ms, now 19 and 19).
+// Long rows: with many nodes (more than 8 per wavefront) one after the other by
+// the wavefront that holds them, else by a wavefront each, or by several blocks
+// each when the frontier is smaller than the grid (late levels: tens of nodes
+// with rows of thousands of entries, which one wavefront walks 512 at a time).
 __device__ __forceinline__ void core_peel(const CoreState& s, const CoreArrays& g, CoreCount* c) {
+  constexpr int WPB = kCoreNT / kWave, GPW = kWave / kPeelG;  // wavefronts a block, groups a wavefront
   const int32_t* F = g.F[s.fb];
   const int32_t nf = s.nf;
-  const int lane = lane_id();
-  const int32_t blocks = (int32_t)gridDim.x;
-  if (nf <= blocks) {
-    const int32_t per = blocks / nf;  // blocks per node
-    const int32_t i = (int32_t)blockIdx.x % nf, part = (int32_t)blockIdx.x / nf;
-    if (part >= per) return;
-    const int32_t v = F[i];
-    const int32_t d = g.deg[v];
-    const int32_t* row = g.adj + g.off[v];
-    for (int32_t j0 = part * kCoreNT * kPeelU; j0 < d; j0 += per * kCoreNT * kPeelU)
-      peel_steps(row, d, j0, kCoreNT, threadIdx.x, s, g, c);
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  const int32_t blocks = (int32_t)gridDim.x, waves = blocks * WPB;
+  if (nf <= GPW * waves) {
+    // groups of eight nodes go to the first wavefront of each block first
+    const int32_t me = wv * blocks + (int32_t)blockIdx.x;
+    const PeelRow mine = peel_row((int64_t)me * GPW + lane / kPeelG, nf, F, g);
+    const int32_t shortest = nf <= kPeelFew ? 0 : kPeelShort;  // rows above it are walked one by one
+    if (nf <= blocks) {
+      const int32_t per = blocks / nf;  // blocks per node
+      const int32_t i = (int32_t)blockIdx.x % nf, part = (int32_t)blockIdx.x / nf;
+      if (part < per) {
+        const PeelRow r = peel_row(i, nf, F, g);
+        if (r.d > shortest)
+          for (int32_t j0 = part * kCoreNT * kPeelU; j0 < r.d; j0 += per * kCoreNT * kPeelU)
+            peel_steps(g.adj + r.at, r.d, j0, kCoreNT, threadIdx.x, s, g, c);
+      }
+    } else {
+      for (int32_t i = me; i < nf; i += waves) {
+        const PeelRow r = peel_row(i, nf, F, g);
+        if (r.d <= shortest) continue;
+        for (int32_t j0 = 0; j0 < r.d; j0 += kWave * kPeelU) peel_steps(g.adj + r.at, r.d, j0, kWave, lane, s, g, c);
+      }
+    }
+    if (nf > kPeelFew) peel_short(mine, s, g, c);
     return;
   }
-  if (nf <= 8 * blocks * (kCoreNT / kWave)) {
-    const int64_t step = (int64_t)blocks * (kCoreNT / kWave);
-    for (int64_t i = (int64_t)blockIdx.x * (kCoreNT / kWave) + threadIdx.x / kWave; i < nf; i += step) {
-      const int32_t v = F[i];
-      const int32_t d = g.deg[v];
-      const int32_t* row = g.adj + g.off[v];
-      for (int32_t j0 = 0; j0 < d; j0 += kWave * kPeelU) peel_steps(row, d, j0, kWave, lane, s, g, c);
-    }
-    return;
-  }
-  constexpr int GPB = kCoreNT / kPeelG;
-  const int t = threadIdx.x % kPeelG;
-  const int64_t step = (int64_t)blocks * GPB;
-  for (int64_t b = (int64_t)blockIdx.x * GPB; b < nf; b += step) {  // uniform trip count
-    const int64_t fi = b + threadIdx.x / kPeelG;
-    int32_t dv = 0;
-    int64_t rb = 0;
-    if (fi < nf) {
-      const int32_t v = F[fi];
-      dv = g.deg[v];
-      rb = g.off[v];
-    }
-    // short rows: each group walks its own, the wavefront its longest short one
-    const int32_t ds = dv <= kPeelShort ? dv : 0;
-    int32_t dmax = ds;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) dmax = max(dmax, __shfl_xor(dmax, o, kWave));
-    for (int32_t j0 = 0; j0 < dmax; j0 += kPeelG * kPeelU) peel_steps(g.adj + rb, ds, j0, kPeelG, t, s, g, c);
+  const int64_t step = (int64_t)waves * GPW;
+  for (int64_t b = ((int64_t)blockIdx.x * WPB + wv) * GPW; b < nf; b += step) {  // wave-uniform
+    const PeelRow r = peel_row(b + lane / kPeelG, nf, F, g);
+    peel_short(r, s, g, c);
     // long rows: the whole wavefront on each in turn (group leaders' bits)
-    uint64_t longs = __ballot(t == 0 && dv > kPeelShort);
+    uint64_t longs = __ballot(lane % kPeelG == 0 && r.d > kPeelShort);
     while (longs) {
       const int src = __builtin_ctzll(longs);
       longs &= longs - 1;
-      const int32_t d = __shfl(dv, src, kWave);
-      const int64_t r = ((int64_t)__shfl((int32_t)(rb >> 32), src, kWave) << 32) |
-                        (uint32_t)__shfl((int32_t)rb, src, kWave);
-      for (int32_t j0 = 0; j0 < d; j0 += kWave * kPeelU) peel_steps(g.adj + r, d, j0, kWave, lane, s, g, c);
+      const int32_t d = __shfl(r.d, src, kWave);
+      const int64_t at = ((int64_t)__shfl((int32_t)(r.at >> 32), src, kWave) << 32) |
+                         (uint32_t)__shfl((int32_t)r.at, src, kWave);
+      for (int32_t j0 = 0; j0 < d; j0 += kWave * kPeelU) peel_steps(g.adj + at, d, j0, kWave, lane, s, g, c);
     }
   }
 }

@@ -111,3 +111,70 @@ def test_empty_graph_and_errors():
     assert L.tricc_graph_core(g._h, -1, ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(ws.data_ptr()),
                               need.value, ctypes.byref(mx), sp) == N.TRICC_OK
     assert mx.value == 6 and bool((out == 6).all().item())
+
+
+def rounds(n, s, d):
+    """Core numbers and removal rounds by peeling level by level: all nodes of
+    current degree at most k together, a level's rounds numbered from a
+    multiple of four."""
+    keep = s != d
+    key = np.unique(np.concatenate([s[keep].astype(np.int64) * n + d[keep], d[keep].astype(np.int64) * n + s[keep]]))
+    u, w = key // n, key % n
+    off = np.searchsorted(u, np.arange(n + 1))
+    cur = np.diff(off)
+    core, order, k, r = np.full(n, -1), np.zeros(n, np.int64), 0, 0
+    while (core < 0).any():
+        k = max(k, cur[core < 0].min())
+        F, first = np.flatnonzero((core < 0) & (cur <= k)), r
+        while F.size:
+            core[F], order[F] = k, r
+            r += 1
+            at = np.repeat(off[F] - np.concatenate([[0], np.cumsum(np.diff(off)[F])[:-1]]), np.diff(off)[F])
+            nb = w[at + np.arange(at.size)]
+            cur -= np.bincount(nb, minlength=n)
+            F = np.unique(nb[(core[nb] < 0) & (cur[nb] <= k)])
+        r = first + (r - first + 3) // 4 * 4
+        k += 1
+    return core, order
+
+
+def hubs_with_leaves(hubs, leaves, tail):
+    """`hubs` stars whose centres fall due in the second round, when their rows
+    are long, together with the second nodes of as many paths of `tail` nodes."""
+    n1 = hubs * (leaves + 1)
+    h = np.repeat(np.arange(hubs), leaves)
+    n2 = hubs * tail
+    p = n1 + np.arange(n2).reshape(hubs, tail)
+    s = np.concatenate([h, p[:, :-1].ravel()])
+    d = np.concatenate([hubs + np.arange(hubs * leaves), p[:, 1:].ravel()])
+    return n1 + n2, s.astype(np.int32), d.astype(np.int32)
+
+
+# frontiers below, at and above the bounds of the peel's ways: 512 nodes, the
+# launch's blocks (1,024), eight nodes to each of its wavefronts (32,768)
+FRONTIERS = {
+    **{f"bipartite_{a}_{b}": (lambda a=a, b=b: F.complete_bipartite(a, b))
+       for a, b in [(100, 511), (100, 512), (100, 513), (100, 1024), (65, 1025), (64, 20_000), (100, 32_768),
+                    (100, 32_769), (100, 40_000), (3, 40_000)]},
+    **{f"hubs_{h}_{k}": (lambda h=h, k=k: hubs_with_leaves(h, k, 6))
+       for h, k in [(1, 3000), (300, 70), (900, 64), (900, 65), (5000, 66), (33_000, 66)]},
+    "grid": lambda: F.grid(400, 300),
+    "ring_lattice": lambda: F.ring_lattice(30_000, 20),
+}
+
+
+@pytest.mark.parametrize("name", list(FRONTIERS))
+def test_frontiers_of_every_size(name):
+    n, s, d = FRONTIERS[name]()
+    s, d = np.asarray(s, np.int32), np.asarray(d, np.int32)
+    g = P.Graph(n, dev(s), dev(d))
+    ref = oracle.core(n, s, d)
+    for k in (-1, 2, 3, 34):
+        got, mx = gpu_core(g, k)
+        np.testing.assert_array_equal(got, ref if k < 0 else np.minimum(ref, k), err_msg=f"k_stop {k}")
+        assert mx == int(ref.max() if k < 0 else min(ref.max(), k))
+    core, order = rounds(n, s, d)
+    np.testing.assert_array_equal(core, ref)
+    got = g.degeneracy()
+    np.testing.assert_array_equal(got[1].cpu().numpy(), ref)
+    np.testing.assert_array_equal(got[0].cpu().numpy(), order)
