@@ -999,27 +999,24 @@ int core_impl(const tricc_graph* g, int32_t k_stop, int32_t* d_core, int32_t* d_
     const CoreBuffers b{g->at<int64_t>(L.raw_off), g->at<int32_t>(L.deg), g->at<int32_t>(L.adj), part(0), d_core,
                         d_order, {part(1), part(2)}, {part(3), part(4)}, {part(5), part(6)}, part(7)};
     HIPCHK(launch_core_init(n, k_stop, b, s));
-    // steps launched ahead of each look at the state: few at first (a small
-    // graph ends early; with a k_stop that is below every degree the second step
-    // is the last: 55 us with two, 76 with one, 92 with eight), then more; those
-    // past the end are empty
-    int step = 0, ahead = k_stop >= 0 ? 2 : 8;
+    // steps launched ahead of each look at the state: with a k_stop one at first
+    // (where it is below every degree the first step is the last: 43 us for 3,000
+    // nodes, 57 when the host saw the end a step later and filled after it), else
+    // eight (a small graph ends early), then more; those past the end are empty.
+    // The look waits for the nodes left to get k_stop, if that was the end.
+    int step = 0, ahead = k_stop >= 0 ? 1 : 8;
     CoreProgress pr;
     do {
       HIPCHK(launch_core_steps(step + 1, ahead, n, k_stop, b, s));
       step += ahead;
-      ahead = std::min(2 * ahead, 64);
+      ahead = std::min(std::max(4, 2 * ahead), 64);
+      if (k_stop >= 0) HIPCHK(launch_core_fill(step, n, k_stop, b, s));
       int32_t cnt[64];
       const int rc = sync_copy(cnt, b.cnt, sizeof(cnt), s);
       if (rc) return rc;
-      pr = core_progress(cnt, step);
+      pr = core_progress(cnt, step, n, k_stop);
     } while (!pr.done);
-    maxc = pr.max_core;
-    if (k_stop >= 0 && pr.left > 0) {
-      HIPCHK(launch_core_fill(n, k_stop, d_core, s));
-      maxc = k_stop;
-    }
-    HIPCHK(hipStreamSynchronize(s));
+    maxc = k_stop >= 0 && pr.left > 0 ? k_stop : pr.max_core;
   }
   if (h_max_core) *h_max_core = maxc;
   return TRICC_OK;

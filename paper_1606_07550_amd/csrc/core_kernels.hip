@@ -30,6 +30,7 @@
 // (round, id) gives out-degrees at most the core number: the degeneracy
 // ordering.
 #include <algorithm>
+#include <cstring>
 
 #include "device_common.h"
 #include "kernels.h"
@@ -63,7 +64,7 @@ struct CoreCount {
 };
 
 // What follows the levels done so far: a scan for level k, or the end.
-__device__ __forceinline__ void core_plan(CoreState& s, int32_t n, int32_t k_stop) {
+__host__ __device__ __forceinline__ void core_plan(CoreState& s, int32_t n, int32_t k_stop) {
   if (!(s.left > 0 && (k_stop < 0 || s.k < k_stop))) {
     s.phase = kCoreDone;
     return;
@@ -73,7 +74,7 @@ __device__ __forceinline__ void core_plan(CoreState& s, int32_t n, int32_t k_sto
   s.listing = 0;
   if (s.full) {
     s.U = s.k + kCoreWindow;
-    if (k_stop >= 0) s.U = min(s.U, k_stop - 1);  // no level at or above k_stop is peeled
+    if (k_stop >= 0 && s.U > k_stop - 1) s.U = k_stop - 1;  // no level at or above k_stop is peeled
     // full scans list the survivors for the next one once at most a quarter
     // of the nodes are left
     s.listing = s.listed || s.left <= n / 4;
@@ -81,7 +82,7 @@ __device__ __forceinline__ void core_plan(CoreState& s, int32_t n, int32_t k_sto
 }
 
 // The state after step s, whose counters were c.
-__device__ __forceinline__ void core_next(CoreState& s, const CoreCount& c, int32_t n, int32_t k_stop) {
+__host__ __device__ __forceinline__ void core_next(CoreState& s, const CoreCount& c, int32_t n, int32_t k_stop) {
   if (s.phase == kCoreScan) {
     s.xb ^= 1;
     s.nx = c.near;
@@ -399,10 +400,14 @@ __global__ __launch_bounds__(kCoreNT) void k_core_step(int step, int32_t n, int3
   else if (s.phase == kCorePeel) core_peel(s, g, c);
 }
 
-__global__ __launch_bounds__(kCoreNT) void k_core_fill(int32_t n, int32_t k, int32_t* __restrict__ core) {
+// After step `step`, if the peeling has ended with it: the nodes left get k_stop.
+__global__ __launch_bounds__(kCoreNT) void k_core_fill(int step, int32_t n, int32_t k_stop, CoreArrays g) {
+  CoreState s = *core_state(g.cnt, step);
+  core_next(s, *core_count(g.cnt, step), n, k_stop);
+  if (s.phase != kCoreDone || s.left == 0) return;
   const int64_t stride = (int64_t)gridDim.x * kCoreNT;
   for (int64_t v = (int64_t)blockIdx.x * kCoreNT + threadIdx.x; v < n; v += stride)
-    if (core[v] < 0) core[v] = k;
+    if (g.core[v] < 0) g.core[v] = k_stop;
 }
 
 unsigned core_grid(int64_t work) {
@@ -431,13 +436,17 @@ hipError_t launch_core_steps(int first, int count, int32_t n, int32_t k_stop, co
   return hipGetLastError();
 }
 
-CoreProgress core_progress(const int32_t* cnt, int step) {
-  const CoreState* s = reinterpret_cast<const CoreState*>(cnt) + (step & 1);
-  return CoreProgress{s->phase == kCoreDone, s->left, s->maxc};
+CoreProgress core_progress(const int32_t* cnt, int step, int32_t n, int32_t k_stop) {
+  CoreState s;
+  CoreCount c;
+  std::memcpy(&s, cnt + (step & 1) * (sizeof(CoreState) / 4), sizeof(s));
+  std::memcpy(&c, cnt + 2 * (sizeof(CoreState) / 4) + step % 3 * (sizeof(CoreCount) / 4), sizeof(c));
+  core_next(s, c, n, k_stop);
+  return CoreProgress{s.phase == kCoreDone, s.left, s.maxc};
 }
 
-hipError_t launch_core_fill(int32_t n, int32_t k, int32_t* core, hipStream_t s) {
-  k_core_fill<<<core_grid(n), kCoreNT, 0, s>>>(n, k, core);
+hipError_t launch_core_fill(int step, int32_t n, int32_t k_stop, const CoreBuffers& b, hipStream_t s) {
+  k_core_fill<<<core_grid(n), kCoreNT, 0, s>>>(step, n, k_stop, core_arrays(b));
   return hipGetLastError();
 }
 

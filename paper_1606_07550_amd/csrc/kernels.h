@@ -269,14 +269,16 @@ hipError_t launch_core_init(int32_t n, int32_t k_stop, const CoreBuffers& b, hip
 // Steps first .. first + count - 1 (the first step is 1; steps after the end
 // do nothing).
 hipError_t launch_core_steps(int first, int count, int32_t n, int32_t k_stop, const CoreBuffers& b, hipStream_t s);
-// From a host copy of cnt after step `step`: whether the peeling has ended,
-// the nodes left and the last level peeled, as that step found them.
+// From a host copy of cnt after step `step` (the last one launched, at least
+// 1): whether the peeling has ended with it, the nodes left and the last level
+// peeled.
 struct CoreProgress {
   bool done;
   int32_t left, max_core;
 };
-CoreProgress core_progress(const int32_t* cnt, int step);
-hipError_t launch_core_fill(int32_t n, int32_t k, int32_t* core, hipStream_t s);
+CoreProgress core_progress(const int32_t* cnt, int step, int32_t n, int32_t k_stop);
+// core = k_stop for the nodes left, if the peeling has ended with step `step`.
+hipError_t launch_core_fill(int step, int32_t n, int32_t k_stop, const CoreBuffers& b, hipStream_t s);
 
 // ---- 4-clique counts ---------------------------------------------------------
 // *total = number of 4-cliques, over the DAG N+(v) = dcol[doff[v] ..
