@@ -72,7 +72,11 @@ __device__ __forceinline__ void TotalNow::add_lanes(uint32_t c) {
   if (lane_id() == 0) add(t);
 }
 
-// LDS of one node group of the wave-stream kernel.
+// LDS of one node group of the wave-stream kernel. It is given out by 1,280
+// bytes: with indices of 32 bits the tables of 4,096 slots for d+ <= 1,024 and the
+// start bits of their wavefronts took 55,040 bytes, two blocks a CU instead of
+// three (variants 3 and 13 on the nodes of d+ 513 to 1,024 of R-MAT 22, three
+// launches: 29.7 and 18.6 ms with two blocks, 23.6 and 15.1 with three).
 template <int SLOTS, int CAP>
 struct WaveGroupLds {
   int4 K[SLOTS / 4];     // bucket table of N+(u)
@@ -81,7 +85,7 @@ struct WaveGroupLds {
   int32_t Wn[CAP];       // |N+(w)|
   int32_t Ws[CAP];       // slot of w
   uint32_t Wc[CAP];      // hits per streamed list (packed phase)
-  int32_t Wl[CAP];       // indices of the lists streamed one by one
+  uint16_t Wl[CAP];      // indices of the lists streamed one by one
   int32_t nlong;         // number of such lists
   int32_t fail;          // a cuckoo insert gave up
 };
@@ -203,7 +207,7 @@ __device__ __forceinline__ uint32_t stream_packed(int32_t i0, int32_t i1, const 
 // the credit's exec mask use the scalar unit. Returns the sum over the lists
 // that this lane held.
 template <int U, typename Probe, typename Done>
-__device__ __forceinline__ uint32_t stream_long(int32_t j0, int32_t step, int32_t nl, const int32_t* Wl,
+__device__ __forceinline__ uint32_t stream_long(int32_t j0, int32_t step, int32_t nl, const uint16_t* Wl,
                                                 const int32_t* Wb, const int32_t* Wn,
                                                 const int32_t* __restrict__ dcol, Probe probe, uint32_t* C,
                                                 Done done) {
@@ -299,7 +303,7 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
                                                 const int32_t* __restrict__ dcol,
                                                 unsigned long long* __restrict__ T,
                                                 Total& tot, int32_t w_max = 0) {
-  static_assert(G % kWave == 0 && SLOTS % 4 == 0 && SLOTS >= 2 * CAP, "shape");
+  static_assert(G % kWave == 0 && SLOTS % 4 == 0 && SLOTS >= 2 * CAP && CAP <= 65536, "shape");
   constexpr int WPG = G / kWave;
   constexpr int NB = SLOTS / 4;
   const int g = threadIdx.x % G;
@@ -333,7 +337,7 @@ __device__ __forceinline__ void node_count_wave(int32_t u, WaveGroupLds<SLOTS, C
     S.Wb[i] = (int32_t)b;
     S.Wn[i] = wn;
     S.Wc[i] = 0;
-    if (wn >= kPackShort) S.Wl[atomicAdd(&S.nlong, 1)] = i;
+    if (wn >= kPackShort) S.Wl[atomicAdd(&S.nlong, 1)] = (uint16_t)i;
   }
   group_sync<G>();
   const int32_t nl = __builtin_amdgcn_readfirstlane(S.nlong);
@@ -424,7 +428,7 @@ __device__ __forceinline__ void node_count_inw(int32_t w, int64_t chunk, WaveGro
       S.Wn[i] = nu;
       S.Ws[i] = u;
       S.Wc[i] = 0;
-      if (nu >= kPackShort) S.Wl[atomicAdd(&S.nlong, 1)] = i;
+      if (nu >= kPackShort) S.Wl[atomicAdd(&S.nlong, 1)] = (uint16_t)i;
     }
     group_sync<G>();
     const int32_t nl = __builtin_amdgcn_readfirstlane(S.nlong);
