@@ -844,15 +844,16 @@ __device__ __forceinline__ uint64_t nodes_count_small(SmallNode h, SmallLds<GS>&
 // each wavefront takes 64 / GS consecutive nodes of the bin, counts those
 // with d+ <= GS together on the packed small-node path, then the others one
 // by one as node_count_wave does. The in-list side (blocks after the first
-// ceil(nlist / (GPB * 64 / GS))) is k_count_ms's.
+// ceil(nlist / (GPB * 64 / GS))) is k_count_ms's. With cuckoo tables eight
+// wavefronts a SIMD leave too few registers (8 spilled; 10^6 nodes, 16M uniform
+// pairs, three launches without in-lists: 2.20 ms, with seven 1.75); with bucket
+// tables seven are slower on R-MAT graphs (scale 22 1.72 -> 1.82 ms).
 template <int NT, int SLOTS, int CAP, int U, bool CK, int GS>
-__global__ __launch_bounds__(NT, 8) void k_count_mss(const int32_t* __restrict__ list, int32_t nlist, InItems in,
-                                                  int32_t w_max, const int64_t* __restrict__ doff,
-                                                  const int32_t* __restrict__ dcol,
-                                                  const int64_t* __restrict__ dinoff,
-                                                  const int32_t* __restrict__ dincol,
-                                                  unsigned long long* __restrict__ T,
-                                                  unsigned long long* __restrict__ tot) {
+__global__ __launch_bounds__(NT, CK ? 7 : 8) void
+k_count_mss(const int32_t* __restrict__ list, int32_t nlist, InItems in, int32_t w_max,
+            const int64_t* __restrict__ doff, const int32_t* __restrict__ dcol, const int64_t* __restrict__ dinoff,
+            const int32_t* __restrict__ dincol, unsigned long long* __restrict__ T,
+            unsigned long long* __restrict__ tot) {
   constexpr int GPB = NT / kWave;
   constexpr int NPW = kWave / GS;
   using WL = WaveGroupLds<SLOTS, CAP>;
