@@ -245,9 +245,9 @@ int sort_merge_rows(tricc_graph* g, int32_t nl, const int32_t* rows_dev) {
   return TRICC_OK;
 }
 
-// DAG offsets, in-degrees, edge records, node bins and in-list items from
-// the degrees (d, d+), into the workspace and its header; no host wait.
-int layout_and_bins(tricc_graph* g) {
+// DAG offsets, in-degrees, edge records (offsets), node bins and in-list items
+// from the degrees (d, d+), into the workspace and its header; no host wait.
+int layout_and_bins(tricc_graph* g, bool offsets) {
   hipStream_t s = g->stream;
   const Layout& L = g->L;
   BinParams bp;
@@ -275,7 +275,7 @@ int layout_and_bins(tricc_graph* g) {
   o.limit = g->hdr32() + kHdrLimits;
   o.cap = g->hdr32() + kHdrInCap;
   // the per-tile sums sit in the chunk-count area, which nothing else uses
-  HIPCHK(launch_layout(g->n, bp, g->at<int32_t>(L.inch), o, s));
+  HIPCHK(launch_layout(g->n, bp, offsets, g->at<int32_t>(L.inch), o, s));
   return TRICC_OK;
 }
 
@@ -333,7 +333,7 @@ int finish_bins(tricc_graph* g) {
 }
 
 int bin_nodes(tricc_graph* g) {
-  int rc = layout_and_bins(g);
+  int rc = layout_and_bins(g, false);
   return rc ? rc : finish_bins(g);
 }
 
@@ -403,7 +403,7 @@ int orient_impl(tricc_graph* g, const int32_t* key) {
     HIPCHK(hipMemsetAsync(g->at<int64_t>(L.dinoff), 0, sizeof(int64_t), s));
   }
   // a5 with the offsets; the copy reads them, and frees tmp for the owner map
-  if ((rc = layout_and_bins(g))) return rc;
+  if ((rc = layout_and_bins(g, true))) return rc;
   HIPCHK(launch_orient_copy(n, raw_off, len, deg, dplus, part, med_rows, nmed, long_rows, nlong, doff, dcol,
                             g->at<int64_t>(L.dinoff), g->at<int32_t>(L.dincol), s));
   g->oriented_by_key = key != nullptr;

@@ -1959,6 +1959,8 @@ __global__ __launch_bounds__(kLayoutNT) void k_layout_count(int32_t n, int64_t t
   if (threadIdx.x < kLayoutQ) sums[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = acc[threadIdx.x];
 }
 
+// OFFSETS: the offsets and records too (of a new DAG), else the bins alone.
+template <bool OFFSETS>
 __global__ __launch_bounds__(kLayoutNT) void k_layout_place(int32_t n, int64_t tile, BinParams bp,
                                                             const int32_t* __restrict__ sums, LayoutOut o) {
   __shared__ int32_t prev[kLayoutQ], all[kLayoutQ];
@@ -1999,13 +2001,15 @@ __global__ __launch_bounds__(kLayoutNT) void k_layout_place(int32_t n, int64_t t
       it += all[kLqItems + q];
     }
     if (me == 0) {
-      o.doff[n] = all[kLqOut];
-      o.dinoff[n] = all[kLqIn];
+      if (OFFSETS) {
+        o.doff[n] = all[kLqOut];
+        o.dinoff[n] = all[kLqIn];
+        o.stats[0] = all[kLqMaxD];
+        o.stats[1] = all[kLqMaxP];
+        o.stats[2] = all[kLqDeg2];
+        *o.m = all[kLqOut];
+      }
       if (bp.min_side) o.incoff[ib] = it;
-      o.stats[0] = all[kLqMaxD];
-      o.stats[1] = all[kLqMaxP];
-      o.stats[2] = all[kLqDeg2];
-      *o.m = all[kLqOut];
       for (int q = 0; q < kNumBins - 1; ++q) o.limit[q] = bp.limit[q];
       for (int q = 0; q < kNumBins; ++q) o.cap[q] = bp.cap[q];
     }
@@ -2017,18 +2021,22 @@ __global__ __launch_bounds__(kLayoutNT) void k_layout_place(int32_t n, int64_t t
     const int64_t v = b + threadIdx.x;
     const bool in = v < t1;
     const int32_t d = in ? o.deg[v] : 0, p = in ? o.dplus[v] : 0;
-    unsigned long long tot;
-    // both sums stay below 2^31: one scan of the two packed
-    const unsigned long long ex = block_excl_scan<unsigned long long, kLayoutNT>(
-        ((unsigned long long)(uint32_t)p << 32) | (unsigned long long)(uint32_t)(d - p), red, &tot);
-    if (in) {
-      o.doff[v] = runp + (int64_t)(ex >> 32);
-      o.dinoff[v] = runi + (int64_t)(ex & 0xffffffffull);
-      o.din[v] = d - p;
-      o.rec[v] = make_int2((int32_t)(uint32_t)o.raw_off[v], d);
+    if (OFFSETS) {
+      unsigned long long tot;
+      // both sums stay below 2^31: one scan of the two packed
+      const unsigned long long ex = block_excl_scan<unsigned long long, kLayoutNT>(
+          ((unsigned long long)(uint32_t)p << 32) | (unsigned long long)(uint32_t)(d - p), red, &tot);
+      if (in) {
+        o.doff[v] = runp + (int64_t)(ex >> 32);
+        o.dinoff[v] = runi + (int64_t)(ex & 0xffffffffull);
+        o.din[v] = d - p;
+        o.rec[v] = make_int2((int32_t)(uint32_t)o.raw_off[v], d);
+      }
+      runp += (int64_t)(tot >> 32);
+      runi += (int64_t)(tot & 0xffffffffull);
+    } else {
+      __syncthreads();  // the lists ascend by 1,024 ids here too
     }
-    runp += (int64_t)(tot >> 32);
-    runi += (int64_t)(tot & 0xffffffffull);
     const int x = node_bin(p, bp), y = in_bin(d, p, bp);
 #pragma unroll
     for (int q = 0; q < kNumBins; ++q) {
@@ -2062,12 +2070,14 @@ __global__ __launch_bounds__(kLayoutNT) void k_layout_place(int32_t n, int64_t t
   }
 }
 
-hipError_t launch_layout(int32_t n, const BinParams& bp, int32_t* sums, const LayoutOut& o, hipStream_t s) {
+hipError_t launch_layout(int32_t n, const BinParams& bp, bool offsets, int32_t* sums, const LayoutOut& o,
+                         hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int64_t tile = layout_tile(n);
   const unsigned nt = (unsigned)((n + tile - 1) / tile);
   k_layout_count<<<nt, kLayoutNT, 0, s>>>(n, tile, o.deg, o.dplus, bp, sums);
-  k_layout_place<<<nt, kLayoutNT, 0, s>>>(n, tile, bp, sums, o);
+  if (offsets) k_layout_place<true><<<nt, kLayoutNT, 0, s>>>(n, tile, bp, sums, o);
+  else k_layout_place<false><<<nt, kLayoutNT, 0, s>>>(n, tile, bp, sums, o);
   return hipGetLastError();
 }
 

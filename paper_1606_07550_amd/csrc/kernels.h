@@ -146,8 +146,11 @@ struct LayoutOut {
   int32_t* limit;
   int32_t* cap;
 };
-// sums: scratch of max(n, 64) int32.
-hipError_t launch_layout(int32_t n, const BinParams& bp, int32_t* sums, const LayoutOut& o, hipStream_t s);
+// offsets: all of it; else the node lists, the in-list owners and their header
+// words alone (a new binning of the same DAG, whose offsets others may be
+// reading). sums: scratch of max(n, 64) int32.
+hipError_t launch_layout(int32_t n, const BinParams& bp, bool offsets, int32_t* sums, const LayoutOut& o,
+                         hipStream_t s);
 // per-bin sums of d+(u) + d+(w), of edges over the DAG edges each bin's
 // kernel counts (min-side ownership with w_max; w_max = 0 disables it), and
 // of the bytes the min-side kernel moves (din / cap: in-degrees and in-list

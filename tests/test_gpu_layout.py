@@ -255,3 +255,32 @@ def test_more_short_rows_than_a_launch_has_blocks():
     assert bool((rows == want).all())
     out = g.count()
     assert bool((out["T"] == 3).all()) and int(out["total"]) == n
+
+
+@pytest.mark.parametrize("n", [1, 1024, 1025, 70_001, (1 << 20) + 1])
+def test_new_bins_of_the_same_dag(n):
+    """Retuning forms the node bins and in-list items anew and nothing else: the
+    offsets, which a count or query on another stream may be reading, are not
+    written (marked here, and put back before the count)."""
+    rng = np.random.default_rng(n)
+    m = min(20 * n, 400_000)
+    s = rng.integers(0, n, m, dtype=np.int32)
+    d = (rng.random(m) ** 3 * n).astype(np.int32)
+    g = P.Graph(n, torch.from_numpy(s).to(DEV), torch.from_numpy(d).to(DEV))
+    a, info = g.arrays(), g.info
+    doff = a["doff"].clone()
+    a["doff"].fill_(-5)
+    lim, var = [4, 8, 16, 64, 4096], [21, 22, 23, 24, 14, 9]
+    g.retune({"bin_limit": lim, "bin_variant": var, "min_side": 1})
+    assert bool((a["doff"] == -5).all())
+    a["doff"].copy_(doff)
+    now = g.info
+    assert all(now[k] == info[k] for k in ("m", "max_deg", "max_outdeg", "n_deg2"))
+    p, deg = np.diff(doff.cpu().numpy()), a["deg"].cpu().numpy()
+    b = np.searchsorted(np.array(lim), p)
+    assert list(now["bin_count"]) == [int(((b == q) & (p >= 2)).sum()) for q in range(6)]
+    items = -(-(deg - p) // np.array([P.variant_capacity(v) for v in var])[b])
+    own = (p >= 3) & (deg - p >= 1) & (p <= 4096)
+    assert list(now["bin_in_items"]) == [int(items[own & (b == q)].sum()) for q in range(6)]
+    ref = oracle.count(n, s, d)
+    np.testing.assert_array_equal(g.count()["T"].cpu().numpy().view(np.uint64), ref["T"])
