@@ -23,54 +23,52 @@ __device__ __forceinline__ bool row_has_short(const int32_t* __restrict__ adj, u
   return false;
 }
 
-// The same (ids in [0, n), inv_n = 1 / n) by aligned blocks of W ids, each read
-// by W / 4 independent loads and settled whole: key is in it, between its ids, or
-// to one side. The first block is the one that would hold key if the row's ids
-// were spread evenly; from there the steps to the key's side double until it is
-// passed, then the bracket is halved, so a row of clustered ids costs at most
-// about twice the blocks of a halving from the start. Blocks at the row's ends
-// hold ids of other rows (the array is padded to whole blocks); only [lo, hi)
-// counts. Bound by misses of the random reads (halving id by id: 4.3 per test on
-// 4M nodes and 67M pairs, two of them the records).
+// The same by aligned blocks of W ids, each read by W / 4 independent loads and
+// settled whole: key is in it, between its ids, or to one side. The first block is
+// the one where key would be if the row's ids were spread as the graph's degrees
+// are: share, the part of all rows' entries that lie before key's own row, which
+// the key's record holds. (Spread evenly over the ids, the guess failed where low
+// ids have high degrees: 3M tests on an R-MAT graph of 65k nodes with its ids as
+// made 82 us, so 63, by halving 66; 4M nodes 184, so 125, by halving 190.) From
+// there the steps to the key's side double until it is passed, then the bracket
+// is halved, so a row of clustered ids costs at most about twice the blocks of a
+// halving from the start. Blocks at the row's ends hold ids of other rows (the
+// array is padded to whole blocks); only [lo, hi) counts. Bound by misses of the
+// random reads (halving id by id: 4.3 per test on 4M nodes and 67M pairs, two of
+// them the records).
 template <int W>
 __device__ __forceinline__ bool row_has(const int32_t* __restrict__ adj, uint32_t lo, uint32_t hi, int32_t key,
-                                        float inv_n) {
+                                        float share) {
   constexpr uint32_t LG = W == 16 ? 4 : 3, ALL = (1u << W) - 1u;
   static_assert(W == 8 || W == 16, "whole 32- or 64-byte blocks");
   const int4* blocks = reinterpret_cast<const int4*>(adj);
   uint32_t blo = lo >> LG, bhi = (hi - 1) >> LG;
-  uint32_t g = min(bhi, blo + (uint32_t)((float)key * inv_n * (float)(bhi - blo + 1)));
+  uint32_t g = min(bhi, blo + (uint32_t)(share * (float)(bhi - blo + 1)));
   uint32_t step = 1;
   int side = 0;  // of the last step; 2 once the key's side has changed
   while (true) {
-    const uint32_t base = g << LG;
-    uint32_t in = ALL;  // this row's ids of the block
-    if (base < lo) in &= ALL << (lo - base);
-    if (hi - base < (uint32_t)W) in &= ALL >> (W - (hi - base));
     int4 x[W / 4];
 #pragma unroll
     for (int k = 0; k < W / 4; ++k) x[k] = blocks[(size_t)g * (W / 4) + k];
-    // lane bits of the ids that pass a test
-    auto ids = [&](auto test) {
-      uint32_t m = 0;
+    uint32_t hit = 0;
 #pragma unroll
-      for (int k = 0; k < W / 4; ++k) {
-        const int32_t v[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
+    for (int k = 0; k < W / 4; ++k) {
+      const int32_t v[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) m |= test(v[j]) ? 1u << (4 * k + j) : 0u;
-      }
-      return m & in;
-    };
-    if (ids([&](int32_t v) { return v == key; })) return true;
-    if (blo == bhi) return false;
-    const uint32_t lt = ids([&](int32_t v) { return v < key; });
+      for (int j = 0; j < 4; ++j) hit |= v[j] == key ? 1u << (4 * k + j) : 0u;
+    }
+    if (hit) {
+      const uint32_t base = g << LG;
+      uint32_t in = ALL;  // this row's ids of the block
+      if (base < lo) in &= ALL << (lo - base);
+      if (hi - base < (uint32_t)W) in &= ALL >> (W - (hi - base));
+      if (hit & in) return true;
+    }
     int d;
-    if (lt == 0u) {
-      if (g == blo) return false;
+    if (g > blo && x[0].x > key) {  // a block that is not the row's first begins with its ids
       bhi = g - 1;
       d = -1;
-    } else if (lt == in) {
-      if (g == bhi) return false;
+    } else if (g < bhi && x[W / 4 - 1].w < key) {  // one that is not its last ends with them
       blo = g + 1;
       d = 1;
     } else {
@@ -98,10 +96,11 @@ template <int W>
 __global__ __launch_bounds__(kQueryNT) void k_has_edges(int64_t q, const int32_t* __restrict__ qu,
                                                         const int32_t* __restrict__ qv, int32_t n,
                                                         const int2* __restrict__ rec,
+                                                        const int64_t* __restrict__ entries,
                                                         const int32_t* __restrict__ adj,
                                                         uint8_t* __restrict__ out) {
   const int64_t stride = (int64_t)gridDim.x * kQueryNT;
-  const float inv_n = 1.0f / (float)n;
+  const float inv = 1.0f / (float)max(*entries, (int64_t)1);
   for (int64_t i = (int64_t)blockIdx.x * kQueryNT + threadIdx.x; i < q; i += stride) {
     const int32_t u = qu[i], v = qv[i];
     uint8_t r = 0;
@@ -114,8 +113,12 @@ __global__ __launch_bounds__(kQueryNT) void k_has_edges(int64_t q, const int32_t
       const uint32_t lo = (uint32_t)ra.x;
       const uint32_t hi = lo + (uint32_t)ra.y;
       const int32_t key = su ? v : u;
-      if constexpr (W == 0) r = row_has_short(adj, lo, hi, key) ? 1 : 0;
-      else r = ra.y > 0 && row_has<W>(adj, lo, hi, key, inv_n) ? 1 : 0;
+      if constexpr (W == 0) {
+        r = row_has_short(adj, lo, hi, key) ? 1 : 0;
+      } else {
+        const float share = (float)(uint32_t)(su ? rv.x : ru.x) * inv;  // of all rows' entries, before key's row
+        r = ra.y > 0 && row_has<W>(adj, lo, hi, key, share) ? 1 : 0;
+      }
     }
     out[i] = r;
   }
@@ -125,25 +128,27 @@ __global__ __launch_bounds__(kQueryNT) void k_has_edges(int64_t q, const int32_t
 
 // m edges in rows of 8m bytes. Blocks of 16 ids (what a miss fetches) once the
 // rows are well past the L2s of 4 MB, blocks of 8 below, and the halving for
-// short rows (mean degree under 10) that an L2 holds a good part of. Tests of
-// which half are edges, ids relabelled, us with halving / 8 / 16: 4M tests on 4M
-// nodes, 67M pairs 325 / 207 / 202; 20M on 1M nodes, 15M pairs 1190 / 697 / 697
-// (uniform 1667 / 1062 / 1005); 3M on 200k nodes, 2.4M pairs 108 / 104 / 112 (uniform
-// 139 / 84 / 88) and 1M pairs 80 / 88 / 94 (82 / 79 / 83); on 50k nodes, 150k
-// pairs 55 / 61 / 63. Ids left as R-MAT makes them, all tests edges: 4M nodes
-// 454 / 447 / 397, 262k nodes and 2M pairs 165 / 175 / 182.
-hipError_t launch_has_edges(int64_t q, const int32_t* qu, const int32_t* qv, int32_t n, int64_t m, const int32_t* rec,
-                            const int32_t* adj, uint8_t* out, hipStream_t s) {
+// short rows: mean degree under 10 that an L2 holds a good part of, or under 5
+// with no long row among them. 3M tests of which half are edges, us with halving
+// / 8 / 16: R-MAT of 4M nodes and 32M pairs 210 / 151 / 148 (ids as made 190 /
+// 125 / 125), of 262k nodes and 2M pairs 105 / 80 / 82 (95 / 82 / 86); uniform 1M
+// nodes and 15M pairs 255 / 163 / 154, 200k and 2.4M 140 / 86 / 90, 50k and 150k
+// 54 / 63 / 64, 400k and 800k 87 / 89 / 91, 4M and 8M 180 / 214 / 201; a grid of
+// 2,048 x 2,048 nodes 169 / 196 / 180. Random pairs alone, nearly all of them with
+// a row of a few ids: R-MAT of 65k nodes and 524k pairs 48 / 50 / 51.
+hipError_t launch_has_edges(int64_t q, const int32_t* qu, const int32_t* qv, int32_t n, int64_t m, int64_t max_deg,
+                            const int32_t* rec, const int64_t* entries, const int32_t* adj, uint8_t* out,
+                            hipStream_t s) {
   if (q <= 0) return hipSuccess;
   int64_t blocks = (q + kQueryNT - 1) / kQueryNT;
   if (blocks > (int64_t(1) << 20)) blocks = int64_t(1) << 20;
   const int2* r = reinterpret_cast<const int2*>(rec);
-  if (m < 5 * (int64_t)n && 8 * m <= (int64_t(12) << 20))
-    k_has_edges<0><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, adj, out);
+  if ((m < 5 * (int64_t)n && 8 * m <= (int64_t(12) << 20)) || (2 * m <= 5 * (int64_t)n && max_deg <= 64))
+    k_has_edges<0><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, entries, adj, out);
   else if (8 * m <= (int64_t(20) << 20))
-    k_has_edges<8><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, adj, out);
+    k_has_edges<8><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, entries, adj, out);
   else
-    k_has_edges<16><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, adj, out);
+    k_has_edges<16><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, entries, adj, out);
   return hipGetLastError();
 }
 

@@ -168,3 +168,43 @@ def test_rows_at_the_edges_of_blocks(spread, more):
     want = np.isin(qu * n + qv, np.concatenate([s * n + d, d * n + s])).astype(np.uint8)
     np.testing.assert_array_equal(gpu_has(g, qu, qv), want)
     np.testing.assert_array_equal(gpu_has(g, qv, qu), want)
+
+
+@pytest.mark.parametrize("hub", [0, 64, 65])
+def test_short_rows_of_a_large_graph(hub):
+    """A ring of a million nodes, each joined to the next two: rows of 4 ids,
+    searched by halving, and by blocks once one row is longer than 64."""
+    n = 1_000_003
+    i = np.arange(n)
+    s, d = np.concatenate([i, i]), np.concatenate([(i + 1) % n, (i + 2) % n])
+    far = 500_000 + 7 * np.arange(max(hub - 4, 0))
+    s, d = np.concatenate([s, np.full(far.size, 10)]), np.concatenate([d, far])
+    g = P.Graph(n, dev(s), dev(d))
+    assert g.info["max_deg"] == (hub or 4) and 2 * g.info["m"] <= 5 * n and 8 * g.info["m"] > 12 << 20
+    u = np.repeat(np.concatenate([i[:40], i[-40:], far[:5], [10]]), 9)
+    v = (u + np.tile(np.arange(-4, 5), u.size // 9)) % n
+    u, v = np.concatenate([u, np.full(far.size, 10), np.full(far.size, 10)]), np.concatenate([v, far, far + 1])
+    gap = np.minimum((u - v) % n, (v - u) % n)
+    want = ((gap == 1) | (gap == 2) | ((u == 10) & np.isin(v, far)) | ((v == 10) & np.isin(u, far))).astype(np.uint8)
+    np.testing.assert_array_equal(gpu_has(g, u, v), want)
+    np.testing.assert_array_equal(gpu_has(g, v, u), want)
+
+
+@pytest.mark.parametrize("top", [1, 50])
+def test_rows_where_degrees_lie_unevenly(top):
+    """The first block is guessed from where the degrees lie: all of them at the
+    low or at the high ids, rows there and away from there, every id tested."""
+    n, m = 60_000, 400_000
+    rng = np.random.default_rng(top)
+    s = rng.integers(0, n, m)
+    d = (rng.random(m) ** 6 * n).astype(np.int64)
+    if top == 50:
+        s, d = n - 1 - s, n - 1 - d
+    g = P.Graph(n, dev(s), dev(d))
+    keep = s != d
+    key = np.unique(np.concatenate([s[keep] * n + d[keep], d[keep] * n + s[keep]]))
+    ids = np.concatenate([rng.integers(0, n, 40), d[:40], [0, n - 1]])
+    u, v = (a.ravel() for a in np.meshgrid(ids, np.arange(0, n, 7), indexing="ij"))
+    u, v = np.concatenate([u, key // n]), np.concatenate([v, key % n])
+    want = np.isin(u * n + v, key).astype(np.uint8)
+    np.testing.assert_array_equal(gpu_has(g, u, v), want)
