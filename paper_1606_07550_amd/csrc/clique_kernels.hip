@@ -23,6 +23,12 @@ constexpr int kK4U = 4;
 // (150 KB); up to kK4Cap = 8,192 the pass kernel over blocks of 64
 // positions (2 words per row, 102 KB).
 constexpr int kK4BitsSmall = 64;
+// A wavefront's node has its lists streamed packed where their mean length is
+// below this, else one by one, 64 ids a step either way (500k nodes of out-degree
+// 20 in a ring, 4-cliques: one by one 3.3 ms, packed 1.8, with NEAR tables 0.50;
+// 60-cliques 1.46 -> 0.81 -> 0.22; R-MAT of 1M nodes and 4M pairs 0.89 -> 0.94;
+// bounds of 16, 32 and 100 took 3.4, 1.8 and 1.8 ms of the ring).
+constexpr int32_t kK4PackMean = 64;
 constexpr int kK4BitsLow = 256;
 constexpr int kK4BitsMid = 512;
 constexpr int kK4BitsMax = 1024;
@@ -40,7 +46,12 @@ __device__ __forceinline__ int32_t pow2_lower_pos(const int32_t* L, int32_t P, i
 
 // Places of the ids of N+(u) in it, by a table in LDS (cuckoo, or buckets where
 // a build gives up): two reads that do not depend on each other find an id,
-// against a chain of log2 d in a search of the sorted list.
+// against a chain of log2 d in a search of the sorted list. The tables of small
+// nodes have few slots, so their keys take NEAR slots: without, every build gave
+// up on lists of neighbouring ids and a bucket chain held most of them (4-cliques
+// of 200k nodes joined to the 50 on each side 3.8 ms, now 0.79; R-MAT of 240k
+// nodes 1.66 ms either way).
+constexpr bool kPlaceNear = true;
 template <int SLOTS>
 struct PlaceTable {
   int4 K[SLOTS / 4];
@@ -57,7 +68,7 @@ __device__ __forceinline__ bool build_places(PlaceTable<SLOTS>& S, const int32_t
   if (g == 0) S.fail = 0;
   group_sync<G>();
   for (int i = g; i < d; i += G)
-    if (!cuckoo_insert<SLOTS>(K, src[i])) S.fail = 1;
+    if (!cuckoo_insert<SLOTS, kPlaceNear>(K, src[i])) S.fail = 1;
   group_sync<G>();
   const bool ck = __builtin_amdgcn_readfirstlane(S.fail) == 0;
   if (!ck) {
@@ -68,7 +79,7 @@ __device__ __forceinline__ bool build_places(PlaceTable<SLOTS>& S, const int32_t
   }
   for (int i = g; i < d; i += G) {
     const int32_t x = src[i];
-    S.place[ck ? cuckoo_find<SLOTS>(K, x) : table_find<SLOTS>(K, x)] = (uint16_t)i;
+    S.place[ck ? cuckoo_find<SLOTS, kPlaceNear>(K, x) : table_find<SLOTS>(K, x)] = (uint16_t)i;
   }
   group_sync<G>();
   return ck;
@@ -135,7 +146,7 @@ __device__ __forceinline__ void stream_rows_of(bool ck, int32_t wv, int32_t d, i
                                                const int64_t* __restrict__ doff, const int32_t* __restrict__ dcol,
                                                const PlaceTable<SLOTS>& S, Set set) {
   if (ck)
-    stream_rows<NW, U>(wv, d, ub, doff, dcol, S.place, CuckooProbe<SLOTS>{reinterpret_cast<const int32_t*>(S.K)}, set);
+    stream_rows<NW, U>(wv, d, ub, doff, dcol, S.place, CuckooProbe<SLOTS, kPlaceNear>{reinterpret_cast<const int32_t*>(S.K)}, set);
   else
     stream_rows<NW, U>(wv, d, ub, doff, dcol, S.place, BucketProbe<SLOTS / 4>{S.K}, set);
 }
@@ -257,10 +268,12 @@ __global__ __launch_bounds__(NT) void k_count_k4_bits(int32_t n, int32_t chunk, 
   k4_block_total<NW>(acc, red, total);
 }
 
-// Nodes with 3 <= d+(u) <= 64: a wavefront per node and no block barrier. Row
-// i is a 64-bit word: built in LDS, then held by lane i. For each place x the
-// lanes whose row has x add popcount(row & row x). The nodes of a block's
-// chunk of ids go to its wavefronts in turn. Three quarters of the nodes of an
+// Nodes with 3 <= d+(u) <= 64: a wavefront per node and no block barrier. The
+// subgraph's adjacency is a 64-bit word per place p, of the places i whose list
+// has p: built in LDS (the ids of a list set bits of different words), then held
+// by lane p. For each place x the lanes whose word has x add popcount(word & word
+// x), every 4-clique once, as by rows. The nodes of a block's chunk of ids go to
+// its wavefronts in turn. Three quarters of the nodes of an
 // R-MAT graph are this small; a block of 256 threads for each spent their time
 // in barriers.
 __global__ __launch_bounds__(kK4NT) void k_count_k4_small(int32_t n, int32_t chunk, const int64_t* __restrict__ doff,
@@ -269,6 +282,8 @@ __global__ __launch_bounds__(kK4NT) void k_count_k4_small(int32_t n, int32_t chu
   constexpr int NW = kK4NT / kWave;
   __shared__ PlaceTable<2 * kK4BitsSmall> S[NW];
   __shared__ unsigned long long R[NW][kWave];
+  __shared__ int2 lists[NW][kWave];  // offset and row of the lists that are not empty
+  __shared__ PackStarts starts[NW];
   __shared__ unsigned long long red[NW];
   const int wv = threadIdx.x / kWave;
   const int lane = lane_id();
@@ -291,11 +306,35 @@ __global__ __launch_bounds__(kK4NT) void k_count_k4_small(int32_t n, int32_t chu
         todo &= todo - 1;
         const int32_t d = __builtin_amdgcn_readlane(d0, src);
         const int64_t ub = __builtin_amdgcn_readlane((int32_t)b0, src);  // DAG offsets stay below 2^30
+        int32_t vb = 0, vn = 0;
+        if (lane < d) {
+          const int32_t w = dcol[ub + lane];
+          const int64_t b = doff[w];
+          vb = (int32_t)b;
+          vn = (int32_t)(doff[w + 1] - b);
+        }
+        const int32_t incl = wave_incl_scan(vn);
+        const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
         wave_sync();  // the table and rows of the previous node are no longer read
         R[wv][lane] = 0ull;
+        const uint64_t some = __ballot(vn > 0);
+        if (vn > 0) lists[wv][mask_below(some)] = make_int2(vb - (incl - vn), lane);
         const bool ck = build_places<kWave>(S[wv], dcol + ub, d, lane);
-        stream_rows_of<1, kK4U>(ck, 0, d, ub, doff, dcol, S[wv],
-                                [&](int32_t i, int32_t p) { atomicOr(&B[2 * i + (p >> 5)], 1u << (p & 31)); });
+        auto set = [&](int32_t i, int32_t p) { atomicOr(&B[2 * p + (i >> 5)], 1u << (i & 31)); };
+        if (total < kK4PackMean * d) {
+          auto packed = [&](auto probe) {
+            stream_lists(
+                vn, incl - vn, total, starts[wv], dcol, [&](int32_t k) { return lists[wv][k]; },
+                [&](int32_t x, int32_t i, bool valid) {
+                  int off;
+                  if (probe(x, valid, &off)) set(i, (int32_t)S[wv].place[off >> 2]);
+                });
+          };
+          if (ck) packed(CuckooProbe<2 * kK4BitsSmall, kPlaceNear>{reinterpret_cast<const int32_t*>(S[wv].K)});
+          else packed(BucketProbe<2 * kK4BitsSmall / 4>{S[wv].K});
+        } else {
+          stream_rows_of<1, kK4U>(ck, 0, d, ub, doff, dcol, S[wv], set);
+        }
         wave_sync();
         const unsigned long long row = R[wv][lane];
         const int32_t lo = (int32_t)(uint32_t)row, hi = (int32_t)(uint32_t)(row >> 32);

@@ -93,62 +93,8 @@ struct WaveGroupLds {
 // Lists shorter than this are streamed packed: a wavefront covers several
 // short lists per step instead of one list per step.
 constexpr int32_t kPackShort = 64;
-// Steps of 64 ids whose gathers are issued together in the packed streams.
-constexpr int kPackUnroll = 3;
-
 // Lanes per node on the packed small-node path by default (d+ <= kSmallGS).
 constexpr int kSmallGS = 16;
-
-// Positions of a concatenation of lists whose starts are marked at a time: five
-// steps of the packed streams, one bit a position.
-constexpr int32_t kPackWindow = 5 * kPackUnroll * kWave;
-struct PackStarts {
-  uint64_t bits[(kPackWindow / kWave + 1) & ~1];
-};
-
-// The concatenation of 64 lists, one per lane (begin b, length n, 0 for none),
-// 64 ids per step: body(x, k, valid) gets the lane's id and the number of its
-// list among the lists that are not empty. The list of position t is the number
-// of list starts in (0, t]: the starts are marked as bits in LDS, so a step
-// takes one read of 64 bits, a lane-mask count and, through where(k), the offset
-// of list k against its place in the concatenation. (A search of the lanes'
-// prefixes by shuffles is six dependent LDS round trips and 30 instructions a
-// step.) kPackUnroll independent gathers are in flight before their bodies.
-template <typename Where, typename Body>
-__device__ __forceinline__ void stream_lists(int32_t n, int32_t ex, int32_t total, PackStarts& P,
-                                             const int32_t* __restrict__ dcol, Where where, Body body) {
-  const int lane = lane_id();
-  uint32_t* bits = reinterpret_cast<uint32_t*>(P.bits);
-  int32_t before = 0;  // starts in (0, t0]
-  for (int32_t w0 = 0; w0 < total; w0 += kPackWindow) {
-    wave_sync();  // the previous window's bits are no longer read
-    if (lane < (int)(sizeof(PackStarts) / 4)) bits[lane] = 0u;
-    wave_sync();
-    const int32_t at = ex - 1 - w0;
-    if (n > 0 && (uint32_t)at < (uint32_t)kPackWindow) atomicOr(&bits[at >> 5], 1u << (at & 31));
-    wave_sync();
-    const int32_t end = min(total, w0 + kPackWindow);
-    for (int32_t t0 = w0; t0 < end; t0 += kPackUnroll * kWave) {
-      int32_t x[kPackUnroll], kk[kPackUnroll];
-#pragma unroll
-      for (int r = 0; r < kPackUnroll; ++r) {
-        const int32_t t = t0 + r * kWave + lane;
-        const uint64_t mv = P.bits[(t0 - w0) / kWave + r];
-        const uint64_t m = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(mv >> 32)) << 32) |
-                           (uint32_t)__builtin_amdgcn_readfirstlane((int)mv);
-        const int2 l = where(before + mask_below(m));
-        before += (int32_t)__popcll(m);
-        x[r] = t < total ? dcol[l.x + t] : -1;
-        kk[r] = l.y;
-      }
-#pragma unroll
-      for (int r = 0; r < kPackUnroll; ++r) {
-        if (t0 + r * kWave >= total) break;
-        body(x[r], kk[r], t0 + r * kWave + lane < total);
-      }
-    }
-  }
-}
 
 // Packed streaming of the short lists among items [i0, i1) of a group, a window
 // of up to 64 lists at a time. A hit credits its table slot and its list's

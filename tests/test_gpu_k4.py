@@ -215,3 +215,30 @@ def test_out_degrees_at_the_kernels_edges(core):
     assert core <= g.info["max_outdeg"] <= max(core, 64)
     assert gpu_k4(g) == oracle.k4(n1 + n2, s, d, order=1)
     assert gpu_k5(g) == oracle.k5(n1 + n2, s, d, order=1)
+
+
+@pytest.mark.parametrize("k", [2, 70, 300, 600])
+def test_place_tables_fall_back_to_buckets(k):
+    """Complete graphs whose last four ids agree in their low 24 bits, so that
+    they share one slot pair and every table that holds them is rebuilt in the
+    bucket layout: in the kernels of out-degrees up to 64, 256, 512 and 1,024."""
+    ids = np.concatenate([2 + np.arange(k), 1 + (np.arange(1, 5) << 24)])
+    i, j = np.triu_indices(ids.size, 1)
+    g = P.Graph(int(ids[-1]) + 1, dev(ids[i]), dev(ids[j]))
+    assert g.info["max_outdeg"] == ids.size - 1
+    assert gpu_k4(g) == comb(ids.size, 4)
+    assert gpu_k5(g) == comb(ids.size, 5)
+
+
+@pytest.mark.parametrize("near", [40, 100, 128, 130, 260])
+@pytest.mark.parametrize("step", [1, 3])
+def test_lists_of_neighbouring_ids(near, step):
+    """Rings of nodes joined to the nearest on both sides: lists of consecutive
+    ids (or every third), streamed packed and one by one, the longest lists of a
+    wavefront's node 64 ids."""
+    n = 1500
+    n0, s, d = F.ring_lattice(n, near)
+    s, d = s.astype(np.int64) * step, d.astype(np.int64) * step
+    g = P.Graph(n * step, dev(s), dev(d))
+    assert gpu_k4(g) == oracle.k4(n * step, s.astype(np.int32), d.astype(np.int32), order=1)
+    assert gpu_k5(g) == oracle.k5(n * step, s.astype(np.int32), d.astype(np.int32), order=1)
