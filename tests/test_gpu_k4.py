@@ -222,7 +222,7 @@ def test_place_tables_fall_back_to_buckets(k):
     """Complete graphs whose last four ids agree in their low 24 bits, so that
     they share one slot pair and every table that holds them is rebuilt in the
     bucket layout: in the kernels of out-degrees up to 64, 256, 512 and 1,024."""
-    ids = np.concatenate([2 + np.arange(k), 1 + (np.arange(1, 5) << 24)])
+    ids = np.concatenate([2 + 27_001 * np.arange(k), 1 + (np.arange(1, 5) << 24)])  # a block takes nodes of close ids
     i, j = np.triu_indices(ids.size, 1)
     g = P.Graph(int(ids[-1]) + 1, dev(ids[i]), dev(ids[j]))
     assert g.info["max_outdeg"] == ids.size - 1
