@@ -284,3 +284,22 @@ def test_new_bins_of_the_same_dag(n):
     assert list(now["bin_in_items"]) == [int(items[own & (b == q)].sum()) for q in range(6)]
     ref = oracle.count(n, s, d)
     np.testing.assert_array_equal(g.count()["T"].cpu().numpy().view(np.uint64), ref["T"])
+
+
+@pytest.mark.parametrize("run", [1, 3, 15, 16, 17, 64, 5000])
+@pytest.mark.parametrize("n", [2000, 300_000])
+def test_runs_of_equal_pairs(n, run):
+    """Rows sorted by bitmap whose entries come in runs of one id, id 0 and the
+    highest among them."""
+    rng = np.random.default_rng(run)
+    ids = np.concatenate([[0, n - 1, 0, 1, 2], rng.integers(0, n, 6000 // run), [0, n - 1]])
+    ids = ids[ids != 7]
+    w = np.repeat(ids, run)
+    w = np.concatenate([w, np.full(max(0, 5000 - w.size), 0)]).astype(np.int32)
+    g = P.Graph(n, torch.full((w.size,), 7, dtype=torch.int32, device=DEV), torch.from_numpy(w).to(DEV))
+    a = g.arrays()
+    want = np.unique(w)
+    off, deg = int(a["off"][7]), int(a["deg"][7])
+    np.testing.assert_array_equal(a["adj"][off:off + deg].cpu().numpy(), want)
+    assert g.info["m"] == want.size
+    np.testing.assert_array_equal(torch.nonzero(a["deg"] == 1).flatten().cpu().numpy(), want)
