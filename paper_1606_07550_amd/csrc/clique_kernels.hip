@@ -273,10 +273,12 @@ __global__ __launch_bounds__(NT) void k_count_k4_bits(int32_t n, int32_t chunk, 
 // has p: built in LDS (the ids of a list set bits of different words), then held
 // by lane p. For each place x the lanes whose word has x add popcount(word & word
 // x), every 4-clique once, as by rows. The nodes of a block's chunk of ids go to
-// its wavefronts in turn. Three quarters of the nodes of an
+// its wavefronts in turn. Eight wavefronts a SIMD are asked for: left to itself the
+// allocation took 87 scalar registers, of 80 that eight may have (1M R-MAT nodes
+// with 4M pairs 0.96 -> 0.92 ms, the ring of out-degree 50 0.80 -> 0.75). Three quarters of the nodes of an
 // R-MAT graph are this small; a block of 256 threads for each spent their time
 // in barriers.
-__global__ __launch_bounds__(kK4NT) void k_count_k4_small(int32_t n, int32_t chunk, const int64_t* __restrict__ doff,
+__global__ __launch_bounds__(kK4NT, 8) void k_count_k4_small(int32_t n, int32_t chunk, const int64_t* __restrict__ doff,
                                                           const int32_t* __restrict__ dcol,
                                                           unsigned long long* __restrict__ total) {
   constexpr int NW = kK4NT / kWave;
