@@ -273,33 +273,35 @@ __device__ __forceinline__ void peel_steps(const int32_t* __restrict__ row, int3
   int32_t old[kPeelU];
 #pragma unroll
   for (int q = 0; q < kPeelU; ++q) old[q] = live[q] ? atomicSub(&g.cur[w[q]], 1) : 0;
-  uint64_t take[kPeelU], enter[kPeelU];
+  // bit q of take: entry q falls to k; of enter: it falls to U (at the window's
+  // last level the frontier is all that enters)
+  uint32_t take = 0, enter = 0;
   int32_t nt = 0, ne = 0;
 #pragma unroll
   for (int q = 0; q < kPeelU; ++q) {
-    take[q] = __ballot(live[q] && old[q] == s.k + 1);
-    // at the window's last level the frontier is all that enters
-    enter[q] = __ballot(live[q] && old[q] == s.U + 1 && s.U > s.k);
-    nt += (int32_t)__popcll(take[q]);
-    ne += (int32_t)__popcll(enter[q]);
+    take |= live[q] && old[q] == s.k + 1 ? 1u << q : 0u;
+    enter |= live[q] && old[q] == s.U + 1 && s.U > s.k ? 1u << q : 0u;
+    nt += (int32_t)__popcll(__ballot((take >> q) & 1u));
+    ne += (int32_t)__popcll(__ballot((enter >> q) & 1u));
   }
   if (nt + ne == 0) return;
-  const int lane = lane_id();
   int32_t at = 0, et = 0;
-  if (lane == 0 && nt) at = atomicAdd(&c->f, nt);
-  if (lane == 0 && ne) et = atomicAdd(&c->near, ne);
+  if (lane_id() == 0 && nt) at = atomicAdd(&c->f, nt);
+  if (lane_id() == 0 && ne) et = atomicAdd(&c->near, ne);
   at = __builtin_amdgcn_readfirstlane(at);
   et = __builtin_amdgcn_readfirstlane(et) + s.nx;
 #pragma unroll
   for (int q = 0; q < kPeelU; ++q) {
-    if ((take[q] >> lane) & 1) {
+    const bool t = (take >> q) & 1u, e = (enter >> q) & 1u;
+    const uint64_t tm = __ballot(t), em = __ballot(e);
+    if (t) {
       g.core[w[q]] = s.k;
       if (g.order) g.order[w[q]] = s.round + s.rounds + 1;
-      g.F[s.fb ^ 1][at + mask_below(take[q])] = w[q];
+      g.F[s.fb ^ 1][at + mask_below(tm)] = w[q];
     }
-    if ((enter[q] >> lane) & 1) g.near[s.xb][et + mask_below(enter[q])] = w[q];
-    at += (int32_t)__popcll(take[q]);
-    et += (int32_t)__popcll(enter[q]);
+    if (e) g.near[s.xb][et + mask_below(em)] = w[q];
+    at += (int32_t)__popcll(tm);
+    et += (int32_t)__popcll(em);
   }
 }
 
