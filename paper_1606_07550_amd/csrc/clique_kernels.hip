@@ -456,19 +456,29 @@ __global__ __launch_bounds__(kK4QNT) void k_count_k4_passes(int32_t n, int32_t c
 // w in turn and walks the x of row w one at a time: every lane forms one
 // word of the AND of rows w and x (lane & (RS - 1)), the y in it are listed
 // in LDS (per lane, in bit order, after a scan of the lanes' popcounts), and
-// groups of 64 / RS lanes add popcount(AND & row y), one word each.
+// groups of 64 / RS lanes add popcount(AND & row y), one word each. The y are
+// listed where the table was: apart they took 44,088 bytes of LDS for out-degrees
+// up to 512, three blocks a CU instead of four (50k nodes in a ring joined to the
+// 200 on each side 555 -> 603 ms, now 474; R-MAT of 262k nodes and 4M pairs 56.3 -> 51.6, now 44.5).
 template <int DMIN, int DMAX, int NT>
 __global__ __launch_bounds__(NT) void k_count_k5_bits(int32_t n, int32_t chunk, const int64_t* __restrict__ doff,
                                                       const int32_t* __restrict__ dcol,
                                                       unsigned long long* __restrict__ total) {
   constexpr int NW = NT / kWave;
   static_assert(DMAX % 32 == 0 && DMAX <= 1024, "rows of at most 32 words");
-  __shared__ PlaceTable<2 * DMAX> S;
+  __shared__ union {
+    PlaceTable<2 * DMAX> S;  // while the rows are built
+    uint16_t Y[NW][DMAX];    // after that
+  } lds;
   __shared__ uint32_t B[DMAX * (DMAX / 32)];
-  __shared__ uint16_t Y[NW][DMAX];
+  PlaceTable<2 * DMAX>& S = lds.S;
+  uint16_t(&Y)[NW][DMAX] = lds.Y;
   __shared__ unsigned long long red[NW];
   __shared__ int32_t Q[NT];
   __shared__ int32_t Qn;
+  static_assert(DMAX > kK4BitsMid ||
+                    sizeof(lds) + sizeof(B) + sizeof(red) + sizeof(Q) + sizeof(Qn) <= 160 * 1024 / 4,
+                "four blocks a CU");
   const int wv = threadIdx.x / kWave;
   const int lane = lane_id();
   unsigned long long acc = 0;
@@ -489,7 +499,7 @@ __global__ __launch_bounds__(NT) void k_count_k5_bits(int32_t n, int32_t chunk, 
       const int32_t d = (int32_t)(doff[u + 1] - ub);
       const int rs = d <= 32 ? 0 : 32 - __builtin_clz((uint32_t)((d + 31) / 32 - 1));
       const int RS = 1 << rs;
-      __syncthreads();  // the table and B of the previous node are no longer read
+      __syncthreads();  // Y and B of the previous node are no longer read
       for (int32_t q = threadIdx.x; q < d * RS; q += NT) B[q] = 0u;
       const bool ck = build_places<NT>(S, dcol + ub, d, threadIdx.x);
       stream_rows_of<NW, kK4U>(ck, wv, d, ub, doff, dcol, S,
