@@ -136,6 +136,17 @@ __global__ __launch_bounds__(kQueryNT) void k_has_edges(int64_t q, const int32_t
 // 54 / 63 / 64, 400k and 800k 87 / 89 / 91, 4M and 8M 180 / 214 / 201; a grid of
 // 2,048 x 2,048 nodes 169 / 196 / 180. Random pairs alone, nearly all of them with
 // a row of a few ids: R-MAT of 65k nodes and 524k pairs 48 / 50 / 51.
+// Up to kQueryFew tests go by halving: a call ends with its slowest lane, whose
+// steps from a guess that failed and back are more, and each longer, than a
+// halving's through ids that its first loads brought. us with halving / blocks,
+// of a call alone, R-MAT of 65k nodes and 1M pairs: 1,000 tests 18.9 / 21.1,
+// 65,000 20.0 / 22.6, 262,144 25.0 / 26.3 and 10^6 44 / 41; 500k nodes joined to
+// 20 hubs: 65,000 tests 20.8 / 29.6, 262,144 32 / 38, 400,000 4% more; uniform 1M
+// nodes and 16M pairs: 65,000 tests 19.9 / 20.5, 180,000 the same, 262,144 35.4 /
+// 32.7. Not where an eighth of all ordered pairs of ids are edges: nearly every
+// guess is right then (2,500 nodes all joined: 65,000 tests 22.5 / 19.1).
+constexpr int64_t kQueryFew = 3 << 16;
+
 hipError_t launch_has_edges(int64_t q, const int32_t* qu, const int32_t* qv, int32_t n, int64_t m, int64_t max_deg,
                             const int32_t* rec, const int64_t* entries, const int32_t* adj, uint8_t* out,
                             hipStream_t s) {
@@ -143,7 +154,10 @@ hipError_t launch_has_edges(int64_t q, const int32_t* qu, const int32_t* qv, int
   int64_t blocks = (q + kQueryNT - 1) / kQueryNT;
   if (blocks > (int64_t(1) << 20)) blocks = int64_t(1) << 20;
   const int2* r = reinterpret_cast<const int2*>(rec);
-  if ((m < 5 * (int64_t)n && 8 * m <= (int64_t(12) << 20)) || (2 * m <= 5 * (int64_t)n && max_deg <= 64))
+  const bool dense = 8 * m >= (int64_t)n * n;
+  const bool short_rows =
+      (m < 5 * (int64_t)n && 8 * m <= (int64_t(12) << 20)) || (2 * m <= 5 * (int64_t)n && max_deg <= 64);
+  if (short_rows || (q <= kQueryFew && !dense))
     k_has_edges<0><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, entries, adj, out);
   else if (8 * m <= (int64_t(20) << 20))
     k_has_edges<8><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, entries, adj, out);

@@ -208,3 +208,44 @@ def test_rows_where_degrees_lie_unevenly(top):
     u, v = np.concatenate([u, key // n]), np.concatenate([v, key % n])
     want = np.isin(u * n + v, key).astype(np.uint8)
     np.testing.assert_array_equal(gpu_has(g, u, v), want)
+
+
+@pytest.mark.parametrize("more", [0, 600_000, 2_800_000], ids=["halving", "blocks_of_8", "blocks_of_16"])
+@pytest.mark.parametrize("q", [3 << 16, (3 << 16) + 1, 500_001])
+def test_few_and_many_queries(q, more):
+    """Few tests go by halving, more by the row search that the graph's size
+    asks for: rows of 1 to 140 ids at every offset against blocks of 8 and 16,
+    their ids spread evenly, in one clump or at both ends, tested with every id
+    that a row holds and the ids beside it, and with ids outside [0, n)."""
+    n, pool = 100_000, 150
+    rng = np.random.default_rng(q)
+    ids = [np.linspace(400, n - 2, pool).astype(np.int64), 50_000 + 2 * np.arange(pool),
+           np.concatenate([600 + np.arange(pool // 2) * 3, n - 400 + np.arange(pool // 2) * 2])]
+    lens = np.tile(np.concatenate([np.arange(1, 71), [95, 96, 97, 127, 128, 129, 140]]), 3)
+    s = [np.full(k, u) for u, k in enumerate(lens)]
+    d = [rng.choice(ids[u * 3 // lens.size], k, replace=False) for u, k in enumerate(lens)]
+    keys = np.unique(np.concatenate([x + o for x in ids for o in (-1, 0, 1)] + [[0, n - 1]]))
+    fill = 240 + np.arange(160)  # they lift the degrees of the rows' ids above the rows' lengths
+    others = np.setdiff1d(np.arange(1000, n), keys)
+    s = np.concatenate(s + [np.repeat(fill, 3 * pool), rng.choice(others, more)])
+    d = np.concatenate(d + [np.tile(np.concatenate(ids), fill.size), rng.choice(others, more)])
+    g = P.Graph(n, dev(s), dev(d))
+    m = g.info["m"]
+    assert (m < 5 * n, 8 * m > 20 << 20) == {0: (True, False), 600_000: (False, False), 2_800_000: (False, True)}[more]
+    qu, qv = (a.ravel() for a in np.meshgrid(np.arange(lens.size), keys, indexing="ij"))
+    qu, qv = np.resize(qu, q), np.resize(qv, q)
+    want = np.isin(qu * n + qv, np.concatenate([s * n + d, d * n + s])).astype(np.uint8)
+    bad = np.arange(0, q, 997)
+    qv[bad], want[bad] = np.where(bad % 2, n, -1), 0xFF
+    np.testing.assert_array_equal(gpu_has(g, qu, qv), want)
+    np.testing.assert_array_equal(gpu_has(g, qv, qu), want)
+
+
+@pytest.mark.parametrize("name", ["K41", "K30_30"])
+def test_few_queries_of_dense_graphs(name):
+    """Dense graphs go by blocks however few the tests are."""
+    n, s, d = F.complete(41) if name == "K41" else F.complete_bipartite(30, 30)
+    g = P.Graph(n, dev(s), dev(d))
+    assert 8 * g.info["m"] >= n * n and g.info["m"] >= 5 * n
+    qu, qv = all_pairs(n)
+    np.testing.assert_array_equal(gpu_has(g, qu, qv), oracle.has_edges(n, s, d, qu, qv))
