@@ -180,7 +180,10 @@ __device__ __forceinline__ void k4_block_total(unsigned long long acc, unsigned 
 // lanes of a wavefront cover 64 / RS rows x at once, one word each. LISTED:
 // the x of row w are first listed in LDS by ballot; otherwise (rows of 32
 // words, DMIN >= 512) they are taken two at a time straight from row w's
-// bits, which leaves the LDS for 1,024 threads.
+// bits, which leaves the LDS for 1,024 threads. The row's words lie in the lanes
+// and those without a bit are passed over: read from LDS one after the other,
+// they were nearly all the time of sparse rows (10,000 nodes with no edge among
+// their 1,000 neighbours: 7.2 ms, 7.6 beside the table look-ups, now 1.36).
 template <int DMIN, int DMAX, int NT, bool LISTED>
 __global__ __launch_bounds__(NT) void k_count_k4_bits(int32_t n, int32_t chunk, const int64_t* __restrict__ doff,
                                                       const int32_t* __restrict__ dcol,
@@ -221,21 +224,29 @@ __global__ __launch_bounds__(NT) void k_count_k4_bits(int32_t n, int32_t chunk, 
                                [&](int32_t i, int32_t p) { atomicOr(&B[i * RS + (p >> 5)], 1u << (p & 31)); });
       __syncthreads();
       for (int32_t i = wv; i < d && !LISTED; i += NW) {
-        // RS == 32: half-wave h takes the h-th of each next two bits of row i
-        const uint32_t* Bi = B + i * 32;
+        // RS == 32: half-wave h takes the h-th of each next two bits of row i, whose
+        // words lie in the lanes
         const int32_t k = lane & 31;
         const bool second = lane >= 32;
-        const uint32_t bik = Bi[k];
+        const uint32_t bik = B[i * 32 + k];
+        uint32_t some = (uint32_t)__ballot(bik != 0u);  // words with bits left
+        uint32_t word = 0u;
         int32_t kw = 0;
-        uint32_t word = Bi[0];
-        while (true) {
-          while (word == 0u && kw < 31) word = Bi[++kw];
-          if (word == 0u) break;
-          const int32_t xa = kw * 32 + __builtin_ctz(word);
+        auto next = [&]() -> int32_t {  // -1 after the last
+          if (word == 0u) {
+            if (some == 0u) return -1;
+            kw = __builtin_ctz(some);
+            some &= some - 1u;
+            word = (uint32_t)__builtin_amdgcn_readlane((int32_t)bik, kw);
+          }
+          const int32_t x = kw * 32 + __builtin_ctz(word);
           word &= word - 1u;
-          while (word == 0u && kw < 31) word = Bi[++kw];
-          const int32_t xb = word ? kw * 32 + __builtin_ctz(word) : -1;
-          word &= word - 1u;  // no effect when word == 0
+          return x;
+        };
+        while (true) {
+          const int32_t xa = next();
+          if (xa < 0) break;
+          const int32_t xb = next();
           const int32_t x = second ? xb : xa;
           if (x >= 0) acc += (unsigned long long)__popc(bik & B[x * 32 + k]);
           if (xb < 0) break;

@@ -242,3 +242,23 @@ def test_lists_of_neighbouring_ids(near, step):
     g = P.Graph(n * step, dev(s), dev(d))
     assert gpu_k4(g) == oracle.k4(n * step, s.astype(np.int32), d.astype(np.int32), order=1)
     assert gpu_k5(g) == oracle.k5(n * step, s.astype(np.int32), d.astype(np.int32), order=1)
+
+
+@pytest.mark.parametrize("core,density", [(513, 0.02), (600, 0.004), (992, 0.01), (993, 0.001), (1024, 0.02), (1000, 0.0)])
+def test_sparse_rows_of_large_out_degrees(core, density):
+    """Centres joined to all of a core whose nodes are joined sparsely: rows with
+    no bit, one or few, most of their words empty, the last word partly used."""
+    rng = np.random.default_rng(core)
+    iu, ju = np.triu_indices(core, 1)
+    keep = rng.random(iu.size) < density
+    centres = 5
+    c = np.repeat(np.arange(core, core + centres), core)
+    leaves = core + centres + 5  # they lift the core above the centres
+    leaf = core + centres + np.arange(core * leaves)
+    s = np.concatenate([iu[keep], c, np.repeat(np.arange(core), leaves)])
+    d = np.concatenate([ju[keep], np.tile(np.arange(core), centres), leaf])
+    n = int(core + centres + leaf.size)
+    g = P.Graph(n, dev(s), dev(d))
+    assert g.info["max_outdeg"] == core
+    assert gpu_k4(g) == oracle.k4(n, s, d, order=1)
+    assert gpu_k5(g) == oracle.k5(n, s, d, order=1)
