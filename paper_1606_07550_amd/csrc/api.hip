@@ -41,7 +41,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Header words (int32 unless stated).
 enum : int {
-  kHdrErr = 0,
+  kHdrErr = 0,        // flags; [1] steps of a trusted CSR that do not rise inside a row
   kHdrStats = 4,      // [0] max d, [1] max d+, [2] nodes with d >= 2
   kHdrBinCnt = 16,    // [kNumBins]
   kHdrLimits = 24,    // [kNumBins - 1]
@@ -474,7 +474,7 @@ int build_impl(tricc_graph* g, const int32_t* src, const int32_t* dst, bool pres
       const int32_t err = h32[kHdrErr];
       if (err & 4) return fail(TRICC_EINVAL, "CSR row offsets are not a non-decreasing sequence from 0 to nnz");
       if (err & 1) return fail(TRICC_ERANGE, "CSR holds a node id outside [0, %d)", n);
-      if (err) return fail(TRICC_EINVAL, "CSR row not strictly ascending or holding its own id");
+      if (err || h32[kHdrErr + 1]) return fail(TRICC_EINVAL, "CSR row not strictly ascending or holding its own id");
     } else if (h32[kHdrErr]) {
       return fail(TRICC_ERANGE, "edge list holds a node id outside [0, %d)", n);
     }

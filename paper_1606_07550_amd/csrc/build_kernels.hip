@@ -1768,21 +1768,24 @@ __global__ __launch_bounds__(256) void k_csr_bounds(int32_t n, int64_t nnz, cons
 }
 
 // Rows taken as they are: off = rowptr, len = deg = row lengths (0 for a row
-// whose bounds are bad: bit 4 of err), adj = col, and the rows checked: ids in
-// [0, n) (else bit 1), strictly ascending and without the row's own id (else
-// bit 2). Entries are shared out evenly, whatever the rows' lengths: one
-// wavefront per row took 446 us at R-MAT 20, most of them on its few rows of
-// 10^4 to 6 10^4 entries. A step down from col[i - 1] to col[i] is right only
-// where a row starts, so an entry searches the row offsets only there (at
-// most once per row in a well-formed CSR), and a row's own id is searched in
-// its sorted row. Both searches stay inside the arrays whatever they hold.
+// whose bounds are bad: bit 4 of err[0]), adj = col, and the rows checked: ids in
+// [0, n) (else bit 1), without the row's own id (else bit 2) and strictly
+// ascending (else err[1] is not 0). Entries are shared out evenly, whatever the
+// rows' lengths: one wavefront per row took 446 us at R-MAT 20, most of them on
+// its few rows of 10^4 to 6 10^4 entries. A step that does not rise from
+// col[i - 1] to col[i] is right only where a row starts: err[1] is the number of
+// such steps less those at row starts. (A search of the row offsets at each such
+// step, one a row, missed the L2 where the offsets outgrow it: a CSR of 4M nodes
+// and 200M entries, whole count, 15.1 ms, now 11.8; 13.4 with a wavefront per row.)
+// A row's own id is searched in its sorted row, inside the array whatever it holds.
 __global__ __launch_bounds__(256) void k_csr_take(int32_t n, int64_t nnz, const int64_t* __restrict__ rowptr,
                                                   const int32_t* __restrict__ col, int64_t* __restrict__ off,
                                                   int32_t* __restrict__ len, int32_t* __restrict__ deg,
                                                   int32_t* __restrict__ adj, int32_t* __restrict__ err) {
+  __shared__ int32_t red[256 / kWave];
   const int64_t stride = (int64_t)gridDim.x * 256;
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  int32_t bad = 0;
+  int32_t bad = 0, falls = 0;
   for (int64_t v = t; v < n; v += stride) {
     const int64_t b = rowptr[v], e = rowptr[v + 1];
     const bool ok = csr_row_ok(v, n, nnz, b, e);
@@ -1792,6 +1795,7 @@ __global__ __launch_bounds__(256) void k_csr_take(int32_t n, int64_t nnz, const 
     len[v] = l;
     deg[v] = l;
     if (l > 0) {
+      if (b > 0 && col[b - 1] >= col[b]) --falls;
       int64_t lo = b, hi = e;
       while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
@@ -1811,7 +1815,7 @@ __global__ __launch_bounds__(256) void k_csr_take(int32_t n, int64_t nnz, const 
     for (int q = 0; q < U; ++q) {
       const int64_t i = i0 + q * stride;
       x[q] = i < nnz ? col[i] : 0;
-      y[q] = i < nnz && i > 0 ? col[i - 1] : -1;
+      y[q] = i < nnz && i > 0 ? col[i - 1] : INT32_MIN;
     }
 #pragma unroll
     for (int q = 0; q < U; ++q) {
@@ -1819,19 +1823,14 @@ __global__ __launch_bounds__(256) void k_csr_take(int32_t n, int64_t nnz, const 
       if (i >= nnz) break;
       adj[i] = x[q];
       if ((uint32_t)x[q] >= (uint32_t)n) bad |= 1;
-      if (y[q] >= x[q]) {
-        int64_t lo = 0, hi = n;  // first offset >= i
-        while (lo < hi) {
-          const int64_t mid = (lo + hi) >> 1;
-          if (rowptr[mid] < i) lo = mid + 1; else hi = mid;
-        }
-        if (rowptr[lo] != i) bad |= 2;
-      }
+      falls += i > 0 && y[q] >= x[q];
     }
   }
 #pragma unroll
   for (int bit = 1; bit <= 4; bit <<= 1)
-    if (__ballot(bad & bit) && lane_id() == 0) atomicOr(err, bit);
+    if (__ballot(bad & bit) && lane_id() == 0) atomicOr(&err[0], bit);
+  falls = block_sum<int32_t, 256>(falls, red);
+  if (threadIdx.x == 0 && falls) atomicAdd(&err[1], falls);
 }
 
 // src[i] = v for every entry i of row v: the CSR as a list of (v, w) pairs.
@@ -1852,7 +1851,8 @@ hipError_t launch_csr_bounds(int32_t n, int64_t nnz, const int64_t* rowptr, int3
 
 hipError_t launch_csr_take(int32_t n, int64_t nnz, const int64_t* rowptr, const int32_t* col, int64_t* off,
                            int32_t* len, int32_t* deg, int32_t* adj, int32_t* err, hipStream_t s) {
-  k_csr_take<<<grid_for(std::max<int64_t>(n, nnz / 4), 256, 1u << 13), 256, 0, s>>>(n, nnz, rowptr, col, off, len,
+  // eight blocks a CU fill it, and each adds to err[1] once
+  k_csr_take<<<grid_for(std::max<int64_t>(n, nnz / 4), 256, 2048), 256, 0, s>>>(n, nnz, rowptr, col, off, len,
                                                                                   deg, adj, err);
   return hipGetLastError();
 }

@@ -96,8 +96,9 @@ hipError_t launch_orient_copy(int32_t n, const int64_t* off, const int32_t* len,
                               const int64_t* dinoff, int32_t* dincol, hipStream_t s);
 
 // Caller CSR: bounds check (err bit 4), the whole check with the copy into
-// the workspace (err bits 1 = id out of range, 2 = not strictly ascending or
-// a self loop, 4 = bounds; off, len, deg, adj written), expansion into (v, w)
+// the workspace (err[0] bits 1 = id out of range, 2 = a self loop, 4 = bounds;
+// err[1], cleared before, not 0: a row not strictly ascending, if the bounds are
+// right; off, len, deg, adj written), expansion into (v, w)
 // pairs (only after the bounds check passed).
 hipError_t launch_csr_bounds(int32_t n, int64_t nnz, const int64_t* rowptr, int32_t* err, hipStream_t s);
 hipError_t launch_csr_take(int32_t n, int64_t nnz, const int64_t* rowptr, const int32_t* col, int64_t* off,

@@ -114,6 +114,29 @@ def test_csr_rows_checked_everywhere(n, deg):
     refused(bad, col, EINVAL)
 
 
+@pytest.mark.parametrize("n", [3, 700, 600_000])
+def test_csr_steps_down_inside_rows(n):
+    """Trusted rows whose starts all fall (every row ends above the next row's
+    first id), rise, or both: one fall inside a row is found, wherever it is."""
+    r = np.random.default_rng(n)
+    ring = np.arange(n)
+    far = r.permutation(n)
+    s, d = np.concatenate([ring, far[:n // 2]]), np.concatenate([(ring + 1) % n, far[n - n // 2:]])
+    rowptr, col = oracle_csr(n, s, d)
+    dev = lambda a: torch.from_numpy(a).to(DEV)  # noqa: E731
+    P.Graph.from_csr(n, dev(rowptr), dev(col), assume_simple_sorted_symmetric=True)
+    path = np.stack([ring[:-1], ring[1:]])  # rows {v - 1, v + 1}: every start from row 2 on falls
+    rp, cl = oracle_csr(n, *path)
+    P.Graph.from_csr(n, dev(rp), dev(cl), assume_simple_sorted_symmetric=True)
+    for rowptr, col in ((rowptr, col), (rp, cl)):
+        for v in (np.flatnonzero(np.diff(rowptr) > 1)[k] for k in (0, -1)):
+            c = col.copy()
+            c[rowptr[v]:rowptr[v] + 2] = c[rowptr[v]:rowptr[v] + 2][::-1]
+            with pytest.raises(P.TriccError) as e:
+                P.Graph.from_csr(n, dev(rowptr), dev(c), assume_simple_sorted_symmetric=True)
+            assert e.value.status == 1
+
+
 def oracle_csr(n, s, d):
     keep = s != d
     a = np.concatenate([s[keep], d[keep]]).astype(np.int64)
