@@ -964,9 +964,8 @@ int tricc_graph_has_edges(const tricc_graph* g, int64_t q, const int32_t* d_u, c
   if (q == 0) return TRICC_OK;
   if (!d_u || !d_v || !d_out) return fail(TRICC_EINVAL, "null query or output array");
   const Layout& L = g->L;
-  HIPCHK(launch_has_edges(q, d_u, d_v, g->n, g->info.m, g->info.max_deg, g->at<int32_t>(L.rec),
-                          g->at<int64_t>(L.raw_off) + g->n, g->at<int32_t>(L.adj), d_out,
-                          static_cast<hipStream_t>(stream)));
+  HIPCHK(launch_has_edges(q, d_u, d_v, g->n, g->info.m, g->at<int32_t>(L.rec), g->at<int64_t>(L.raw_off) + g->n,
+                          g->at<int32_t>(L.adj), d_out, static_cast<hipStream_t>(stream)));
   return TRICC_OK;
 }
 

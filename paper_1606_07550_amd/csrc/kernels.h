@@ -249,9 +249,8 @@ hipError_t launch_batch_relabel(int32_t num_graphs, const int64_t* node_off, con
 // included), kEdgeQueryBadId if an id lies outside [0, n).
 constexpr uint8_t kEdgeQueryBadId = 0xFF;
 // *entries (device): the raw entries of all rows.
-hipError_t launch_has_edges(int64_t q, const int32_t* qu, const int32_t* qv, int32_t n, int64_t m, int64_t max_deg,
-                            const int32_t* rec, const int64_t* entries, const int32_t* adj, uint8_t* out,
-                            hipStream_t s);
+hipError_t launch_has_edges(int64_t q, const int32_t* qu, const int32_t* qv, int32_t n, int64_t m, const int32_t* rec,
+                            const int64_t* entries, const int32_t* adj, uint8_t* out, hipStream_t s);
 
 // ---- Core numbers ------------------------------------------------------------
 // Level-synchronous peeling over the simple graph's rows (row v =

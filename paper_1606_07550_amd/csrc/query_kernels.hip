@@ -10,8 +10,7 @@ namespace tricc {
 
 namespace {
 
-// True when key is in adj[lo, hi) (ascending, unique, lo < hi): halving, id by
-// id. Few instructions: for graphs of short rows that the L2 holds.
+// True when key is in adj[lo, hi) (ascending, unique): halving, id by id.
 __device__ __forceinline__ bool row_has_short(const int32_t* __restrict__ adj, uint32_t lo, uint32_t hi, int32_t key) {
   while (lo < hi) {
     const uint32_t mid = lo + ((hi - lo) >> 1);
@@ -23,7 +22,7 @@ __device__ __forceinline__ bool row_has_short(const int32_t* __restrict__ adj, u
   return false;
 }
 
-// The same by aligned blocks of W ids, each read by W / 4 independent loads and
+// The same (lo < hi) by aligned blocks of W ids, each read by W / 4 independent loads and
 // settled whole: key is in it, between its ids, or to one side. The first block is
 // the one where key would be if the row's ids were spread as the graph's degrees
 // are: share, the part of all rows' entries that lie before key's own row, which
@@ -91,7 +90,14 @@ constexpr int kQueryNT = 256;
 // so a query fetches its two records in one round trip.
 // One query per thread (grid-stride): out[i] = 1 if {u[i], v[i]} is an edge,
 // 0 if not (u == v included), kEdgeQueryBadId if an id is outside [0, n).
-// W: ids per block of the row search, 0 for the halving.
+// W: ids per block of the row search, 0 for the halving. A wavefront whose rows are
+// all short goes by halving in any case: whole blocks of them are mostly other rows'
+// ids. 3M tests, half edges, us by blocks / with this: 2M nodes joined to one hub 156 /
+// 124, by preferential attachment 4M nodes with one edge each 206 / 165 and 1M
+// with 16 158 / 142, uniform 8M nodes and 40M pairs 235 / 187, R-MAT of 4M nodes and
+// 64M pairs 160 / 152 (rows up to 16 and 32 halved: 168, 142, 233, 152 and 169, 142,
+// 242, 152; all by halving 123, 169, 234, 241, 263).
+constexpr int32_t kShortRow = 8;
 template <int W>
 __global__ __launch_bounds__(kQueryNT) void k_has_edges(int64_t q, const int32_t* __restrict__ qu,
                                                         const int32_t* __restrict__ qv, int32_t n,
@@ -117,7 +123,8 @@ __global__ __launch_bounds__(kQueryNT) void k_has_edges(int64_t q, const int32_t
         r = row_has_short(adj, lo, hi, key) ? 1 : 0;
       } else {
         const float share = (float)(uint32_t)(su ? rv.x : ru.x) * inv;  // of all rows' entries, before key's row
-        r = ra.y > 0 && row_has<W>(adj, lo, hi, key, share) ? 1 : 0;
+        if (!__ballot(ra.y > kShortRow)) r = row_has_short(adj, lo, hi, key) ? 1 : 0;
+        else r = ra.y > 0 && row_has<W>(adj, lo, hi, key, share) ? 1 : 0;
       }
     }
     out[i] = r;
@@ -126,38 +133,33 @@ __global__ __launch_bounds__(kQueryNT) void k_has_edges(int64_t q, const int32_t
 
 }  // namespace
 
-// m edges in rows of 8m bytes. Blocks of 16 ids (what a miss fetches) once the
-// rows are well past the L2s of 4 MB, blocks of 8 below, and the halving for
-// short rows: mean degree under 10 that an L2 holds a good part of, or under 5
-// with no long row among them. 3M tests of which half are edges, us with halving
-// / 8 / 16: R-MAT of 4M nodes and 32M pairs 210 / 151 / 148 (ids as made 190 /
-// 125 / 125), of 262k nodes and 2M pairs 105 / 80 / 82 (95 / 82 / 86); uniform 1M
-// nodes and 15M pairs 255 / 163 / 154, 200k and 2.4M 140 / 86 / 90, 50k and 150k
-// 54 / 63 / 64, 400k and 800k 87 / 89 / 91, 4M and 8M 180 / 214 / 201; a grid of
-// 2,048 x 2,048 nodes 169 / 196 / 180. Random pairs alone, nearly all of them with
-// a row of a few ids: R-MAT of 65k nodes and 524k pairs 48 / 50 / 51.
+// m edges in rows of 8m bytes: blocks of 16 ids (what a miss fetches) once the
+// rows are well past the L2s of 4 MB, blocks of 8 below. 3M tests of which half
+// are edges, us with halving / 8 / 16: R-MAT of 4M nodes and 32M pairs 232 / 149
+// / 147 (ids as made 220 / 137 / 134), of 262k nodes and 2M pairs 113 / 70 / 72
+// (100 / 71 / 73); uniform 1M nodes and 15M pairs 266 / 149 / 147, 200k and 2.4M
+// 155 / 83 / 85, 50k and 150k 68 / 57 / 59, 400k and 800k 98 / 97 / 97, 4M and 8M
+// 191 / 189 / 188; a grid of 2,048 x 2,048 nodes 186 with each. Random pairs
+// alone, R-MAT of 65k nodes and 524k pairs 52 / 49 / 50.
 // Up to kQueryFew tests go by halving: a call ends with its slowest lane, whose
 // steps from a guess that failed and back are more, and each longer, than a
 // halving's through ids that its first loads brought. us with halving / blocks,
-// of a call alone, R-MAT of 65k nodes and 1M pairs: 1,000 tests 18.9 / 21.1,
-// 65,000 20.0 / 22.6, 262,144 25.0 / 26.3 and 10^6 44 / 41; 500k nodes joined to
-// 20 hubs: 65,000 tests 20.8 / 29.6, 262,144 32 / 38, 400,000 4% more; uniform 1M
-// nodes and 16M pairs: 65,000 tests 19.9 / 20.5, 180,000 the same, 262,144 35.4 /
-// 32.7. Not where an eighth of all ordered pairs of ids are edges: nearly every
+// of a call alone, R-MAT of 65k nodes and 1M pairs: 1,000 tests 18.7 / 20.2,
+// 65,000 19.9 / 22.3, 262,144 24.7 / 24.9, 400,000 29.8 / 27.8; 500k nodes joined
+// to 20 hubs: 65,000 tests 20.6 / 28.6, 262,144 32 / 36, 400,000 45 / 42; uniform
+// 1M nodes and 16M pairs: 65,000 tests 20 / 20, 180,000 28.3 / 26.8, 262,144 35.5
+// / 30.1. Not where an eighth of all ordered pairs of ids are edges: nearly every
 // guess is right then (2,500 nodes all joined: 65,000 tests 22.5 / 19.1).
 constexpr int64_t kQueryFew = 3 << 16;
 
-hipError_t launch_has_edges(int64_t q, const int32_t* qu, const int32_t* qv, int32_t n, int64_t m, int64_t max_deg,
-                            const int32_t* rec, const int64_t* entries, const int32_t* adj, uint8_t* out,
-                            hipStream_t s) {
+hipError_t launch_has_edges(int64_t q, const int32_t* qu, const int32_t* qv, int32_t n, int64_t m, const int32_t* rec,
+                            const int64_t* entries, const int32_t* adj, uint8_t* out, hipStream_t s) {
   if (q <= 0) return hipSuccess;
   int64_t blocks = (q + kQueryNT - 1) / kQueryNT;
   if (blocks > (int64_t(1) << 20)) blocks = int64_t(1) << 20;
   const int2* r = reinterpret_cast<const int2*>(rec);
   const bool dense = 8 * m >= (int64_t)n * n;
-  const bool short_rows =
-      (m < 5 * (int64_t)n && 8 * m <= (int64_t(12) << 20)) || (2 * m <= 5 * (int64_t)n && max_deg <= 64);
-  if (short_rows || (q <= kQueryFew && !dense))
+  if (q <= kQueryFew && !dense)
     k_has_edges<0><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, entries, adj, out);
   else if (8 * m <= (int64_t(20) << 20))
     k_has_edges<8><<<(unsigned)blocks, kQueryNT, 0, s>>>(q, qu, qv, n, r, entries, adj, out);
