@@ -43,7 +43,6 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 enum : int {
   kHdrErr = 0,        // flags; [1] steps of a trusted CSR that do not rise inside a row
   kHdrStats = 4,      // [0] max d, [1] max d+, [2] nodes with d >= 2
-  kHdrBinCnt = 16,    // [kNumBins]
   kHdrLimits = 24,    // [kNumBins - 1]
   kHdrListElems = 32, // u64 at byte 128
   kHdrClsOff = 64,    // int64[kNumRowClasses + 1] at byte 256
@@ -714,7 +713,6 @@ int count_bins(tricc_graph* g, int b0, int b1, uint64_t* d_node_tri, void* strea
     bl.in_coff = g->at<int64_t>(L.incoff) + g->in_off[b0];
     bl.in_owner = g->at<int32_t>(L.tmp) + g->in_items[b0];
     bl.in_base = (int32_t)g->in_off[b0];
-    bl.in_nodes = (int32_t)(g->in_off[b1 + 1] - g->in_off[b0]);
     bl.in_items = g->in_items[b1 + 1] - g->in_items[b0];
     bl.w_max = g->tuning.bin_limit[kNumBins - 2];
     bl.dinoff = g->at<int64_t>(L.dinoff);

@@ -14,10 +14,6 @@
 
 namespace tricc {
 
-namespace {
-
-}  // namespace
-
 // ---------------------------------------------------------------------------
 // a1: validation and raw degree count (both directions, loops dropped)
 __global__ __launch_bounds__(256) void k_degree_raw(const int32_t* __restrict__ src,
@@ -122,9 +118,6 @@ static hipError_t scan_impl(const Tin* in, int64_t n, int64_t* out, int64_t* tmp
 
 hipError_t launch_scan_i32(const int32_t* in, int64_t n, int64_t* out, int64_t* tmp, hipStream_t s) {
   return scan_impl<int32_t>(in, n, out, tmp, s);
-}
-hipError_t launch_scan_i64(const int64_t* in, int64_t n, int64_t* out, int64_t* tmp, hipStream_t s) {
-  return scan_impl<int64_t>(in, n, out, tmp, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -432,7 +432,6 @@ struct InItems {
   const int64_t* coff;
   const int32_t* owner;
   int32_t base;
-  int32_t nodes;
   int64_t items;
 };
 
@@ -668,8 +667,8 @@ __global__ __launch_bounds__(kHubNT) void k_count_bitmap(const int32_t* __restri
 // 64 / GS nodes per wave. Lane j of a node's lanes owns the out-edge to the
 // j-th entry w of N+(u); each node has a bucket table of 4 * GS slots in
 // LDS. The 64 lanes' lists N+(w) are streamed packed (one id per lane per
-// step, its list found by a shuffle binary search over the lanes' length
-// prefix) and each id is probed against the table of its list's node, so a
+// step, its list found by the marked starts of stream_lists) and each id is
+// probed against the table of its list's node, so a
 // wave keeps 64 independent loads in flight instead of walking dependent
 // merge chains. Credits: x per table slot, w per list, u per node.
 template <int GS>
@@ -1192,7 +1191,7 @@ static void launch_ms(const BinLaunch& b, const int64_t* doff, const int32_t* dc
   const int64_t nbu = ((int64_t)b.count + GPB - 1) / GPB;
   const int64_t nbw = (b.in_items + GPB - 1) / GPB;
   if (nbu + nbw == 0) return;
-  InItems in{b.in_list, b.in_coff, b.in_owner, b.in_base, b.in_nodes, b.in_items};
+  InItems in{b.in_list, b.in_coff, b.in_owner, b.in_base, b.in_items};
   k_count_ms<NT, G, SLOTS, CAP, U, CK, CH><<<(unsigned)(nbu + nbw), NT, 0, s>>>(b.list, b.count, in, b.w_max, doff, dcol,
                                                                         b.dinoff, b.dincol, T, tot);
 }
@@ -1204,7 +1203,7 @@ static void launch_mss(const BinLaunch& b, const int64_t* doff, const int32_t* d
   const int64_t nbu = ((int64_t)b.count + GPB * (kWave / GS) - 1) / (GPB * (kWave / GS));
   const int64_t nbw = (b.in_items + GPB - 1) / GPB;
   if (nbu + nbw == 0) return;
-  InItems in{b.in_list, b.in_coff, b.in_owner, b.in_base, b.in_nodes, b.in_items};
+  InItems in{b.in_list, b.in_coff, b.in_owner, b.in_base, b.in_items};
   k_count_mss<NT, 256, 64, U, CK, GS><<<(unsigned)(nbu + nbw), NT, 0, s>>>(b.list, b.count, in, b.w_max, doff, dcol,
                                                                        b.dinoff, b.dincol, T, tot);
 }

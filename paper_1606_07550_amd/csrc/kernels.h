@@ -14,7 +14,6 @@ hipError_t launch_degree_raw(const int32_t* src, const int32_t* dst, int64_t m_r
 // `tmp` needs scan_tmp_elems(n) int64 slots.
 int64_t scan_tmp_elems(int64_t n);
 hipError_t launch_scan_i32(const int32_t* in, int64_t n, int64_t* out, int64_t* tmp, hipStream_t s);
-hipError_t launch_scan_i64(const int64_t* in, int64_t n, int64_t* out, int64_t* tmp, hipStream_t s);
 hipError_t launch_scatter(const int32_t* src, const int32_t* dst, int64_t m_raw, const int64_t* off,
                           int32_t* cur, int32_t* adj, hipStream_t s);
 // Partitioned raw rows (same result as degree_raw + scan + scatter, rows
@@ -46,7 +45,7 @@ hipError_t launch_build_clear(int32_t* hdr, int32_t words, uint32_t* part, int32
 // set). sums: scratch of max(n, 64) int32.
 hipError_t launch_row_classes(int32_t n, const int32_t* len, int32_t* deg, int32_t* sums, int32_t* list,
                               int64_t* cls_off, hipStream_t s);
-// out[i] = prefix[at[i]] for i < k (k <= 64)
+// out[i] = prefix[at[i]] for i < k
 hipError_t launch_gather_offsets(const int64_t* prefix, const int64_t* at, int k, int64_t* out, hipStream_t s);
 // Sorts + dedups every listed row in place (rowlist, cls_off: the row
 // classes) but those of kRowMerge; writes deg. tmp: scratch laid out as adj;
@@ -171,7 +170,6 @@ struct BinLaunch {
   const int64_t* in_coff = nullptr;
   const int32_t* in_owner = nullptr;  // owner index (+ in_base) of each of the bin's chunks
   int32_t in_base = 0;
-  int32_t in_nodes = 0;
   int64_t in_items = 0;
   int32_t w_max = 0;
   const int64_t* dinoff = nullptr;

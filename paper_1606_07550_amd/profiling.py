@@ -28,13 +28,16 @@ import os
 import sqlite3
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-COUNT_SOURCE = os.path.join(PKG, "csrc", "count_kernels.hip")
+COUNT_SOURCES = [os.path.join(PKG, "csrc", f) for f in ("count_kernels.hip", "tables.h")]
 PROBE_BYTES = 2 << 30  # size of the copy the benchmark's bandwidth probe runs
 
 
 def count_source_sha256():
-    with open(COUNT_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in COUNT_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def _per_kernel(db, counter, every=1, offset=0):
