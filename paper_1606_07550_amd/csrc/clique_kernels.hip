@@ -16,8 +16,8 @@ constexpr int kK4NT = 256;
 // steps of 1 to 3 loads measured no faster).
 constexpr int kK4U = 4;
 // Out-degrees up to 64 take the kernel with a wavefront per node; up to
-// kK4BitsLow and kK4BitsMid the bit-row kernel with 256 and 512 threads (16 and
-// 47 KB of LDS); up to kK4BitsMax the one with 1,024 threads and 146 KB (one
+// kK4BitsLow and kK4BitsMid the bit-row kernel with 256 and 512 threads (14 and
+// 48 KB of LDS); up to kK4BitsMax the one with 1,024 threads and 144 KB (one
 // block per CU); up to 2,048 the pass kernel over quarters of the positions
 // (1,024 threads, 142 KB); up to 4,096 the pass kernel over sixteenths
 // (150 KB); up to kK4Cap = 8,192 the pass kernel over blocks of 64
