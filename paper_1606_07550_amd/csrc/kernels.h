@@ -280,8 +280,7 @@ struct CoreProgress {
   int32_t left, max_core;
 };
 CoreProgress core_progress(const int32_t* cnt, int step, int32_t n, int32_t k_stop);
-// core = k_stop for the nodes left, if the peeling has ended with step `step`
-// (0: before the first).
+// core = k_stop for the nodes left, if the peeling has ended with step `step`.
 hipError_t launch_core_fill(int step, int32_t n, int32_t k_stop, const CoreBuffers& b, hipStream_t s);
 
 // ---- 4-clique counts ---------------------------------------------------------
